@@ -155,8 +155,8 @@ struct BwdAcc {
     __device__ float *slot(int ab, int t) { return v[ab] + t * kGrad; }
 };
 
-// Deterministic backward: each wavefront stores its per-batch sums in a slice of its own (no
-// atomics); the flush adds the four slices in a fixed order. Two buffers, as BwdAcc.
+// Deterministic backward: each wavefront adds its per-batch sums in a slice of its own (a fixed
+// order); the flush adds the four slices in a fixed order. Two buffers, as BwdAcc.
 template <int NB>
 struct BwdAccDet {
     float v[2][kBlock / 64][NB * kGrad];
@@ -371,13 +371,16 @@ struct Lane {
     int a_g;
 };
 
+// kByCol: lane l holds pixel (l / 8, l % 8) of the quadrant instead of (l % 8, l / 8), which the
+// backward's reduction needs (wave_grads).
+template <bool kByCol>
 __device__ inline Lane lane_setup(int64_t tile, int gx, int W, int H) {
     Lane L;
     L.t = threadIdx.x; L.w = L.t >> 6; L.l = L.t & 63;
     // wave w owns the 8x8 quadrant (w & 1, w >> 1) of the tile: compact footprints touch fewer
     // waves than with 4-row strips, so fewer (Gaussian, wave) pairs have work
-    L.col = 8 * (L.w & 1) + (L.l & 7);
-    L.row = 8 * (L.w >> 1) + (L.l >> 3);
+    L.col = 8 * (L.w & 1) + (kByCol ? L.l >> 3 : L.l & 7);
+    L.row = 8 * (L.w >> 1) + (kByCol ? L.l & 7 : L.l >> 3);
     const int x0 = int(tile % gx) * kTile, y0 = int(tile / gx) * kTile;
     L.px = float(x0 + L.col); L.py = float(y0 + L.row);
     L.inside = (x0 + L.col < W) && (y0 + L.row < H);
@@ -508,7 +511,7 @@ __device__ inline void fwd_tile(const ViewDesc &v, int64_t tile, Stage<M, NB> &S
     const uint32_t *plist = v.point_list;
     const uint32_t n = uint32_t(v.n);
     const Attrs<kPacked> src(v);
-    const Lane L = lane_setup(tile, v.gx, v.W, v.H);
+    const Lane L = lane_setup<false>(tile, v.gx, v.W, v.H);
     const float xc = float(int(tile % v.gx) * kTile) + 7.5f, yc = float(int(tile / v.gx) * kTile) + 7.5f;
     typename Op<M>::vec bhi, blo;
     pixel_basis<M>(L, bhi, blo);
@@ -590,20 +593,9 @@ __device__ inline float dpp_add2(float u, float v) {
 constexpr int kDppRowRor8 = 0x128, kDppRowHalfMirror = 0x141;
 constexpr int kDppQuadRev = 0x1b, kDppQuadSwap = 0xb1;       // quad_perm [3,2,1,0], [1,0,3,2]
 
-// Sum of 9 values over the whole wavefront, transposed so that the 9 totals land in distinct
-// lanes (two values share each swap-and-add, so the wavefront is halved per value pair, not per
-// value):
-//   permlane32_swap + add on the pairs (s0,s1) (s2,s3) (s4,s5) (s6,s7): lanes 0-31 hold the
-//       first value's 32 partial sums, lanes 32-63 the second's; s8, which has no partner, adds
-//       lane l ^ 32 through ds_bpermute;
-//   permlane16_swap + add on the register pairs: rows (16 lanes) of a hold (s0, s2, s1, s3),
-//       rows of b hold (s4, s6, s5, s7); s8 adds lane l ^ 16 through ds_swizzle, so every row of
-//       c holds s8;
-//   a and b share one register from here: lanes 0-7 of a row take a's row values, lanes 8-15
-//       b's, each summed with the lane 8 away (row_ror 8); then half_mirror, and two quad
-//       permutations finish each 8-lane half; c takes the same four steps alone.
-// Result: lanes 16r .. 16r+7 of ab hold s[{0,2,1,3}[r]], lanes 16r+8 .. 16r+15 hold
-// s[4 + {0,2,1,3}[r]]; lanes 0-7 of c hold s8. Every lane must be active.
+// The wavefront is halved for a pair of values at a time: permlane32_swap + add leaves the first
+// value's 32 partial sums in lanes 0-31 and the second's in lanes 32-63, permlane16_swap + add does
+// the same on 16-lane rows. Every lane must be active.
 __device__ inline float swap_add32(float &x, float y) {   // returns [x.lo + x.hi | y.lo + y.hi]
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
@@ -612,12 +604,54 @@ __device__ inline float swap_add16(float x, float y) {    // rows: [x0+x1, y0+y1
     const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
+
+// The nine gradient sums of one Gaussian over the wavefront's 8x8 pixels, with lane l at column
+// l / 8 and row l % 8 (Lane<kByCol>). The geometric terms are separable, dL/dpower dx^i dy^j, so
+// only six values per lane are summed over the columns (three levels of swaps): g0 = dL/dpower,
+// g0 dx, g0 dx^2 and the three colours. The eight slots of 8 lanes that these leave in one register
+// hold each row's six sums, and g0 and g0 dx a second time, which the row's dy then turns into the
+// terms of S_y and S_xy, and g0 dy once more into S_yy; three more levels add the rows. 24 vector
+// instructions (the products by dx and dy included) against 29, and two LDS crossbar operations,
+// for nine values formed per pixel and summed over all six levels; measured on the 4K BF16
+// backward: @@.
+//   a: rows (16 lanes) g0, g0 dx^2, g0 dx, colour r;  b: rows colour g, g0, colour b, g0 dx;
+//   a and b share one register: lanes 0-7 of a row take a's, lanes 8-15 b's.
+// Result: lane l with l % 8 == 0 and lane 28 hold the word sum_word(l) of the Gaussian's sums.
+__device__ inline float wave_grads(float g0, float dx, float dy, float cr, float cg, float cb,
+                                   int lane) {
+    const float g1 = g0 * dx;
+    float x0 = g0, x2 = g1 * dx, x4 = cg;
+    const float p0 = swap_add32(x0, g1), p1 = swap_add32(x2, cr), p2 = swap_add32(x4, cb);
+    const float a = swap_add16(p0, p1), b = swap_add16(p2, p0);
+    const bool lo8 = (lane & 8) == 0, lo4 = (lane & 4) == 0, by_dy = (lane & 24) == 24;
+    float s = dpp_add2<kDppRowRor8>(lo8 ? a : b, lo8 ? b : a);
+    s *= by_dy ? dy : 1.0f;
+    const float t = s * dy;
+    s = dpp_add2<kDppRowHalfMirror>(lo4 ? s : t, lo4 ? t : s);
+    s = dpp_add2<kDppQuadRev>(s, s);
+    s = dpp_add2<kDppQuadSwap>(s, s);
+    // keep the last add here, where it is one DPP add, not moved into the callers' leader branch
+    // (where it would need a separate move)
+    asm volatile("" : "+v"(s));
+    return s;
+}
+
+// The word of a Gaussian's nine sums (S_xx, S_xy, S_yy, S_x, S_y, S, r, g, b) that a leader lane
+// (l % 8 == 0, or 28) holds after wave_grads.
+__device__ inline bool sum_leader(int l) { return (l & 7) == 0 || l == 28; }
+__device__ inline int sum_word(int l) {
+    // 8-lane group l / 8: S, g, S_xx, S_y, S_x, b, r, S_xy
+    return l == 28 ? 2 : int((0x16834075u >> (4 * (l >> 3))) & 15u);
+}
+
+// Sum of 9 values over the whole wavefront (the deterministic gather's lane sums), transposed so
+// that the 9 totals land in distinct lanes: lanes 16r .. 16r+7 of ab hold s[{0,2,1,3}[r]], lanes
+// 16r+8 .. 16r+15 hold s[4 + {0,2,1,3}[r]]; lanes 0-7 of c hold s8 (whose first two levels go
+// through the LDS crossbar). Every lane must be active.
 __device__ inline void wave_sum9(const float (&s)[kGrad], int lane, float &ab, float &c) {
     float x0 = s[0], x2 = s[2], x4 = s[4], x6 = s[6];
     const float p01 = swap_add32(x0, s[1]), p23 = swap_add32(x2, s[3]);
     const float p45 = swap_add32(x4, s[5]), p67 = swap_add32(x6, s[7]);
-    // the ninth value alone: lane l adds lane l ^ 32 (ds_bpermute), then lane l ^ 16 (ds_swizzle,
-    // xor mask 16 within each 32-lane half); both go through the LDS crossbar, not the VALU
     const float p88 = s[8] + __int_as_float(__builtin_amdgcn_ds_bpermute((lane ^ 32) << 2,
                                                                         __float_as_int(s[8])));
     const float a = swap_add16(p01, p23);
@@ -629,16 +663,6 @@ __device__ inline void wave_sum9(const float (&s)[kGrad], int lane, float &ab, f
     ab = dpp_add2<kDppRowHalfMirror>(ab, ab); c = dpp_add2<kDppRowHalfMirror>(c, c);
     ab = dpp_add2<kDppQuadRev>(ab, ab);       c = dpp_add2<kDppQuadRev>(c, c);
     ab = dpp_add2<kDppQuadSwap>(ab, ab);      c = dpp_add2<kDppQuadSwap>(c, c);
-    // keep the last add here, where it is one DPP add, not moved into the callers' leader branch
-    // (where it would need a separate move)
-    asm volatile("" : "+v"(ab), "+v"(c));
-}
-
-// The word of a Gaussian's nine sums that a leader lane (l % 8 == 0) adds after wave_sum9:
-// lane 16r holds s[{0,2,1,3}[r]], lane 16r + 8 holds s[4 + {0,2,1,3}[r]] (lane 0 also s8).
-__device__ inline int sum_word(int l) {
-    const int r = l >> 4;
-    return 2 * (r & 1) + (r >> 1) + (l & 8 ? 4 : 0);
 }
 
 struct BwdState {
@@ -656,17 +680,17 @@ struct BwdState {
 // spent when no lane of the wave has a live pair. Otherwise every lane evaluates the step, with no
 // branch but a rare one for the clamps (a dead lane takes alpha = 0: its terms vanish and its
 // state is unchanged exactly, since 1 / (1 - 0) = 1),
-// the pair's 9 gradient terms are summed over the wavefront, and the totals are added into the
-// Gaussian's LDS accumulator (`acc` points at the word this lane adds when it leads, see
+// the pair's 9 gradient terms are summed over the wavefront (wave_grads), and the totals are added
+// into the Gaussian's LDS accumulator (`acc` points at the word this lane adds when it leads, see
 // sum_word), which the block flushes to global memory once per batch. Raw
 // sums: S_xx, S_xy, S_yy, S_x, S_y (times dL/dpower), the sum of dL/dpower without the clamp test
 // (o dL/do: the final pass divides it by o, once per Gaussian instead of once per pair), and the
 // three colour gradients.
 // kRanged = false: the caller has checked that the whole group lies before every lane's last
 // contributor, so the skip test alone decides (one compare, whose mask is the ballot).
-// kDet: `acc` points into the wavefront's own slice of the batch's sums, which this Gaussian's
-// totals are stored into (no other wavefront writes there), so no atomic.
-template <bool kRanged, bool kDet = false>
+// In the deterministic backward `acc` points into the wavefront's own slice of the batch's sums
+// (zero before; no other wavefront adds there, so the sum has a fixed order).
+template <bool kRanged>
 __device__ inline void reverse_pair(float q, bool in_range, const float4 *ga, const float2 *gb,
                                     int u, const Lane &L, BwdState &st, float *acc) {
     bool alive;
@@ -691,8 +715,11 @@ __device__ inline void reverse_pair(float q, bool in_range, const float4 *ga, co
     if (live == 0ull) return;
     const float4 attr = ga[u];   // one address for every lane: LDS broadcasts
     const float2 bw = gb[u];
-    // a dead lane has q < log2(1/255) or is past its last contributor: it blended nothing here
-    const float a = alive ? __builtin_amdgcn_exp2f(fminf(fminf(q, attr.x), kQAlphaMax)) : 0.f;
+    // a dead lane has q < log2(1/255) or is past its last contributor: it blended nothing here.
+    // (The clamp at the lowest argument that gives 0.99f, so that an exponent the minimum cut,
+    // q > m, is the one test for both clamps: the same alpha bit for bit.)
+    const float m = fminf(fminf(q, attr.x), kQAlphaMaxLo);
+    const float a = alive ? __builtin_amdgcn_exp2f(m) : 0.f;
     const float r = __builtin_amdgcn_rcpf(1.0f - a);  // exactly 1 for a dead lane
     const float Tb = st.T * r;                           // T in front of this Gaussian
     const float wc = a * Tb;                             // the pair's weight alpha T
@@ -700,48 +727,32 @@ __device__ inline void reverse_pair(float q, bool in_range, const float4 *ga, co
     const float gmb = fmaf(st.gb, attr.w, fmaf(st.gg, attr.z, fmaf(st.gr, attr.y, -st.beta)));
     st.beta = fmaf(a, gmb, st.beta);
     st.T = Tb;
-    const float da = wc * gmb;                           // dL/dpower = alpha dL/dalpha
-    const float dx = bw.x - L.px, dy = bw.y - L.py;
-    const float tx = da * dx, ty = da * dy;
-    float s[kGrad] = {tx * dx, tx * dy, ty * dy, tx, ty, da,   // dL/do = alpha/o dL/dalpha
-                      wc * st.gr, wc * st.gg, wc * st.gb};
+    float da = wc * gmb;                                 // dL/dpower = alpha dL/dalpha
     // The clamps are rare, so one scalar test stands for them and the terms of the live lanes they
     // touch are zeroed in place: with the 0.99 clamp active dL/dpower is 0, and no gradient
-    // reaches the geometry through a clamped (positive) power. (One ballot per compare, kept
-    // apart by the empty asm statements, as above.)
-    // (The 0.99 clamp is active where min(q, log2 o) >= kQAlphaMaxLo, so only where q is too.)
-    unsigned long long m_a = __builtin_amdgcn_ballot_w64(q >= kQAlphaMaxLo);
-    unsigned long long m_q = __builtin_amdgcn_ballot_w64(q > attr.x);
-    asm volatile("" : "+s"(m_a));
-    asm volatile("" : "+s"(m_q));
-    if (((m_a | m_q) & live) != 0ull) {
-        // (min(q, log2 o) >= kQAlphaMaxLo, as two compares: the step above keeps its three-way min)
-        // The lane predicates are read back from the two masks: recomparing q would make the
-        // compiler keep each compare's result beside its ballot, a scalar copy per live pair.
-        const bool clamp_a = __builtin_amdgcn_inverse_ballot_w64(m_a);
-        const bool clamp_q = __builtin_amdgcn_inverse_ballot_w64(m_q);
-        const bool keep_a = !(clamp_a && attr.x >= kQAlphaMaxLo);
-        const bool keep_g = keep_a && !clamp_q;
-#pragma unroll
-        for (int k = 0; k < 5; ++k) s[k] = keep_g ? s[k] : 0.f;
-        s[5] = keep_a ? s[5] : 0.f;
+    // reaches the geometry through a clamped (positive) power.
+    if ((__builtin_amdgcn_ballot_w64(q > m) & live) != 0ull) {
+        const bool keep_a = !(q > kQAlphaMaxLo && attr.x > kQAlphaMaxLo);
+        const bool keep_g = keep_a && !(q > attr.x);
+        // a clamped power still passes its gradient to the opacity (dL/do = alpha/o dL/dalpha):
+        // those lanes' part of that sum is added here, apart from the geometry's
+        float e = keep_a && !keep_g ? da : 0.f;
+        da = keep_g ? da : 0.f;
+        e = swap_add32(e, e);
+        e = swap_add16(e, e);
+        e = dpp_add2<kDppRowRor8>(e, e);
+        e = dpp_add2<kDppRowHalfMirror>(e, e);
+        e = dpp_add2<kDppQuadRev>(e, e);
+        e = dpp_add2<kDppQuadSwap>(e, e);
+        if (L.l == 0) atomicAdd(acc, e);                 // lane 0's word is the opacity sum
     }
-    float rab, rc;
-    wave_sum9(s, L.l, rab, rc);
-    if constexpr (kDet) {
-        if ((L.l & 7) == 0) {
-            // acc is this lane's word of the Gaussian's sums (see sum_word); lane 0's is word 0
-            *acc = rab;
-            if (L.l == 0) acc[8] = rc;
-        }
-    } else {
-        // one LDS atomic for all nine sums: lane 1 adds s8 (its acc points at word 8)
-        const float val = L.l == 1 ? rc : rab;
-        if ((L.l & 7) == 0 || L.l == 1) atomicAdd(acc, val);
-    }
+    const float dx = bw.x - L.px, dy = bw.y - L.py;
+    const float sum = wave_grads(da, dx, dy, wc * st.gr, wc * st.gg, wc * st.gb, L.l);
+    // one LDS atomic for all nine sums
+    if (sum_leader(L.l)) atomicAdd(acc, sum);
 }
 
-// Sum of 4 values over the wavefront (wave_sum9's first stages on two value pairs): lanes 16r ..
+// Sum of 4 values over the wavefront (two value pairs share each swap): lanes 16r ..
 // 16r + 15 of the result hold s[{0,2,1,3}[r]]. Every lane must be active.
 __device__ inline float wave_sum4(const float (&s)[4]) {
     float x0 = s[0], x2 = s[2];
@@ -908,7 +919,7 @@ __device__ inline void bwd_tile(const ViewDesc &v, int64_t tile, Stage<M, NB> &S
     const uint32_t *plist = v.point_list;
     const uint32_t n = uint32_t(v.n);
     const Attrs<kPacked> src(v);
-    const Lane L = lane_setup(tile, v.gx, v.W, v.H);
+    const Lane L = lane_setup<!kMM>(tile, v.gx, v.W, v.H);
     const int word = sum_word(L.l);   // the sum this lane adds when it leads a reduction
     const float xc = float(int(tile % v.gx) * kTile) + 7.5f, yc = float(int(tile / v.gx) * kTile) + 7.5f;
     typename Op<M>::vec bhi, blo;
@@ -1087,8 +1098,7 @@ __device__ inline void bwd_tile(const ViewDesc &v, int64_t tile, Stage<M, NB> &S
             // the group's sums, Gaussian 0 (deterministic: this wavefront's slice)
             float *accw = kDet ? det->v[buf][L.w] + g * kGroup * kGrad
                                : acc_->slot(buf, g * kGroup);
-            // this lane's word (VALU reduction; with atomics lane 1 adds word 8)
-            float *acc = accw + (kMM ? 0 : !kDet && L.l == 1 ? 8 : word);
+            float *acc = accw + (kMM ? 0 : word);   // this lane's word (VALU reduction)
             const int rel = st.last - (base + g * kGroup);   // positions < last are in range
             // the whole group is in range for every lane (the common case once past the lanes'
             // last contributors; never for a partial tile, whose outside lanes have last = 0)
@@ -1130,13 +1140,13 @@ __device__ inline void bwd_tile(const ViewDesc &v, int64_t tile, Stage<M, NB> &S
 #pragma unroll
                 for (int u = kGroup - 1; u >= 0; --u) {
                     if (((reach >> u) & 1u) == 0u) continue;
-                    reverse_pair<false, kDet>(q_of(u), true, ga, gb, u, L, st, acc + u * kGrad);
+                    reverse_pair<false>(q_of(u), true, ga, gb, u, L, st, acc + u * kGrad);
                 }
             } else {
 #pragma unroll
                 for (int u = kGroup - 1; u >= 0; --u) {
                     if (((reach >> u) & 1u) == 0u) continue;
-                    reverse_pair<true, kDet>(q_of(u), u < rel, ga, gb, u, L, st, acc + u * kGrad);
+                    reverse_pair<true>(q_of(u), u < rel, ga, gb, u, L, st, acc + u * kGrad);
                 }
             }
         }
