@@ -981,9 +981,12 @@ __device__ inline void bwd_tile(const ViewDesc &v, int64_t tile, Stage<M, NB> &S
     };
     // Wavefront w flushes slots [w NB/4, (w + 1) NB/4). It lists the slots that
     // received a nonzero sum, in slot order, and then spreads their nine sums over its lanes,
-    // item j the sum j % 9 of listed slot j / 9, so that consecutive lanes add consecutive words
-    // of one Gaussian (a wavefront's atomic instruction reaches about 30 cache lines instead of
-    // 64) and no lane is spent on the slots without a sum (over half of a 3-sigma list's). Each
+    // seven listed slots at a time: lane l < 63 adds sum l % 9 of slot l / 9, so that consecutive
+    // lanes add consecutive words of one Gaussian (a wavefront's atomic instruction reaches about
+    // 30 cache lines instead of 64), no lane is spent on the slots without a sum (over half of a
+    // 3-sigma list's; six of a wavefront's 32 slots are listed on average on the 4K frame), and
+    // the array and word that a lane adds to are the same for every slot: found once per tile, not
+    // once per sum (@@). Each
     // item is zeroed by the lane that reads it (an unlisted slot's sums are all +-0 already),
     // ready for batch bb - 2, which reuses the buffers after the next barrier.
     // Deterministic form: word k < 9 of slot i's row is the four wavefronts' sum k added in
@@ -1009,6 +1012,12 @@ __device__ inline void bwd_tile(const ViewDesc &v, int64_t tile, Stage<M, NB> &S
             if (j < items) dst[j] = sum;
         }
     };
+    constexpr int kItemSlots = 64 / kGrad;
+    const int item_slot = L.l < kItemSlots * kGrad ? L.l / kGrad : NB, item_k = L.l % kGrad;
+    float *const item_dst = item_k < 3 ? v.dL_dconics + item_k
+                          : item_k < 5 ? v.dL_dmeans2d + (item_k - 3)
+                          : item_k == 5 ? v.dL_dopacity : v.dL_dcolors + (item_k - 6);
+    const uint32_t item_stride = item_k < 3 ? 3 : item_k < 5 ? 2 : item_k == 5 ? 1 : 3;
     const auto flush = [&](int bb) {     // batch bb's sums, accumulator buffer bb & 1
         if constexpr (kDet) {
             flush_det(bb);
@@ -1033,22 +1042,14 @@ __device__ inline void bwd_tile(const ViewDesc &v, int64_t tile, Stage<M, NB> &S
         const unsigned long long m = __ballot(touched);
         if (touched) list[__popcll(m & ((1ull << L.l) - 1ull))] = uint16_t(s0 + L.l);
         __builtin_amdgcn_wave_barrier();   // the list is written and read by this wavefront only
-        const int items = kGrad * __popcll(m);
+        const int listed = __popcll(m);
 #pragma unroll 1
-        for (int j = L.l; j < items; j += 64) {
-            const int i = j / kGrad, k = j - kGrad * i;
+        for (int i = item_slot; i < listed; i += kItemSlots) {
             const int slot = list[i];
-            float *p = acc + slot * kGrad + k;
+            float *p = acc + slot * kGrad + item_k;
             const float val = *p;
             *p = 0.f;
-            if (val != 0.f) {
-                const int64_t id = ids[slot];
-                float *dst = k < 3 ? v.dL_dconics + 3 * id + k
-                           : k < 5 ? v.dL_dmeans2d + 2 * id + (k - 3)
-                           : k == 5 ? v.dL_dopacity + id
-                                    : v.dL_dcolors + 3 * id + (k - 6);
-                unsafeAtomicAdd(dst, val);
-            }
+            if (val != 0.f) unsafeAtomicAdd(item_dst + size_t(ids[slot]) * item_stride, val);
         }
     };
     GRaw nxt = src.fetch(entry(nb - 1).id(), n);
