@@ -152,6 +152,9 @@ struct BwdAcc {
     float v[2][NB * kGrad];
     // each wavefront's list of the slots with a nonzero sum, built when it flushes
     uint16_t list[kBlock / 64][64];
+    // where lane l of a flush adds: the word l % 9 of its Gaussian, from `dst` at `stride` floats
+    // per Gaussian (the same for the whole tile; kept here, not in three registers per lane)
+    struct Item { float *dst; uint32_t stride, pad; } item[64];
     __device__ float *slot(int ab, int t) { return v[ab] + t * kGrad; }
 };
 
@@ -374,14 +377,14 @@ struct Lane {
 // kByCol: lane l holds pixel (l / 8, l % 8) of the quadrant instead of (l % 8, l / 8), which the
 // backward's reduction needs (wave_grads).
 template <bool kByCol>
-__device__ inline Lane lane_setup(int64_t tile, int gx, int W, int H) {
+__device__ inline Lane lane_setup(int tid, TileXY tile, int W, int H) {
     Lane L;
-    L.t = threadIdx.x; L.w = L.t >> 6; L.l = L.t & 63;
+    L.t = tid; L.w = L.t >> 6; L.l = L.t & 63;
     // wave w owns the 8x8 quadrant (w & 1, w >> 1) of the tile: compact footprints touch fewer
     // waves than with 4-row strips, so fewer (Gaussian, wave) pairs have work
     L.col = 8 * (L.w & 1) + (kByCol ? L.l >> 3 : L.l & 7);
     L.row = 8 * (L.w >> 1) + (kByCol ? L.l & 7 : L.l >> 3);
-    const int x0 = int(tile % gx) * kTile, y0 = int(tile / gx) * kTile;
+    const int x0 = tile.x * kTile, y0 = tile.y * kTile;
     L.px = float(x0 + L.col); L.py = float(y0 + L.row);
     L.inside = (x0 + L.col < W) && (y0 + L.row < H);
     const int i = L.l & 31, h = L.l >> 5;
@@ -505,21 +508,22 @@ __device__ inline void composite_group(const float4 *attr, int base, uint32_t re
 // Forward of one tile of one view (all 256 threads of the block take part; block-uniform control
 // flow around every barrier).
 template <Mode M, int NB, bool kPacked = false>
-__device__ inline void fwd_tile(const ViewDesc &v, int64_t tile, Stage<M, NB> &S) {
+__device__ inline void fwd_tile(const ViewDesc &v, TileXY tile, Stage<M, NB> &S,
+                                int tid = threadIdx.x) {
     static_assert(NB % kGroup == 0 && NB <= kBlock, "batch must be whole groups, <= block");
     constexpr int kGroups = NB / kGroup;
     const uint32_t *plist = v.point_list;
     const uint32_t n = uint32_t(v.n);
     const Attrs<kPacked> src(v);
-    const Lane L = lane_setup<false>(tile, v.gx, v.W, v.H);
-    const float xc = float(int(tile % v.gx) * kTile) + 7.5f, yc = float(int(tile / v.gx) * kTile) + 7.5f;
+    const Lane L = lane_setup<false>(tid, tile, v.W, v.H);
+    const float xc = float(tile.x * kTile) + 7.5f, yc = float(tile.y * kTile) + 7.5f;
     typename Op<M>::vec bhi, blo;
     pixel_basis<M>(L, bhi, blo);
     if (L.t == 0) {
         float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         if constexpr (M != Mode::Plain) S.zero_hi = S.zero_lo = Op<M>::cvt(z);
     }
-    const uint2 rg = reinterpret_cast<const uint2 *>(v.ranges)[tile];
+    const uint2 rg = reinterpret_cast<const uint2 *>(v.ranges)[tile.y * v.gx + tile.x];
     // without Gaussians every list entry would be invalid: the tile shows the background
     const int64_t start = rg.x, len = n == 0 ? 0 : int64_t(rg.y) - int64_t(rg.x);
     const int nb = int((len + NB - 1) / NB);
@@ -910,18 +914,18 @@ __device__ inline void mm_reduce(uint32_t (*rows)[kDgStride], const h8 (&B)[2], 
 // writes each list position's nine sums to v.det_partial in place of the global atomics (every
 // position of the tile's list is written, those past the last contributor with zeros).
 template <Mode M, int NB, bool kMM, bool kPacked = false, bool kDet = false>
-__device__ inline void bwd_tile(const ViewDesc &v, int64_t tile, Stage<M, NB> &S, StageBwd<NB> &SB,
+__device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, Stage<M, NB> &S, StageBwd<NB> &SB,
                                 BwdAcc<NB> *acc_, int &s_maxlast, BwdMM *mm,
-                                BwdAccDet<NB> *det = nullptr) {
+                                BwdAccDet<NB> *det = nullptr, int tid = threadIdx.x) {
     static_assert(NB % kGroup == 0 && NB <= kBlock, "batch must be whole groups, <= block");
     static_assert(!(kMM && kDet), "the deterministic backward reduces on the vector ALUs");
     constexpr int kGroups = NB / kGroup;
     const uint32_t *plist = v.point_list;
     const uint32_t n = uint32_t(v.n);
     const Attrs<kPacked> src(v);
-    const Lane L = lane_setup<!kMM>(tile, v.gx, v.W, v.H);
+    const Lane L = lane_setup<!kMM>(tid, tile, v.W, v.H);
     const int word = sum_word(L.l);   // the sum this lane adds when it leads a reduction
-    const float xc = float(int(tile % v.gx) * kTile) + 7.5f, yc = float(int(tile / v.gx) * kTile) + 7.5f;
+    const float xc = float(tile.x * kTile) + 7.5f, yc = float(tile.y * kTile) + 7.5f;
     typename Op<M>::vec bhi, blo;
     pixel_basis<M>(L, bhi, blo);
     if (L.t == 0) {
@@ -951,7 +955,7 @@ __device__ inline void bwd_tile(const ViewDesc &v, int64_t tile, Stage<M, NB> &S
     __syncthreads();
     if (st.last > 0) atomicMax(&s_maxlast, st.last);
     __syncthreads();
-    const uint2 rg = reinterpret_cast<const uint2 *>(v.ranges)[tile];
+    const uint2 rg = reinterpret_cast<const uint2 *>(v.ranges)[tile.y * v.gx + tile.x];
     const int64_t start = rg.x;
     // positions [0, max last) are the only ones that matter (never more than the list holds)
     // (the same value in every lane: made wavefront-uniform, so that the batch and group loops
@@ -1014,10 +1018,13 @@ __device__ inline void bwd_tile(const ViewDesc &v, int64_t tile, Stage<M, NB> &S
     };
     constexpr int kItemSlots = 64 / kGrad;
     const int item_slot = L.l < kItemSlots * kGrad ? L.l / kGrad : NB, item_k = L.l % kGrad;
-    float *const item_dst = item_k < 3 ? v.dL_dconics + item_k
-                          : item_k < 5 ? v.dL_dmeans2d + (item_k - 3)
-                          : item_k == 5 ? v.dL_dopacity : v.dL_dcolors + (item_k - 6);
-    const uint32_t item_stride = item_k < 3 ? 3 : item_k < 5 ? 2 : item_k == 5 ? 1 : 3;
+    if constexpr (!kDet) {
+        if (L.t < 64)            // (ordered before the first flush by the batch loop's barrier)
+            acc_->item[L.t] = {item_k < 3 ? v.dL_dconics + item_k
+                               : item_k < 5 ? v.dL_dmeans2d + (item_k - 3)
+                               : item_k == 5 ? v.dL_dopacity : v.dL_dcolors + (item_k - 6),
+                               item_k < 3 ? 3u : item_k < 5 ? 2u : item_k == 5 ? 1u : 3u, 0u};
+    }
     const auto flush = [&](int bb) {     // batch bb's sums, accumulator buffer bb & 1
         if constexpr (kDet) {
             flush_det(bb);
@@ -1043,13 +1050,14 @@ __device__ inline void bwd_tile(const ViewDesc &v, int64_t tile, Stage<M, NB> &S
         if (touched) list[__popcll(m & ((1ull << L.l) - 1ull))] = uint16_t(s0 + L.l);
         __builtin_amdgcn_wave_barrier();   // the list is written and read by this wavefront only
         const int listed = __popcll(m);
+        const auto item = s_acc.item[L.l];
 #pragma unroll 1
         for (int i = item_slot; i < listed; i += kItemSlots) {
             const int slot = list[i];
             float *p = acc + slot * kGrad + item_k;
             const float val = *p;
             *p = 0.f;
-            if (val != 0.f) unsafeAtomicAdd(item_dst + size_t(ids[slot]) * item_stride, val);
+            if (val != 0.f) unsafeAtomicAdd(item.dst + size_t(ids[slot]) * item.stride, val);
         }
     };
     GRaw nxt = src.fetch(entry(nb - 1).id(), n);
@@ -1188,13 +1196,17 @@ template <bool kMM> __device__ inline BwdMM *mm_ptr(MMTiles<kMM> &t) {
 template <Mode M, bool kMM> constexpr int waves_bwd_tile() {
     return kMM ? (M == Mode::Plain ? 5 : 4) : (M == Mode::Plain ? 7 : 5);
 }
-// Single view: block b renders tile xcd_tile(b).
+__device__ inline TileXY view_tile(const ViewDesc &v, uint32_t rank) {
+    return strip_tile(rank, uint32_t(v.gx), uint32_t(v.H + kTile - 1) / kTile);
+}
+// Single view: block b renders the tile of rank xcd_rank(b).
 template <Mode M, int NB>
 __global__ __launch_bounds__(kBlock, fit_waves(M == Mode::Plain ? 8 : 7, lds_fwd<M, NB>()))
 void k_blend_fwd(ViewDesc v) {
     __shared__ Stage<M, NB> S;
-    const int64_t tile = xcd_tile(blockIdx.x, v.n_tiles, v.gx);
-    if (tile >= v.n_tiles) return;
+    const uint32_t rank = xcd_rank(blockIdx.x, uint32_t(v.n_tiles));
+    if (rank >= uint32_t(v.n_tiles)) return;
+    const TileXY tile = view_tile(v, rank);
     fwd_tile<M, NB>(v, tile, S);
 }
 
@@ -1206,8 +1218,9 @@ void k_blend_bwd(ViewDesc v) {
     __shared__ BwdAcc<NB> s_acc;   // per-Gaussian gradient sums of the current batch
     __shared__ MMTiles<kMM> s_mm;
     __shared__ int s_maxlast;
-    const int64_t tile = xcd_tile(blockIdx.x, v.n_tiles, v.gx);
-    if (tile >= v.n_tiles) return;
+    const uint32_t rank = xcd_rank(blockIdx.x, uint32_t(v.n_tiles));
+    if (rank >= uint32_t(v.n_tiles)) return;
+    const TileXY tile = view_tile(v, rank);
     bwd_tile<M, NB, kMM>(v, tile, S, SB, &s_acc, s_maxlast, mm_ptr<kMM>(s_mm));
 }
 
@@ -1217,8 +1230,9 @@ template <Mode M>
 __global__ __launch_bounds__(kBlock, fit_waves(M == Mode::Plain ? 8 : 7, lds_fwd<M, 128>()))
 void k_blend_fwd_rec(ViewDesc v) {
     __shared__ Stage<M, 128> S;
-    const int64_t tile = xcd_tile(blockIdx.x, v.n_tiles, v.gx);
-    if (tile >= v.n_tiles) return;
+    const uint32_t rank = xcd_rank(blockIdx.x, uint32_t(v.n_tiles));
+    if (rank >= uint32_t(v.n_tiles)) return;
+    const TileXY tile = view_tile(v, rank);
     fwd_tile<M, 128, true>(v, tile, S);
 }
 
@@ -1229,8 +1243,9 @@ void k_blend_bwd_rec(ViewDesc v) {
     __shared__ StageBwd<128> SB;
     __shared__ BwdAcc<128> s_acc;
     __shared__ int s_maxlast;
-    const int64_t tile = xcd_tile(blockIdx.x, v.n_tiles, v.gx);
-    if (tile >= v.n_tiles) return;
+    const uint32_t rank = xcd_rank(blockIdx.x, uint32_t(v.n_tiles));
+    if (rank >= uint32_t(v.n_tiles)) return;
+    const TileXY tile = view_tile(v, rank);
     bwd_tile<M, 128, false, true>(v, tile, S, SB, &s_acc, s_maxlast, nullptr);
 }
 
@@ -1248,8 +1263,9 @@ void k_blend_bwd_det(ViewDesc v) {
     __shared__ StageBwd<kDetBatch> SB;
     __shared__ BwdAccDet<kDetBatch> s_det;
     __shared__ int s_maxlast;
-    const int64_t tile = xcd_tile(blockIdx.x, v.n_tiles, v.gx);
-    if (tile >= v.n_tiles) return;
+    const uint32_t rank = xcd_rank(blockIdx.x, uint32_t(v.n_tiles));
+    if (rank >= uint32_t(v.n_tiles)) return;
+    const TileXY tile = view_tile(v, rank);
     bwd_tile<M, kDetBatch, false, true, true>(v, tile, S, SB, nullptr, s_maxlast, nullptr, &s_det);
 }
 
@@ -1364,14 +1380,33 @@ struct Queues {
 
 __device__ inline int64_t band_lo(int64_t n_tiles, int x) { return n_tiles * x / kXcds; }
 
-__device__ inline int64_t uniform_i64(int64_t x) {
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(uint64_t(x)));
-    const uint32_t hi = __builtin_amdgcn_readfirstlane(uint32_t(uint64_t(x) >> 32));
-    return int64_t((uint64_t(hi) << 32) | lo);
+// The descriptor of a (block-uniform) view, read through the constant address space: no kernel
+// writes the table, and only so does the compiler read it with scalar loads into scalar registers
+// also inside the persistent loop, whose stores might alias it otherwise.
+__device__ inline ViewDesc load_view(const Queues &Q, int view) {
+    typedef const __attribute__((address_space(4))) uint32_t *ConstWords;
+    static_assert(sizeof(ViewDesc) % 4 == 0, "copied by words");
+    constexpr int kWords = int(sizeof(ViewDesc) / 4);
+    const ConstWords src = (ConstWords)(reinterpret_cast<const uint32_t *>(Q.views + view));
+    uint32_t w[kWords];
+#pragma unroll
+    for (int k = 0; k < kWords; ++k) w[k] = src[k];
+    ViewDesc vd;
+    __builtin_memcpy(&vd, w, sizeof(vd));
+    return vd;
+}
+
+// The thread's index, opaque to the compiler in each iteration of the persistent loop: what a tile
+// derives from it (pixel coordinates, bases, masks) is formed again per tile instead of being kept
+// in registers across the loop.
+__device__ inline int loop_tid() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
 }
 
 // Next item for the calling block (thread 0 only): returns false when every queue is drained.
-__device__ inline bool next_item(const Queues &Q, int &q, int &tried, int &view, int64_t &tile) {
+__device__ inline bool next_item(const Queues &Q, int &q, int &tried, int &view, uint32_t &rank) {
     while (tried < kXcds) {
         const int64_t *pre = Q.prefix + int64_t(q) * (Q.n_views + 1);
         const int64_t total = pre[Q.n_views];
@@ -1383,8 +1418,7 @@ __device__ inline bool next_item(const Queues &Q, int &q, int &tried, int &view,
                 if (pre[mid] <= i) lo = mid; else hi = mid - 1;
             }
             view = lo;
-            const ViewDesc &vw = Q.views[lo];
-            tile = strip_tile(band_lo(vw.n_tiles, q) + (i - pre[lo]), vw.n_tiles, vw.gx);
+            rank = uint32_t(band_lo(Q.views[lo].n_tiles, q) + (i - pre[lo]));
             return true;
         }
         q = (q + 1) % kXcds;
@@ -1396,33 +1430,33 @@ __device__ inline bool next_item(const Queues &Q, int &q, int &tried, int &view,
 // Register budgets for the persistent kernels (waves per SIMD): left alone the compiler spreads
 // their registers over the loop and gives up a wave or more against the single-view kernels;
 // these are the highest targets reached without spilling.
-template <Mode M> constexpr int waves_fwd() { return M == Mode::Plain ? 7 : 4; }
-template <Mode M> constexpr int waves_bwd() { return M == Mode::Plain ? 5 : 4; }
+template <Mode M> constexpr int waves_fwd() { return M == Mode::Plain ? 8 : 7; }
+template <Mode M> constexpr int waves_bwd() { return M == Mode::Plain ? 6 : 5; }
 
 template <Mode M, int NB>
 __global__ __launch_bounds__(kBlock, fit_waves(waves_fwd<M>(), lds_fwd<M, NB>()))
 void k_blend_fwd_batched(Queues Q) {
     __shared__ Stage<M, NB> S;
     __shared__ int s_view;
-    __shared__ int64_t s_tile;
+    __shared__ uint32_t s_rank;
     int q = int(blockIdx.x % kXcds), tried = 0;
     for (;;) {
         if (threadIdx.x == 0) {
             int view = -1;
-            int64_t tile = 0;
-            if (!next_item(Q, q, tried, view, tile)) view = -1;
+            uint32_t rank = 0;
+            if (!next_item(Q, q, tried, view, rank)) view = -1;
             s_view = view;
-            s_tile = tile;
+            s_rank = rank;
         }
         __syncthreads();
         // the item is block-uniform: move it to scalar registers so the view descriptor is read
         // with scalar loads and its pointers stay in SGPRs
         const int view = __builtin_amdgcn_readfirstlane(s_view);
-        const int64_t tile = uniform_i64(s_tile);
+        const uint32_t rank = __builtin_amdgcn_readfirstlane(s_rank);
         __syncthreads();
         if (view < 0) break;
-        const ViewDesc vd = Q.views[view];
-        fwd_tile<M, NB>(vd, tile, S);
+        const ViewDesc vd = load_view(Q, view);
+        fwd_tile<M, NB>(vd, view_tile(vd, rank), S, loop_tid());
         __syncthreads();
     }
 }
@@ -1436,23 +1470,24 @@ void k_blend_bwd_batched(Queues Q) {
     __shared__ MMTiles<kMM> s_mm;
     __shared__ int s_maxlast;
     __shared__ int s_view;
-    __shared__ int64_t s_tile;
+    __shared__ uint32_t s_rank;
     int q = int(blockIdx.x % kXcds), tried = 0;
     for (;;) {
         if (threadIdx.x == 0) {
             int view = -1;
-            int64_t tile = 0;
-            if (!next_item(Q, q, tried, view, tile)) view = -1;
+            uint32_t rank = 0;
+            if (!next_item(Q, q, tried, view, rank)) view = -1;
             s_view = view;
-            s_tile = tile;
+            s_rank = rank;
         }
         __syncthreads();
         const int view = __builtin_amdgcn_readfirstlane(s_view);
-        const int64_t tile = uniform_i64(s_tile);
+        const uint32_t rank = __builtin_amdgcn_readfirstlane(s_rank);
         __syncthreads();
         if (view < 0) break;
-        const ViewDesc vd = Q.views[view];
-        bwd_tile<M, NB, kMM>(vd, tile, S, SB, &s_acc, s_maxlast, mm_ptr<kMM>(s_mm));
+        const ViewDesc vd = load_view(Q, view);
+        bwd_tile<M, NB, kMM>(vd, view_tile(vd, rank), S, SB, &s_acc, s_maxlast,
+                             mm_ptr<kMM>(s_mm), nullptr, loop_tid());
         __syncthreads();
     }
 }
@@ -1461,7 +1496,7 @@ void k_blend_bwd_batched(Queues Q) {
 // dispatcher places block b on XCD b % 8 and hands out blocks in index order, so each XCD still
 // walks its own bands heaviest view first). No loop state: registers as in the single-view
 // kernels.
-__device__ inline bool grid_item(const Queues &Q, int64_t b, int &view, int64_t &tile) {
+__device__ inline bool grid_item(const Queues &Q, int64_t b, int &view, uint32_t &rank) {
     const int x = int(b % kXcds);
     const int64_t i = b / kXcds;
     const int64_t *pre = Q.prefix + int64_t(x) * (Q.n_views + 1);
@@ -1472,8 +1507,7 @@ __device__ inline bool grid_item(const Queues &Q, int64_t b, int &view, int64_t 
         if (pre[mid] <= i) lo = mid; else hi = mid - 1;
     }
     view = lo;
-    const ViewDesc &vw = Q.views[lo];
-    tile = strip_tile(band_lo(vw.n_tiles, x) + (i - pre[lo]), vw.n_tiles, vw.gx);
+    rank = uint32_t(band_lo(Q.views[lo].n_tiles, x) + (i - pre[lo]));
     return true;
 }
 
@@ -1482,10 +1516,10 @@ __global__ __launch_bounds__(kBlock, fit_waves(M == Mode::Plain ? 8 : 7, lds_fwd
 void k_blend_fwd_grid(Queues Q) {
     __shared__ Stage<M, NB> S;
     int view;
-    int64_t tile;
-    if (!grid_item(Q, blockIdx.x, view, tile)) return;
-    const ViewDesc vd = Q.views[view];
-    fwd_tile<M, NB>(vd, tile, S);
+    uint32_t rank;
+    if (!grid_item(Q, blockIdx.x, view, rank)) return;
+    const ViewDesc vd = load_view(Q, view);
+    fwd_tile<M, NB>(vd, view_tile(vd, rank), S);
 }
 
 template <Mode M, int NB, bool kMM>
@@ -1497,10 +1531,10 @@ void k_blend_bwd_grid(Queues Q) {
     __shared__ MMTiles<kMM> s_mm;
     __shared__ int s_maxlast;
     int view;
-    int64_t tile;
-    if (!grid_item(Q, blockIdx.x, view, tile)) return;
-    const ViewDesc vd = Q.views[view];
-    bwd_tile<M, NB, kMM>(vd, tile, S, SB, &s_acc, s_maxlast, mm_ptr<kMM>(s_mm));
+    uint32_t rank;
+    if (!grid_item(Q, blockIdx.x, view, rank)) return;
+    const ViewDesc vd = load_view(Q, view);
+    bwd_tile<M, NB, kMM>(vd, view_tile(vd, rank), S, SB, &s_acc, s_maxlast, mm_ptr<kMM>(s_mm));
 }
 
 // Raw sums -> gradients of the stored scalars: d/dA = -S_xx/2, d/dB = -S_xy, d/dC = -S_yy/2,

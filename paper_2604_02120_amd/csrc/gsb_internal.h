@@ -34,19 +34,21 @@ inline int64_t xcd_grid(int64_t n_tiles) {
     const int64_t chunk = (n_tiles + kXcds - 1) / kXcds;
     return chunk * kXcds;
 }
-// Tile of rank r (< n_tiles) of the strip order on a grid gx tiles wide.
-__device__ inline int64_t strip_tile(int64_t r, int64_t n_tiles, int64_t gx) {
-    const int64_t gy = n_tiles / gx;
-    const int64_t s = r / (kStrip * gx), r0 = s * kStrip;
-    const int64_t hs = gy - r0 < kStrip ? gy - r0 : kStrip;   // rows of this strip
-    const int64_t j = r - s * kStrip * gx;
-    return (r0 + j % hs) * gx + j / hs;
+// Column and row of the tile of rank r (< gx * gy) of the strip order on a gx x gy grid. 32-bit
+// arithmetic (a grid has at most 4096 x 4096 tiles), one division for the strip and, in a last strip
+// of fewer than kStrip rows, one more: every block starts with this, and as 64-bit divisions of the
+// tile index it took about 500 scalar instructions before a wavefront's first load.
+struct TileXY { int32_t x, y; };
+__device__ inline TileXY strip_tile(uint32_t r, uint32_t gx, uint32_t gy) {
+    const uint32_t s = r / (kStrip * gx), r0 = s * kStrip, j = r - r0 * gx;
+    if (gy - r0 >= kStrip) return TileXY{int32_t(j / kStrip), int32_t(r0 + j % kStrip)};
+    const uint32_t hs = gy - r0, x = j / hs;                 // rows of this strip
+    return TileXY{int32_t(x), int32_t(r0 + (j - x * hs))};
 }
-// Tile of block `block` (>= n_tiles: past the end).
-__device__ inline int64_t xcd_tile(int64_t block, int64_t n_tiles, int64_t gx) {
-    const int64_t chunk = (n_tiles + kXcds - 1) / kXcds;
-    const int64_t r = (block % kXcds) * chunk + block / kXcds;
-    return r < n_tiles ? strip_tile(r, n_tiles, gx) : r;
+// Rank of block `block` (>= n_tiles: past the end).
+__device__ inline uint32_t xcd_rank(uint32_t block, uint32_t n_tiles) {
+    const uint32_t chunk = (n_tiles + kXcds - 1) / kXcds;
+    return (block % kXcds) * chunk + block / kXcds;
 }
 
 // Covered tiles [tx0, tx1) x [ty0, ty1) of a Gaussian at (x, y) with radius r: tx in
