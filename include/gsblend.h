@@ -302,9 +302,9 @@ gsb_status gsb_blend_backward_deterministic(
  * Batched views: many images (views) of uneven size, each with its own Gaussians and binning,
  * blended by ONE launch per direction. The (view, tile) items form 8 queues, one per XCD of the
  * MI355X (each XCD takes a contiguous band of every view), views in order of decreasing Gaussians
- * per tile (heaviest first). By default the launch is persistent: resident blocks pull items from
- * their own XCD's queue and take items from the others once it runs dry; GSB_LAUNCH_GRID instead
- * launches one block per item in the same order. The per-tile computation is exactly gsb_blend_forward /
+ * per tile (heaviest first). The launch is either persistent (resident blocks pull items from
+ * their own XCD's queue and take items from the others once it runs dry) or one block per item in
+ * the same order (GSB_LAUNCH_GRID), as the tuning says; without a tuning the library chooses. The per-tile computation is exactly gsb_blend_forward /
  * gsb_blend_backward's, so each view's results equal the single-view calls'.
  *
  * A plan holds the view table (device copy), the queue counters and the launch shape. Those are
@@ -327,7 +327,7 @@ typedef struct gsb_view {
     float *dL_dmeans2d, *dL_dconics, *dL_dopacity, *dL_dcolors;   /* backward outputs */
 } gsb_view;
 
-/* Launch shape. Zero fields take the defaults. */
+/* Launch shape. Zero fields take the defaults in parentheses. */
 #define GSB_LAUNCH_PERSISTENT 0   /* resident blocks pull items from the per-XCD queues */
 #define GSB_LAUNCH_GRID 1         /* one block per item: block b takes item b/8 of queue b%8 */
 /* How the backward sums each Gaussian's per-pixel gradient terms over a wavefront's 64 pixels:
@@ -350,7 +350,7 @@ typedef struct gsb_plan_s *gsb_plan;
 
 /* Validates every view as gsb_blend_forward / gsb_blend_backward would (all outputs, including
  * the gradients, must be given), uploads the view table and sizes the persistent grids.
- * tuning may be NULL. On error *plan is NULL and nothing is allocated.
+ * tuning may be NULL (the library then chooses the launch shape). On error *plan is NULL and nothing is allocated.
  * Errors: INVALID, UNSUPPORTED, HIP. */
 gsb_status gsb_plan_create(const gsb_view *views, int32_t n_views, gsb_precision prec,
                            const gsb_tuning *tuning, gsb_plan *plan);

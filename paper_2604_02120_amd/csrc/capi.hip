@@ -402,7 +402,11 @@ gsb_status gsb_plan_create(const gsb_view *views, int32_t n_views, gsb_precision
     GSB_REQUIRE(prec_base(prec) == GSB_FP32_PLAIN || prec_base(prec) == GSB_FP16_GEMM ||
                     prec_base(prec) == GSB_BF16_GEMM,
                 "unknown precision %d", int(prec));
-    Tuning t{kDefaultBatchFwd, kDefaultBatchBwd, 0, kLaunchPersistent, 0};
+    // Without a tuning the library chooses one block per item: the hardware starts the next block
+    // as each wavefront of the last one ends, while a persistent block's four wavefronts wait for
+    // the slowest at every tile (8 views of 300k Gaussians: forward 0.96 ms persistent, 0.86 with a
+    // block per item; backward 2.08 and 2.01). A tuning's launch field is taken as it is.
+    Tuning t{kDefaultBatchFwd, kDefaultBatchBwd, 0, kLaunchGrid, 0};
     if (tuning) {
         if (tuning->batch_fwd) t.batch_fwd = tuning->batch_fwd;
         if (tuning->batch_bwd) t.batch_bwd = tuning->batch_bwd;
