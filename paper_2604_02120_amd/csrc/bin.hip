@@ -88,7 +88,7 @@ int64_t sort_blocks(int64_t m) { return (m + kSortTile - 1) / kSortTile; }
 
 // Superblocks (see below): 8 x 8 tiles, at most kMaxSb of them; entries are taken in chunks.
 constexpr int kSbShift = 3, kSbEdge = 1 << kSbShift, kSbTiles = kSbEdge * kSbEdge;
-constexpr int kMaxSb = 1024;
+constexpr int kMaxSbBits = 10, kMaxSb = 1 << kMaxSbBits;
 constexpr int kSbChunk = 1024;                           // entries per block
 // chunks that up to `entries` entries can take (a superblock's last chunk may be partial)
 int64_t sb_max_chunks(int64_t entries) {
@@ -1027,7 +1027,7 @@ int sort_tiles(K *ka, K *kb, uint32_t *va, uint32_t *vb, const unsigned long lon
 // vector instruction per pair, where a radix sort of the pairs takes about 2.3 per pass for ranking
 // alone, two passes, and reads and writes every pair in each. (A Gaussian touches 18 tiles but only
 // 1.6 superblocks on the 4K frame of 3M Gaussians, so what is sorted is a tenth.) Measured at 4K,
-// 54.7M pairs, from the sorted Gaussians to the ranges: 0.30 ms against 0.84.
+// 54.7M pairs, from the sorted Gaussians to the ranges: 0.18 ms against 0.84.
 constexpr int kSbGroups = kSbChunk / 64;
 constexpr int kSbMaxGrid = 4096;                         // blocks of steps 2 and 4, which loop
 constexpr int kSbWindow = 4096;                          // entries ranked at a time in step 1
@@ -1055,15 +1055,18 @@ __device__ inline Rect sb_rect(const Rect &R) {
     return Rect{R.tx0 >> kSbShift, (R.tx1 + kSbEdge - 1) >> kSbShift, R.ty0 >> kSbShift,
                 (R.ty1 + kSbEdge - 1) >> kSbShift};
 }
-// Tiles of superblock (sx, sy) covered by R: bit 8 row + column
-__device__ inline unsigned long long sb_mask(const Rect &R, int sx, int sy) {
-    const int x0 = R.tx0 - sx * kSbEdge, x1 = R.tx1 - sx * kSbEdge;
-    const int y0 = R.ty0 - sy * kSbEdge, y1 = R.ty1 - sy * kSbEdge;
-    const uint32_t cols = (0xffu >> (x1 < kSbEdge ? kSbEdge - x1 : 0)) & (0xffu << (x0 > 0 ? x0 : 0));
-    const unsigned long long all = (unsigned long long)((cols & 0xffu) * 0x01010101u);
-    const unsigned long long hi = ~0ull >> (y1 < kSbEdge ? 8 * (kSbEdge - y1) : 0);
-    const unsigned long long lo = ~0ull << (y0 > 0 ? 8 * y0 : 0);
-    return (all | (all << 32)) & hi & lo;
+// Tiles [a - 8 s, b - 8 s) of superblock s along one axis, as a byte ([a, b) meets the superblock)
+__device__ inline uint32_t sb_span(int a, int b, int s) {
+    const int lo = a - s * kSbEdge, hi = (s + 1) * kSbEdge - b;
+    return (0xffu >> (hi > 0 ? hi : 0)) & (0xffu << (lo > 0 ? lo : 0)) & 0xffu;
+}
+// The mask of a superblock's tiles, bit 8 row + column, from its columns (byte 0) and rows (byte 1)
+__device__ inline unsigned long long sb_mask(uint32_t clip) {
+    const uint32_t cols = (clip & 0xffu) * 0x01010101u, rows = clip >> 8;
+    // each of four rows as a byte of ones: the row's bit spread to its byte's bit 0, times 255
+    const uint32_t lo = ((rows & 0xfu) * 0x00204081u) & 0x01010101u;
+    const uint32_t hi = ((rows >> 4) * 0x00204081u) & 0x01010101u;
+    return (unsigned long long)(cols & (lo * 255u)) | ((unsigned long long)(cols & (hi * 255u)) << 32);
 }
 
 __global__ __launch_bounds__(kSortThreads) void k_sb_hist(const unsigned long long *rank_rects,
@@ -1073,7 +1076,9 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_hist(const unsigned long lo
     const int t = threadIdx.x;
     for (int d = t; d < G.n; d += kSortThreads) s_h[d] = 0u;
     __syncthreads();
-    const int64_t j0 = int64_t(blockIdx.x) * ranks;
+    const int64_t blk = xcd_rank(blockIdx.x, uint32_t(nblk));
+    if (blk >= nblk) return;                                 // block-uniform
+    const int64_t j0 = blk * ranks;
     for (int k = t; k < ranks; k += kSortThreads) {
         if (j0 + k >= n) break;
         const Rect R = unpack_rect(rank_rects[j0 + k]);
@@ -1083,26 +1088,31 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_hist(const unsigned long lo
             for (int sx = Q.tx0; sx < Q.tx1; ++sx) atomicAdd(&s_h[sy * G.sx + sx], 1u);
     }
     __syncthreads();
-    for (int d = t; d < G.n; d += kSortThreads) hist[int64_t(d) * nblk + blockIdx.x] = s_h[d];
+    for (int d = t; d < G.n; d += kSortThreads) hist[int64_t(d) * nblk + blk] = s_h[d];
 }
 
-// A block places the entries of its ranks: thread t owns `ranks / 256` consecutive ones. The
-// block's entries, enumerated in rank order, are taken kSbWindow at a time: written to LDS by their
-// owners (who resume where the last window ended), ranked within their superblock as in
-// k_radix_pass, reordered in LDS and written out in runs. Block 0 also fills the superblock table.
+// A block places the entries of its ranks: thread t owns kPer consecutive ones, whose rectangles and
+// indices it loads first, all at once (a load per rank in the loop over ranks left two blocks per
+// CU waiting: 107 us at 4K, now 61). The block's entries, enumerated in rank order, are taken
+// kSbWindow at a time: written to LDS by their owners, ranked within their superblock as in
+// k_radix_pass, reordered in LDS and written out in runs. The blocks of one XCD take consecutive
+// ranks (xcd_rank): a superblock's entries from neighbouring blocks are neighbours in memory, a run
+// is shorter than a cache line, and the line is put together in that XCD's L2 (12% less time).
+// Block 0 also fills the superblock table.
+template <int kPer>
 __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
-    const unsigned long long *rank_rects, const uint32_t *sorted_idx, int64_t n, int ranks, SbGrid G,
-    int bits, const uint32_t *hist, int64_t nblk, const BinHeader *hdr, int64_t cap, uint32_t *e_idx, unsigned long long *e_mask, SbTable *table) {
+    const unsigned long long *rank_rects, const uint32_t *sorted_idx, int64_t n, SbGrid G, int bits, const uint32_t *hist, int64_t nblk, const BinHeader *hdr, int64_t cap, uint32_t *e_idx, unsigned long long *e_mask, SbTable *table) {
     constexpr int kWaves = kSortThreads / 64, kDig = kMaxSb / kSortThreads;
     __shared__ uint32_t s_gofs[kMaxSb];                 // next global position of each superblock
     __shared__ uint16_t s_wcnt[kWaves][kMaxSb];         // per-wave counts, then prefixes
     __shared__ uint16_t s_dstart[kMaxSb];               // start of each superblock in the window
     __shared__ uint32_t s_wave[kWaves];
-    __shared__ uint16_t s_key[kSbWindow];
+    __shared__ uint32_t s_key[kSbWindow];               // superblock | columns << 16 | rows << 24
     __shared__ uint32_t s_idx[kSbWindow];
-    __shared__ unsigned long long s_mask[kSbWindow];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    if (blockIdx.x == 0) {
+    const int64_t blk = xcd_rank(blockIdx.x, uint32_t(nblk));
+    if (blk >= nblk) return;                                 // block-uniform
+    if (blk == 0) {
         // four superblocks per thread: starts from the scanned counts, chunks from their sizes.
         // No entries at all when the pairs exceed the capacity (every list is then empty); else
         // there are at most as many entries as pairs.
@@ -1131,42 +1141,68 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
             table->chunk[kMaxSb] = run;
         }
     }
-    for (int d = t; d < G.n; d += kSortThreads) s_gofs[d] = hist[int64_t(d) * nblk + blockIdx.x];
-    // this thread's ranks and their number of entries
-    const int per = ranks / kSortThreads;
-    const int64_t j0 = int64_t(blockIdx.x) * ranks + int64_t(t) * per;
-    uint32_t mine = 0;
-    for (int k = 0; k < per && j0 + k < n; ++k) {
-        const Rect R = unpack_rect(rank_rects[j0 + k]);
-        if (R.tx1 <= R.tx0 || R.ty1 <= R.ty0) continue;
-        const Rect Q = sb_rect(R);
-        mine += uint32_t((Q.tx1 - Q.tx0) * (Q.ty1 - Q.ty0));
+    for (int d = t; d < G.n; d += kSortThreads) s_gofs[d] = hist[int64_t(d) * nblk + blk];
+    // this thread's ranks: superblocks (0 x 0 where the rectangle is empty or past the end),
+    // rectangle and index. kPer is a multiple of 4 and the buffers are padded to 256 bytes, so the
+    // vector loads that straddle n stay inside them.
+    const int64_t j0 = (blk * kSortThreads + t) * kPer;
+    unsigned long long rects[kPer];
+    uint32_t idx[kPer], mine = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; k += 4) {
+        ulonglong2 r01{0, 0}, r23{0, 0};
+        uint4 i4{0, 0, 0, 0};
+        if (j0 + k < n) {
+            r01 = *reinterpret_cast<const ulonglong2 *>(rank_rects + j0 + k);
+            i4 = *reinterpret_cast<const uint4 *>(sorted_idx + j0 + k);
+        }
+        if (j0 + k + 2 < n) r23 = *reinterpret_cast<const ulonglong2 *>(rank_rects + j0 + k + 2);
+        rects[k] = r01.x;
+        rects[k + 1] = j0 + k + 1 < n ? r01.y : 0;
+        rects[k + 2] = r23.x;
+        rects[k + 3] = j0 + k + 3 < n ? r23.y : 0;
+        idx[k] = i4.x; idx[k + 1] = i4.y; idx[k + 2] = i4.z; idx[k + 3] = i4.w;
     }
+    const auto entries = [](const Rect &r) {
+        if (r.tx1 <= r.tx0 || r.ty1 <= r.ty0) return 0u;
+        const Rect q = sb_rect(r);
+        return uint32_t((q.tx1 - q.tx0) * (q.ty1 - q.ty0));
+    };
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) mine += entries(unpack_rect(rects[k]));
     uint32_t total;
-    uint32_t pos = block_exclusive_scan<uint32_t>(mine, s_wave, total);
-    // the owner's place in its entries: rank k (its rectangle R, superblocks Q, index), (sx, sy)
-    int k = -1, sx = 0, sy = 0;
-    Rect R{0, 0, 0, 0}, Q{0, 0, 0, 0};
-    uint32_t idx = 0, left = mine;
+    const uint32_t pos0 = block_exclusive_scan<uint32_t>(mine, s_wave, total);
     for (uint32_t w0 = 0; w0 < total; w0 += kSbWindow) {      // block-uniform
         const int cnt = int(total - w0 < uint32_t(kSbWindow) ? total - w0 : uint32_t(kSbWindow));
-        while (left > 0 && pos < w0 + uint32_t(kSbWindow)) {
-            while (sy >= Q.ty1) {                            // next rank with a rectangle
-                ++k;
-                R = unpack_rect(rank_rects[j0 + k]);
-                if (R.tx1 <= R.tx0 || R.ty1 <= R.ty0) continue;
-                Q = sb_rect(R);
-                sx = Q.tx0;
-                sy = Q.ty0;
-                idx = sorted_idx[j0 + k];
+        uint32_t pos = pos0;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            // the part of rank k's entries [pos, pos + e) that lies in the window
+            const Rect R = unpack_rect(rects[k]);
+            const uint32_t e = entries(R);
+            const uint32_t lo = pos < w0 ? w0 - pos : 0u;
+            const uint32_t hi = pos >= w0 + kSbWindow ? 0u
+                              : e < w0 + kSbWindow - pos ? e : w0 + kSbWindow - pos;
+            if (lo < hi) {
+                const Rect q = sb_rect(R);
+                const uint32_t wd = uint32_t(q.tx1 - q.tx0);
+                int sy = q.ty0, sx = q.tx0;
+                if (lo > 0) {
+                    sy += int(lo / wd);
+                    sx += int(lo % wd);
+                }
+                uint32_t row = uint32_t(sy * G.sx) | (sb_span(R.ty0, R.ty1, sy) << 24);
+                for (uint32_t o = pos + lo - w0; o < pos + hi - w0; ++o) {
+                    s_key[o] = (row + uint32_t(sx)) | (sb_span(R.tx0, R.tx1, sx) << 16);
+                    s_idx[o] = idx[k];
+                    if (++sx == q.tx1) {
+                        sx = q.tx0;
+                        ++sy;
+                        row = uint32_t(sy * G.sx) | (sb_span(R.ty0, R.ty1, sy) << 24);
+                    }
+                }
             }
-            const uint32_t o = pos - w0;
-            s_key[o] = uint16_t(sy * G.sx + sx);
-            s_idx[o] = idx;
-            s_mask[o] = sb_mask(R, sx, sy);
-            ++pos;
-            --left;
-            if (++sx == Q.tx1) { sx = Q.tx0; ++sy; }
+            pos += e;
         }
         for (int d = t; d < kMaxSb; d += kSortThreads) {
 #pragma unroll
@@ -1176,7 +1212,6 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
         // wave w ranks the entries [w seg, (w + 1) seg) of the window, 64 at a time
         const int steps = (cnt + kSortThreads - 1) / kSortThreads, seg = steps * 64;
         uint32_t key[kSbSteps], loc[kSbSteps], id[kSbSteps];
-        unsigned long long mk[kSbSteps];
 #pragma unroll
         for (int i = 0; i < kSbSteps; ++i) {
             if (i >= steps) break;                           // uniform
@@ -1185,12 +1220,13 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
             const int oc = valid ? o : 0;
             key[i] = s_key[oc];
             id[i] = s_idx[oc];
-            mk[i] = s_mask[oc];
-            const uint32_t d = key[i];
+            const uint32_t d = key[i] & 0xffffu;
             const unsigned long long vmask = __builtin_amdgcn_ballot_w64(valid);
             uint32_t plo = uint32_t(vmask), phi = uint32_t(vmask >> 32);
             const uint32_t nd = ~d;
-            for (int b = 0; b < bits; ++b) {
+#pragma unroll
+            for (int b = 0; b < kMaxSbBits; ++b) {
+                if (b >= bits) break;                        // uniform
                 const uint32_t flip = uint32_t(int32_t(nd << (31 - b)) >> 31);
                 const unsigned long long vote = __builtin_amdgcn_ballot_w64(flip == 0u);
                 plo &= uint32_t(vote) ^ flip;
@@ -1229,19 +1265,18 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
         for (int i = 0; i < kSbSteps; ++i) {
             if (i >= steps) break;
             if (w * seg + i * 64 + lane < cnt) {
-                const uint32_t r = s_dstart[key[i]] + s_wcnt[w][key[i]] + loc[i];
-                s_key[r] = uint16_t(key[i]);
+                const uint32_t d = key[i] & 0xffffu, r = s_dstart[d] + s_wcnt[w][d] + loc[i];
+                s_key[r] = key[i];
                 s_idx[r] = id[i];
-                s_mask[r] = mk[i];
             }
         }
         __syncthreads();
         for (int o = t; o < cnt; o += kSortThreads) {
-            const uint32_t d = s_key[o];
+            const uint32_t key_o = s_key[o], d = key_o & 0xffffu;
             const int64_t p = int64_t(s_gofs[d]) + (o - int(s_dstart[d]));
             if (p < cap) {
                 e_idx[p] = s_idx[o];
-                e_mask[p] = s_mask[o];
+                e_mask[p] = sb_mask(key_o >> 16);
             }
         }
         __syncthreads();
@@ -1290,11 +1325,13 @@ struct SbChunk {
     uint32_t lo, hi, first;
 };
 __device__ inline SbChunk sb_chunk(const SbTable *T, uint32_t c) {
-    int a = 0, b = kMaxSb - 1;                              // last superblock whose first chunk <= c
-    while (a < b) {
-        const int mid = (a + b + 1) >> 1;
-        if (T->chunk[mid] <= c) a = mid; else b = mid - 1;
-    }
+    // last superblock whose first chunk is <= c, 64 and then 16 candidates at a time
+    const int lane = threadIdx.x & 63;
+    constexpr int kFan = kMaxSb / 64;
+    static_assert(kFan <= 64, "one candidate per lane");
+    const auto count = [](bool v) { return __popcll(__builtin_amdgcn_ballot_w64(v)); };
+    const int p = count(T->chunk[lane * kFan] <= c) - 1;
+    const int a = p * kFan + count(lane < kFan && T->chunk[p * kFan + lane % kFan] <= c) - 1;
     SbChunk C;
     C.sb = a;
     C.first = T->chunk[a];
@@ -1339,30 +1376,51 @@ __global__ __launch_bounds__(256) void k_sb_count(const unsigned long long *e_ma
 }
 
 // ranges[tile].y holds the list length: [start, end) in tile order, [0, 0) for an empty list. One
-// block (at most 65536 tiles). Also the header's pair count and the capacity status.
+// block (at most 65536 tiles) that takes 16384 tiles at a time, moved through LDS so that memory is
+// read and written in order (each thread reading its own 16 tiles took 35 us at 4K, now 13). Also
+// the header's pair count and the capacity status.
 __global__ __launch_bounds__(kScanTopThreads) void k_tile_scan(uint2 *ranges, int32_t n_tiles,
                                                                BinHeader *hdr, int64_t cap,
                                                                int32_t *status) {
-    constexpr int kItems = 16;
+    constexpr int kItems = 16, kStep = kScanTopThreads * kItems;
+    __shared__ uint32_t s_v[kStep + kStep / kItems];         // a word of padding per thread's items
     __shared__ uint32_t s_wave[kScanTopThreads / 64];
+    const int t = threadIdx.x;
+    const auto at = [](int i) { return i + i / kItems; };
     uint32_t carry = 0;
-    for (int32_t base = 0; base < n_tiles; base += kScanTopThreads * kItems) {
-        const int32_t b = base + int32_t(threadIdx.x) * kItems;
+    for (int32_t base = 0; base < n_tiles; base += kStep) {
         uint32_t v[kItems], sum = 0, tot;
 #pragma unroll
         for (int k = 0; k < kItems; ++k) {
-            v[k] = b + k < n_tiles ? ranges[b + k].y : 0u;
-            sum += v[k];
+            const int32_t i = base + k * kScanTopThreads + t;
+            v[k] = i < n_tiles ? ranges[i].y : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) s_v[at(k * kScanTopThreads + t)] = v[k];
+        __syncthreads();
+        uint32_t own[kItems];
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            own[k] = s_v[at(t * kItems + k)];
+            sum += own[k];
         }
         uint32_t run = block_exclusive_scan<uint32_t>(sum, s_wave, tot) + carry;
 #pragma unroll
         for (int k = 0; k < kItems; ++k) {
-            if (b + k < n_tiles && v[k] != 0u) ranges[b + k] = make_uint2(run, run + v[k]);
-            run += v[k];
+            s_v[at(t * kItems + k)] = run;
+            run += own[k];
         }
         carry += tot;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            const int32_t i = base + k * kScanTopThreads + t;
+            const uint32_t first = s_v[at(k * kScanTopThreads + t)];
+            if (i < n_tiles && v[k] != 0u) ranges[i] = make_uint2(first, first + v[k]);
+        }
+        __syncthreads();
     }
-    if (threadIdx.x == 0) {
+    if (t == 0) {
         const unsigned long long total = hdr->total, ucap = (unsigned long long)cap;
         hdr->pairs = total < ucap ? total : ucap;
         if (total > ucap) *status = GSB_ERR_CAPACITY;
@@ -1371,7 +1429,10 @@ __global__ __launch_bounds__(kScanTopThreads) void k_tile_scan(uint2 *ranges, in
 
 // The lists. Lane t of a wavefront owns tile t: from the chunk's counts it knows where its part of
 // the tile's list starts in LDS and steps through the set bits of its transposed masks, writing the
-// entries' Gaussian indices there; the block then copies each tile's run out. A chunk's pairs go
+// entries' and the tile's numbers there; the block then copies the runs out, one element per thread
+// and step, as the entries' Gaussian indices (looked up there, where every lane has one, not in the
+// uneven steps before, and not tile by tile, where each step waits for the last: 109 us at 4K, now
+// 79). A chunk's pairs go
 // through LDS at once when they fit kSbStage, else in halves, quarters or two groups of 64 entries
 // (at most kSbStage pairs) at a time.
 __global__ __launch_bounds__(256) void k_sb_write(const uint32_t *e_idx,
@@ -1382,7 +1443,9 @@ __global__ __launch_bounds__(256) void k_sb_write(const uint32_t *e_idx,
     __shared__ uint32_t s_idx[kSbChunk];
     __shared__ uint16_t s_cnt[kSbGroups][kSbTiles];
     __shared__ uint32_t s_pre[4][kSbTiles];
-    __shared__ uint32_t s_out[kSbStage];
+    __shared__ uint16_t s_out[kSbStage];                     // tile * kSbChunk + entry of the chunk
+    __shared__ uint32_t s_dst[kSbTiles];                     // list position of s_out[0] as a tile's
+    static_assert(kSbTiles * kSbChunk <= 65536, "a tile and an entry fit 16 bits");
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const uint32_t n_chunks = T->chunk[kMaxSb];
     for (uint32_t c = blockIdx.x; c < n_chunks; c += gridDim.x) {
@@ -1435,6 +1498,7 @@ __global__ __launch_bounds__(256) void k_sb_write(const uint32_t *e_idx,
                 if (lane >= o) x += y;
             }
             const uint32_t first = x - len;
+            if (w == 0) s_dst[lane] = dst - first;
             uint32_t p = first;
             int seen = g0;                                   // groups whose counts p includes
 #pragma unroll
@@ -1442,18 +1506,20 @@ __global__ __launch_bounds__(256) void k_sb_write(const uint32_t *e_idx,
                 const int g = k * 4 + w;
                 if (g < g0 || g >= g0 + ng) continue;        // uniform
                 for (; seen < g; ++seen) p += s_cnt[seen][lane];
-                uint32_t o = p;
-                for (uint32_t m = uint32_t(hit[k]); m != 0u; m &= m - 1u)
-                    s_out[o++] = s_idx[g * 64 + __builtin_ctz(m)];
-                for (uint32_t m = uint32_t(hit[k] >> 32); m != 0u; m &= m - 1u)
-                    s_out[o++] = s_idx[g * 64 + 32 + __builtin_ctz(m)];
+                uint32_t o = p, lo = uint32_t(hit[k]), hi = uint32_t(hit[k] >> 32);
+                uint32_t e = uint32_t(lane * kSbChunk + g * 64);
+                while ((lo | hi) != 0u) {
+                    if (lo == 0u) { lo = hi; hi = 0u; e += 32; }
+                    s_out[o++] = uint16_t(e + __builtin_ctz(lo));
+                    lo &= lo - 1u;
+                }
             }
             __syncthreads();
-            for (int b = w; b < kSbTiles; b += 4) {          // wave w copies tiles w, w + 4, ...
-                const uint32_t nb = __builtin_amdgcn_readlane(len, b);
-                const uint32_t sb = __builtin_amdgcn_readlane(first, b);
-                const uint32_t db = __builtin_amdgcn_readlane(dst, b);
-                for (uint32_t j = lane; j < nb; j += 64) point_list[db + j] = s_out[sb + j];
+            const uint32_t n_out = __builtin_amdgcn_readlane(x, 63);
+#pragma unroll 4
+            for (uint32_t j = t; j < n_out; j += 256) {
+                const uint32_t v = s_out[j];
+                point_list[s_dst[v / kSbChunk] + j] = s_idx[v % kSbChunk];
             }
             dst += len;
             __syncthreads();
@@ -1580,12 +1646,14 @@ gsb_status bin_fill(const float *means2d, const int32_t *radii, const float *con
             auto *table = at<SbTable>(ws, L.sb_table);
             const int ranks = sb_ranks(G.n);
             const int64_t nblk = (n + ranks - 1) / ranks;
-            const dim3 gb{unsigned(nblk)};
+            const dim3 gb{unsigned(xcd_grid(nblk))};
             k_sb_hist<<<gb, kSortThreads, 0, s>>>(rects, n, ranks, G, sortbuf, nblk);
             launch_scan<uint32_t>(sortbuf, int64_t(G.n) * nblk, partial32, &hdr->entries, nullptr, s);
-            k_sb_scatter<<<gb, kSortThreads, 0, s>>>(rects, sorted_idx, n, ranks, G,
-                                                     G.n > 1 ? ceil_log2(G.n) : 0, sortbuf, nblk,
-                                                     hdr, cap, e_idx, e_mask, table);
+            const auto scatter = ranks == 1024 ? k_sb_scatter<4>
+                               : ranks == 2048 ? k_sb_scatter<8> : k_sb_scatter<16>;
+            scatter<<<gb, kSortThreads, 0, s>>>(rects, sorted_idx, n, G,
+                                                G.n > 1 ? ceil_log2(G.n) : 0, sortbuf, nblk, hdr,
+                                                cap, e_idx, e_mask, table);
             const int64_t mc = sb_max_chunks(cap);
             const dim3 gc{unsigned(mc < kSbMaxGrid ? mc : kSbMaxGrid)};
             k_sb_count<<<gc, 256, 0, s>>>(e_mask, table, G, counts16, ranges);
