@@ -125,6 +125,28 @@ struct Stage<Mode::Plain, NB> {  // plain form
     alignas(16) uint32_t live[2][4];   // forward: whether wavefront w still has a live pixel
 };
 
+// Forward: one batch of the entries that can reach the tile, in list order.
+template <Mode M, int NB>
+struct FwdStage {              // GEMM form
+    typedef typename Op<M>::vec vec;
+    vec ahi[NB], zero, alo[NB];
+    float kc[NB];
+    float4 attr[NB];           // (log2 o, r, g, b)
+    uint8_t pos[NB];           // the entry's place in the batch as fetched
+    // per wavefront: entries it keeps, + kWaveLive while it has a live pixel
+    alignas(16) uint32_t post[4];
+};
+template <int NB>
+struct FwdStage<Mode::Plain, NB> {
+    float4 geo[NB];            // (x, y, A, B)
+    float2 geo2[NB];           // (C, log2 o)
+    float4 attr[NB];
+    uint8_t pos[NB];
+    uint8_t reach[NB];         // reach_mask
+    alignas(16) uint32_t post[4];
+};
+constexpr uint32_t kWaveLive = 1u << 16;
+
 template <int NB>
 struct StageBwd {
     float2 bwd[2][NB];         // the mean (x, y)
@@ -276,6 +298,8 @@ template <> struct Attrs<true> {
 // A wavefront then skips, without evaluating q, the Gaussians that cannot reach its quadrant.
 // Only the plain form uses it: there q costs a dozen instructions per pixel, while the GEMM form
 // gets the q of a whole group from one product and skips a Gaussian with one compare.
+struct Eval;
+__device__ inline uint32_t reach_mask(const GRaw &g, const Eval &e);
 __device__ inline uint32_t reach_mask(const GRaw &g, float lo2o, float xh, float yh) {
     const float gxh = fmaf(g.A, xh, g.B * yh), gyh = fmaf(g.C, yh, g.B * xh);
     const float Qh = fmaf(xh, gxh, yh * gyh);
@@ -295,6 +319,56 @@ __device__ inline uint32_t reach_mask(const GRaw &g, float lo2o, float xh, float
     const bool r0 = yl - hy <= 7.f && yl + hy >= 0.f, r1 = yl - hy <= 15.f && yl + hy >= 8.f;
     return uint32_t(c0 && r0) | uint32_t(c1 && r0) << 1 | uint32_t(c0 && r1) << 2 |
            uint32_t(c1 && r1) << 3;
+}
+
+// What the staging of a list entry works out before it is written to LDS: the centre relative to the
+// tile centre, log2 o (-inf for an entry that is never blended: alpha <= o < 1/255, or invalid), and
+// g = Sigma^-1 (xh, yh) and Q there, to full FP32 accuracy.
+struct Eval {
+    bool live;
+    float xh, yh, lo2o, gxh, gyh, Qh;
+};
+__device__ inline Eval evaluate(const GRaw &g, float xc, float yc) {
+    Eval e;
+    e.live = g.valid && g.o >= kTauCull;
+    e.xh = g.x - xc;
+    e.yh = g.y - yc;
+    e.lo2o = e.live ? __log2f(g.o) : -INFINITY;
+    e.Qh = quad_acc(g.A, g.B, g.C, e.xh, e.yh, e.gxh, e.gyh);
+    return e;
+}
+
+__device__ inline uint32_t reach_mask(const GRaw &g, const Eval &e) {
+    return reach_mask(g, e.lo2o, e.xh, e.yh);
+}
+
+// Whether a live entry can reach alpha >= 1/255 at a pixel of the tile; false only when the q that
+// the kernels compute is below kQCull at all of them. Over the square of the pixel centres
+// (7.5 px to each side of the tile centre) the smallest Q is 0 if the mean lies inside, else it lies
+// on an edge that faces the mean: on the line dx = a (a the nearest dx of the square, 0 if the mean
+// lies between its sides) at dy = -B a / C clamped to the square, or on dy = b likewise; the smaller
+// of the two is the minimum, whichever edges face the mean. The entry is kept unless that minimum
+// exceeds t, the level at which q = kQCull, enlarged by a bound on the error of the computed q (2^-14
+// of the magnitudes of the terms that it is formed from, about eight times the BF16 form's error and
+// far above the others') and of the minimum (2^-20 of its terms). Not a definite conic, a NaN or
+// coefficients that the FP16 form clamps: kept. On the 4K frame this keeps 39% of a 3-sigma list's
+// entries; the bounding box of the ellipse would keep 55%.
+__device__ inline bool reaches_tile(const GRaw &g, const Eval &e) {
+    const float mag = kLog2e * (28.125f * (fabsf(g.A) + fabsf(g.C)) + 56.25f * fabsf(g.B) +
+                                7.5f * (fabsf(e.gxh) + fabsf(e.gyh)) + 0.5f * fabsf(e.Qh)) +
+                      fabsf(e.lo2o);
+    const float t = (e.lo2o - kQCull + fmaf(mag, 0x1p-14f, 0x1p-16f)) * (2.0f / kLog2e);
+    const float bb = g.B * g.B;
+    const float det = fmaf(g.A, g.C, -bb) - fmaf(g.B, g.B, -bb);
+    const float a = e.xh - fminf(fmaxf(e.xh, -7.5f), 7.5f);
+    const float b = e.yh - fminf(fmaxf(e.yh, -7.5f), 7.5f);
+    const float v = fminf(fmaxf(-g.B * a * __builtin_amdgcn_rcpf(g.C), e.yh - 7.5f), e.yh + 7.5f);
+    const float u = fminf(fmaxf(-g.B * b * __builtin_amdgcn_rcpf(g.A), e.xh - 7.5f), e.xh + 7.5f);
+    const float s1 = fmaf(g.A * a, a, g.C * v * v), s2 = fmaf(g.C * b, b, g.A * u * u);
+    constexpr float kLess = 1.0f - 0x1p-20f;
+    const float q1 = fmaf(2.0f * g.B * a, v, s1 * kLess), q2 = fmaf(2.0f * g.B * b, u, s2 * kLess);
+    const bool out = q1 > t && q2 > t && g.A > 0.f && g.C > 0.f && det > 0.f && mag < kF16Max;
+    return !out;
 }
 
 // The reach masks of a staged batch as one 16-bit word per (quadrant, group): bit u of
@@ -320,6 +394,29 @@ __device__ inline uint32_t group_reach(const Stage<M, NB> &S, int buf, int w, in
 
 // Writes one Gaussian into slot `slot` of buffer `buf`. (xc, yc) is the tile centre. `reach`:
 // whether the plain form culls by reach (otherwise every Gaussian reaches every quadrant).
+// The 16-bit hi and lo terms of a live entry's coefficients (zeros otherwise) and the accumulator
+// init.
+template <Mode M>
+__device__ inline void coefficients(const GRaw &g, const Eval &e, typename Op<M>::vec &ahi,
+                                    typename Op<M>::vec &alo, float &kc) {
+    float hi[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float lo[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float k0 = -INFINITY;
+    if (e.live) {
+        const float v[5] = {-0.5f * kLog2e * g.A, -0.5f * kLog2e * g.C, -kLog2e * g.B,
+                            -kLog2e * e.gxh, -kLog2e * e.gyh};
+        k0 = fmaf(e.Qh, -0.5f * kLog2e, e.lo2o);
+#pragma unroll
+        for (int k = 0; k < 5; ++k) hi[k] = v[k];
+        const typename Op<M>::vec vh = Op<M>::cvt(hi);
+#pragma unroll
+        for (int k = 0; k < 5; ++k) lo[k] = (v[k] - Op<M>::back(vh, k)) * kLoScale;
+    }
+    ahi = Op<M>::cvt(hi);
+    alo = Op<M>::cvt(lo);
+    kc = k0;
+}
+
 template <Mode M, int NB, bool Bwd>
 __device__ inline void stage(const GRaw &g, int buf, int slot, float xc, float yc, Stage<M, NB> &S,
                              StageBwd<NB> *SB, bool reach) {
@@ -448,10 +545,7 @@ __device__ inline f16x group_q_mfma(const Stage<M, NB> &S, int buf, int g, const
 }
 
 // q of one staged Gaussian for this lane's pixel, per pixel in FP32 (Eq. (power)).
-template <int NB>
-__device__ inline float plain_q(const Stage<Mode::Plain, NB> &S, int buf, int idx, const Lane &L) {
-    const float4 geo = S.geo[buf][idx];
-    const float2 g2 = S.geo2[buf][idx];
+__device__ inline float plain_q(const float4 &geo, const float2 &g2, const Lane &L) {
     const float dx = geo.x - L.px, dy = geo.y - L.py;
     float gx, gy;
     return fmaf(quad_acc(geo.z, geo.w, g2.x, dx, dy, gx, gy), -0.5f * kLog2e, g2.y);
@@ -460,6 +554,8 @@ __device__ inline float plain_q(const Stage<Mode::Plain, NB> &S, int buf, int id
 // ------------------------------------------------------------------------------- forward
 struct FwdState {
     float T, r, g, b, thr;   // thr = kQCull while live, +inf once done
+    // 1-based list position of the last blended entry; ~slot for one blended in this batch, until
+    // the batch ends
     int last;
 };
 
@@ -468,7 +564,7 @@ struct FwdState {
 // the lanes that blend update their state under the execution mask rather than through a select
 // per value. (The end of a pixel stays a select: as a scalar branch on a ballot it costs more
 // than it saves, since the branch waits for the compare.)
-__device__ inline void composite(float q, float lo2o, float cr, float cg, float cb, int pos,
+__device__ inline void composite(float q, float lo2o, float cr, float cg, float cb, int slot,
                                  FwdState &st) {
     const bool hit = q >= st.thr;
     const float a = __builtin_amdgcn_exp2f(fminf(fminf(q, lo2o), kQAlphaMax));   // <= 0.99
@@ -480,7 +576,7 @@ __device__ inline void composite(float q, float lo2o, float cr, float cg, float 
         st.g = fmaf(wgt, cg, st.g);
         st.b = fmaf(wgt, cb, st.b);
         st.T = Tn;
-        st.last = pos + 1;
+        st.last = ~slot;
     }
     st.thr = (hit && stop) ? INFINITY : st.thr;
 }
@@ -505,13 +601,29 @@ __device__ inline void composite_group(const float4 *attr, int base, uint32_t re
     }
 }
 
+// q of the 16 staged Gaussians from slot s0 (as group_q_mfma).
+template <Mode M, int NB>
+__device__ inline f16x fwd_group_q(const FwdStage<M, NB> &S, int s0, const Lane &L,
+                                   const typename Op<M>::vec &bhi, const typename Op<M>::vec &blo) {
+    f16x acc;
+    const float4 *kc4 = reinterpret_cast<const float4 *>(&S.kc[s0]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float4 k = kc4[j];
+        acc[4 * j + 0] = k.x; acc[4 * j + 1] = k.y; acc[4 * j + 2] = k.z; acc[4 * j + 3] = k.w;
+    }
+    const auto ah = *(L.a_valid ? &S.ahi[s0 + L.a_g] : &S.zero);
+    const auto al = *(L.a_valid ? &S.alo[s0 + L.a_g] : &S.zero);
+    acc = Op<M>::mfma(ah, bhi, acc);
+    return Op<M>::mfma(al, blo, acc);
+}
+
 // Forward of one tile of one view (all 256 threads of the block take part; block-uniform control
 // flow around every barrier).
 template <Mode M, int NB, bool kPacked = false>
-__device__ inline void fwd_tile(const ViewDesc &v, TileXY tile, Stage<M, NB> &S,
+__device__ inline void fwd_tile(const ViewDesc &v, TileXY tile, FwdStage<M, NB> &S,
                                 int tid = threadIdx.x) {
     static_assert(NB % kGroup == 0 && NB <= kBlock, "batch must be whole groups, <= block");
-    constexpr int kGroups = NB / kGroup;
     const uint32_t *plist = v.point_list;
     const uint32_t n = uint32_t(v.n);
     const Attrs<kPacked> src(v);
@@ -521,7 +633,7 @@ __device__ inline void fwd_tile(const ViewDesc &v, TileXY tile, Stage<M, NB> &S,
     pixel_basis<M>(L, bhi, blo);
     if (L.t == 0) {
         float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        if constexpr (M != Mode::Plain) S.zero_hi = S.zero_lo = Op<M>::cvt(z);
+        if constexpr (M != Mode::Plain) S.zero = Op<M>::cvt(z);
     }
     const uint2 rg = reinterpret_cast<const uint2 *>(v.ranges)[tile.y * v.gx + tile.x];
     // without Gaussians every list entry would be invalid: the tile shows the background
@@ -542,37 +654,79 @@ __device__ inline void fwd_tile(const ViewDesc &v, TileXY tile, Stage<M, NB> &S,
         ent = entry(1);
     }
     for (int b = 0; b < nb; ++b) {
-        const int buf = b & 1;
-        if (L.t < NB) stage<M, NB, false>(nxt, buf, L.t, xc, yc, S, nullptr, v.reach != 0);
-        // Barrier. Each wavefront also posts whether it still has a live pixel, and the whole
-        // block leaves once none has (one barrier; the flags are double-buffered with the batch,
-        // so that batch b + 2's post cannot overtake a wavefront still reading batch b's).
-        const bool wave_live = __ballot(st.thr != INFINITY) != 0;   // (the whole wavefront's)
-        if (L.l == 0) S.live[buf][L.w] = wave_live ? 1u : 0u;
-        __syncthreads();
-        {
-            const uint4 f = *reinterpret_cast<const uint4 *>(S.live[buf]);
-            if (__builtin_amdgcn_readfirstlane(f.x | f.y | f.z | f.w) == 0u) break;
+        const int base = b * NB;
+        // Of the batch's entries only those that can reach the tile are staged, in order: a wavefront
+        // posts how many it keeps and whether it still has a live pixel; the block leaves once none
+        // has. (v.reach 0: every entry is staged, also those that are never blended.)
+        const Eval e = evaluate(nxt, xc, yc);
+        uint32_t quad = 0xfu;
+        bool keep = e.live && reaches_tile(nxt, e);
+        if constexpr (M == Mode::Plain) {
+            quad = keep ? reach_mask(nxt, e) : 0u;
+            keep = quad != 0u;
         }
+        if (v.reach == 0) {
+            keep = L.t < NB && base + L.t < len;
+            quad = 0xfu;
+        }
+        const unsigned long long kept = __builtin_amdgcn_ballot_w64(keep);
+        const bool wave_live = __ballot(st.thr != INFINITY) != 0;   // (the whole wavefront's)
+        if (L.l == 0) S.post[L.w] = uint32_t(__popcll(kept)) + (wave_live ? kWaveLive : 0u);
+        __syncthreads();             // every wavefront is done with the last batch
+        const uint4 f = *reinterpret_cast<const uint4 *>(S.post);
+        const auto uniform = [](uint32_t x) { return uint32_t(__builtin_amdgcn_readfirstlane(int(x))); };
+        const uint32_t p[4] = {uniform(f.x), uniform(f.y), uniform(f.z), uniform(f.w)};
+        const uint32_t all = p[0] + p[1] + p[2] + p[3];
+        if (all < kWaveLive) break;
+        const int total = int(all & (kWaveLive - 1));
+        if (keep) {
+            uint32_t before = 0;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) before += k < L.w ? p[k] & (kWaveLive - 1) : 0u;
+            const int slot = int(__builtin_amdgcn_mbcnt_hi(
+                uint32_t(kept >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(kept), before)));
+            if constexpr (M == Mode::Plain) {
+                S.geo[slot] = e.live ? make_float4(nxt.x, nxt.y, nxt.A, nxt.B) : make_float4(0.f, 0.f, 0.f, 0.f);
+                S.geo2[slot] = make_float2(e.live ? nxt.C : 0.f, e.lo2o);
+                S.reach[slot] = uint8_t(quad);
+            } else {
+                typename Op<M>::vec ah, al;
+                coefficients<M>(nxt, e, ah, al, S.kc[slot]);
+                S.ahi[slot] = ah;
+                S.alo[slot] = al;
+            }
+            S.attr[slot] = make_float4(e.lo2o, nxt.r, nxt.g, nxt.b);
+            S.pos[slot] = uint8_t(L.t);
+        }
+        const int ng = (total + kGroup - 1) / kGroup;
+        if constexpr (M != Mode::Plain) {      // the last group's open slots: q = -inf
+            const int slot = total + L.t;
+            if (slot < ng * kGroup) {
+                const float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                S.kc[slot] = -INFINITY;
+                S.ahi[slot] = S.alo[slot] = Op<M>::cvt(z);
+            }
+        }
+        __syncthreads();
         // unconditional: past the last batch these read entry `start` and Gaussian 0, unused
         nxt = src.fetch(ent.id(), n);
         ent = entry(b + 2);
-        const int base = b * NB;
-        const int ng = int((len - base + kGroup - 1) / kGroup) < kGroups
-                           ? int((len - base + kGroup - 1) / kGroup) : kGroups;
         for (int g = 0; g < ng; ++g) {
             if (__ballot(st.thr != INFINITY) == 0) break;
-            const uint32_t reach = group_reach<M, NB>(S, buf, L.w, g);
-            if (reach == 0u) continue;                 // no Gaussian of the group reaches this wave
-            const float4 *attr = &S.attr[buf][g * kGroup];
+            const int s0 = g * kGroup;
+            const float4 *attr = &S.attr[s0];
             if constexpr (M == Mode::Plain) {
-                composite_group(attr, base + g * kGroup, reach, st,
-                                [&](int u) { return plain_q(S, buf, g * kGroup + u, L); });
+                const int u = L.l & (kGroup - 1);
+                const uint32_t r = s0 + u < total ? S.reach[s0 + u] : 0u;
+                const uint32_t reach = uint32_t(__builtin_amdgcn_ballot_w64(((r >> L.w) & 1u) != 0u)) & 0xffffu;
+                composite_group(attr, s0, reach, st,
+                                [&](int k) { return plain_q(S.geo[s0 + k], S.geo2[s0 + k], L); });
             } else {
-                const f16x q = group_q_mfma<M, NB, false>(S, buf, g, L, bhi, blo);
-                composite_group(attr, base + g * kGroup, reach, st, [&](int u) { return q[u]; });
+                const f16x q = fwd_group_q<M, NB>(S, s0, L, bhi, blo);
+                composite_group(attr, s0, 0xffffu, st, [&](int k) { return q[k]; });
             }
         }
+        if (st.last < 0) st.last = base + int(S.pos[~st.last]) + 1;
     }
     if (L.inside) {
         const int64_t p = int64_t(L.py) * v.W + int64_t(L.px);
@@ -1115,7 +1269,7 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, Stage<M, NB> &S,
             f16x qm;
             if constexpr (M != Mode::Plain) qm = group_q_mfma<M, NB, true>(S, buf, g, L, bhi, blo);
             const auto q_of = [&](int u) {
-                if constexpr (M == Mode::Plain) return plain_q(S, buf, slot0 + u, L);
+                if constexpr (M == Mode::Plain) return plain_q(S.geo[buf][slot0 + u], S.geo2[buf][slot0 + u], L);
                 else return qm[u];
             };
             if constexpr (kMM) {
@@ -1177,7 +1331,7 @@ constexpr int fit_waves(int target, size_t lds) {
 }
 // LDS of one block: the staged batches (and, backward, the gradient accumulators), plus the few
 // scalars the kernels share
-template <Mode M, int NB> constexpr size_t lds_fwd() { return sizeof(Stage<M, NB>) + 64; }
+template <Mode M, int NB> constexpr size_t lds_fwd() { return sizeof(FwdStage<M, NB>) + 64; }
 template <Mode M, int NB, bool kMM> constexpr size_t lds_bwd() {
     return sizeof(Stage<M, NB>) + sizeof(StageBwd<NB>) + sizeof(BwdAcc<NB>) +
            (kMM ? sizeof(BwdMM) : 0) + 64;
@@ -1203,7 +1357,7 @@ __device__ inline TileXY view_tile(const ViewDesc &v, uint32_t rank) {
 template <Mode M, int NB>
 __global__ __launch_bounds__(kBlock, fit_waves(M == Mode::Plain ? 8 : 7, lds_fwd<M, NB>()))
 void k_blend_fwd(ViewDesc v) {
-    __shared__ Stage<M, NB> S;
+    __shared__ FwdStage<M, NB> S;
     const uint32_t rank = xcd_rank(blockIdx.x, uint32_t(v.n_tiles));
     if (rank >= uint32_t(v.n_tiles)) return;
     const TileXY tile = view_tile(v, rank);
@@ -1227,13 +1381,13 @@ void k_blend_bwd(ViewDesc v) {
 // Single view, packed records (gsb_pack_gaussians): the default launch shape (LDS batches of 128,
 // vector-ALU reduction), attributes from one 48-byte record per list entry.
 template <Mode M>
-__global__ __launch_bounds__(kBlock, fit_waves(M == Mode::Plain ? 8 : 7, lds_fwd<M, 128>()))
+__global__ __launch_bounds__(kBlock, fit_waves(M == Mode::Plain ? 8 : 7, lds_fwd<M, kDefaultBatchFwd>()))
 void k_blend_fwd_rec(ViewDesc v) {
-    __shared__ Stage<M, 128> S;
+    __shared__ FwdStage<M, kDefaultBatchFwd> S;
     const uint32_t rank = xcd_rank(blockIdx.x, uint32_t(v.n_tiles));
     if (rank >= uint32_t(v.n_tiles)) return;
     const TileXY tile = view_tile(v, rank);
-    fwd_tile<M, 128, true>(v, tile, S);
+    fwd_tile<M, kDefaultBatchFwd, true>(v, tile, S);
 }
 
 template <Mode M>
@@ -1436,7 +1590,7 @@ template <Mode M> constexpr int waves_bwd() { return M == Mode::Plain ? 6 : 5; }
 template <Mode M, int NB>
 __global__ __launch_bounds__(kBlock, fit_waves(waves_fwd<M>(), lds_fwd<M, NB>()))
 void k_blend_fwd_batched(Queues Q) {
-    __shared__ Stage<M, NB> S;
+    __shared__ FwdStage<M, NB> S;
     __shared__ int s_view;
     __shared__ uint32_t s_rank;
     int q = int(blockIdx.x % kXcds), tried = 0;
@@ -1514,7 +1668,7 @@ __device__ inline bool grid_item(const Queues &Q, int64_t b, int &view, uint32_t
 template <Mode M, int NB>
 __global__ __launch_bounds__(kBlock, fit_waves(M == Mode::Plain ? 8 : 7, lds_fwd<M, NB>()))
 void k_blend_fwd_grid(Queues Q) {
-    __shared__ Stage<M, NB> S;
+    __shared__ FwdStage<M, NB> S;
     int view;
     uint32_t rank;
     if (!grid_item(Q, blockIdx.x, view, rank)) return;

@@ -80,7 +80,7 @@ gsb_status check_blend_common(int32_t W, int32_t H, const uint32_t *ranges,
 // The precision of a (validated) precision argument, and the view's reach setting from its flag.
 gsb_precision prec_base(gsb_precision prec) { return prec & ~GSB_FULL_SCAN; }
 void set_reach(ViewDesc &v, gsb_precision prec) {
-    v.reach = prec_base(prec) == GSB_FP32_PLAIN && (prec & GSB_FULL_SCAN) == 0 ? 1 : 0;
+    v.reach = (prec & GSB_FULL_SCAN) == 0 ? 1 : 0;
 }
 
 }  // namespace
