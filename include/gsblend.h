@@ -51,13 +51,12 @@ typedef int32_t gsb_precision;
 #define GSB_FP32_PLAIN 0  /* exponent per pixel in FP32 on the vector ALUs (Alg. 1, Eq. (power)) */
 #define GSB_FP16_GEMM 1   /* exponent as an MFMA product, FP16 hi+lo operands, FP32 accumulate */
 #define GSB_BF16_GEMM 2   /* same with BF16 hi+lo operands */
-/* Flag that may be OR'ed into any precision argument below. Without it, the plain form skips,
- * for each 8x8 quadrant of a tile, the staged Gaussians whose alpha cannot reach 1/255 at any of
- * its pixels (a conservative ellipse test made once per staged Gaussian, Eq. (power) and the
- * 1/255 skip of Alg. 1), so that their exponent is never evaluated there; the outputs are the
- * same bit for bit. GSB_FULL_SCAN evaluates every staged Gaussian at every pixel, the per-pixel
- * loop of Alg. 1 as written. The GEMM forms always evaluate the whole group (one MFMA product
- * gives every exponent of 16 Gaussians), so the flag changes nothing for them. */
+/* Flag that may be OR'ed into any precision argument below. Without it the blends skip, for a whole
+ * tile, the list entries whose alpha cannot reach 1/255 at any of its pixels (the smallest exponent
+ * over the tile's square, Eq. (power), with a bound on the rounding of the computed one, against the
+ * 1/255 skip of Alg. 1), and the plain form also, for each 8x8 quadrant of a tile, those that cannot
+ * reach it; the outputs are the same bit for bit. GSB_FULL_SCAN evaluates every list entry at every
+ * pixel, the per-pixel loop of Alg. 1 as written. */
 #define GSB_FULL_SCAN 0x100
 
 #define GSB_ABI_VERSION 8
@@ -339,8 +338,8 @@ typedef struct gsb_view {
 #define GSB_REDUCE_VALU 0
 #define GSB_REDUCE_MFMA 1
 typedef struct gsb_tuning {
-    int32_t batch_fwd;       /* Gaussians staged in LDS per batch, forward: 64, 128, 256 (128) */
-    int32_t batch_bwd;       /* same, backward (128) */
+    int32_t batch_fwd;       /* list entries per LDS batch, forward: 64, 128, 256 (256) */
+    int32_t batch_bwd;       /* same, backward (256) */
     int32_t blocks_per_cu;   /* persistent: resident blocks per compute unit; 0 = as many as fit */
     int32_t launch;          /* GSB_LAUNCH_PERSISTENT (default) or GSB_LAUNCH_GRID */
     int32_t bwd_reduce;      /* GSB_REDUCE_VALU (default) or GSB_REDUCE_MFMA */

@@ -6,10 +6,14 @@
 //
 // Launch shape: one 256-thread block (4 wavefronts) per 16x16 tile, one pixel per lane; wave w
 // owns the 8x8 quadrant (w mod 2, w div 2) of the tile. The tile's sorted list is walked in
-// batches of NB Gaussians (a template parameter: 64, 128 or 256): every thread below NB stages
-// one Gaussian into LDS (double-buffered; the next batch's global loads are issued before the
-// current batch is composited), then each wave composites the batch for its pixels, 16 Gaussians
-// (one MFMA group) at a time.
+// batches of NB entries (a template parameter: 64, 128 or 256, 256 by default): every thread below
+// NB fetches one (the next batch's global loads are issued before the current batch is composited)
+// and, if the Gaussian can reach the tile (reaches_tile), stages it into the next free LDS slot;
+// each wave composites the staged Gaussians for its pixels, 16 (one MFMA group) at a time.
+// Of a 3-sigma list only 39% reach (4K frame of 3M Gaussians): staging all of them, 128 at a time,
+// took 822 us forward and 2203 backward there (BF16), now 640 and 1976; lists that hold only
+// reaching entries pay the test with nothing to drop (forward 541 -> 564 us, backward 2094 -> 1880
+// with this and the column-first sums).
 //
 // Exponent in log2 units. With L = log2(e), every path evaluates
 //     q = L * power + log2(o),   alpha = min(0.99, 2^min(q, log2 o))  (= min(0.99, o e^min(power,0)))
@@ -105,26 +109,6 @@ template <> struct Op<Mode::BF16> {
 template <> struct Op<Mode::Plain> { typedef h8 vec; };
 
 // ------------------------------------------------------------------------------- LDS staging
-template <Mode M, int NB>
-struct Stage {                 // GEMM form
-    typedef typename Op<M>::vec vec;
-    vec ahi[2][NB];            // v_g hi terms, 5 used of 8
-    vec zero_hi;               // zeros: the A operand of the lanes off the block diagonal
-    vec alo[2][NB];            // v_g lo terms * 2^12
-    vec zero_lo;               // zeros, as far from zero_hi as alo[b][i] is from ahi[b][i]
-    float kc[2][NB];           // accumulator init: constant term + log2 o (-inf = inert)
-    float4 attr[2][NB];        // (log2 o, r, g, b)
-    alignas(16) uint32_t live[2][4];   // forward: whether wavefront w still has a live pixel
-};
-template <int NB>
-struct Stage<Mode::Plain, NB> {  // plain form
-    float4 geo[2][NB];         // (x, y, A, B)
-    float2 geo2[2][NB];        // (C, log2 o)
-    float4 attr[2][NB];        // (log2 o, r, g, b)
-    uint16_t reach[2][4][NB / kGroup];   // reach masks per quadrant and group (stage_reach)
-    alignas(16) uint32_t live[2][4];   // forward: whether wavefront w still has a live pixel
-};
-
 // Forward: one batch of the entries that can reach the tile, in list order.
 template <Mode M, int NB>
 struct FwdStage {              // GEMM form
@@ -147,13 +131,31 @@ struct FwdStage<Mode::Plain, NB> {
 };
 constexpr uint32_t kWaveLive = 1u << 16;
 
+// Backward: the same, with what the reverse step needs besides.
 template <int NB>
-struct StageBwd {
-    float2 bwd[2][NB];         // the mean (x, y)
-    // The Gaussian index of each slot of batch b, in ids[b % 3]. The flush of batch
-    // b + 1 reads other threads' slots while the next batch is staged; three buffers keep that
-    // staging out of the ones being read.
-    uint32_t ids[3][NB];
+struct BwdSlots {
+    float4 attr[NB];           // (log2 o, r, g, b)
+    float2 mean[NB];
+    // The Gaussian index of each slot of batch b, in ids[b & 1]: the flush of batch b + 1 reads
+    // other threads' slots while batch b is staged.
+    uint32_t ids[2][NB];
+    // which of its 64 entries each wavefront keeps
+    alignas(16) unsigned long long kept[4];
+};
+template <Mode M, int NB>
+struct BwdStage : BwdSlots<NB> {   // GEMM form
+    typedef typename Op<M>::vec vec;
+    vec ahi[NB];               // v_g hi terms, 5 used of 8
+    vec zero_hi;               // zeros: the A operand of the lanes off the block diagonal
+    vec alo[NB];               // v_g lo terms * 2^12
+    vec zero_lo;               // zeros, as far from zero_hi as alo[i] is from ahi[i]
+    float kc[NB];              // accumulator init: constant term + log2 o (-inf = inert)
+};
+template <int NB>
+struct BwdStage<Mode::Plain, NB> : BwdSlots<NB> {
+    float4 geo[NB];            // (x, y, A, B)
+    float2 geo2[NB];           // (C, log2 o)
+    uint8_t reach[NB];         // reach_mask
 };
 
 constexpr int kGrad = 9;   // per-Gaussian sums kept per batch
@@ -167,24 +169,25 @@ constexpr int kDetStride = 16;
 __device__ inline float opacity_grad(float sum, float o) { return o >= kTauCull ? sum / o : 0.f; }
 
 // Per-Gaussian gradient sums of a batch: 9 consecutive words per staged Gaussian, which the
-// flush reads as consecutive words across lanes. Two buffers: batch b sums into buffer b & 1
-// while batch b + 1's sums are flushed from the other.
+// flush reads as consecutive words across lanes.
 template <int NB>
 struct BwdAcc {
-    float v[2][NB * kGrad];
+    float v[NB * kGrad];
     // each wavefront's list of the slots with a nonzero sum, built when it flushes
     uint16_t list[kBlock / 64][64];
     // where lane l of a flush adds: the word l % 9 of its Gaussian, from `dst` at `stride` floats
     // per Gaussian (the same for the whole tile; kept here, not in three registers per lane)
     struct Item { float *dst; uint32_t stride, pad; } item[64];
-    __device__ float *slot(int ab, int t) { return v[ab] + t * kGrad; }
 };
 
 // Deterministic backward: each wavefront adds its per-batch sums in a slice of its own (a fixed
-// order); the flush adds the four slices in a fixed order. Two buffers, as BwdAcc.
+// order); the flush adds the four slices in a fixed order. map[b & 1]: the slot of each entry of
+// batch b as fetched, kNoSlot for one that is not staged (its sums are zero).
+constexpr int kNoSlot = 0xffff;
 template <int NB>
 struct BwdAccDet {
-    float v[2][kBlock / 64][NB * kGrad];
+    float v[kBlock / 64][NB * kGrad];
+    uint16_t map[2][NB];
 };
 
 // Backward reduction on the matrix cores: each wavefront's dL/dpower values of 8 Gaussians for its
@@ -371,29 +374,6 @@ __device__ inline bool reaches_tile(const GRaw &g, const Eval &e) {
     return !out;
 }
 
-// The reach masks of a staged batch as one 16-bit word per (quadrant, group): bit u of
-// reach[buf][w][g] is set when Gaussian u of group g can reach quadrant w (wavefront w's pixels).
-// Called by whole wavefronts (slot = thread).
-template <int NB>
-__device__ inline void stage_reach(uint32_t m4, int buf, int slot,
-                                   uint16_t (&reach)[2][4][NB / kGroup]) {
-    const int l = slot & 63;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        const unsigned long long bal = __builtin_amdgcn_ballot_w64(((m4 >> w) & 1u) != 0u);
-        if (l < 4) reach[buf][w][(slot >> 6) * 4 + l] = uint16_t(bal >> (16 * l));
-    }
-}
-
-// This wavefront's reach mask of group g (every Gaussian reaches every wavefront in the GEMM form).
-template <Mode M, int NB>
-__device__ inline uint32_t group_reach(const Stage<M, NB> &S, int buf, int w, int g) {
-    if constexpr (M == Mode::Plain) return __builtin_amdgcn_readfirstlane(uint32_t(S.reach[buf][w][g]));
-    else return 0xffffu;
-}
-
-// Writes one Gaussian into slot `slot` of buffer `buf`. (xc, yc) is the tile centre. `reach`:
-// whether the plain form culls by reach (otherwise every Gaussian reaches every quadrant).
 // The 16-bit hi and lo terms of a live entry's coefficients (zeros otherwise) and the accumulator
 // init.
 template <Mode M>
@@ -417,47 +397,45 @@ __device__ inline void coefficients(const GRaw &g, const Eval &e, typename Op<M>
     kc = k0;
 }
 
-template <Mode M, int NB, bool Bwd>
-__device__ inline void stage(const GRaw &g, int buf, int slot, float xc, float yc, Stage<M, NB> &S,
-                             StageBwd<NB> *SB, bool reach) {
-    // a Gaussian with o < 1/255 never reaches the skip threshold (alpha <= o); stage it inert
-    const bool live = g.valid && g.o >= kTauCull;
-    const float lo2o = live ? __log2f(g.o) : -INFINITY;
+// Which of a batch's entries are staged: those that can reach the tile (`all`: every one of the
+// `len` entries of the batch, also those that are never blended). quad: the quadrants (wavefronts)
+// that the entry can reach in the plain form.
+template <Mode M>
+__device__ inline bool keep_entry(const GRaw &g, const Eval &e, bool all, bool inside, uint32_t &quad) {
+    bool keep = e.live && reaches_tile(g, e);
+    quad = 0xfu;
     if constexpr (M == Mode::Plain) {
-        S.geo[buf][slot] = live ? make_float4(g.x, g.y, g.A, g.B) : make_float4(0.f, 0.f, 0.f, 0.f);
-        S.geo2[buf][slot] = make_float2(live ? g.C : 0.f, lo2o);
+        quad = keep ? reach_mask(g, e) : 0u;
+        keep = quad != 0u;
+    }
+    if (all) {
+        keep = inside;
+        quad = 0xfu;
+    }
+    return keep;
+}
+
+// Writes a kept entry into its slot (S: FwdStage or BwdStage).
+template <Mode M, typename St>
+__device__ inline void stage(const GRaw &g, const Eval &e, uint32_t quad, int slot, St &S) {
+    if constexpr (M == Mode::Plain) {
+        S.geo[slot] = e.live ? make_float4(g.x, g.y, g.A, g.B) : make_float4(0.f, 0.f, 0.f, 0.f);
+        S.geo2[slot] = make_float2(e.live ? g.C : 0.f, e.lo2o);
+        S.reach[slot] = uint8_t(quad);
     } else {
-        float hi[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        float lo[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        float k0 = -INFINITY;
-        if (live) {
-            const float xh = g.x - xc, yh = g.y - yc;
-            float v[5];
-            v[0] = -0.5f * kLog2e * g.A;
-            v[1] = -0.5f * kLog2e * g.C;
-            v[2] = -kLog2e * g.B;
-            float gxh, gyh;
-            const float Qh = quad_acc(g.A, g.B, g.C, xh, yh, gxh, gyh);
-            v[3] = -kLog2e * gxh;
-            v[4] = -kLog2e * gyh;
-            k0 = fmaf(Qh, -0.5f * kLog2e, lo2o);
-#pragma unroll
-            for (int k = 0; k < 5; ++k) hi[k] = v[k];
-            const typename Op<M>::vec vh = Op<M>::cvt(hi);
-#pragma unroll
-            for (int k = 0; k < 5; ++k) lo[k] = (v[k] - Op<M>::back(vh, k)) * kLoScale;
-        }
-        S.ahi[buf][slot] = Op<M>::cvt(hi);
-        S.alo[buf][slot] = Op<M>::cvt(lo);
-        S.kc[buf][slot] = k0;
+        typename Op<M>::vec ah, al;
+        coefficients<M>(g, e, ah, al, S.kc[slot]);
+        S.ahi[slot] = ah;
+        S.alo[slot] = al;
     }
-    S.attr[buf][slot] = make_float4(lo2o, g.r, g.g, g.b);
-    if constexpr (M == Mode::Plain)
-        stage_reach<NB>(!reach ? 0xfu : live ? reach_mask(g, lo2o, g.x - xc, g.y - yc) : 0u, buf,
-                        slot, S.reach);
-    if constexpr (Bwd) {
-        SB->bwd[buf][slot] = make_float2(g.x, g.y);
-    }
+    S.attr[slot] = make_float4(e.lo2o, g.r, g.g, g.b);
+}
+// An open slot of the last group (GEMM form): q = -inf.
+template <Mode M, typename St>
+__device__ inline void stage_inert(int slot, St &S) {
+    const float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    S.kc[slot] = -INFINITY;
+    S.ahi[slot] = S.alo[slot] = Op<M>::cvt(z);
 }
 
 // ------------------------------------------------------------------------------- per-lane setup
@@ -503,46 +481,60 @@ __device__ inline void pixel_basis(const Lane &L, typename Op<M>::vec &bhi, type
     }
 }
 
-// q for 16 consecutive staged Gaussians (group g of buffer buf): one value per register.
-// kOnePtr: address the A operands through one per-lane pointer (below); otherwise through a
-// select per operand, which holds fewer registers (the forward's 64 keep it at 8 wavefronts per
-// SIMD, the one-pointer form's 70 would not).
-template <Mode M, int NB, bool kOnePtr>
-__device__ inline f16x group_q_mfma(const Stage<M, NB> &S, int buf, int g, const Lane &L,
-                                    const typename Op<M>::vec &bhi,
-                                    const typename Op<M>::vec &blo) {
+// q of the 16 staged Gaussians from slot s0: one value per register, from the accumulator init and
+// the two A operands.
+template <Mode M>
+__device__ inline f16x group_q(const float *kc, const typename Op<M>::vec &ah,
+                               const typename Op<M>::vec &al, const typename Op<M>::vec &bhi,
+                               const typename Op<M>::vec &blo) {
     f16x acc;
-    const float4 *kc4 = reinterpret_cast<const float4 *>(&S.kc[buf][g * kGroup]);
+    const float4 *kc4 = reinterpret_cast<const float4 *>(kc);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const float4 k = kc4[j];
         acc[4 * j + 0] = k.x; acc[4 * j + 1] = k.y; acc[4 * j + 2] = k.z; acc[4 * j + 3] = k.w;
     }
-    typedef typename Op<M>::vec vec;
-    vec ah, al;
-    if constexpr (kOnePtr) {
-        // One address per lane: a lane off the diagonal reads zero_hi and zero_lo whatever buf
-        // and g are (its steps are 0), and every lane's lo operand lies at one fixed offset from
-        // its hi operand, so the lo read takes no address arithmetic of its own (the selects
-        // depend on the lane only and leave the loops): one vector instruction per group instead
-        // of five.
-        const vec *base = L.a_valid ? &S.ahi[0][L.a_g] : &S.zero_hi;
-        const int bstep = L.a_valid ? NB : 0, gstep = L.a_valid ? kGroup : 0;
-        const vec *ph = base + buf * bstep + g * gstep;
-        typedef Stage<M, NB> St;
-        constexpr size_t kLoOff = offsetof(St, alo) - offsetof(St, ahi);
-        static_assert(offsetof(St, zero_lo) - offsetof(St, zero_hi) == kLoOff,
-                      "zero_lo must mirror zero_hi");
-        ah = *ph;
-        al = *reinterpret_cast<const vec *>(reinterpret_cast<const char *>(ph) + kLoOff);
-    } else {
-        ah = *(L.a_valid ? &S.ahi[buf][g * kGroup + L.a_g] : &S.zero_hi);
-        al = *(L.a_valid ? &S.alo[buf][g * kGroup + L.a_g] : &S.zero_hi);
-    }
     acc = Op<M>::mfma(ah, bhi, acc);
-    acc = Op<M>::mfma(al, blo, acc);
-    return acc;
+    return Op<M>::mfma(al, blo, acc);
 }
+// Forward: the operands through a select per operand, which holds fewer registers than the
+// backward's one pointer (8 wavefronts per SIMD).
+template <Mode M, int NB>
+__device__ inline f16x group_q(const FwdStage<M, NB> &S, int s0, const Lane &L,
+                               const typename Op<M>::vec &bhi, const typename Op<M>::vec &blo) {
+    return group_q<M>(&S.kc[s0], *(L.a_valid ? &S.ahi[s0 + L.a_g] : &S.zero),
+                      *(L.a_valid ? &S.alo[s0 + L.a_g] : &S.zero), bhi, blo);
+}
+// Backward: one address per lane. A lane off the diagonal reads zero_hi and zero_lo whatever s0 is
+// (its step is 0), and every lane's lo operand lies at one fixed offset from its hi operand, so the
+// lo read takes no address arithmetic of its own (the selects depend on the lane only and leave the
+// loops): one vector instruction per group instead of five.
+template <Mode M, int NB>
+__device__ inline f16x group_q(const BwdStage<M, NB> &S, int s0, const Lane &L,
+                               const typename Op<M>::vec &bhi, const typename Op<M>::vec &blo) {
+    typedef typename Op<M>::vec vec;
+    typedef BwdStage<M, NB> St;
+    const vec *base = L.a_valid ? &S.ahi[L.a_g] : &S.zero_hi;
+    const int step = L.a_valid ? 1 : 0;
+    const vec *ph = base + s0 * step;
+    // (the same distance for every slot: zero_hi follows ahi as zero_lo follows alo)
+    const ptrdiff_t lo_off = reinterpret_cast<const char *>(&S.zero_lo) -
+                             reinterpret_cast<const char *>(&S.zero_hi);
+    static_assert(sizeof(St::ahi) == sizeof(St::alo), "zero_lo must mirror zero_hi");
+    return group_q<M>(&S.kc[s0], *ph,
+                      *reinterpret_cast<const vec *>(reinterpret_cast<const char *>(ph) + lo_off),
+                      bhi, blo);
+}
+
+// Plain form: which of the 16 staged Gaussians from slot s0 (below `total`) can reach the
+// wavefront's quadrant.
+template <typename St>
+__device__ inline uint32_t group_reach(const St &S, int s0, int total, const Lane &L) {
+    const int u = L.l & (kGroup - 1);
+    const uint32_t r = s0 + u < total ? S.reach[s0 + u] : 0u;
+    return uint32_t(__builtin_amdgcn_ballot_w64(((r >> L.w) & 1u) != 0u)) & 0xffffu;
+}
+__device__ inline uint32_t uniform(uint32_t x) { return uint32_t(__builtin_amdgcn_readfirstlane(int(x))); }
 
 // q of one staged Gaussian for this lane's pixel, per pixel in FP32 (Eq. (power)).
 __device__ inline float plain_q(const float4 &geo, const float2 &g2, const Lane &L) {
@@ -601,23 +593,6 @@ __device__ inline void composite_group(const float4 *attr, int base, uint32_t re
     }
 }
 
-// q of the 16 staged Gaussians from slot s0 (as group_q_mfma).
-template <Mode M, int NB>
-__device__ inline f16x fwd_group_q(const FwdStage<M, NB> &S, int s0, const Lane &L,
-                                   const typename Op<M>::vec &bhi, const typename Op<M>::vec &blo) {
-    f16x acc;
-    const float4 *kc4 = reinterpret_cast<const float4 *>(&S.kc[s0]);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const float4 k = kc4[j];
-        acc[4 * j + 0] = k.x; acc[4 * j + 1] = k.y; acc[4 * j + 2] = k.z; acc[4 * j + 3] = k.w;
-    }
-    const auto ah = *(L.a_valid ? &S.ahi[s0 + L.a_g] : &S.zero);
-    const auto al = *(L.a_valid ? &S.alo[s0 + L.a_g] : &S.zero);
-    acc = Op<M>::mfma(ah, bhi, acc);
-    return Op<M>::mfma(al, blo, acc);
-}
-
 // Forward of one tile of one view (all 256 threads of the block take part; block-uniform control
 // flow around every barrier).
 template <Mode M, int NB, bool kPacked = false>
@@ -659,22 +634,13 @@ __device__ inline void fwd_tile(const ViewDesc &v, TileXY tile, FwdStage<M, NB> 
         // posts how many it keeps and whether it still has a live pixel; the block leaves once none
         // has. (v.reach 0: every entry is staged, also those that are never blended.)
         const Eval e = evaluate(nxt, xc, yc);
-        uint32_t quad = 0xfu;
-        bool keep = e.live && reaches_tile(nxt, e);
-        if constexpr (M == Mode::Plain) {
-            quad = keep ? reach_mask(nxt, e) : 0u;
-            keep = quad != 0u;
-        }
-        if (v.reach == 0) {
-            keep = L.t < NB && base + L.t < len;
-            quad = 0xfu;
-        }
+        uint32_t quad;
+        const bool keep = keep_entry<M>(nxt, e, v.reach == 0, L.t < NB && base + L.t < len, quad);
         const unsigned long long kept = __builtin_amdgcn_ballot_w64(keep);
         const bool wave_live = __ballot(st.thr != INFINITY) != 0;   // (the whole wavefront's)
         if (L.l == 0) S.post[L.w] = uint32_t(__popcll(kept)) + (wave_live ? kWaveLive : 0u);
         __syncthreads();             // every wavefront is done with the last batch
         const uint4 f = *reinterpret_cast<const uint4 *>(S.post);
-        const auto uniform = [](uint32_t x) { return uint32_t(__builtin_amdgcn_readfirstlane(int(x))); };
         const uint32_t p[4] = {uniform(f.x), uniform(f.y), uniform(f.z), uniform(f.w)};
         const uint32_t all = p[0] + p[1] + p[2] + p[3];
         if (all < kWaveLive) break;
@@ -685,27 +651,12 @@ __device__ inline void fwd_tile(const ViewDesc &v, TileXY tile, FwdStage<M, NB> 
             for (int k = 0; k < 3; ++k) before += k < L.w ? p[k] & (kWaveLive - 1) : 0u;
             const int slot = int(__builtin_amdgcn_mbcnt_hi(
                 uint32_t(kept >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(kept), before)));
-            if constexpr (M == Mode::Plain) {
-                S.geo[slot] = e.live ? make_float4(nxt.x, nxt.y, nxt.A, nxt.B) : make_float4(0.f, 0.f, 0.f, 0.f);
-                S.geo2[slot] = make_float2(e.live ? nxt.C : 0.f, e.lo2o);
-                S.reach[slot] = uint8_t(quad);
-            } else {
-                typename Op<M>::vec ah, al;
-                coefficients<M>(nxt, e, ah, al, S.kc[slot]);
-                S.ahi[slot] = ah;
-                S.alo[slot] = al;
-            }
-            S.attr[slot] = make_float4(e.lo2o, nxt.r, nxt.g, nxt.b);
+            stage<M>(nxt, e, quad, slot, S);
             S.pos[slot] = uint8_t(L.t);
         }
         const int ng = (total + kGroup - 1) / kGroup;
         if constexpr (M != Mode::Plain) {      // the last group's open slots: q = -inf
-            const int slot = total + L.t;
-            if (slot < ng * kGroup) {
-                const float z[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                S.kc[slot] = -INFINITY;
-                S.ahi[slot] = S.alo[slot] = Op<M>::cvt(z);
-            }
+            if (total + L.t < ng * kGroup) stage_inert<M>(total + L.t, S);
         }
         __syncthreads();
         // unconditional: past the last batch these read entry `start` and Gaussian 0, unused
@@ -716,13 +667,10 @@ __device__ inline void fwd_tile(const ViewDesc &v, TileXY tile, FwdStage<M, NB> 
             const int s0 = g * kGroup;
             const float4 *attr = &S.attr[s0];
             if constexpr (M == Mode::Plain) {
-                const int u = L.l & (kGroup - 1);
-                const uint32_t r = s0 + u < total ? S.reach[s0 + u] : 0u;
-                const uint32_t reach = uint32_t(__builtin_amdgcn_ballot_w64(((r >> L.w) & 1u) != 0u)) & 0xffffu;
-                composite_group(attr, s0, reach, st,
+                composite_group(attr, s0, group_reach(S, s0, total, L), st,
                                 [&](int k) { return plain_q(S.geo[s0 + k], S.geo2[s0 + k], L); });
             } else {
-                const f16x q = fwd_group_q<M, NB>(S, s0, L, bhi, blo);
+                const f16x q = group_q<M, NB>(S, s0, L, bhi, blo);
                 composite_group(attr, s0, 0xffffu, st, [&](int k) { return q[k]; });
             }
         }
@@ -947,7 +895,6 @@ __device__ inline bool reverse_pair_mm(float q, bool in_range, const float4 *ga,
     }
     if (live == 0ull) return false;
     const float4 attr = ga[u];
-    const float2 bw = gb[u];
     const float araw = __builtin_amdgcn_exp2f(fminf(q, attr.x));
     const float a = alive ? fminf(araw, kAlphaMax) : 0.f;
     const float r = __builtin_amdgcn_rcpf(1.0f - a);
@@ -1068,12 +1015,11 @@ __device__ inline void mm_reduce(uint32_t (*rows)[kDgStride], const h8 (&B)[2], 
 // writes each list position's nine sums to v.det_partial in place of the global atomics (every
 // position of the tile's list is written, those past the last contributor with zeros).
 template <Mode M, int NB, bool kMM, bool kPacked = false, bool kDet = false>
-__device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, Stage<M, NB> &S, StageBwd<NB> &SB,
+__device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, BwdStage<M, NB> &S,
                                 BwdAcc<NB> *acc_, int &s_maxlast, BwdMM *mm,
                                 BwdAccDet<NB> *det = nullptr, int tid = threadIdx.x) {
     static_assert(NB % kGroup == 0 && NB <= kBlock, "batch must be whole groups, <= block");
     static_assert(!(kMM && kDet), "the deterministic backward reduces on the vector ALUs");
-    constexpr int kGroups = NB / kGroup;
     const uint32_t *plist = v.point_list;
     const uint32_t n = uint32_t(v.n);
     const Attrs<kPacked> src(v);
@@ -1128,16 +1074,12 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, Stage<M, NB> &S,
     }
     if (nb == 0) return;
 
-    // Memory operations of a batch are issued before its compute: the attribute loads of the next
-    // batch, the list entries of the one after, and the global atomics that flush the previous
-    // batch's sums (from the other accumulator buffer). Every wait at the top of an iteration is
-    // then for operations issued a whole compute phase earlier; with the flush after the compute,
-    // the next wait (the memory counter also counts atomics) would expose their latency.
+    // List entries are loaded two batches ahead and attributes one batch ahead.
     const auto entry = [&](int bb) {          // batch bb's entry for this thread (bb may be < 0)
         const int64_t o = int64_t(bb) * NB + L.t;
         return load_entry(plist, start + o, bb >= 0 && L.t < NB && o < len, start);
     };
-    // Wavefront w flushes slots [w NB/4, (w + 1) NB/4). It lists the slots that
+    // Each wavefront flushes a quarter of the batch's slots. It lists the slots that
     // received a nonzero sum, in slot order, and then spreads their nine sums over its lanes,
     // seven listed slots at a time: lane l < 63 adds sum l % 9 of slot l / 9, so that consecutive
     // lanes add consecutive words of one Gaussian (a wavefront's atomic instruction reaches about
@@ -1146,10 +1088,10 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, Stage<M, NB> &S,
     // the array and word that a lane adds to are the same for every slot: found once per tile, not
     // once per sum (@@). Each
     // item is zeroed by the lane that reads it (an unlisted slot's sums are all +-0 already),
-    // ready for batch bb - 2, which reuses the buffers after the next barrier.
-    // Deterministic form: word k < 9 of slot i's row is the four wavefronts' sum k added in
-    // wavefront order (and zeroed in the slices), words 9..15 are zero; the row is stored at list
-    // position start + bb NB + i (consecutive threads, consecutive words).
+    // ready for batch bb - 1, which adds after the next barrier.
+    // Deterministic form: word k < 9 of entry i's row is the four wavefronts' sum k of its slot added
+    // in wavefront order (0 for an entry that was not staged), words 9..15 are zero; the row is stored
+    // at list position start + bb NB + i (consecutive threads, consecutive words).
     const auto flush_det = [&](int bb) {
         const int64_t base = int64_t(bb) * NB;
         float *dst = v.det_partial + (start + base) * kDetStride;
@@ -1159,10 +1101,11 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, Stage<M, NB> &S,
         for (int j = L.t; j < NB * kDetStride; j += kBlock) {
             const int i = j / kDetStride, k = j % kDetStride;
             float sum = 0.f;
-            if (k < kGrad) {
+            const int slot = det->map[bb & 1][i];
+            if (k < kGrad && slot != kNoSlot) {
 #pragma unroll
                 for (int w = 0; w < kBlock / 64; ++w) {
-                    float *p = det->v[bb & 1][w] + i * kGrad + k;
+                    float *p = det->v[w] + slot * kGrad + k;
                     sum += *p;
                     *p = 0.f;
                 }
@@ -1179,21 +1122,21 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, Stage<M, NB> &S,
                                : item_k == 5 ? v.dL_dopacity : v.dL_dcolors + (item_k - 6),
                                item_k < 3 ? 3u : item_k < 5 ? 2u : item_k == 5 ? 1u : 3u, 0u};
     }
-    const auto flush = [&](int bb) {     // batch bb's sums, accumulator buffer bb & 1
+    const auto flush = [&](int bb, int staged) {     // the sums of batch bb and its slots
         if constexpr (kDet) {
             flush_det(bb);
             return;
         }
         BwdAcc<NB> &s_acc = *acc_;
-        constexpr int kPer = NB / (kBlock / 64);   // slots per wavefront, at most 64
-        float *acc = s_acc.v[bb & 1];
-        const uint32_t *ids = SB.ids[bb % 3];
+        const int per = (staged + 3) >> 2;         // slots per wavefront, at most 64
+        float *acc = s_acc.v;
+        const uint32_t *ids = S.ids[bb & 1];
         uint16_t *list = s_acc.list[L.w];
-        const int s0 = L.w * kPer;
+        const int s0 = L.w * per;
         // a slot is listed if any of its nine sums is nonzero (NaN included); one whose sums
         // are all +-0 adds nothing to the gradients, whether or not a pair reached it
         bool touched = false;
-        if (L.l < kPer) {
+        if (L.l < per && s0 + L.l < staged) {
             const float *p = acc + (s0 + L.l) * kGrad;
             uint32_t bits = 0u;
 #pragma unroll
@@ -1216,60 +1159,92 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, Stage<M, NB> &S,
     };
     GRaw nxt = src.fetch(entry(nb - 1).id(), n);
     Entry ent = entry(nb - 2);
-    // both accumulator buffers and their flags start at zero
     if constexpr (kDet) {
         for (int e = L.t; e < NB * kGrad; e += kBlock) {
 #pragma unroll
-            for (int w = 0; w < kBlock / 64; ++w) {
-                det->v[0][w][e] = 0.f;
-                det->v[1][w][e] = 0.f;
-            }
+            for (int w = 0; w < kBlock / 64; ++w) det->v[w][e] = 0.f;
         }
     } else {
-        for (int e = L.t; e < NB * kGrad; e += kBlock) {
-            acc_->v[0][e] = 0.f;
-            acc_->v[1][e] = 0.f;
-        }
+        for (int e = L.t; e < NB * kGrad; e += kBlock) acc_->v[e] = 0.f;
     }
+    int staged = 0;                            // slots of the batch before
     for (int b = nb - 1; b >= 0; --b) {
-        const int buf = b & 1;
-        if (L.t < NB) {
-            stage<M, NB, true>(nxt, buf, L.t, xc, yc, S, &SB, v.reach != 0);
-            SB.ids[b % 3][L.t] = nxt.id;
+        const int base = b * NB;
+        // as in the forward, only the entries that can reach the tile are staged, in order
+        const Eval e = evaluate(nxt, xc, yc);
+        uint32_t quad;
+        const bool keep = keep_entry<M>(nxt, e, v.reach == 0, L.t < NB && base + L.t < len, quad);
+        const unsigned long long kept = __builtin_amdgcn_ballot_w64(keep);
+        if (L.l == 0) S.kept[L.w] = kept;
+        __syncthreads();             // every wavefront is done with batch b + 1
+        // The batch's memory operations come before its compute, and the flush's atomics before the
+        // loads of the next batch: the wait for those, a whole compute later, finds both done (with
+        // the flush after the compute it would expose the atomics' latency).
+        if (b + 1 < nb) flush(b + 1, staged);
+        // entries kept before each wavefront's, and by this lane's wavefronts before a list position
+        const uint4 ka = reinterpret_cast<const uint4 *>(S.kept)[0];
+        const uint4 kb = reinterpret_cast<const uint4 *>(S.kept)[1];
+        const int c0 = __popc(uniform(ka.x)) + __popc(uniform(ka.y));
+        const int c1 = c0 + __popc(uniform(ka.z)) + __popc(uniform(ka.w));
+        const int c2 = c1 + __popc(uniform(kb.x)) + __popc(uniform(kb.y));
+        const int total = c2 + __popc(uniform(kb.z)) + __popc(uniform(kb.w));
+        const auto before = [&](int w) { return w == 0 ? 0 : w == 1 ? c0 : w == 2 ? c1 : c2; };
+        int slot = kNoSlot;
+        if (keep) {
+            slot = int(__builtin_amdgcn_mbcnt_hi(
+                uint32_t(kept >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(kept), uint32_t(before(L.w)))));
+            stage<M>(nxt, e, quad, slot, S);
+            S.mean[slot] = make_float2(nxt.x, nxt.y);
+            S.ids[b & 1][slot] = nxt.id;
         }
+        if constexpr (kDet) {
+            if (L.t < NB) det->map[b & 1][L.t] = uint16_t(slot);
+        }
+        const int ng = (total + kGroup - 1) / kGroup;
+        if constexpr (M != Mode::Plain) {
+            if (total + L.t < ng * kGroup) stage_inert<M>(total + L.t, S);
+        }
+        // slots below `last` hold entries up to the lane's last contributor
+        int last;
+        {
+            const int r = st.last - base < NB ? st.last - base : NB;      // entries of this batch
+            const int w = r > 0 ? (r - 1) >> 6 : 0, in = r - 64 * w;       // 1 <= in <= 64 if r > 0
+            const unsigned long long m = S.kept[w];
+            const unsigned long long low = in <= 0 ? 0ull : ~0ull >> (64 - in);
+            last = before(w) + __popcll(m & low);
+        }
+        staged = total;
         __syncthreads();
         // unconditional: before the first batch these read entry `start` and Gaussian 0, unused
         nxt = src.fetch(ent.id(), n);
         ent = entry(b - 2);
-        if (b + 1 < nb) flush(b + 1);
-        const int base = b * NB;
-        const int ng = int((len - base + kGroup - 1) / kGroup) < kGroups
-                           ? int((len - base + kGroup - 1) / kGroup) : kGroups;
         for (int g = ng - 1; g >= 0; --g) {
-            // nothing to do for this wave unless one of its pixels blended past the group start
-            // and a Gaussian of the group can reach it (see reach_mask)
-            if (__ballot(st.last > base + g * kGroup) == 0) continue;
-            const uint32_t reach = group_reach<M, NB>(S, buf, L.w, g);
-            if (reach == 0u) continue;
+            // nothing to do for this wave unless one of its pixels blended past the group's start
+            // and (plain form) a Gaussian of the group can reach it
+            if (__ballot(last > g * kGroup) == 0) continue;
+            uint32_t reach = 0xffffu;
+            if constexpr (M == Mode::Plain) {
+                reach = group_reach(S, g * kGroup, total, L);
+                if (reach == 0u) continue;
+            }
             // the group's first slot, held in a vector register: each Gaussian's LDS addresses are
             // then immediate offsets from it (from a scalar base the compiler copies the base
             // into a vector register again for every Gaussian)
             int slot0 = g * kGroup;
             asm volatile("" : "+v"(slot0));
-            const float4 *ga = &S.attr[buf][slot0];   // the group's staged values
-            const float2 *gb = &SB.bwd[buf][slot0];
+            const float4 *ga = &S.attr[slot0];   // the group's staged values
+            const float2 *gb = &S.mean[slot0];
             // the group's sums, Gaussian 0 (deterministic: this wavefront's slice)
-            float *accw = kDet ? det->v[buf][L.w] + g * kGroup * kGrad
-                               : acc_->slot(buf, g * kGroup);
+            float *accw = (kDet ? det->v[L.w] : acc_->v) + g * kGroup * kGrad;
             float *acc = accw + (kMM ? 0 : word);   // this lane's word (VALU reduction)
-            const int rel = st.last - (base + g * kGroup);   // positions < last are in range
+            const int rel = last - g * kGroup;      // slots < rel are in range
             // the whole group is in range for every lane (the common case once past the lanes'
             // last contributors; never for a partial tile, whose outside lanes have last = 0)
             const bool whole = __builtin_amdgcn_ballot_w64(rel < kGroup) == 0ull;
             f16x qm;
-            if constexpr (M != Mode::Plain) qm = group_q_mfma<M, NB, true>(S, buf, g, L, bhi, blo);
+            if constexpr (M != Mode::Plain) qm = group_q<M, NB>(S, g * kGroup, L, bhi, blo);
             const auto q_of = [&](int u) {
-                if constexpr (M == Mode::Plain) return plain_q(S.geo[buf][slot0 + u], S.geo2[buf][slot0 + u], L);
+                if constexpr (M == Mode::Plain) return plain_q(S.geo[slot0 + u], S.geo2[slot0 + u], L);
                 else return qm[u];
             };
             if constexpr (kMM) {
@@ -1313,12 +1288,9 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, Stage<M, NB> &S,
                 }
             }
         }
-        // Buffers: the next iteration stages into the other stage buffer. The accumulator buffer
-        // of batch b + 1 and its flags, flushed above, were zeroed by the flush itself, item by
-        // item; the barrier orders that before batch b - 1 adds into them.
     }
     __syncthreads();
-    flush(0);
+    flush(0, staged);
 }
 
 // ------------------------------------------------------------------------------- kernels
@@ -1333,8 +1305,7 @@ constexpr int fit_waves(int target, size_t lds) {
 // scalars the kernels share
 template <Mode M, int NB> constexpr size_t lds_fwd() { return sizeof(FwdStage<M, NB>) + 64; }
 template <Mode M, int NB, bool kMM> constexpr size_t lds_bwd() {
-    return sizeof(Stage<M, NB>) + sizeof(StageBwd<NB>) + sizeof(BwdAcc<NB>) +
-           (kMM ? sizeof(BwdMM) : 0) + 64;
+    return sizeof(BwdStage<M, NB>) + sizeof(BwdAcc<NB>) + (kMM ? sizeof(BwdMM) : 0) + 64;
 }
 // The transposition tiles exist only in the matrix-core reduction's kernels.
 struct NoMM {};
@@ -1367,15 +1338,14 @@ void k_blend_fwd(ViewDesc v) {
 template <Mode M, int NB, bool kMM>
 __global__ __launch_bounds__(kBlock, fit_waves(waves_bwd_tile<M, kMM>(), lds_bwd<M, NB, kMM>()))
 void k_blend_bwd(ViewDesc v) {
-    __shared__ Stage<M, NB> S;
-    __shared__ StageBwd<NB> SB;
+    __shared__ BwdStage<M, NB> S;
     __shared__ BwdAcc<NB> s_acc;   // per-Gaussian gradient sums of the current batch
     __shared__ MMTiles<kMM> s_mm;
     __shared__ int s_maxlast;
     const uint32_t rank = xcd_rank(blockIdx.x, uint32_t(v.n_tiles));
     if (rank >= uint32_t(v.n_tiles)) return;
     const TileXY tile = view_tile(v, rank);
-    bwd_tile<M, NB, kMM>(v, tile, S, SB, &s_acc, s_maxlast, mm_ptr<kMM>(s_mm));
+    bwd_tile<M, NB, kMM>(v, tile, S, &s_acc, s_maxlast, mm_ptr<kMM>(s_mm));
 }
 
 // Single view, packed records (gsb_pack_gaussians): the default launch shape (LDS batches of 128,
@@ -1391,36 +1361,33 @@ void k_blend_fwd_rec(ViewDesc v) {
 }
 
 template <Mode M>
-__global__ __launch_bounds__(kBlock, fit_waves(waves_bwd_tile<M, false>(), lds_bwd<M, 128, false>()))
+__global__ __launch_bounds__(kBlock, fit_waves(waves_bwd_tile<M, false>(), lds_bwd<M, kDefaultBatchBwd, false>()))
 void k_blend_bwd_rec(ViewDesc v) {
-    __shared__ Stage<M, 128> S;
-    __shared__ StageBwd<128> SB;
-    __shared__ BwdAcc<128> s_acc;
+    __shared__ BwdStage<M, kDefaultBatchBwd> S;
+    __shared__ BwdAcc<kDefaultBatchBwd> s_acc;
     __shared__ int s_maxlast;
     const uint32_t rank = xcd_rank(blockIdx.x, uint32_t(v.n_tiles));
     if (rank >= uint32_t(v.n_tiles)) return;
     const TileXY tile = view_tile(v, rank);
-    bwd_tile<M, 128, false, true>(v, tile, S, SB, &s_acc, s_maxlast, nullptr);
+    bwd_tile<M, kDefaultBatchBwd, false, true>(v, tile, S, &s_acc, s_maxlast, nullptr);
 }
 
 // Deterministic backward, one tile per block: LDS batches of 64 (the four wavefront slices of the
 // batch sums take four times the LDS of the shared accumulator), records as attributes.
-constexpr int kDetBatch = 64;
+constexpr int kDetBatch = 128;
 template <Mode M> constexpr size_t lds_bwd_det() {
-    return sizeof(Stage<M, kDetBatch>) + sizeof(StageBwd<kDetBatch>) +
-           sizeof(BwdAccDet<kDetBatch>) + 64;
+    return sizeof(BwdStage<M, kDetBatch>) + sizeof(BwdAccDet<kDetBatch>) + 64;
 }
 template <Mode M>
 __global__ __launch_bounds__(kBlock, fit_waves(waves_bwd_tile<M, false>(), lds_bwd_det<M>()))
 void k_blend_bwd_det(ViewDesc v) {
-    __shared__ Stage<M, kDetBatch> S;
-    __shared__ StageBwd<kDetBatch> SB;
+    __shared__ BwdStage<M, kDetBatch> S;
     __shared__ BwdAccDet<kDetBatch> s_det;
     __shared__ int s_maxlast;
     const uint32_t rank = xcd_rank(blockIdx.x, uint32_t(v.n_tiles));
     if (rank >= uint32_t(v.n_tiles)) return;
     const TileXY tile = view_tile(v, rank);
-    bwd_tile<M, kDetBatch, false, true, true>(v, tile, S, SB, nullptr, s_maxlast, nullptr, &s_det);
+    bwd_tile<M, kDetBatch, false, true, true>(v, tile, S, nullptr, s_maxlast, nullptr, &s_det);
 }
 
 // Grouping of the list positions by Gaussian: keys = the list's Gaussian indices, values = the
@@ -1618,8 +1585,7 @@ void k_blend_fwd_batched(Queues Q) {
 template <Mode M, int NB, bool kMM>
 __global__ __launch_bounds__(kBlock, fit_waves(kMM ? 3 : waves_bwd<M>(), lds_bwd<M, NB, kMM>()))
 void k_blend_bwd_batched(Queues Q) {
-    __shared__ Stage<M, NB> S;
-    __shared__ StageBwd<NB> SB;
+    __shared__ BwdStage<M, NB> S;
     __shared__ BwdAcc<NB> s_acc;
     __shared__ MMTiles<kMM> s_mm;
     __shared__ int s_maxlast;
@@ -1640,7 +1606,7 @@ void k_blend_bwd_batched(Queues Q) {
         __syncthreads();
         if (view < 0) break;
         const ViewDesc vd = load_view(Q, view);
-        bwd_tile<M, NB, kMM>(vd, view_tile(vd, rank), S, SB, &s_acc, s_maxlast,
+        bwd_tile<M, NB, kMM>(vd, view_tile(vd, rank), S, &s_acc, s_maxlast,
                              mm_ptr<kMM>(s_mm), nullptr, loop_tid());
         __syncthreads();
     }
@@ -1679,8 +1645,7 @@ void k_blend_fwd_grid(Queues Q) {
 template <Mode M, int NB, bool kMM>
 __global__ __launch_bounds__(kBlock, fit_waves(waves_bwd_tile<M, kMM>(), lds_bwd<M, NB, kMM>()))
 void k_blend_bwd_grid(Queues Q) {
-    __shared__ Stage<M, NB> S;
-    __shared__ StageBwd<NB> SB;
+    __shared__ BwdStage<M, NB> S;
     __shared__ BwdAcc<NB> s_acc;
     __shared__ MMTiles<kMM> s_mm;
     __shared__ int s_maxlast;
@@ -1688,7 +1653,7 @@ void k_blend_bwd_grid(Queues Q) {
     uint32_t rank;
     if (!grid_item(Q, blockIdx.x, view, rank)) return;
     const ViewDesc vd = load_view(Q, view);
-    bwd_tile<M, NB, kMM>(vd, view_tile(vd, rank), S, SB, &s_acc, s_maxlast, mm_ptr<kMM>(s_mm));
+    bwd_tile<M, NB, kMM>(vd, view_tile(vd, rank), S, &s_acc, s_maxlast, mm_ptr<kMM>(s_mm));
 }
 
 // Raw sums -> gradients of the stored scalars: d/dA = -S_xx/2, d/dB = -S_xy, d/dC = -S_yy/2,

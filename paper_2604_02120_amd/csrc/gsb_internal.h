@@ -165,7 +165,7 @@ struct Tuning {
 constexpr int kLaunchPersistent = 0;
 constexpr int kLaunchGrid = 1;
 constexpr int kDefaultBatchFwd = 256;
-constexpr int kDefaultBatchBwd = 128;
+constexpr int kDefaultBatchBwd = 256;
 
 gsb_status blend_forward(const ViewDesc &v, gsb_precision prec, int batch, hipStream_t s);
 gsb_status blend_backward(const ViewDesc &v, gsb_precision prec, int batch, bool mm, hipStream_t s);
