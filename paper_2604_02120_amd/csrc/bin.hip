@@ -34,7 +34,7 @@ constexpr int64_t kScanMaxLen = int64_t(kScanTile) * kScanMaxBlocks;  // 16.7M e
 constexpr int kScanSmallBlocks = 1;   // arrays of at most one block: the one-block scan (one launch)
 
 constexpr int kSortThreads = 256;
-constexpr int kSortItems = 16;                           // keys per thread
+constexpr int kSortItems = 16;                           // keys per thread (depth sort: or fewer)
 constexpr int kSortTile = kSortThreads * kSortItems;     // 4096 keys per block
 constexpr int kRadixBits = 8;
 constexpr int kRadix = 1 << kRadixBits;
@@ -84,15 +84,22 @@ struct Layout {
     size_t sb_mask, sb_idx, sb_counts, sb_table;   // superblock path, in the places of others
 };
 
-int64_t sort_blocks(int64_t m) { return (m + kSortTile - 1) / kSortTile; }
+int64_t sort_blocks(int64_t m, int items = kSortItems) {
+    const int64_t tile = int64_t(kSortThreads) * items;
+    return (m + tile - 1) / tile;
+}
 
 // Superblocks (see below): 8 x 8 tiles, at most kMaxSb of them; entries are taken in chunks.
 constexpr int kSbShift = 3, kSbEdge = 1 << kSbShift, kSbTiles = kSbEdge * kSbEdge;
 constexpr int kMaxSbBits = 10, kMaxSb = 1 << kMaxSbBits;
-constexpr int kSbChunk = 1024;                           // entries per block
-// chunks that up to `entries` entries can take (a superblock's last chunk may be partial)
-int64_t sb_max_chunks(int64_t entries) {
-    return entries / kSbChunk + (entries < kMaxSb ? entries : kMaxSb);
+// Entries per block: 1024, or 256 where the list is short enough that 1024 would leave most of the
+// GPU without a block (the two blocks of 2000 Gaussians took 13 us, the eight take 7).
+constexpr int kSbChunkLarge = 1024, kSbChunkSmall = 256;
+constexpr int64_t kSbSmallPairs = int64_t(1) << 19;
+int sb_chunk_size(int64_t cap) { return cap <= kSbSmallPairs ? kSbChunkSmall : kSbChunkLarge; }
+// chunks that up to `cap` entries can take (a superblock's last chunk may be partial)
+int64_t sb_max_chunks(int64_t cap) {
+    return cap / sb_chunk_size(cap) + (cap < kMaxSb ? cap : kMaxSb);
 }
 
 Layout layout(int64_t n, int64_t cap) {
@@ -165,8 +172,8 @@ __device__ T block_exclusive_scan(T v, T *s_wave, T &total) {
 // ------------------------------------------------------------------------------- device scan
 // Exclusive prefix sum, in place. Short arrays: one block walks the array in chunks with a running
 // carry. Long arrays: per-block sums, then a per-block scan whose blocks add up the sums before
-// them. The total goes to *total_a / *total_b if given (a total-only call scans the per-block
-// sums in one block instead).
+// them. The total goes to *total_a / *total_b if given. k_scan_top: up to 4096 per-block sums in one
+// block.
 template <typename T>
 __global__ __launch_bounds__(kScanTopThreads) void k_scan_small(T *data, int64_t m,
                                                                 unsigned long long *total_a,
@@ -269,21 +276,17 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down_fused(T *data, int64
     }
 }
 
-// scan (down = true) or total only (down = false)
 template <typename T>
 void launch_scan(T *data, int64_t m, T *partial, unsigned long long *total_a, long long *total_b,
-                 hipStream_t s, bool down = true) {
+                 hipStream_t s) {
     const int64_t nb = (m + kScanTile - 1) / kScanTile;
-    if (down && nb <= kScanSmallBlocks) {
+    if (nb <= kScanSmallBlocks) {
         k_scan_small<T><<<1, kScanTopThreads, 0, s>>>(data, m, total_a, total_b);
         return;
     }
-    if (nb > 0) k_scan_reduce<T><<<dim3(unsigned(nb)), kScanThreads, 0, s>>>(data, m, partial);
-    if (down)
-        k_scan_down_fused<T><<<dim3(unsigned(nb)), kScanThreads, 0, s>>>(data, m, partial, nb,
-                                                                          total_a, total_b);
-    else
-        k_scan_top<T><<<1, kScanTopThreads, 0, s>>>(partial, nb, total_a, total_b);
+    k_scan_reduce<T><<<dim3(unsigned(nb)), kScanThreads, 0, s>>>(data, m, partial);
+    k_scan_down_fused<T><<<dim3(unsigned(nb)), kScanThreads, 0, s>>>(data, m, partial, nb, total_a,
+                                                                      total_b);
 }
 
 // ------------------------------------------------------------------------------- mode 1
@@ -474,25 +477,13 @@ __device__ inline Rect unpack_rect(unsigned long long p) {
     return Rect{int32_t(x & 0xffffu), int32_t(x >> 16), int32_t(y & 0xffffu), int32_t(y >> 16)};
 }
 
-__global__ __launch_bounds__(256) void k_bin_count(const float2 *means, const int32_t *radii,
-                                                   const float *conics, const float *opac,
-                                                   int32_t mode, int64_t n, int32_t gx,
-                                                   int32_t gy, int32_t W, int32_t H,
+// Mode 1, the Gaussian i of this thread (i >= n: none; every lane of a wavefront takes part).
+__device__ inline unsigned long long count_visible(const float2 *means, const int32_t *radii,
+                                                   const float *conics, const float *opac, int64_t i,
+                                                   int64_t n, int32_t gx, int32_t gy, int32_t W,
+                                                   int32_t H, GaussVis *s_vis,
                                                    unsigned long long *counts,
                                                    unsigned long long *masks, uint4 *recs) {
-    __shared__ GaussVis s_vis[256];
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (mode == 0) {
-        if (i >= n) return;
-        const float2 m = means[i];
-        const Rect R = tile_rect(m.x, m.y, radii[i], gx, gy);
-        const unsigned long long cnt =
-            (unsigned long long)(R.tx1 - R.tx0) * (unsigned long long)(R.ty1 - R.ty0);
-        counts[i] = cnt;
-        recs[i] = count_rect(cnt, R);
-        return;
-    }
-    if (int64_t(blockIdx.x) * blockDim.x >= n) return;   // block-uniform
     const bool valid = i < n;
     Rect CR{0, 0, 0, 0};
     GaussVis g{};
@@ -529,9 +520,59 @@ __global__ __launch_bounds__(256) void k_bin_count(const float2 *means, const in
         }
     }
     if (valid) {
-        counts[i] = cnt;
+        if (counts) counts[i] = cnt;
         masks[i] = mask;
         recs[i] = count_rect(cnt, CR);
+    }
+    return cnt;
+}
+
+// A block counts the pairs of `iters` x kThreads Gaussians and leaves their sum in partial[block] (a
+// single block writes the total itself), so that no other pass reads the counts; they are stored
+// only where the pair sort needs them (counts not null).
+template <int kMode, int kThreads>
+__global__ __launch_bounds__(kThreads) void k_bin_count(const float2 *means, const int32_t *radii,
+                                                        const float *conics, const float *opac,
+                                                        int64_t n, int iters, int32_t gx,
+                                                        int32_t gy, int32_t W, int32_t H,
+                                                        unsigned long long *counts,
+                                                        unsigned long long *masks, uint4 *recs,
+                                                        unsigned long long *partial,
+                                                        unsigned long long *total_a,
+                                                        long long *total_b) {
+    __shared__ GaussVis s_vis[kMode == 1 ? kThreads : 1];
+    __shared__ unsigned long long s_wave[kThreads / 64];
+    const int64_t i0 = int64_t(blockIdx.x) * iters * kThreads + threadIdx.x;
+    unsigned long long sum = 0, all;
+    if constexpr (kMode == 0) {
+#pragma unroll 4
+        for (int it = 0; it < iters; ++it) {
+            const int64_t i = i0 + int64_t(it) * kThreads;
+            if (i >= n) continue;
+            const float2 m = means[i];
+            const Rect R = tile_rect(m.x, m.y, radii[i], gx, gy);
+            const unsigned long long cnt =
+                (unsigned long long)(R.tx1 - R.tx0) * (unsigned long long)(R.ty1 - R.ty0);
+            if (counts) counts[i] = cnt;
+            recs[i] = count_rect(cnt, R);
+            sum += cnt;
+        }
+    } else {
+        for (int it = 0; it < iters; ++it) {
+            const int64_t i = i0 + int64_t(it) * kThreads;
+            if (i - threadIdx.x >= n) break;                 // block-uniform
+            sum += count_visible(means, radii, conics, opac, i, n, gx, gy, W, H, s_vis, counts,
+                                 masks, recs);
+        }
+    }
+    block_exclusive_scan<unsigned long long>(sum, s_wave, all);
+    if (threadIdx.x == 0) {
+        if (gridDim.x > 1) {
+            partial[blockIdx.x] = all;
+        } else {
+            *total_a = all;
+            *total_b = (long long)all;
+        }
     }
 }
 
@@ -714,9 +755,8 @@ __global__ void k_zero_u32(uint32_t *p, int64_t m) {
     if (i < m) p[i] = 0u;
 }
 
-// kDepth: the keys are made here from the depths (and written with the identity values);
-// otherwise they are read from keys_io.
-template <bool kDepth>
+// The keys are made here from the depths (and written with the identity values).
+template <int kItems>
 __global__ __launch_bounds__(kSortThreads) void k_sort_hist(const float *depths, uint32_t *keys_io,
                                                             uint32_t *vals_out,
                                                             const unsigned long long *count,
@@ -731,31 +771,26 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_hist(const float *depths,
     __syncthreads();
     const int64_t P = int64_t(*count);
     for (int64_t b = blockIdx.x; b < nblk; b += gridDim.x) {
-        const int64_t base = b * kSortTile;
+        const int64_t base = b * (kSortThreads * kItems);
         if (base >= P) break;
         // four consecutive entries per thread and step: the keys and identity values are stored
         // with 16-byte writes (the workspace buffers are 256-byte aligned)
 #pragma unroll
-        for (int k = 0; k < kSortItems / 4; ++k) {
+        for (int k = 0; k < kItems / 4; ++k) {
             const int64_t idx = base + 4 * (int64_t(k) * kSortThreads + t);
             if (idx >= P) continue;
             uint32_t key[4];
-            if constexpr (kDepth) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) key[j] = idx + j < P ? depth_key(depths[idx + j]) : 0u;
-                if (idx + 4 <= P) {
-                    *reinterpret_cast<uint4 *>(keys_io + idx) = make_uint4(key[0], key[1], key[2], key[3]);
-                    const uint32_t i0 = uint32_t(idx);
-                    *reinterpret_cast<uint4 *>(vals_out + idx) = make_uint4(i0, i0 + 1, i0 + 2, i0 + 3);
-                } else {
-                    for (int j = 0; idx + j < P; ++j) {
-                        keys_io[idx + j] = key[j];
-                        vals_out[idx + j] = uint32_t(idx + j);
-                    }
-                }
+            for (int j = 0; j < 4; ++j) key[j] = idx + j < P ? depth_key(depths[idx + j]) : 0u;
+            if (idx + 4 <= P) {
+                *reinterpret_cast<uint4 *>(keys_io + idx) = make_uint4(key[0], key[1], key[2], key[3]);
+                const uint32_t i0 = uint32_t(idx);
+                *reinterpret_cast<uint4 *>(vals_out + idx) = make_uint4(i0, i0 + 1, i0 + 2, i0 + 3);
             } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) key[j] = idx + j < P ? keys_io[idx + j] : 0u;
+                for (int j = 0; idx + j < P; ++j) {
+                    keys_io[idx + j] = key[j];
+                    vals_out[idx + j] = uint32_t(idx + j);
+                }
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -819,18 +854,19 @@ __device__ inline uint32_t lb_read(const uint32_t *w) {
 // kChained: the block's tile comes from `ticket` and its digit offsets from the look-back over
 // `lookback` plus the pass's digit counts `ghist`; otherwise tile = blockIdx.x and the offsets are
 // read from `hist_off` ([digit][block], the exclusive scan of the per-block histograms).
-template <bool kChained, bool kRankCounts, typename K = uint32_t>
+template <bool kChained, bool kRankCounts, typename K = uint32_t, int kItems = kSortItems>
 __global__ __launch_bounds__(kSortThreads) void k_radix_pass(
     const K *kin, const uint32_t *vin, K *kout, uint32_t *vout,
     const unsigned long long *count, int shift, const uint32_t *ghist, uint32_t *lookback,
     uint32_t *ticket, int32_t *status, const uint32_t *hist_off, int64_t nblk,
     const uint4 *recs_by_idx, unsigned long long *rank_counts, unsigned long long *rank_rects) {
+    constexpr int kTileKeys = kSortThreads * kItems;
     __shared__ uint32_t s_wcnt[kSortThreads / 64][kRadix];  // per-wave digit counts, then prefixes
     __shared__ uint32_t s_dstart[kRadix];                     // block-local start of each digit
     __shared__ uint32_t s_gofs[kRadix];                       // global start of each digit
     __shared__ uint32_t s_wave[kSortThreads / 64];
-    __shared__ K s_key[kSortTile];
-    __shared__ uint32_t s_val[kSortTile];
+    __shared__ K s_key[kTileKeys];
+    __shared__ uint32_t s_val[kTileKeys];
     __shared__ uint32_t s_tile;
 
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
@@ -840,28 +876,29 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_pass(
     __syncthreads();
     const int64_t tile = kChained ? int64_t(s_tile) : int64_t(blockIdx.x);
     const int64_t P = int64_t(*count);
-    const int64_t base = tile * kSortTile;
+    const int64_t base = tile * kTileKeys;
     if (base >= P) return;   // block-uniform; every later ticket is empty too
 
     // Wave w ranks keys [base + 1024 w, base + 1024 (w + 1)) in 16 steps of 64 consecutive keys,
     // so rank order within the wave is index order. All loads are issued first, from an index
     // clamped into [base, P) (validity applied afterwards), so that they are in flight together.
-    uint32_t key[kSortItems], val[kSortItems], loc[kSortItems];
+    uint32_t key[kItems], val[kItems], loc[kItems];
 #pragma unroll
-    for (int k = 0; k < kSortItems; ++k) {
-        const int64_t idx = base + int64_t(w) * (kSortItems * 64) + k * 64 + lane;
+    for (int k = 0; k < kItems; ++k) {
+        const int64_t idx = base + int64_t(w) * (kItems * 64) + k * 64 + lane;
         const int64_t ci = idx < P ? idx : P - 1;   // P > base here
         key[k] = uint32_t(kin[ci]);
         val[k] = vin[ci];
     }
 #pragma unroll
-    for (int k = 0; k < kSortItems; ++k) {
-        const int64_t idx = base + int64_t(w) * (kSortItems * 64) + k * 64 + lane;
+    for (int k = 0; k < kItems; ++k) {
+        const int64_t idx = base + int64_t(w) * (kItems * 64) + k * 64 + lane;
         const bool valid = idx < P;
         const uint32_t d = (key[k] >> shift) & (kRadix - 1);
         // lanes holding the same digit: intersect, over the digit's bits, the lanes whose bit
         // equals this lane's (the ballot of the set bits, flipped where this lane's bit is clear),
-        // on the two 32-bit halves of the mask
+        // on the two 32-bit halves of the mask (written in place: from a function of its own the
+        // compiler makes two more instructions per bit)
         const unsigned long long vmask = __builtin_amdgcn_ballot_w64(valid);
         uint32_t plo = uint32_t(vmask), phi = uint32_t(vmask >> 32);
         const uint32_t nd = ~d;
@@ -931,8 +968,8 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_pass(
     s_dstart[t] = block_exclusive_scan<uint32_t>(run, s_wave, tot);
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kSortItems; ++k) {
-        const int64_t idx = base + int64_t(w) * (kSortItems * 64) + k * 64 + lane;
+    for (int k = 0; k < kItems; ++k) {
+        const int64_t idx = base + int64_t(w) * (kItems * 64) + k * 64 + lane;
         if (idx < P) {
             const uint32_t d = (key[k] >> shift) & (kRadix - 1);
             const uint32_t r = s_dstart[d] + s_wcnt[w][d] + loc[k];
@@ -941,7 +978,7 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_pass(
         }
     }
     __syncthreads();
-    const int64_t nvalid = (P - base) < kSortTile ? (P - base) : kSortTile;
+    const int64_t nvalid = (P - base) < kTileKeys ? (P - base) : kTileKeys;
     for (int64_t j = t; j < nvalid; j += kSortThreads) {
         const K k = s_key[j];
         const uint32_t d = (uint32_t(k) >> shift) & (kRadix - 1);
@@ -956,31 +993,127 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_pass(
     }
 }
 
+// The depth sort of up to kSmallSort Gaussians in one block and one launch: four stable passes in
+// LDS, as k_radix_pass ranks them, then the rectangles in rank order; it also does k_bin_init's work
+// when `ranges_n` words are given. (A histogram and four chained passes over one tile of keys are
+// five launches of 5-9 us each that wait for one another: 36 us at 2000 Gaussians, this one 15.)
+constexpr int kSmallSort = 4096, kSmallThreads = 1024;
+// Up to this many Gaussians the depth sort takes 1024 keys per block instead of 4096: more, shorter
+// blocks (the whole binning at 20k 109 -> 91 us, 60k 118 -> 106, 130k 127 -> 122; at 300k it is even,
+// at 1M smaller tiles' longer look-back costs more: 201 -> 260).
+constexpr int64_t kSort4 = 131072;
+__global__ __launch_bounds__(kSmallThreads) void k_sort_small(const float *depths, int n,
+                                                              uint32_t *sorted_idx,
+                                                              const uint4 *recs_by_idx,
+                                                              unsigned long long *rank_rects,
+                                                              uint32_t *ranges, int ranges_n,
+                                                              int32_t *status) {
+    constexpr int kWaves = kSmallThreads / 64, kItems = kSmallSort / kSmallThreads;
+    __shared__ uint16_t s_wcnt[kWaves][kRadix];
+    __shared__ uint32_t s_dstart[kRadix];
+    __shared__ uint32_t s_wave[kWaves];
+    __shared__ uint32_t s_key[kSmallSort];
+    __shared__ uint16_t s_val[kSmallSort];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    if (t == 0) *status = GSB_OK;
+    for (int k = t; k < ranges_n; k += kSmallThreads) ranges[k] = 0u;
+    // wave w holds keys [256 w, 256 (w + 1)) in four steps of 64
+    uint32_t key[kItems], val[kItems];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const int i = w * (kItems * 64) + k * 64 + lane;
+        key[k] = i < n ? depth_key(depths[i]) : 0u;
+        val[k] = uint32_t(i);
+    }
+    for (int shift = 0; shift < 32; shift += kRadixBits) {
+        for (int k = t; k < kWaves * kRadix; k += kSmallThreads) (&s_wcnt[0][0])[k] = 0;
+        __syncthreads();
+        uint32_t loc[kItems];
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            const bool valid = w * (kItems * 64) + k * 64 + lane < n;
+            const uint32_t d = (key[k] >> shift) & (kRadix - 1);
+            const unsigned long long vmask = __builtin_amdgcn_ballot_w64(valid);
+            uint32_t plo = uint32_t(vmask), phi = uint32_t(vmask >> 32);
+            const uint32_t nd = ~d;
+#pragma unroll
+            for (int b = 0; b < kRadixBits; ++b) {
+                const uint32_t flip = uint32_t(int32_t(nd << (31 - b)) >> 31);  // ones if bit b clear
+                const unsigned long long vote = __builtin_amdgcn_ballot_w64(flip == 0u);
+                plo &= uint32_t(vote) ^ flip;
+                phi &= uint32_t(vote >> 32) ^ flip;
+            }
+            const uint32_t rank = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0u));
+            uint32_t prior = 0;
+            if (valid) prior = s_wcnt[w][d];
+            if (valid && rank == 0) s_wcnt[w][d] = uint16_t(prior + uint32_t(__popc(plo) + __popc(phi)));
+            loc[k] = prior + rank;
+        }
+        __syncthreads();
+        uint32_t run = 0, tot;
+        if (t < kRadix) {
+#pragma unroll
+            for (int i = 0; i < kWaves; ++i) {
+                const uint32_t c = s_wcnt[i][t];
+                s_wcnt[i][t] = uint16_t(run);
+                run += c;
+            }
+        }
+        const uint32_t start = block_exclusive_scan<uint32_t>(run, s_wave, tot);
+        if (t < kRadix) s_dstart[t] = start;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            if (w * (kItems * 64) + k * 64 + lane < n) {
+                const uint32_t d = (key[k] >> shift) & (kRadix - 1);
+                const uint32_t r = s_dstart[d] + s_wcnt[w][d] + loc[k];
+                s_key[r] = key[k];
+                s_val[r] = uint16_t(val[k]);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            const int i = w * (kItems * 64) + k * 64 + lane;
+            if (i < n) {
+                key[k] = s_key[i];
+                val[k] = s_val[i];
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const int i = w * (kItems * 64) + k * 64 + lane;
+        if (i < n) {
+            const uint4 r = recs_by_idx[val[k]];
+            sorted_idx[i] = val[k];
+            rank_rects[i] = (static_cast<unsigned long long>(r.w) << 32) | r.z;
+        }
+    }
+}
+
 // Depth sort of the n Gaussians (count on the device): keys made from `depths`, values the
 // indices, 4 chained passes; the last one also writes each Gaussian's pair count at its rank
 // (rank_counts). The sorted indices end in va (4 passes, an even number).
+template <int kItems>
 void sort_depth(const float *depths, uint32_t *ka, uint32_t *kb, uint32_t *va, uint32_t *vb,
                 const unsigned long long *count, int64_t n, SortState *st, uint32_t *lookback,
                 int32_t *status, const uint4 *recs_by_idx, unsigned long long *rank_counts,
                 unsigned long long *rank_rects, hipStream_t s) {
     constexpr int passes = 32 / kRadixBits;
-    const int64_t nblk = sort_blocks(n);
+    const int64_t nblk = sort_blocks(n, kItems);
     if (nblk == 0) return;
     const int64_t hb = nblk < kHistBlocks ? nblk : kHistBlocks;
-    k_sort_hist<true><<<dim3(unsigned(hb)), kSortThreads, 0, s>>>(depths, ka, va, count, passes,
-                                                                  st, lookback, nblk);
+    k_sort_hist<kItems><<<dim3(unsigned(hb)), kSortThreads, 0, s>>>(depths, ka, va, count, passes,
+                                                                    st, lookback, nblk);
     uint32_t *kin = ka, *kout = kb, *vin = va, *vout = vb;
     for (int p = 0; p < passes; ++p) {
-        const int shift = p * kRadixBits;
-        uint32_t *lb = lookback + int64_t(p) * nblk * kRadix;
-        if (p == passes - 1)
-            k_radix_pass<true, true><<<dim3(unsigned(nblk)), kSortThreads, 0, s>>>(
-                kin, vin, kout, vout, count, shift, st->hist[p], lb, &st->ticket[p], status,
-                nullptr, nblk, recs_by_idx, rank_counts, rank_rects);
-        else
-            k_radix_pass<true, false><<<dim3(unsigned(nblk)), kSortThreads, 0, s>>>(
-                kin, vin, kout, vout, count, shift, st->hist[p], lb, &st->ticket[p], status,
-                nullptr, nblk, nullptr, nullptr, nullptr);
+        const auto pass = p == passes - 1 ? k_radix_pass<true, true, uint32_t, kItems>
+                                          : k_radix_pass<true, false, uint32_t, kItems>;
+        pass<<<dim3(unsigned(nblk)), kSortThreads, 0, s>>>(
+            kin, vin, kout, vout, count, p * kRadixBits, st->hist[p],
+            lookback + int64_t(p) * nblk * kRadix, &st->ticket[p], status, nullptr, nblk, recs_by_idx,
+            rank_counts, rank_rects);
         std::swap(kin, kout);
         std::swap(vin, vout);
     }
@@ -1028,7 +1161,6 @@ int sort_tiles(K *ka, K *kb, uint32_t *va, uint32_t *vb, const unsigned long lon
 // alone, two passes, and reads and writes every pair in each. (A Gaussian touches 18 tiles but only
 // 1.6 superblocks on the 4K frame of 3M Gaussians, so what is sorted is a tenth.) Measured at 4K,
 // 54.7M pairs, from the sorted Gaussians to the ranges: 0.18 ms against 0.84.
-constexpr int kSbGroups = kSbChunk / 64;
 constexpr int kSbMaxGrid = 4096;                         // blocks of steps 2 and 4, which loop
 constexpr int kSbWindow = 4096;                          // entries ranked at a time in step 1
 constexpr int kSbSteps = kSbWindow / kSortThreads;
@@ -1044,6 +1176,11 @@ __host__ __device__ inline SbGrid sb_grid(int32_t gx, int32_t gy) {
 // Ranks per block of step 1: the digit counts (superblocks x blocks) then fit the words of the
 // depth sort's look-back, which they replace (256 per 1024 Gaussians).
 inline int sb_ranks(int32_t n_sb) { return n_sb <= 256 ? 1024 : n_sb <= 512 ? 2048 : 4096; }
+// The superblock path where it applies: mode 0 (mode 1 keeps its tests' answers per pair) and a grid
+// of at most kMaxSb superblocks
+inline bool by_superblock(int32_t mode, const SbGrid &G) {
+    return mode == GSB_BIN_RECT && G.n <= kMaxSb;
+}
 
 // First entry and first chunk of every superblock, and the ends
 struct SbTable {
@@ -1098,10 +1235,11 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_hist(const unsigned long lo
 // k_radix_pass, reordered in LDS and written out in runs. The blocks of one XCD take consecutive
 // ranks (xcd_rank): a superblock's entries from neighbouring blocks are neighbours in memory, a run
 // is shorter than a cache line, and the line is put together in that XCD's L2 (12% less time).
-// Block 0 also fills the superblock table.
-template <int kPer>
+// Block 0 also fills the superblock table. kOne: the only block (nblk = 1) counts its entries per
+// superblock itself, with no launches of k_sb_hist and its scan.
+template <int kPer, bool kOne>
 __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
-    const unsigned long long *rank_rects, const uint32_t *sorted_idx, int64_t n, SbGrid G, int bits, const uint32_t *hist, int64_t nblk, const BinHeader *hdr, int64_t cap, uint32_t *e_idx, unsigned long long *e_mask, SbTable *table) {
+    const unsigned long long *rank_rects, const uint32_t *sorted_idx, int64_t n, SbGrid G, int bits, const uint32_t *hist, int64_t nblk, BinHeader *hdr, int64_t cap, uint32_t chunk, uint32_t *e_idx, unsigned long long *e_mask, SbTable *table) {
     constexpr int kWaves = kSortThreads / 64, kDig = kMaxSb / kSortThreads;
     __shared__ uint32_t s_gofs[kMaxSb];                 // next global position of each superblock
     __shared__ uint16_t s_wcnt[kWaves][kMaxSb];         // per-wave counts, then prefixes
@@ -1112,36 +1250,6 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int64_t blk = xcd_rank(blockIdx.x, uint32_t(nblk));
     if (blk >= nblk) return;                                 // block-uniform
-    if (blk == 0) {
-        // four superblocks per thread: starts from the scanned counts, chunks from their sizes.
-        // No entries at all when the pairs exceed the capacity (every list is then empty); else
-        // there are at most as many entries as pairs.
-        const uint32_t total = hdr->total <= (unsigned long long)cap ? uint32_t(hdr->entries) : 0u;
-        uint32_t st[kDig + 1], ch[kDig], sum = 0, tot;
-#pragma unroll
-        for (int k = 0; k <= kDig; ++k) {
-            const int d = t * kDig + k;
-            const uint32_t v = d < G.n ? hist[int64_t(d) * nblk] : total;
-            st[k] = v < total ? v : total;              // (entries past the capacity do not exist)
-        }
-#pragma unroll
-        for (int k = 0; k < kDig; ++k) {
-            ch[k] = (st[k + 1] - st[k] + kSbChunk - 1) / kSbChunk;
-            sum += ch[k];
-        }
-        uint32_t run = block_exclusive_scan<uint32_t>(sum, s_wave, tot);
-#pragma unroll
-        for (int k = 0; k < kDig; ++k) {
-            table->start[t * kDig + k] = st[k];
-            table->chunk[t * kDig + k] = run;
-            run += ch[k];
-        }
-        if (t == kSortThreads - 1) {
-            table->start[kMaxSb] = total;
-            table->chunk[kMaxSb] = run;
-        }
-    }
-    for (int d = t; d < G.n; d += kSortThreads) s_gofs[d] = hist[int64_t(d) * nblk + blk];
     // this thread's ranks: superblocks (0 x 0 where the rectangle is empty or past the end),
     // rectangle and index. kPer is a multiple of 4 and the buffers are padded to 256 bytes, so the
     // vector loads that straddle n stay inside them.
@@ -1170,6 +1278,62 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
     };
 #pragma unroll
     for (int k = 0; k < kPer; ++k) mine += entries(unpack_rect(rects[k]));
+    uint32_t n_entries;
+    if constexpr (kOne) {
+        for (int d = t; d < kMaxSb; d += kSortThreads) s_gofs[d] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const Rect R = unpack_rect(rects[k]);
+            if (entries(R) == 0u) continue;
+            const Rect q = sb_rect(R);
+            for (int sy = q.ty0; sy < q.ty1; ++sy)
+                for (int sx = q.tx0; sx < q.tx1; ++sx) atomicAdd(&s_gofs[sy * G.sx + sx], 1u);
+        }
+        __syncthreads();
+        uint32_t c[kDig], sum = 0;
+#pragma unroll
+        for (int q = 0; q < kDig; ++q) sum += c[q] = s_gofs[t * kDig + q];
+        uint32_t run = block_exclusive_scan<uint32_t>(sum, s_wave, n_entries);
+#pragma unroll
+        for (int q = 0; q < kDig; ++q) {
+            s_gofs[t * kDig + q] = run;
+            run += c[q];
+        }
+        __syncthreads();
+    } else {
+        for (int d = t; d < G.n; d += kSortThreads) s_gofs[d] = hist[int64_t(d) * nblk + blk];
+        n_entries = uint32_t(hdr->entries);
+    }
+    if (blk == 0) {
+        // four superblocks per thread: starts from the scanned counts, chunks from their sizes.
+        // No entries at all when the pairs exceed the capacity (every list is then empty); else
+        // there are at most as many entries as pairs.
+        const uint32_t total = hdr->total <= (unsigned long long)cap ? n_entries : 0u;
+        uint32_t st[kDig + 1], ch[kDig], sum = 0, tot;
+#pragma unroll
+        for (int k = 0; k <= kDig; ++k) {
+            const int d = t * kDig + k;
+            const uint32_t v = d < G.n ? (kOne ? s_gofs[d] : hist[int64_t(d) * nblk]) : total;
+            st[k] = v < total ? v : total;              // (entries past the capacity do not exist)
+        }
+#pragma unroll
+        for (int k = 0; k < kDig; ++k) {
+            ch[k] = (st[k + 1] - st[k] + chunk - 1) / chunk;
+            sum += ch[k];
+        }
+        uint32_t run = block_exclusive_scan<uint32_t>(sum, s_wave, tot);
+#pragma unroll
+        for (int k = 0; k < kDig; ++k) {
+            table->start[t * kDig + k] = st[k];
+            table->chunk[t * kDig + k] = run;
+            run += ch[k];
+        }
+        if (t == kSortThreads - 1) {
+            table->start[kMaxSb] = total;
+            table->chunk[kMaxSb] = run;
+        }
+    }
     uint32_t total;
     const uint32_t pos0 = block_exclusive_scan<uint32_t>(mine, s_wave, total);
     for (uint32_t w0 = 0; w0 < total; w0 += kSbWindow) {      // block-uniform
@@ -1324,6 +1488,7 @@ struct SbChunk {
     int sb;
     uint32_t lo, hi, first;
 };
+template <uint32_t kSbChunk>
 __device__ inline SbChunk sb_chunk(const SbTable *T, uint32_t c) {
     // last superblock whose first chunk is <= c, 64 and then 16 candidates at a time
     const int lane = threadIdx.x & 63;
@@ -1348,14 +1513,16 @@ __device__ inline int32_t sb_tile(const SbGrid &G, int sb, int bit) {
 
 // Per chunk and tile of its superblock the number of entries that cover it (counts[chunk][tile]),
 // added up per tile in ranges[tile].y. Integer sums: the order of the atomics does not matter.
+template <int kSbChunk>
 __global__ __launch_bounds__(256) void k_sb_count(const unsigned long long *e_mask,
                                                   const SbTable *T, SbGrid G, uint16_t *counts,
                                                   uint32_t *ranges) {
+    constexpr int kSbGroups = kSbChunk / 64;
     __shared__ uint32_t s_c[4][kSbTiles];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const uint32_t n_chunks = T->chunk[kMaxSb];
     for (uint32_t c = blockIdx.x; c < n_chunks; c += gridDim.x) {
-        const SbChunk C = sb_chunk(T, c);
+        const SbChunk C = sb_chunk<kSbChunk>(T, c);
         uint32_t cnt = 0;
 #pragma unroll
         for (int g = 0; g < kSbGroups / 4; ++g) {
@@ -1435,11 +1602,13 @@ __global__ __launch_bounds__(kScanTopThreads) void k_tile_scan(uint2 *ranges, in
 // 79). A chunk's pairs go
 // through LDS at once when they fit kSbStage, else in halves, quarters or two groups of 64 entries
 // (at most kSbStage pairs) at a time.
+template <int kSbChunk>
 __global__ __launch_bounds__(256) void k_sb_write(const uint32_t *e_idx,
                                                   const unsigned long long *e_mask,
                                                   const SbTable *T, SbGrid G,
                                                   const uint16_t *counts, const uint2 *ranges,
                                                   uint32_t *point_list) {
+    constexpr int kSbGroups = kSbChunk / 64;
     __shared__ uint32_t s_idx[kSbChunk];
     __shared__ uint16_t s_cnt[kSbGroups][kSbTiles];
     __shared__ uint32_t s_pre[4][kSbTiles];
@@ -1449,7 +1618,7 @@ __global__ __launch_bounds__(256) void k_sb_write(const uint32_t *e_idx,
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const uint32_t n_chunks = T->chunk[kMaxSb];
     for (uint32_t c = blockIdx.x; c < n_chunks; c += gridDim.x) {
-        const SbChunk C = sb_chunk(T, c);
+        const SbChunk C = sb_chunk<kSbChunk>(T, c);
         unsigned long long hit[kSbGroups / 4];
 #pragma unroll
         for (int g = 0; g < kSbGroups / 4; ++g) {
@@ -1593,15 +1762,36 @@ gsb_status bin_count(const float *means2d, const int32_t *radii, const float *co
     const Layout L = layout(n, 0);
     auto *hdr = at<BinHeader>(ws, L.hdr);
     auto *counts = at<unsigned long long>(ws, L.counts);
+    auto *masks = at<unsigned long long>(ws, L.masks);
+    auto *recs = at<uint4>(ws, L.recs);
     auto *partial = at<unsigned long long>(ws, L.partials);
+    auto *total_b = reinterpret_cast<long long *>(n_pairs_dev);
+    const auto *means = reinterpret_cast<const float2 *>(means2d);
     const int32_t gx = int32_t(grid_x(W)), gy = int32_t(grid_y(H));
-    if (n > 0)
-        k_bin_count<<<dim3(unsigned((n + 255) / 256)), 256, 0, s>>>(
-            reinterpret_cast<const float2 *>(means2d), radii, conics, opacity, mode, n, gx, gy, W,
-            H, counts, at<unsigned long long>(ws, L.masks), at<uint4>(ws, L.recs));
+    // Gaussians per block: mode 0 one block up to 4096 (no second launch), then 1024; mode 1, whose
+    // tests are long, 256; more where the blocks would exceed the partial sums' place
+    if (mode == GSB_BIN_RECT && by_superblock(mode, sb_grid(gx, gy))) counts = nullptr;
+    int64_t nb = 0;
+    const auto blocks = [&](int per) { return dim3(unsigned(nb = (n + per - 1) / per)); };
+    constexpr int64_t kTop = kScanMaxBlocks;
+    if (n > 0 && mode == GSB_BIN_RECT && n <= 4096) {
+        k_bin_count<0, 1024><<<blocks(4096), 1024, 0, s>>>(means, radii, conics, opacity, n, 4, gx, gy,
+                                                           W, H, counts, masks, recs, partial,
+                                                           &hdr->total, total_b);
+    } else if (n > 0 && mode == GSB_BIN_RECT) {
+        const int iters = n <= 1024 * kTop ? 4 : 16;
+        k_bin_count<0, 256><<<blocks(256 * iters), 256, 0, s>>>(means, radii, conics, opacity, n,
+                                                                iters, gx, gy, W, H, counts, masks,
+                                                                recs, partial, &hdr->total, total_b);
+    } else if (n > 0) {
+        const int iters = n <= 256 * kTop ? 1 : n <= 1024 * kTop ? 4 : 16;
+        k_bin_count<1, 256><<<blocks(256 * iters), 256, 0, s>>>(means, radii, conics, opacity, n,
+                                                                iters, gx, gy, W, H, counts, masks,
+                                                                recs, partial, &hdr->total, total_b);
+    }
     // the total only: offsets are formed in depth order by bin_fill
-    launch_scan<unsigned long long>(counts, n, partial, &hdr->total,
-                                    reinterpret_cast<long long *>(n_pairs_dev), s, false);
+    if (nb != 1)
+        k_scan_top<unsigned long long><<<1, kScanTopThreads, 0, s>>>(partial, nb, &hdr->total, total_b);
     return check_launch("bin_count");
 }
 
@@ -1624,49 +1814,65 @@ gsb_status bin_fill(const float *means2d, const int32_t *radii, const float *con
     const int64_t n_tiles = int64_t(gx) * gy;
     const unsigned gn = unsigned(n > 0 ? (n + 255) / 256 : 1);
 
-    // The superblock path where it applies: mode 0 (mode 1 keeps its tests' answers per pair) and a
-    // grid of at most kMaxSb superblocks
     const SbGrid G = sb_grid(gx, gy);
-    const bool by_superblock = mode == GSB_BIN_RECT && G.n <= kMaxSb;
-
-    k_bin_init<<<dim3(unsigned((2 * n_tiles + 255) / 256)), 256, 0, s>>>(ranges, 2 * n_tiles,
-                                                                       sorts, hdr, n, status_dev);
-    // 1. Gaussians by depth (ties by index: the sort is stable over index order); the last pass
-    //    also lays out each Gaussian's pair count and emission rectangle in rank order
-    sort_depth(depths, dka, dkb, dva, dvb, &hdr->gaussians, n, sorts, sortbuf, status_dev,
-               at<uint4>(ws, L.recs), by_superblock ? nullptr : offs,
-               at<unsigned long long>(ws, L.rects), s);
-    const uint32_t *sorted_idx = dva;
-    if (by_superblock) {
-        if (n > 0 && cap > 0) {
-            const auto *rects = at<unsigned long long>(ws, L.rects);
-            auto *e_mask = at<unsigned long long>(ws, L.sb_mask);
-            auto *e_idx = at<uint32_t>(ws, L.sb_idx);
-            auto *counts16 = at<uint16_t>(ws, L.sb_counts);
-            auto *table = at<SbTable>(ws, L.sb_table);
+    if (by_superblock(mode, G) && n > 0 && cap > 0) {
+        const auto *rects = at<unsigned long long>(ws, L.rects);
+        auto *e_mask = at<unsigned long long>(ws, L.sb_mask);
+        auto *e_idx = at<uint32_t>(ws, L.sb_idx);
+        auto *counts16 = at<uint16_t>(ws, L.sb_counts);
+        auto *table = at<SbTable>(ws, L.sb_table);
+        const int bits = G.n > 1 ? ceil_log2(G.n) : 0;
+        const int chunk = sb_chunk_size(cap);
+        if (n <= kSmallSort) {
+            k_sort_small<<<1, kSmallThreads, 0, s>>>(depths, int(n), dva, at<uint4>(ws, L.recs),
+                                                     at<unsigned long long>(ws, L.rects), ranges,
+                                                     int(2 * n_tiles), status_dev);
+            const auto scatter = n <= 4 * kSortThreads ? k_sb_scatter<4, true>
+                               : n <= 8 * kSortThreads ? k_sb_scatter<8, true> : k_sb_scatter<16, true>;
+            scatter<<<1, kSortThreads, 0, s>>>(rects, dva, n, G, bits, nullptr, 1, hdr, cap, chunk, e_idx,
+                                               e_mask, table);
+        } else {
+            k_bin_init<<<dim3(unsigned((2 * n_tiles + 255) / 256)), 256, 0, s>>>(
+                ranges, 2 * n_tiles, sorts, hdr, n, status_dev);
+            // the look-back words of the smaller tiles (4096 bytes per 1024 Gaussians) take the
+            // offsets' place (8 bytes per Gaussian, and n > kSmallSort here)
+            const auto sort = n <= kSort4 ? sort_depth<4> : sort_depth<kSortItems>;
+            sort(depths, dka, dkb, dva, dvb, &hdr->gaussians, n, sorts,
+                 n <= kSort4 ? at<uint32_t>(ws, L.offs) : sortbuf, status_dev, at<uint4>(ws, L.recs),
+                 nullptr, at<unsigned long long>(ws, L.rects), s);
             const int ranks = sb_ranks(G.n);
             const int64_t nblk = (n + ranks - 1) / ranks;
             const dim3 gb{unsigned(xcd_grid(nblk))};
             k_sb_hist<<<gb, kSortThreads, 0, s>>>(rects, n, ranks, G, sortbuf, nblk);
             launch_scan<uint32_t>(sortbuf, int64_t(G.n) * nblk, partial32, &hdr->entries, nullptr, s);
-            const auto scatter = ranks == 1024 ? k_sb_scatter<4>
-                               : ranks == 2048 ? k_sb_scatter<8> : k_sb_scatter<16>;
-            scatter<<<gb, kSortThreads, 0, s>>>(rects, sorted_idx, n, G,
-                                                G.n > 1 ? ceil_log2(G.n) : 0, sortbuf, nblk, hdr,
-                                                cap, e_idx, e_mask, table);
-            const int64_t mc = sb_max_chunks(cap);
-            const dim3 gc{unsigned(mc < kSbMaxGrid ? mc : kSbMaxGrid)};
-            k_sb_count<<<gc, 256, 0, s>>>(e_mask, table, G, counts16, ranges);
-            k_tile_scan<<<1, kScanTopThreads, 0, s>>>(reinterpret_cast<uint2 *>(ranges),
-                                                      int32_t(n_tiles), hdr, cap, status_dev);
-            k_sb_write<<<gc, 256, 0, s>>>(e_idx, e_mask, table, G, counts16,
-                                          reinterpret_cast<const uint2 *>(ranges), point_list);
-        } else {
-            k_tile_scan<<<1, kScanTopThreads, 0, s>>>(reinterpret_cast<uint2 *>(ranges), 0, hdr, cap,
-                                                      status_dev);
+            const auto scatter = ranks == 1024 ? k_sb_scatter<4, false>
+                               : ranks == 2048 ? k_sb_scatter<8, false> : k_sb_scatter<16, false>;
+            scatter<<<gb, kSortThreads, 0, s>>>(rects, dva, n, G, bits, sortbuf, nblk, hdr, cap, chunk,
+                                                e_idx, e_mask, table);
         }
+        const int64_t mc = sb_max_chunks(cap);
+        const dim3 gc{unsigned(mc < kSbMaxGrid ? mc : kSbMaxGrid)};
+        const auto count = chunk == kSbChunkSmall ? k_sb_count<kSbChunkSmall> : k_sb_count<kSbChunkLarge>;
+        const auto write = chunk == kSbChunkSmall ? k_sb_write<kSbChunkSmall> : k_sb_write<kSbChunkLarge>;
+        count<<<gc, 256, 0, s>>>(e_mask, table, G, counts16, ranges);
+        k_tile_scan<<<1, kScanTopThreads, 0, s>>>(reinterpret_cast<uint2 *>(ranges),
+                                                  int32_t(n_tiles), hdr, cap, status_dev);
+        write<<<gc, 256, 0, s>>>(e_idx, e_mask, table, G, counts16,
+                                 reinterpret_cast<const uint2 *>(ranges), point_list);
         return check_launch("bin_fill");
     }
+    k_bin_init<<<dim3(unsigned((2 * n_tiles + 255) / 256)), 256, 0, s>>>(ranges, 2 * n_tiles,
+                                                                       sorts, hdr, n, status_dev);
+    if (by_superblock(mode, G)) {       // no Gaussians, or no room for a pair
+        k_tile_scan<<<1, kScanTopThreads, 0, s>>>(reinterpret_cast<uint2 *>(ranges), 0, hdr, cap,
+                                                  status_dev);
+        return check_launch("bin_fill");
+    }
+    // 1. Gaussians by depth (ties by index: the sort is stable over index order); the last pass
+    //    also lays out each Gaussian's pair count and emission rectangle in rank order
+    sort_depth<kSortItems>(depths, dka, dkb, dva, dvb, &hdr->gaussians, n, sorts, sortbuf, status_dev,
+                           at<uint4>(ws, L.recs), offs, at<unsigned long long>(ws, L.rects), s);
+    const uint32_t *sorted_idx = dva;
     // 2. offsets in rank order; pairs emitted in rank order
     launch_scan<unsigned long long>(offs, n, partial64, nullptr, nullptr, s);
     const int tile_bits = ceil_log2(n_tiles) > 0 ? ceil_log2(n_tiles) : 1;

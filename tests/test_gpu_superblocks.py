@@ -33,6 +33,10 @@ SCENES = {
     "quarters of a chunk": lambda: scene(128, 128, 2500, 40, 70, 5),
     "one column": lambda: scene(7, 3000, 5000, 1, 300, 6),
     "windows": lambda: scene(1030, 1000, 1300, 1500, 2000, 7, levels=3),
+    "1025 ranks": lambda: scene(300, 200, 1025, 0, 60, 12),
+    "2049 ranks": lambda: scene(300, 200, 2049, 0, 60, 13),
+    "4096 ranks": lambda: scene(300, 200, 4096, 0, 60, 14, levels=7),
+    "131073 ranks": lambda: scene(700, 500, 131073, 0, 12, 15, levels=100),
     "many ranks": lambda: scene(4200, 2100, 30000, 0, 20, 8),        # 561 superblocks
     "wide": lambda: scene(65536, 16, 9000, 0, 700, 9),               # 512 x 1
     "1024 superblocks": lambda: scene(4096, 4096, 6000, 0, 120, 10),
