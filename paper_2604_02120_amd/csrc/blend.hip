@@ -136,9 +136,9 @@ template <int NB>
 struct BwdSlots {
     float4 attr[NB];           // (log2 o, r, g, b)
     float2 mean[NB];
-    // The Gaussian index of each slot of batch b, in ids[b & 1]: the flush of batch b + 1 reads
-    // other threads' slots while batch b is staged.
-    uint32_t ids[2][NB];
+    // The Gaussian index of each slot (written after the barrier that ends the staging: the flush of
+    // the batch before reads other threads' slots until then).
+    uint32_t ids[NB];
     // which of its 64 entries each wavefront keeps
     alignas(16) unsigned long long kept[4];
 };
@@ -1130,7 +1130,7 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, BwdStage<M, NB> 
         BwdAcc<NB> &s_acc = *acc_;
         const int per = (staged + 3) >> 2;         // slots per wavefront, at most 64
         float *acc = s_acc.v;
-        const uint32_t *ids = S.ids[bb & 1];
+        const uint32_t *ids = S.ids;
         uint16_t *list = s_acc.list[L.w];
         const int s0 = L.w * per;
         // a slot is listed if any of its nine sums is nonzero (NaN included); one whose sums
@@ -1195,7 +1195,6 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, BwdStage<M, NB> 
                 uint32_t(kept >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(kept), uint32_t(before(L.w)))));
             stage<M>(nxt, e, quad, slot, S);
             S.mean[slot] = make_float2(nxt.x, nxt.y);
-            S.ids[b & 1][slot] = nxt.id;
         }
         if constexpr (kDet) {
             if (L.t < NB) det->map[b & 1][L.t] = uint16_t(slot);
@@ -1215,6 +1214,7 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, BwdStage<M, NB> 
         }
         staged = total;
         __syncthreads();
+        if (keep) S.ids[slot] = nxt.id;
         // unconditional: before the first batch these read entry `start` and Gaussian 0, unused
         nxt = src.fetch(ent.id(), n);
         ent = entry(b - 2);
