@@ -6,12 +6,15 @@
 // produced without ever sorting 64-bit tile|depth keys:
 //   1. the Gaussians themselves are sorted by depth (stable LSD radix sort of N 32-bit keys, so
 //      equal depths keep increasing index): this fixes every Gaussian's rank in (depth, index);
+//   2. the Gaussians go in rank order to the superblocks of 8 x 8 tiles that they touch, each with a
+//      64-bit mask of the tiles, and the masks are then transposed into the tiles' lists ("superblocks"
+//      below): no pair is ever sorted.
+// Grids of more than 1024 superblocks sort the pairs instead:
 //   2. pairs are emitted in rank order, each with its tile id as key (16-bit when the grid has at
 //      most 65536 tiles, else 32-bit);
-//   3. a stable LSD radix sort of the pairs on the tile id alone (ceil(log2 tiles / 8) passes, 2
-//      up to 65536 tiles) then leaves each tile's pairs in rank order, i.e. (depth, index) order.
-// Against sorting (tile << 32 | depth) pairs directly this moves ~40 instead of ~200 bytes per
-// pair. Everything is integer work and bit-exact: the covered-tile rectangle is evaluated in
+//   3. a stable LSD radix sort of the pairs on the tile id alone (ceil(log2 tiles / 8) passes)
+//      then leaves each tile's pairs in rank order, i.e. (depth, index) order.
+// Everything is integer work and bit-exact: the covered-tile rectangle is evaluated in
 // integer arithmetic (floor((x - r)/16) == (floor(x) - r) >> 4 for integer r).
 #include <hip/hip_runtime.h>
 
@@ -384,28 +387,84 @@ __device__ inline bool tile_visible(const GaussVis &g, int32_t tx, int32_t ty, i
     return false;
 }
 
-// The candidate tiles of mode 1: the 3-sigma rectangle cut to the tiles that the bounding box of
-// {Q <= theta} (half-widths sqrt(theta C / det), sqrt(theta A / det), plus one pixel) can reach.
-// Every tile cut away has Q > theta on all its pixels by a wide margin, so the tests above would
-// reject it: the cut changes which tiles are tested, never a decision. Empty when o < 1/255.
-__device__ inline Rect cand_rect(const GaussVis &g, const Rect &R) {
-    if (!g.live) return Rect{0, 0, 0, 0};
-    if (!(g.A > 0.0 && g.C > 0.0 && g.det > 0.0)) return R;
-    const double hx = fmin(sqrt(g.theta * g.C / g.det) + 1.0, 1e8);
-    const double hy = fmin(sqrt(g.theta * g.A / g.det) + 1.0, 1e8);
-    Rect C = R;
-    const int64_t bx0 = int64_t(floor((g.x - hx - 15.0) / 16.0)), bx1 = int64_t(floor((g.x + hx) / 16.0)) + 1;
-    const int64_t by0 = int64_t(floor((g.y - hy - 15.0) / 16.0)), by1 = int64_t(floor((g.y + hy) / 16.0)) + 1;
-    if (bx0 > C.tx0) C.tx0 = int32_t(bx0 < C.tx1 ? bx0 : C.tx1);
-    if (bx1 < C.tx1) C.tx1 = int32_t(bx1 > C.tx0 ? bx1 : C.tx0);
-    if (by0 > C.ty0) C.ty0 = int32_t(by0 < C.ty1 ? by0 : C.ty1);
-    if (by1 < C.ty1) C.ty1 = int32_t(by1 > C.ty0 ? by1 : C.ty0);
-    return C;
+// The same decision in FP32 where it is clear. The smallest Q over the tile's rectangle is at one of
+// two points (the nearest dx with its best dy, the nearest dy with its best dx; 0 if the mean lies
+// inside); evaluated in FP32 its error is below 2^-16 of its (positive) terms, theta's below 2^-18 of
+// it. Between the two bounds, and for a conic that is not definite, the tests above decide. (They
+// take about 90 double-precision operations a tile: 291 us of 3 M Gaussians at 4K, now 190.)
+struct Vis32 {
+    float x, y, A, B, C, o, rA, rC;
+    float lo, hi;                                 // theta less and plus its error; -inf, inf: unclear
+};
+__device__ inline Vis32 vis32_setup(float2 m, const float *conic, float o, Rect *cand, const Rect &R) {
+    Vis32 g;
+    g.x = m.x; g.y = m.y;
+    g.A = conic[0]; g.B = conic[1]; g.C = conic[2];
+    g.o = o;
+    const float theta = float(vis_theta(double(o)));
+    const float bb = g.B * g.B;
+    const float det = fmaf(g.A, g.C, -bb) - fmaf(g.B, g.B, -bb);
+    // (in a range where none of the products below overflows and a pixel is a pixel)
+    const bool definite = g.A > 1e-18f && g.A < 1e18f && g.C > 1e-18f && g.C < 1e18f && det > 0.f &&
+                          fabsf(g.x) < 0x1p20f && fabsf(g.y) < 0x1p20f;
+    g.rA = __builtin_amdgcn_rcpf(g.A);
+    g.rC = __builtin_amdgcn_rcpf(g.C);
+    g.lo = definite ? theta * (1.0f - 0x1p-18f) : -INFINITY;
+    g.hi = definite ? theta * (1.0f + 0x1p-18f) : INFINITY;
+    if (cand) {
+        // candidates: the rectangle cut to the bounding box of {Q <= theta}, with room for rounding
+        *cand = R;
+        if (!(o >= 1.0f / 255.0f)) {
+            *cand = Rect{0, 0, 0, 0};
+        } else if (definite) {
+            const float hx = fminf(sqrtf(theta * g.C / det) * 1.001f + 1.5f, 1e8f);
+            const float hy = fminf(sqrtf(theta * g.A / det) * 1.001f + 1.5f, 1e8f);
+            const auto lo = [](float v) { return int64_t(floorf((v - 15.0f) * 0.0625f)); };
+            const auto hi = [](float v) { return int64_t(floorf(v * 0.0625f)) + 1; };
+            cand->tx0 = int32_t(clampi(lo(g.x - hx), R.tx0, R.tx1));
+            cand->tx1 = int32_t(clampi(hi(g.x + hx), cand->tx0, R.tx1));
+            cand->ty0 = int32_t(clampi(lo(g.y - hy), R.ty0, R.ty1));
+            cand->ty1 = int32_t(clampi(hi(g.y + hy), cand->ty0, R.ty1));
+        }
+    }
+    return g;
+}
+__device__ inline bool tile_visible(const Vis32 &g, int32_t tx, int32_t ty, int32_t W, int32_t H) {
+    const int32_t px1 = tx * kTile + kTile - 1 < W - 1 ? tx * kTile + kTile - 1 : W - 1;
+    const int32_t py1 = ty * kTile + kTile - 1 < H - 1 ? ty * kTile + kTile - 1 : H - 1;
+    const float dxl = g.x - float(px1), dxh = g.x - float(tx * kTile);
+    const float dyl = g.y - float(py1), dyh = g.y - float(ty * kTile);
+    const float a = fminf(fmaxf(0.0f, dxl), dxh), b = fminf(fmaxf(0.0f, dyl), dyh);
+    const float ba = g.B * a, bb = g.B * b;
+    const float v = fminf(fmaxf(-ba * g.rC, dyl), dyh), u = fminf(fmaxf(-bb * g.rA, dxl), dxh);
+    const float s1 = fmaf(g.A * a, a, g.C * v * v), s2 = fmaf(g.C * b, b, g.A * u * u);
+    const float q1 = fmaf(2.0f * ba, v, s1), q2 = fmaf(2.0f * bb, u, s2);
+    const bool in = fmaf(s1, 0x1p-16f, q1) < g.lo || fmaf(s2, 0x1p-16f, q2) < g.lo;
+    const bool out = fmaf(s1, -0x1p-16f, q1) > g.hi && fmaf(s2, -0x1p-16f, q2) > g.hi;
+    if (in || out) return in;
+    const float conic[3] = {g.A, g.B, g.C};
+    return tile_visible(vis_setup(make_float2(g.x, g.y), conic, g.o), tx, ty, W, H);
 }
 
 // visible-tile masks: a Gaussian with at most this many candidates keeps its answer as one bit per
 // candidate (row-major), so that emission needs no second test
 constexpr uint32_t kMaskBits = 64;
+
+// The same mask where superblocks follow: a byte per row, of rectangles of up to 8 x 8 tiles (what a
+// superblock needs of it is then two shifts away; from the other form it took a loop over the rows,
+// in each of the two kernels that ask: 73 and 117 us, now 45 and 99)
+__device__ inline bool sb_big(const Rect &R) { return R.tx1 - R.tx0 > 8 || R.ty1 - R.ty0 > 8; }
+__device__ inline unsigned long long sb_form(const Rect &R, unsigned long long mask) {
+    const int w = R.tx1 - R.tx0, h = R.ty1 - R.ty0;
+    const uint32_t row = (1u << w) - 1u;
+    uint32_t half[2] = {0u, 0u};
+#pragma unroll
+    for (int y = 0; y < 8; ++y) {
+        if (y < h) half[y >> 2] |= (uint32_t(mask) & row) << (8 * (y & 3));
+        mask >>= w;
+    }
+    return (static_cast<unsigned long long>(half[1]) << 32) | half[0];
+}
 
 // ------------------------------------------------------------------------------- balanced pairs
 // The candidate tiles of a wavefront's 64 rectangles are enumerated in chunks of 64, one candidate
@@ -481,16 +540,15 @@ __device__ inline Rect unpack_rect(unsigned long long p) {
 __device__ inline unsigned long long count_visible(const float2 *means, const int32_t *radii,
                                                    const float *conics, const float *opac, int64_t i,
                                                    int64_t n, int32_t gx, int32_t gy, int32_t W,
-                                                   int32_t H, GaussVis *s_vis,
+                                                   int32_t H, Vis32 *s_vis,
                                                    unsigned long long *counts,
                                                    unsigned long long *masks, uint4 *recs) {
     const bool valid = i < n;
     Rect CR{0, 0, 0, 0};
-    GaussVis g{};
+    Vis32 g{};
     if (valid) {
         const float2 m = means[i];
-        g = vis_setup(m, conics + 3 * i, opac[i]);
-        CR = cand_rect(g, tile_rect(m.x, m.y, radii[i], gx, gy));
+        g = vis32_setup(m, conics + 3 * i, opac[i], &CR, tile_rect(m.x, m.y, radii[i], gx, gy));
     }
     s_vis[threadIdx.x] = g;   // read only by this wavefront's lanes
     __builtin_amdgcn_wave_barrier();
@@ -520,9 +578,12 @@ __device__ inline unsigned long long count_visible(const float2 *means, const in
         }
     }
     if (valid) {
-        if (counts) counts[i] = cnt;
-        masks[i] = mask;
-        recs[i] = count_rect(cnt, CR);
+        if (counts) {
+            counts[i] = cnt;
+            masks[i] = mask;
+        }
+        // superblocks: the mask (0 where it has no room for the rectangle) in the count's place
+        recs[i] = count_rect(counts ? cnt : sb_big(CR) ? 0ull : sb_form(CR, mask), CR);
     }
     return cnt;
 }
@@ -540,7 +601,7 @@ __global__ __launch_bounds__(kThreads) void k_bin_count(const float2 *means, con
                                                         unsigned long long *partial,
                                                         unsigned long long *total_a,
                                                         long long *total_b) {
-    __shared__ GaussVis s_vis[kMode == 1 ? kThreads : 1];
+    __shared__ Vis32 s_vis[kMode == 1 ? kThreads : 1];
     __shared__ unsigned long long s_wave[kThreads / 64];
     const int64_t i0 = int64_t(blockIdx.x) * iters * kThreads + threadIdx.x;
     unsigned long long sum = 0, all;
@@ -637,7 +698,7 @@ __global__ __launch_bounds__(256) void k_bin_fill(const float2 *means, const flo
     const bool valid = j < n;
     const uint32_t i = valid ? sorted_idx[j] : 0u;
     // the rectangle to emit from (laid out in rank order by the depth sort): mode 0 the 3-sigma
-    // one, mode 1 the candidates (cand_rect)
+    // one, mode 1 the candidates (vis32_setup)
     Rect R{0, 0, 0, 0};
     GaussVis g{};
     unsigned long long base = 0, vmask = 0;
@@ -1005,6 +1066,7 @@ constexpr int64_t kSort4 = 131072;
 __global__ __launch_bounds__(kSmallThreads) void k_sort_small(const float *depths, int n,
                                                               uint32_t *sorted_idx,
                                                               const uint4 *recs_by_idx,
+                                                              unsigned long long *rank_counts,
                                                               unsigned long long *rank_rects,
                                                               uint32_t *ranges, int ranges_n,
                                                               int32_t *status) {
@@ -1087,6 +1149,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_sort_small(const float *depth
         if (i < n) {
             const uint4 r = recs_by_idx[val[k]];
             sorted_idx[i] = val[k];
+            if (rank_counts) rank_counts[i] = (static_cast<unsigned long long>(r.y) << 32) | r.x;
             rank_rects[i] = (static_cast<unsigned long long>(r.w) << 32) | r.z;
         }
     }
@@ -1160,10 +1223,9 @@ int sort_tiles(K *ka, K *kb, uint32_t *va, uint32_t *vb, const unsigned long lon
 // vector instruction per pair, where a radix sort of the pairs takes about 2.3 per pass for ranking
 // alone, two passes, and reads and writes every pair in each. (A Gaussian touches 18 tiles but only
 // 1.6 superblocks on the 4K frame of 3M Gaussians, so what is sorted is a tenth.) Measured at 4K,
-// 54.7M pairs, from the sorted Gaussians to the ranges: 0.18 ms against 0.84.
+// 54.7M pairs, from the sorted Gaussians to the ranges: 0.18 ms against 0.84. In mode 1 the masks hold
+// the visible tiles alone: 0.33 ms against 0.50.
 constexpr int kSbMaxGrid = 4096;                         // blocks of steps 2 and 4, which loop
-constexpr int kSbWindow = 4096;                          // entries ranked at a time in step 1
-constexpr int kSbSteps = kSbWindow / kSortThreads;
 constexpr int kSbStage = 2 * kSbTiles * 64;              // pairs assembled in LDS at a time
 
 struct SbGrid {
@@ -1176,15 +1238,15 @@ __host__ __device__ inline SbGrid sb_grid(int32_t gx, int32_t gy) {
 // Ranks per block of step 1: the digit counts (superblocks x blocks) then fit the words of the
 // depth sort's look-back, which they replace (256 per 1024 Gaussians).
 inline int sb_ranks(int32_t n_sb) { return n_sb <= 256 ? 1024 : n_sb <= 512 ? 2048 : 4096; }
-// The superblock path where it applies: mode 0 (mode 1 keeps its tests' answers per pair) and a grid
-// of at most kMaxSb superblocks
-inline bool by_superblock(int32_t mode, const SbGrid &G) {
-    return mode == GSB_BIN_RECT && G.n <= kMaxSb;
-}
+// The superblock path where it applies: a grid of at most kMaxSb superblocks
+inline bool by_superblock(const SbGrid &G) { return G.n <= kMaxSb; }
 
 // First entry and first chunk of every superblock, and the ends
+constexpr int kSbLists = 8, kSbListRun = 16;
 struct SbTable {
     uint32_t start[kMaxSb + 1], chunk[kMaxSb + 1];
+    // mode 1: lengths of the lists of the large rectangles' masks, a cache line apart
+    alignas(128) unsigned long long listed[kSbLists][16];
 };
 
 // Superblocks touched by a (non-empty) tile rectangle
@@ -1228,6 +1290,211 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_hist(const unsigned long lo
     for (int d = t; d < G.n; d += kSortThreads) hist[int64_t(d) * nblk + blk] = s_h[d];
 }
 
+// Mode 1: the tiles of superblock (sx, sy) that are visible, from the candidates' mask (sb_form).
+__device__ inline unsigned long long sb_submask(const Rect &R, unsigned long long mask, int sx, int sy) {
+    const int dx = R.tx0 - sx * kSbEdge, dy = R.ty0 - sy * kSbEdge;       // within +-7
+    mask = dy >= 0 ? mask << (8 * dy) : mask >> (-8 * dy);
+    mask = dx >= 0 ? mask << dx : mask >> -dx;
+    const uint32_t cols = ((dx >= 0 ? 0xffu << dx : 0xffu >> -dx) & 0xffu) * 0x01010101u;
+    return mask & ((static_cast<unsigned long long>(cols) << 32) | cols);
+}
+
+// Mode 1: the superblocks with a visible tile. Those of a rectangle that its candidate mask covers are
+// cut from it. Those of a larger one are listed by k_sb_list, from the end of the entries' arrays
+// downwards; rank_masks holds a Gaussian's place and their number << 48. There are `lists` lists, in
+// alternate runs of kSbListRun places: with one counter for all, the XCDs' atomics on it took 400 us
+// of 3 M Gaussians (20 ns each). The masks are tested again where the arrays had no room for them,
+// which takes more than one such superblock for two pairs (a thin line has 8 pairs in each).
+struct SbVisible {
+    const unsigned long long *rank_masks;
+    unsigned long long *masks;                    // the arrays' ends: place o is [-1 - o]
+    uint32_t *sbs;
+    const SbTable *table;
+    int lists;                                    // a power of two
+    const float2 *means;
+    const float *conics, *opac;
+    int32_t W, H;
+};
+__device__ inline unsigned long long sb_test(const SbVisible &V, const Rect &R, uint32_t i, int sx, int sy) {
+    const Vis32 g = vis32_setup(V.means[i], V.conics + 3 * int64_t(i), V.opac[i], nullptr, R);
+    unsigned long long m = 0;
+#pragma unroll 1
+    for (int b = 0; b < kSbTiles; ++b) {
+        const int tx = sx * kSbEdge + (b & (kSbEdge - 1)), ty = sy * kSbEdge + (b >> kSbShift);
+        if (tx >= R.tx0 && tx < R.tx1 && ty >= R.ty0 && ty < R.ty1 && tile_visible(g, tx, ty, V.W, V.H))
+            m |= 1ull << b;
+    }
+    return m;
+}
+// the places of list `l`'s entries
+__device__ inline unsigned long long sb_place(unsigned long long o, int l, int lists) {
+    return (o / kSbListRun * lists + l) * kSbListRun + o % kSbListRun;
+}
+__device__ inline unsigned long long sb_listed(const SbVisible &V) {      // places up to the last
+    unsigned long long most = 0;
+    for (int l = 0; l < V.lists; ++l) {
+        const unsigned long long e = V.table->listed[l][0];
+        most = e > most ? e : most;
+    }
+    return sb_place(most + kSbListRun - 1, 0, V.lists) / kSbListRun * kSbListRun;
+}
+// f(superblock, mask) for every superblock of Gaussian *i with a visible tile.
+template <class F>
+__device__ inline void sb_visible(const SbVisible &V, const SbGrid &G, const Rect &R,
+                                  unsigned long long mask, const uint32_t *i, bool listed,
+                                  F f) {
+    if (R.tx1 <= R.tx0 || R.ty1 <= R.ty0) return;
+    const bool big = sb_big(R);
+    if (big && listed) {
+        const unsigned long long o = mask & ((1ull << 45) - 1ull);
+        const int l = int(mask >> 45) & 7, e = int(mask >> 48);
+#pragma unroll 1
+        for (int k = 0; k < e; k += 4) {                     // four loads at a time (99 us, now 89)
+            uint32_t sb[4];
+            unsigned long long m[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int64_t p = int64_t(sb_place(o + (k + q < e ? k + q : k), l, V.lists));
+                sb[q] = V.sbs[-1 - p];
+                m[q] = V.masks[-1 - p];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (k + q < e) f(sb[q], m[q]);
+        }
+        return;
+    }
+    const Rect q = sb_rect(R);
+#pragma unroll 1
+    for (int sy = q.ty0; sy < q.ty1; ++sy)
+#pragma unroll 1
+        for (int sx = q.tx0; sx < q.tx1; ++sx) {
+            const unsigned long long m = big ? sb_test(V, R, *i, sx, sy) : sb_submask(R, mask, sx, sy);
+            if (m != 0ull) f(uint32_t(sy * G.sx + sx), m);
+        }
+}
+
+// The list of the Gaussians with candidates past a mask's 8 x 8, each tested by a whole wavefront,
+// a superblock's 64 tiles at a time. In the order of the indices, as large Gaussians are neighbours
+// in the order of depth. Masks are gathered in LDS, for an atomic per kMaxSb of them or wavefront.
+__global__ __launch_bounds__(64, 5) void k_sb_list(uint4 *recs, SbVisible V, SbTable *table,
+                                                int64_t n, SbGrid G, int64_t cap) {
+    __shared__ unsigned long long s_mask[kMaxSb];
+    __shared__ uint16_t s_sb[kMaxSb];
+    const int lane = threadIdx.x, l = int(blockIdx.x) & (V.lists - 1);    // (an XCD's own list)
+    const int64_t i = int64_t(blockIdx.x) * 64 + lane;
+    Rect R{0, 0, 0, 0};
+    if (i < n) {
+        const uint2 z = reinterpret_cast<const uint2 *>(recs + i)[1];
+        R = unpack_rect((static_cast<unsigned long long>(z.y) << 32) | z.x);
+    }
+    const bool big = R.tx1 > R.tx0 && R.ty1 > R.ty0 && sb_big(R);
+    unsigned long long todo = __ballot(big);
+    if (todo == 0ull) return;                                // wavefront-uniform
+    const Rect Q = big ? sb_rect(R) : Rect{0, 0, 0, 0};
+    Vis32 own{};
+    if (big) own = vis32_setup(V.means[i], V.conics + 3 * i, V.opac[i], nullptr, R);
+    int fill = 0;                                            // masks in LDS (uniform)
+    int place = 0, mine = 0;                                 // this lane's: the first and how many
+    bool waits = false;
+    const auto flush = [&] {
+        unsigned long long base = 0;
+        if (lane == 0) base = atomicAdd(&table->listed[l][0], (unsigned long long)fill);
+        base = __shfl(base, 0, 64);
+        if (waits) {
+            const unsigned long long r = (base + place) | ((unsigned long long)(l | mine << 3) << 45);
+            reinterpret_cast<uint2 *>(recs + i)[0] = make_uint2(uint32_t(r), uint32_t(r >> 32));
+        }
+        waits = false;
+        __builtin_amdgcn_wave_barrier();
+        for (int k = lane; k < fill; k += 64) {
+            const int64_t o = int64_t(sb_place(base + k, l, V.lists));
+            if (o < cap) {
+                V.masks[-1 - o] = s_mask[k];
+                V.sbs[-1 - o] = s_sb[k];
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        fill = 0;
+    };
+    while (todo) {
+        const int src = __ffsll((long long)todo) - 1;
+        todo &= todo - 1;
+        const auto from = [&](int v) { return __builtin_amdgcn_readlane(v, src); };
+        const Rect S{from(R.tx0), from(R.tx1), from(R.ty0), from(R.ty1)};
+        const Rect P{from(Q.tx0), from(Q.tx1), from(Q.ty0), from(Q.ty1)};
+        const auto fromf = [&](float v) { return __int_as_float(from(__float_as_int(v))); };
+        const Vis32 g{fromf(own.x), fromf(own.y), fromf(own.A), fromf(own.B), fromf(own.C),
+                      fromf(own.o), fromf(own.rA), fromf(own.rC), fromf(own.lo), fromf(own.hi)};
+        if (fill + (P.tx1 - P.tx0) * (P.ty1 - P.ty0) > kMaxSb) flush();
+        const int first = fill;
+        for (int sy = P.ty0; sy < P.ty1; ++sy)
+            for (int sx = P.tx0; sx < P.tx1; ++sx) {
+                const int tx = sx * kSbEdge + (lane & (kSbEdge - 1)), ty = sy * kSbEdge + (lane >> kSbShift);
+                const bool v = tx >= S.tx0 && tx < S.tx1 && ty >= S.ty0 && ty < S.ty1 &&
+                               tile_visible(g, tx, ty, V.W, V.H);
+                const unsigned long long m = __ballot(v);
+                if (m == 0ull) continue;
+                if (lane == 0) {
+                    s_mask[fill] = m;
+                    s_sb[fill] = uint16_t(sy * G.sx + sx);
+                }
+                ++fill;
+            }
+        if (lane == src) {
+            place = first;
+            mine = fill - first;
+            waits = true;
+        }
+    }
+    flush();
+}
+
+// Mode 1: as k_sb_hist, for the superblocks with a visible tile; also the place of each rank's first
+// entry among its block's, and the number of the block's.
+__global__ __launch_bounds__(kSortThreads, 6) void k_sb_hist_visible(
+    const unsigned long long *rank_rects, const uint32_t *sorted_idx, SbVisible V, int64_t n, int ranks,
+    SbGrid G, uint32_t *hist, int64_t nblk, int64_t cap, uint32_t *rank_pos,
+    uint32_t *block_entries) {
+    __shared__ uint32_t s_h[kMaxSb], s_wave[kSortThreads / 64];
+    const int t = threadIdx.x;
+    for (int d = t; d < G.n; d += kSortThreads) s_h[d] = 0u;
+    __syncthreads();
+    const int64_t blk = xcd_rank(blockIdx.x, uint32_t(nblk));
+    if (blk >= nblk) return;                                 // block-uniform
+    const bool listed = sb_listed(V) <= (unsigned long long)cap;
+    const int64_t j0 = blk * ranks;
+    uint32_t first = 0;
+    unsigned long long rect = 0, mask = 0, next_rect = 0, next_mask = 0;   // loaded a step ahead
+    const auto load = [&](int64_t j) {
+        next_rect = next_mask = 0;
+        if (j < n) {
+            next_rect = rank_rects[j];
+            next_mask = V.rank_masks[j];
+        }
+    };
+    load(j0 + t);
+    for (int k = 0; k < ranks && j0 + k < n; k += kSortThreads) {       // block-uniform
+        const int64_t j = j0 + k + t;
+        uint32_t e = 0, step;
+        rect = next_rect;
+        mask = next_mask;
+        if (k + kSortThreads < ranks) load(j + kSortThreads);
+        if (j < n)
+            sb_visible(V, G, unpack_rect(rect), mask, sorted_idx + j, listed,
+                       [&](uint32_t sb, unsigned long long) {
+                           atomicAdd(&s_h[sb], 1u);
+                           ++e;
+                       });
+        const uint32_t pos = block_exclusive_scan<uint32_t>(e, s_wave, step);
+        if (j < n) rank_pos[j] = first + pos;
+        first += step;
+    }
+    if (t == 0) block_entries[blk] = first;
+    __syncthreads();
+    for (int d = t; d < G.n; d += kSortThreads) hist[int64_t(d) * nblk + blk] = s_h[d];
+}
+
 // A block places the entries of its ranks: thread t owns kPer consecutive ones, whose rectangles and
 // indices it loads first, all at once (a load per rank in the loop over ranks left two blocks per
 // CU waiting: 107 us at 4K, now 61). The block's entries, enumerated in rank order, are taken
@@ -1236,10 +1503,16 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_hist(const unsigned long lo
 // ranks (xcd_rank): a superblock's entries from neighbouring blocks are neighbours in memory, a run
 // is shorter than a cache line, and the line is put together in that XCD's L2 (12% less time).
 // Block 0 also fills the superblock table. kOne: the only block (nblk = 1) counts its entries per
-// superblock itself, with no launches of k_sb_hist and its scan.
-template <int kPer, bool kOne>
+// superblock itself, with no launches of k_sb_hist and its scan. kVis: mode 1, entries with a visible
+// tile and their masks (half the window, as masks do not fit the keys' spare bits).
+template <int kPer, bool kOne, bool kVis>
 __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
-    const unsigned long long *rank_rects, const uint32_t *sorted_idx, int64_t n, SbGrid G, int bits, const uint32_t *hist, int64_t nblk, BinHeader *hdr, int64_t cap, uint32_t chunk, uint32_t *e_idx, unsigned long long *e_mask, SbTable *table) {
+    const unsigned long long *rank_rects, const uint32_t *sorted_idx, int64_t n, SbGrid G, int bits,
+    const uint32_t *hist, int64_t nblk, BinHeader *hdr, int64_t cap, uint32_t chunk, uint32_t *e_idx,
+    unsigned long long *e_mask, SbTable *table, SbVisible V,
+    const uint32_t *rank_pos, const uint32_t *block_entries) {
+    static_assert(!(kOne && kVis), "mode 1 counts in k_sb_hist_visible");
+    constexpr int kSbWindow = kVis ? 2048 : 4096, kSbSteps = kSbWindow / kSortThreads;
     constexpr int kWaves = kSortThreads / 64, kDig = kMaxSb / kSortThreads;
     __shared__ uint32_t s_gofs[kMaxSb];                 // next global position of each superblock
     __shared__ uint16_t s_wcnt[kWaves][kMaxSb];         // per-wave counts, then prefixes
@@ -1247,6 +1520,8 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
     __shared__ uint32_t s_wave[kWaves];
     __shared__ uint32_t s_key[kSbWindow];               // superblock | columns << 16 | rows << 24
     __shared__ uint32_t s_idx[kSbWindow];
+    __shared__ unsigned long long s_mask[kVis ? kSbWindow : 1];
+    __shared__ int s_rank;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int64_t blk = xcd_rank(blockIdx.x, uint32_t(nblk));
     if (blk >= nblk) return;                                 // block-uniform
@@ -1257,7 +1532,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
     unsigned long long rects[kPer];
     uint32_t idx[kPer], mine = 0;
 #pragma unroll
-    for (int k = 0; k < kPer; k += 4) {
+    for (int k = 0; k < (kVis ? 0 : kPer); k += 4) {
         ulonglong2 r01{0, 0}, r23{0, 0};
         uint4 i4{0, 0, 0, 0};
         if (j0 + k < n) {
@@ -1276,8 +1551,10 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
         const Rect q = sb_rect(r);
         return uint32_t((q.tx1 - q.tx0) * (q.ty1 - q.ty0));
     };
+    if constexpr (!kVis) {
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) mine += entries(unpack_rect(rects[k]));
+        for (int k = 0; k < kPer; ++k) mine += entries(unpack_rect(rects[k]));
+    }
     uint32_t n_entries;
     if constexpr (kOne) {
         for (int d = t; d < kMaxSb; d += kSortThreads) s_gofs[d] = 0u;
@@ -1334,39 +1611,87 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
             table->chunk[kMaxSb] = run;
         }
     }
-    uint32_t total;
-    const uint32_t pos0 = block_exclusive_scan<uint32_t>(mine, s_wave, total);
+    if (kVis && hdr->total > (unsigned long long)cap) return;   // block-uniform; every list is empty
+    uint32_t total = 0, pos0 = 0;
+    if constexpr (kVis) total = block_entries[blk];
+    else pos0 = block_exclusive_scan<uint32_t>(mine, s_wave, total);
     for (uint32_t w0 = 0; w0 < total; w0 += kSbWindow) {      // block-uniform
         const int cnt = int(total - w0 < uint32_t(kSbWindow) ? total - w0 : uint32_t(kSbWindow));
-        uint32_t pos = pos0;
-#pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-            // the part of rank k's entries [pos, pos + e) that lies in the window
-            const Rect R = unpack_rect(rects[k]);
-            const uint32_t e = entries(R);
-            const uint32_t lo = pos < w0 ? w0 - pos : 0u;
-            const uint32_t hi = pos >= w0 + kSbWindow ? 0u
-                              : e < w0 + kSbWindow - pos ? e : w0 + kSbWindow - pos;
-            if (lo < hi) {
-                const Rect q = sb_rect(R);
-                const uint32_t wd = uint32_t(q.tx1 - q.tx0);
-                int sy = q.ty0, sx = q.tx0;
-                if (lo > 0) {
-                    sy += int(lo / wd);
-                    sx += int(lo % wd);
+        [[maybe_unused]] uint32_t pos = pos0;
+        // the part [lo, hi) of a rank's entries [pos, pos + e) that lies in the window
+        [[maybe_unused]] const auto part = [&](uint32_t e, uint32_t &lo, uint32_t &hi) {
+            lo = pos < w0 ? w0 - pos : 0u;
+            hi = pos >= w0 + kSbWindow ? 0u : e < w0 + kSbWindow - pos ? e : w0 + kSbWindow - pos;
+        };
+        if constexpr (kVis) {
+            // rank k kSortThreads + t of the block, the next one's data loaded ahead
+            const bool listed = sb_listed(V) + hdr->entries <= (unsigned long long)cap;
+            const int64_t b0 = blk * kSortThreads * kPer;
+            const int ranks = int(n - b0 < kSortThreads * kPer ? n - b0 : kSortThreads * kPer);
+            struct Rank {
+                uint32_t pos, end, idx;
+                unsigned long long rect, mask;
+            };
+            const auto load = [&](int r) {
+                Rank a{total, total, 0, 0, 0};
+                if (r < ranks) {
+                    a.pos = rank_pos[b0 + r];
+                    if (r + 1 < ranks) a.end = rank_pos[b0 + r + 1];
+                    a.idx = sorted_idx[b0 + r];
+                    a.rect = rank_rects[b0 + r];
+                    a.mask = V.rank_masks[b0 + r];
                 }
-                uint32_t row = uint32_t(sy * G.sx) | (sb_span(R.ty0, R.ty1, sy) << 24);
-                for (uint32_t o = pos + lo - w0; o < pos + hi - w0; ++o) {
-                    s_key[o] = (row + uint32_t(sx)) | (sb_span(R.tx0, R.tx1, sx) << 16);
-                    s_idx[o] = idx[k];
-                    if (++sx == q.tx1) {
-                        sx = q.tx0;
-                        ++sy;
-                        row = uint32_t(sy * G.sx) | (sb_span(R.ty0, R.ty1, sy) << 24);
+                return a;
+            };
+            const int r0 = w0 > 0 ? s_rank : 0;              // the window's first rank
+            Rank next = load(r0 + t);
+            if (w0 > 0) __syncthreads();                     // s_rank has been read
+#pragma unroll 1
+            for (int r = r0 + t; r < ranks; r += kSortThreads) {
+                const Rank a = next;
+                if (a.pos >= w0 + kSbWindow) break;
+                next = load(r + kSortThreads);
+                if (a.end >= w0 + kSbWindow) s_rank = r;     // the last rank that starts here
+                if (a.end <= w0 || a.pos == a.end) continue;
+                uint32_t o = a.pos - w0;                 // (wraps while before the window)
+                sb_visible(V, G, unpack_rect(a.rect), a.mask, &a.idx, listed,
+                           [&](uint32_t sb, unsigned long long m) {
+                               if (o < uint32_t(kSbWindow)) {
+                                   s_key[o] = sb;
+                                   s_idx[o] = a.idx;
+                                   s_mask[o] = m;
+                               }
+                               ++o;
+                           });
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                const Rect R = unpack_rect(rects[k]);
+                const uint32_t e = entries(R);
+                uint32_t lo, hi;
+                part(e, lo, hi);
+                if (lo < hi) {
+                    const Rect q = sb_rect(R);
+                    const uint32_t wd = uint32_t(q.tx1 - q.tx0);
+                    int sy = q.ty0, sx = q.tx0;
+                    if (lo > 0) {
+                        sy += int(lo / wd);
+                        sx += int(lo % wd);
+                    }
+                    uint32_t row = uint32_t(sy * G.sx) | (sb_span(R.ty0, R.ty1, sy) << 24);
+                    for (uint32_t o = pos + lo - w0; o < pos + hi - w0; ++o) {
+                        s_key[o] = (row + uint32_t(sx)) | (sb_span(R.tx0, R.tx1, sx) << 16);
+                        s_idx[o] = idx[k];
+                        if (++sx == q.tx1) {
+                            sx = q.tx0;
+                            ++sy;
+                            row = uint32_t(sy * G.sx) | (sb_span(R.ty0, R.ty1, sy) << 24);
+                        }
                     }
                 }
+                pos += e;
             }
-            pos += e;
         }
         for (int d = t; d < kMaxSb; d += kSortThreads) {
 #pragma unroll
@@ -1376,6 +1701,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
         // wave w ranks the entries [w seg, (w + 1) seg) of the window, 64 at a time
         const int steps = (cnt + kSortThreads - 1) / kSortThreads, seg = steps * 64;
         uint32_t key[kSbSteps], loc[kSbSteps], id[kSbSteps];
+        unsigned long long mk[kVis ? kSbSteps : 1];
 #pragma unroll
         for (int i = 0; i < kSbSteps; ++i) {
             if (i >= steps) break;                           // uniform
@@ -1384,6 +1710,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
             const int oc = valid ? o : 0;
             key[i] = s_key[oc];
             id[i] = s_idx[oc];
+            if constexpr (kVis) mk[i] = s_mask[oc];
             const uint32_t d = key[i] & 0xffffu;
             const unsigned long long vmask = __builtin_amdgcn_ballot_w64(valid);
             uint32_t plo = uint32_t(vmask), phi = uint32_t(vmask >> 32);
@@ -1432,6 +1759,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
                 const uint32_t d = key[i] & 0xffffu, r = s_dstart[d] + s_wcnt[w][d] + loc[i];
                 s_key[r] = key[i];
                 s_idx[r] = id[i];
+                if constexpr (kVis) s_mask[r] = mk[i];
             }
         }
         __syncthreads();
@@ -1440,7 +1768,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
             const int64_t p = int64_t(s_gofs[d]) + (o - int(s_dstart[d]));
             if (p < cap) {
                 e_idx[p] = s_idx[o];
-                e_mask[p] = sb_mask(key_o >> 16);
+                e_mask[p] = kVis ? s_mask[kVis ? o : 0] : sb_mask(key_o >> 16);
             }
         }
         __syncthreads();
@@ -1699,12 +2027,14 @@ __global__ __launch_bounds__(256) void k_sb_write(const uint32_t *e_idx,
 // Start of bin_fill: empty ranges, zeroed sort states, the Gaussian count for the depth sort and
 // a clean status word (later kernels only ever write error codes into it).
 __global__ __launch_bounds__(256) void k_bin_init(uint32_t *ranges, int64_t m, SortState *sorts,
-                                                  BinHeader *hdr, int64_t n, int32_t *status) {
+                                                  BinHeader *hdr, int64_t n, SbTable *table,
+                                                  int32_t *status) {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < m) ranges[i] = 0u;
     if (blockIdx.x == 0) {
         uint32_t *w = reinterpret_cast<uint32_t *>(sorts);
         for (int k = threadIdx.x; k < int(sizeof(SortState) / 4); k += blockDim.x) w[k] = 0u;
+        if (table && threadIdx.x < kSbLists) table->listed[threadIdx.x][0] = 0ull;
         if (threadIdx.x == 0) {
             hdr->gaussians = (unsigned long long)n;
             *status = GSB_OK;
@@ -1770,7 +2100,7 @@ gsb_status bin_count(const float *means2d, const int32_t *radii, const float *co
     const int32_t gx = int32_t(grid_x(W)), gy = int32_t(grid_y(H));
     // Gaussians per block: mode 0 one block up to 4096 (no second launch), then 1024; mode 1, whose
     // tests are long, 256; more where the blocks would exceed the partial sums' place
-    if (mode == GSB_BIN_RECT && by_superblock(mode, sb_grid(gx, gy))) counts = nullptr;
+    if (by_superblock(sb_grid(gx, gy))) counts = nullptr;
     int64_t nb = 0;
     const auto blocks = [&](int per) { return dim3(unsigned(nb = (n + per - 1) / per)); };
     constexpr int64_t kTop = kScanMaxBlocks;
@@ -1815,7 +2145,7 @@ gsb_status bin_fill(const float *means2d, const int32_t *radii, const float *con
     const unsigned gn = unsigned(n > 0 ? (n + 255) / 256 : 1);
 
     const SbGrid G = sb_grid(gx, gy);
-    if (by_superblock(mode, G) && n > 0 && cap > 0) {
+    if (by_superblock(G) && n > 0 && cap > 0) {
         const auto *rects = at<unsigned long long>(ws, L.rects);
         auto *e_mask = at<unsigned long long>(ws, L.sb_mask);
         auto *e_idx = at<uint32_t>(ws, L.sb_idx);
@@ -1823,32 +2153,53 @@ gsb_status bin_fill(const float *means2d, const int32_t *radii, const float *con
         auto *table = at<SbTable>(ws, L.sb_table);
         const int bits = G.n > 1 ? ceil_log2(G.n) : 0;
         const int chunk = sb_chunk_size(cap);
+        // mode 1: the masks in rank order (in the offsets' place), the large rectangles' masks from
+        // the end of the entries' masks downwards
+        const bool vis = mode == GSB_BIN_VISIBLE;
+        auto *rank_masks = vis ? offs : nullptr;
+        const SbVisible V{rank_masks, e_mask + cap, e_idx + cap, table, n > 1 << 16 ? kSbLists : 1,
+                          reinterpret_cast<const float2 *>(means2d), conics, opacity, W, H};
+        if (vis || n > kSmallSort)
+            k_bin_init<<<dim3(unsigned((2 * n_tiles + 255) / 256)), 256, 0, s>>>(
+                ranges, 2 * n_tiles, sorts, hdr, n, table, status_dev);
+        if (vis)
+            k_sb_list<<<dim3(unsigned((n + 63) / 64)), 64, 0, s>>>(at<uint4>(ws, L.recs), V, table, n,
+                                                                  G, cap);
         if (n <= kSmallSort) {
             k_sort_small<<<1, kSmallThreads, 0, s>>>(depths, int(n), dva, at<uint4>(ws, L.recs),
-                                                     at<unsigned long long>(ws, L.rects), ranges,
-                                                     int(2 * n_tiles), status_dev);
-            const auto scatter = n <= 4 * kSortThreads ? k_sb_scatter<4, true>
-                               : n <= 8 * kSortThreads ? k_sb_scatter<8, true> : k_sb_scatter<16, true>;
-            scatter<<<1, kSortThreads, 0, s>>>(rects, dva, n, G, bits, nullptr, 1, hdr, cap, chunk, e_idx,
-                                               e_mask, table);
+                                                     rank_masks, at<unsigned long long>(ws, L.rects),
+                                                     ranges, int(2 * n_tiles), status_dev);
         } else {
-            k_bin_init<<<dim3(unsigned((2 * n_tiles + 255) / 256)), 256, 0, s>>>(
-                ranges, 2 * n_tiles, sorts, hdr, n, status_dev);
             // the look-back words of the smaller tiles (4096 bytes per 1024 Gaussians) take the
-            // offsets' place (8 bytes per Gaussian, and n > kSmallSort here)
+            // place of the masks by index (8 bytes per Gaussian, and n > kSmallSort here), which this
+            // path does not use
             const auto sort = n <= kSort4 ? sort_depth<4> : sort_depth<kSortItems>;
             sort(depths, dka, dkb, dva, dvb, &hdr->gaussians, n, sorts,
-                 n <= kSort4 ? at<uint32_t>(ws, L.offs) : sortbuf, status_dev, at<uint4>(ws, L.recs),
-                 nullptr, at<unsigned long long>(ws, L.rects), s);
+                 n <= kSort4 ? at<uint32_t>(ws, L.masks) : sortbuf, status_dev, at<uint4>(ws, L.recs),
+                 rank_masks, at<unsigned long long>(ws, L.rects), s);
+        }
+        if (n <= kSmallSort && !vis) {
+            const auto scatter = n <= 4 * kSortThreads ? k_sb_scatter<4, true, false>
+                               : n <= 8 * kSortThreads ? k_sb_scatter<8, true, false>
+                                                       : k_sb_scatter<16, true, false>;
+            scatter<<<1, kSortThreads, 0, s>>>(rects, dva, n, G, bits, nullptr, 1, hdr, cap, chunk, e_idx,
+                                               e_mask, table, V, nullptr, nullptr);
+        } else {
             const int ranks = sb_ranks(G.n);
             const int64_t nblk = (n + ranks - 1) / ranks;
             const dim3 gb{unsigned(xcd_grid(nblk))};
-            k_sb_hist<<<gb, kSortThreads, 0, s>>>(rects, n, ranks, G, sortbuf, nblk);
+            if (vis)
+                k_sb_hist_visible<<<gb, kSortThreads, 0, s>>>(rects, dva, V, n, ranks, G, sortbuf, nblk,
+                                                              cap, dka, dkb);
+            else
+                k_sb_hist<<<gb, kSortThreads, 0, s>>>(rects, n, ranks, G, sortbuf, nblk);
             launch_scan<uint32_t>(sortbuf, int64_t(G.n) * nblk, partial32, &hdr->entries, nullptr, s);
-            const auto scatter = ranks == 1024 ? k_sb_scatter<4, false>
-                               : ranks == 2048 ? k_sb_scatter<8, false> : k_sb_scatter<16, false>;
+            const auto scatter =
+                ranks == 1024 ? (vis ? k_sb_scatter<4, false, true> : k_sb_scatter<4, false, false>)
+              : ranks == 2048 ? (vis ? k_sb_scatter<8, false, true> : k_sb_scatter<8, false, false>)
+                              : (vis ? k_sb_scatter<16, false, true> : k_sb_scatter<16, false, false>);
             scatter<<<gb, kSortThreads, 0, s>>>(rects, dva, n, G, bits, sortbuf, nblk, hdr, cap, chunk,
-                                                e_idx, e_mask, table);
+                                                e_idx, e_mask, table, V, dka, dkb);
         }
         const int64_t mc = sb_max_chunks(cap);
         const dim3 gc{unsigned(mc < kSbMaxGrid ? mc : kSbMaxGrid)};
@@ -1862,8 +2213,9 @@ gsb_status bin_fill(const float *means2d, const int32_t *radii, const float *con
         return check_launch("bin_fill");
     }
     k_bin_init<<<dim3(unsigned((2 * n_tiles + 255) / 256)), 256, 0, s>>>(ranges, 2 * n_tiles,
-                                                                       sorts, hdr, n, status_dev);
-    if (by_superblock(mode, G)) {       // no Gaussians, or no room for a pair
+                                                                       sorts, hdr, n, nullptr,
+                                                                       status_dev);
+    if (by_superblock(G)) {       // no Gaussians, or no room for a pair
         k_tile_scan<<<1, kScanTopThreads, 0, s>>>(reinterpret_cast<uint2 *>(ranges), 0, hdr, cap,
                                                   status_dev);
         return check_launch("bin_fill");
