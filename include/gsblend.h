@@ -162,9 +162,9 @@ gsb_status gsb_bin_count(const float *means2d, const int32_t *radii, const float
 
 /* Emits, sorts and ranges the pairs counted by the preceding gsb_bin_count on the same `ws`
  * (a workspace at least as large, whose leading gsb_bin_workspace_bytes(n, 0, W, H) bytes are the
- * ones gsb_bin_count wrote). Implementation: the Gaussians are sorted by depth, pairs are emitted
- * in that order and stably sorted on the tile id alone, which yields the same (tile, depth, index)
- * order as sorting the 64-bit keys.
+ * ones gsb_bin_count wrote). Implementation: the Gaussians are sorted by depth and distributed to
+ * the tiles in that order (by way of superblocks of 8 x 8 tiles, or by a stable sort of the pairs on
+ * the tile id), which yields the same (tile, depth, index) order as sorting the 64-bit keys.
  * point_list: device u32[pair_capacity], receives the Gaussian index of each sorted pair.
  * ranges:     device u32[gx*gy][2], receives [start, end) of each tile in point_list, [0, 0) for
  *             an empty tile.
@@ -178,6 +178,21 @@ gsb_status gsb_bin_fill(const float *means2d, const int32_t *radii, const float 
                         int32_t W, int32_t H, void *ws, size_t ws_bytes, uint32_t *point_list,
                         int64_t pair_capacity, uint32_t *ranges, int32_t *status_dev,
                         void *stream);
+
+/* gsb_bin_fill in two calls: gsb_bin_sort, the part that needs no capacity (the depth order, empty
+ * ranges, a clean status word), then gsb_bin_fill_sorted on the same stream with the same arguments.
+ * A host that reads *n_pairs to size the list calls gsb_bin_sort before it waits, so that the GPU
+ * sorts meanwhile. Here ws_bytes must be >= gsb_bin_workspace_bytes(n, 0, W, H); the workspace of the
+ * second call may be another one whose leading so many bytes are a copy, as for gsb_bin_fill. */
+gsb_status gsb_bin_sort(const float *means2d, const int32_t *radii, const float *conics,
+                        const float *opacity, gsb_bin_mode mode, const float *depths, int64_t n,
+                        int32_t W, int32_t H, void *ws, size_t ws_bytes, uint32_t *ranges,
+                        int32_t *status_dev, void *stream);
+gsb_status gsb_bin_fill_sorted(const float *means2d, const int32_t *radii, const float *conics,
+                               const float *opacity, gsb_bin_mode mode, const float *depths,
+                               int64_t n, int32_t W, int32_t H, void *ws, size_t ws_bytes,
+                               uint32_t *point_list, int64_t pair_capacity, uint32_t *ranges,
+                               int32_t *status_dev, void *stream);
 
 /* For callers that cannot allocate device memory (code under hipGraph capture, tight serving
  * loops, harnesses that forbid hipMalloc): gsb_bin_count followed by gsb_bin_fill in one call, with

@@ -38,7 +38,8 @@ GSB_REDUCE_MFMA = 1
 
 # every function declared in include/gsblend.h
 EXPORTS = ("gsb_abi_version", "gsb_last_error", "gsb_project", "gsb_bin_workspace_bytes",
-           "gsb_bin_count", "gsb_bin_fill", "gsb_bin_noalloc", "gsb_pack_gaussians",
+           "gsb_bin_count", "gsb_bin_fill", "gsb_bin_sort", "gsb_bin_fill_sorted",
+           "gsb_bin_noalloc", "gsb_pack_gaussians",
            "gsb_blend_forward_packed", "gsb_blend_backward_packed",
            "gsb_backward_det_workspace_bytes", "gsb_blend_backward_deterministic",
            "gsb_blend_forward", "gsb_blend_backward", "gsb_plan_create",
@@ -100,6 +101,8 @@ def load() -> ctypes.CDLL:
     lib.gsb_bin_workspace_bytes.argtypes = [i64, i64, i32, i32, ctypes.POINTER(sz)]
     lib.gsb_bin_count.argtypes = [P, P, P, P, i32, i64, i32, i32, P, sz, P, P]
     lib.gsb_bin_fill.argtypes = [P, P, P, P, i32, P, i64, i32, i32, P, sz, P, i64, P, P, P]
+    lib.gsb_bin_sort.argtypes = [P, P, P, P, i32, P, i64, i32, i32, P, sz, P, P, P]
+    lib.gsb_bin_fill_sorted.argtypes = lib.gsb_bin_fill.argtypes
     lib.gsb_bin_noalloc.argtypes = [P, P, P, P, i32, P, i64, i32, i32, P, i64, P, P, P, P]
     lib.gsb_pack_gaussians.argtypes = [P, P, P, P, i64, P, P]
     lib.gsb_blend_forward_packed.argtypes = [i32, i32, P, P, P, i64, P, i32, P, P, P, P]
@@ -169,6 +172,22 @@ def gsb_bin_fill(means2d: int, radii: int, depths: int, n: int, W: int, H: int, 
                  mode: int = 0) -> None:
     _check(load().gsb_bin_fill(means2d, radii, conics, opacity, mode, depths, n, W, H, ws,
                                ws_bytes, point_list, pair_capacity, ranges, status_dev, stream))
+
+
+def gsb_bin_sort(means2d: int, radii: int, depths: int, n: int, W: int, H: int, ws: int,
+                 ws_bytes: int, ranges: int, status_dev: int, stream: int = 0, conics: int = 0,
+                 opacity: int = 0, mode: int = 0) -> None:
+    _check(load().gsb_bin_sort(means2d, radii, conics, opacity, mode, depths, n, W, H, ws,
+                               ws_bytes, ranges, status_dev, stream))
+
+
+def gsb_bin_fill_sorted(means2d: int, radii: int, depths: int, n: int, W: int, H: int, ws: int,
+                        ws_bytes: int, point_list: int, pair_capacity: int, ranges: int,
+                        status_dev: int, stream: int = 0, conics: int = 0, opacity: int = 0,
+                        mode: int = 0) -> None:
+    _check(load().gsb_bin_fill_sorted(means2d, radii, conics, opacity, mode, depths, n, W, H, ws,
+                                      ws_bytes, point_list, pair_capacity, ranges, status_dev,
+                                      stream))
 
 
 def gsb_bin_noalloc(means2d: int, radii: int, depths: int, n: int, W: int, H: int,

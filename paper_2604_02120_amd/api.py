@@ -97,6 +97,10 @@ class BinWorkspace:
         return self.buf.data_ptr()
 
 
+# pairs per Gaussian that bin_tiles makes room for at first: 3-sigma squares of a standard deviation of
+# 2 to 3 pixels cover 9 to 18 tiles; a frame with more pays a copy of the Gaussians' part
+_GUESS = 16
+
 BIN_MODES = {"rect": _lib.GSB_BIN_RECT, "visible": _lib.GSB_BIN_VISIBLE}
 
 
@@ -145,18 +149,44 @@ def bin_fill(means2d, radii, depths, W: int, H: int, ws: BinWorkspace, point_lis
 def bin_tiles(means2d, radii, depths, W: int, H: int, stream=None, conics=None, opacity=None,
               mode="rect"):
     """Count, then fill with an exactly sized list. Returns (point_list i32[P], ranges
-    i32[gx*gy][2]). Synchronises once to read the pair count."""
+    i32[gx*gy][2]). Waits once for the pair count, while the GPU sorts the Gaussians."""
     n = radii.shape[0]
-    ws0 = BinWorkspace(n, 0, W, H, device=means2d.device)
-    n_pairs = int(bin_count(means2d, radii, W, H, ws0, stream, conics, opacity, mode).item())
-    ws = BinWorkspace(n, n_pairs, W, H, device=means2d.device)
-    ws.buf[: ws0.nbytes].copy_(ws0.buf)          # per-Gaussian offsets from the count
+    dev = means2d.device
     gx, gy = grid(W, H)
-    point_list = torch.empty(max(n_pairs, 1), dtype=torch.int32, device=means2d.device)
-    ranges = torch.empty((gx * gy, 2), dtype=torch.int32, device=means2d.device)
-    bin_fill(means2d, radii, depths, W, H, ws, point_list[:n_pairs] if n_pairs else point_list[:0],
-             ranges, stream, conics, opacity, mode)
-    return point_list[:n_pairs], ranges
+    # room for _GUESS pairs per Gaussian, so that the usual frame needs no second workspace
+    ws = BinWorkspace(n, min(_GUESS * n, n * gx * gy, 1 << 26), W, H, device=dev)
+    _req(means2d, torch.float32, "means2d")
+    _req(radii, torch.int32, "radii")
+    code, cp, op = _bin_mode(mode, conics, opacity)
+    _req(depths, torch.float32, "depths")
+    s = torch.cuda.current_stream() if stream is None else stream
+    if not isinstance(s, torch.cuda.Stream):
+        s = torch.cuda.ExternalStream(_stream(s))
+    ranges = torch.empty((gx * gy, 2), dtype=torch.int32, device=dev)
+    status = torch.empty(1, dtype=torch.int32, device=dev)
+    n_pairs = torch.empty(1, dtype=torch.int64, pin_memory=True)     # written by the GPU
+    counted = torch.cuda.Event()
+    geom = (means2d.data_ptr(), radii.data_ptr())
+    try:
+        _lib.gsb_bin_count(*geom, n, W, H, ws.ptr(), ws.nbytes, n_pairs.data_ptr(), s.cuda_stream,
+                           cp, op, code)
+        counted.record(s)
+        _lib.gsb_bin_sort(*geom, depths.data_ptr(), n, W, H, ws.ptr(), ws.nbytes,
+                          ranges.data_ptr(), status.data_ptr(), s.cuda_stream, cp, op, code)
+    finally:
+        counted.synchronize()
+    P = int(n_pairs)
+    if P > ws.capacity:
+        lead = _lib.gsb_bin_workspace_bytes(n, 0, W, H)
+        full = BinWorkspace(n, P, W, H, device=dev)
+        with torch.cuda.stream(s):
+            full.buf[:lead].copy_(ws.buf[:lead])
+        ws = full
+    point_list = torch.empty(max(P, 1), dtype=torch.int32, device=dev)
+    _lib.gsb_bin_fill_sorted(*geom, depths.data_ptr(), n, W, H, ws.ptr(), ws.nbytes,
+                             point_list.data_ptr(), P, ranges.data_ptr(), status.data_ptr(),
+                             s.cuda_stream, cp, op, code)
+    return point_list[:P], ranges
 
 
 def blend_forward(means2d, conics, opacity, colors, ranges, point_list, W: int, H: int,

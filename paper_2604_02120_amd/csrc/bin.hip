@@ -100,6 +100,13 @@ constexpr int kMaxSbBits = 10, kMaxSb = 1 << kMaxSbBits;
 constexpr int kSbChunkLarge = 1024, kSbChunkSmall = 256;
 constexpr int64_t kSbSmallPairs = int64_t(1) << 19;
 int sb_chunk_size(int64_t cap) { return cap <= kSbSmallPairs ? kSbChunkSmall : kSbChunkLarge; }
+// First entry and first chunk of every superblock, and the ends
+constexpr int kSbLists = 8, kSbListRun = 16;
+struct SbTable {
+    uint32_t start[kMaxSb + 1], chunk[kMaxSb + 1];
+    // mode 1: lengths of the lists of the large rectangles' masks, a cache line apart
+    alignas(128) unsigned long long listed[kSbLists][16];
+};
 // chunks that up to `cap` entries can take (a superblock's last chunk may be partial)
 int64_t sb_max_chunks(int64_t cap) {
     return cap / sb_chunk_size(cap) + (cap < kMaxSb ? cap : kMaxSb);
@@ -131,7 +138,11 @@ Layout layout(int64_t n, int64_t cap) {
     const int64_t lb_d = int64_t(kMaxPasses) * sort_blocks(n > 0 ? n : 1);
     const int64_t lb_t = sort_blocks(cap > 0 ? cap : 1);
     const size_t words = sizeof(uint32_t) * kRadix * size_t(lb_d > lb_t ? lb_d : lb_t);
-    const size_t chunk_counts = sizeof(uint16_t) * kSbTiles * size_t(sb_max_chunks(int64_t(cc)));
+    // (never less than a smaller capacity's: a workspace also serves every shorter list)
+    int64_t chunks = sb_max_chunks(int64_t(cc));
+    if (int64_t(cc) > kSbSmallPairs && chunks < sb_max_chunks(kSbSmallPairs))
+        chunks = sb_max_chunks(kSbSmallPairs);
+    const size_t chunk_counts = sizeof(uint16_t) * kSbTiles * size_t(chunks);
     const bool in_offs = chunk_counts <= sizeof(unsigned long long) * nn;
     L.sortbuf = o;   o += align256(in_offs || words > chunk_counts ? words : chunk_counts);
     L.sb_counts = in_offs ? L.offs : L.sortbuf;
@@ -1069,7 +1080,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_sort_small(const float *depth
                                                               unsigned long long *rank_counts,
                                                               unsigned long long *rank_rects,
                                                               uint32_t *ranges, int ranges_n,
-                                                              int32_t *status) {
+                                                              SbTable *table, int32_t *status) {
     constexpr int kWaves = kSmallThreads / 64, kItems = kSmallSort / kSmallThreads;
     __shared__ uint16_t s_wcnt[kWaves][kRadix];
     __shared__ uint32_t s_dstart[kRadix];
@@ -1077,6 +1088,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_sort_small(const float *depth
     __shared__ uint32_t s_key[kSmallSort];
     __shared__ uint16_t s_val[kSmallSort];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    if (t < kSbLists) table->listed[t][0] = 0ull;
     if (t == 0) *status = GSB_OK;
     for (int k = t; k < ranges_n; k += kSmallThreads) ranges[k] = 0u;
     // wave w holds keys [256 w, 256 (w + 1)) in four steps of 64
@@ -1241,14 +1253,6 @@ inline int sb_ranks(int32_t n_sb) { return n_sb <= 256 ? 1024 : n_sb <= 512 ? 20
 // The superblock path where it applies: a grid of at most kMaxSb superblocks
 inline bool by_superblock(const SbGrid &G) { return G.n <= kMaxSb; }
 
-// First entry and first chunk of every superblock, and the ends
-constexpr int kSbLists = 8, kSbListRun = 16;
-struct SbTable {
-    uint32_t start[kMaxSb + 1], chunk[kMaxSb + 1];
-    // mode 1: lengths of the lists of the large rectangles' masks, a cache line apart
-    alignas(128) unsigned long long listed[kSbLists][16];
-};
-
 // Superblocks touched by a (non-empty) tile rectangle
 __device__ inline Rect sb_rect(const Rect &R) {
     return Rect{R.tx0 >> kSbShift, (R.tx1 + kSbEdge - 1) >> kSbShift, R.ty0 >> kSbShift,
@@ -1301,12 +1305,13 @@ __device__ inline unsigned long long sb_submask(const Rect &R, unsigned long lon
 
 // Mode 1: the superblocks with a visible tile. Those of a rectangle that its candidate mask covers are
 // cut from it. Those of a larger one are listed by k_sb_list, from the end of the entries' arrays
-// downwards; rank_masks holds a Gaussian's place and their number << 48. There are `lists` lists, in
+// downwards; a Gaussian's record holds its place and their number << 48. There are `lists` lists, in
 // alternate runs of kSbListRun places: with one counter for all, the XCDs' atomics on it took 400 us
 // of 3 M Gaussians (20 ns each). The masks are tested again where the arrays had no room for them,
 // which takes more than one such superblock for two pairs (a thin line has 8 pairs in each).
 struct SbVisible {
     const unsigned long long *rank_masks;
+    uint4 *recs;
     unsigned long long *masks;                    // the arrays' ends: place o is [-1 - o]
     uint32_t *sbs;
     const SbTable *table;
@@ -1346,6 +1351,8 @@ __device__ inline void sb_visible(const SbVisible &V, const SbGrid &G, const Rec
     if (R.tx1 <= R.tx0 || R.ty1 <= R.ty0) return;
     const bool big = sb_big(R);
     if (big && listed) {
+        const uint2 r = reinterpret_cast<const uint2 *>(V.recs + *i)[0];
+        mask = (static_cast<unsigned long long>(r.y) << 32) | r.x;
         const unsigned long long o = mask & ((1ull << 45) - 1ull);
         const int l = int(mask >> 45) & 7, e = int(mask >> 48);
 #pragma unroll 1
@@ -1377,7 +1384,7 @@ __device__ inline void sb_visible(const SbVisible &V, const SbGrid &G, const Rec
 // The list of the Gaussians with candidates past a mask's 8 x 8, each tested by a whole wavefront,
 // a superblock's 64 tiles at a time. In the order of the indices, as large Gaussians are neighbours
 // in the order of depth. Masks are gathered in LDS, for an atomic per kMaxSb of them or wavefront.
-__global__ __launch_bounds__(64, 5) void k_sb_list(uint4 *recs, SbVisible V, SbTable *table,
+__global__ __launch_bounds__(64, 5) void k_sb_list(SbVisible V, SbTable *table,
                                                 int64_t n, SbGrid G, int64_t cap) {
     __shared__ unsigned long long s_mask[kMaxSb];
     __shared__ uint16_t s_sb[kMaxSb];
@@ -1385,7 +1392,7 @@ __global__ __launch_bounds__(64, 5) void k_sb_list(uint4 *recs, SbVisible V, SbT
     const int64_t i = int64_t(blockIdx.x) * 64 + lane;
     Rect R{0, 0, 0, 0};
     if (i < n) {
-        const uint2 z = reinterpret_cast<const uint2 *>(recs + i)[1];
+        const uint2 z = reinterpret_cast<const uint2 *>(V.recs + i)[1];
         R = unpack_rect((static_cast<unsigned long long>(z.y) << 32) | z.x);
     }
     const bool big = R.tx1 > R.tx0 && R.ty1 > R.ty0 && sb_big(R);
@@ -1403,7 +1410,7 @@ __global__ __launch_bounds__(64, 5) void k_sb_list(uint4 *recs, SbVisible V, SbT
         base = __shfl(base, 0, 64);
         if (waits) {
             const unsigned long long r = (base + place) | ((unsigned long long)(l | mine << 3) << 45);
-            reinterpret_cast<uint2 *>(recs + i)[0] = make_uint2(uint32_t(r), uint32_t(r >> 32));
+            reinterpret_cast<uint2 *>(V.recs + i)[0] = make_uint2(uint32_t(r), uint32_t(r >> 32));
         }
         waits = false;
         __builtin_amdgcn_wave_barrier();
@@ -2125,19 +2132,52 @@ gsb_status bin_count(const float *means2d, const int32_t *radii, const float *co
     return check_launch("bin_count");
 }
 
-gsb_status bin_fill(const float *means2d, const int32_t *radii, const float *conics,
-                    const float *opacity, int32_t mode, const float *depths, int64_t n, int32_t W,
-                    int32_t H, void *ws, uint32_t *point_list, int64_t cap, uint32_t *ranges,
-                    int32_t *status_dev, hipStream_t s) {
+// bin_fill's part that needs no capacity: empty ranges, clean states and status word, and the
+// Gaussians in depth order (ties by index: the sort is stable over index order). The last pass also
+// lays out in rank order each Gaussian's rectangle and its pair count or mask.
+gsb_status bin_sort(int32_t mode, const float *depths, int64_t n, int32_t W, int32_t H, void *ws,
+                    uint32_t *ranges, int32_t *status_dev, hipStream_t s) {
+    const Layout L = layout(n, 0);       // (the look-back words' place in the smallest workspace)
+    auto *hdr = at<BinHeader>(ws, L.hdr);
+    auto *sorts = at<SortState>(ws, L.sorts);
+    uint32_t *dka = at<uint32_t>(ws, L.dkey_a), *dkb = at<uint32_t>(ws, L.dkey_b);
+    uint32_t *dva = at<uint32_t>(ws, L.dval_a), *dvb = at<uint32_t>(ws, L.dval_b);
+    const int64_t n_tiles = grid_x(W) * grid_y(H);
+    const bool sb = by_superblock(sb_grid(int32_t(grid_x(W)), int32_t(grid_y(H))));
+    auto *rank_counts = sb && mode == GSB_BIN_RECT ? nullptr : at<unsigned long long>(ws, L.offs);
+    auto *rects = at<unsigned long long>(ws, L.rects);
+    if (sb && n > 0 && n <= kSmallSort) {
+        k_sort_small<<<1, kSmallThreads, 0, s>>>(depths, int(n), dva, at<uint4>(ws, L.recs),
+                                                 rank_counts, rects, ranges, int(2 * n_tiles),
+                                                 at<SbTable>(ws, L.sb_table), status_dev);
+        return check_launch("bin_sort");
+    }
+    k_bin_init<<<dim3(unsigned((2 * n_tiles + 255) / 256)), 256, 0, s>>>(
+        ranges, 2 * n_tiles, sorts, hdr, n, at<SbTable>(ws, L.sb_table), status_dev);
+    // the look-back words of the smaller tiles (4096 bytes per 1024 Gaussians) take the place of the
+    // masks by index (8 bytes per Gaussian, and n > kSmallSort here), which superblocks do not use
+    if (sb && n > 0 && n <= kSort4)
+        sort_depth<4>(depths, dka, dkb, dva, dvb, &hdr->gaussians, n, sorts, at<uint32_t>(ws, L.masks),
+                      status_dev, at<uint4>(ws, L.recs), rank_counts, rects, s);
+    else if (n > 0)
+        sort_depth<kSortItems>(depths, dka, dkb, dva, dvb, &hdr->gaussians, n, sorts,
+                               at<uint32_t>(ws, L.sortbuf), status_dev, at<uint4>(ws, L.recs),
+                               rank_counts, rects, s);
+    return check_launch("bin_sort");
+}
+
+gsb_status bin_fill_sorted(const float *means2d, const float *conics, const float *opacity,
+                           int32_t mode, int64_t n, int32_t W, int32_t H, void *ws,
+                           uint32_t *point_list, int64_t cap, uint32_t *ranges,
+                           int32_t *status_dev, hipStream_t s) {
     const Layout L = layout(n, cap);
     auto *hdr = at<BinHeader>(ws, L.hdr);
     auto *counts = at<unsigned long long>(ws, L.counts);
     auto *partial64 = at<unsigned long long>(ws, L.partials);
     auto *partial32 = at<uint32_t>(ws, L.partials);
-    auto *sorts = at<SortState>(ws, L.sorts);
     auto *sortbuf = at<uint32_t>(ws, L.sortbuf);
     uint32_t *dka = at<uint32_t>(ws, L.dkey_a), *dkb = at<uint32_t>(ws, L.dkey_b);
-    uint32_t *dva = at<uint32_t>(ws, L.dval_a), *dvb = at<uint32_t>(ws, L.dval_b);
+    const uint32_t *dva = at<uint32_t>(ws, L.dval_a);
     auto *offs = at<unsigned long long>(ws, L.offs);
     uint32_t *vtmp = at<uint32_t>(ws, L.vals_tmp);
     const int32_t gx = int32_t(grid_x(W)), gy = int32_t(grid_y(H));
@@ -2157,27 +2197,10 @@ gsb_status bin_fill(const float *means2d, const int32_t *radii, const float *con
         // the end of the entries' masks downwards
         const bool vis = mode == GSB_BIN_VISIBLE;
         auto *rank_masks = vis ? offs : nullptr;
-        const SbVisible V{rank_masks, e_mask + cap, e_idx + cap, table, n > 1 << 16 ? kSbLists : 1,
+        const SbVisible V{rank_masks, at<uint4>(ws, L.recs), e_mask + cap, e_idx + cap, table, n > 1 << 16 ? kSbLists : 1,
                           reinterpret_cast<const float2 *>(means2d), conics, opacity, W, H};
-        if (vis || n > kSmallSort)
-            k_bin_init<<<dim3(unsigned((2 * n_tiles + 255) / 256)), 256, 0, s>>>(
-                ranges, 2 * n_tiles, sorts, hdr, n, table, status_dev);
         if (vis)
-            k_sb_list<<<dim3(unsigned((n + 63) / 64)), 64, 0, s>>>(at<uint4>(ws, L.recs), V, table, n,
-                                                                  G, cap);
-        if (n <= kSmallSort) {
-            k_sort_small<<<1, kSmallThreads, 0, s>>>(depths, int(n), dva, at<uint4>(ws, L.recs),
-                                                     rank_masks, at<unsigned long long>(ws, L.rects),
-                                                     ranges, int(2 * n_tiles), status_dev);
-        } else {
-            // the look-back words of the smaller tiles (4096 bytes per 1024 Gaussians) take the
-            // place of the masks by index (8 bytes per Gaussian, and n > kSmallSort here), which this
-            // path does not use
-            const auto sort = n <= kSort4 ? sort_depth<4> : sort_depth<kSortItems>;
-            sort(depths, dka, dkb, dva, dvb, &hdr->gaussians, n, sorts,
-                 n <= kSort4 ? at<uint32_t>(ws, L.masks) : sortbuf, status_dev, at<uint4>(ws, L.recs),
-                 rank_masks, at<unsigned long long>(ws, L.rects), s);
-        }
+            k_sb_list<<<dim3(unsigned((n + 63) / 64)), 64, 0, s>>>(V, table, n, G, cap);
         if (n <= kSmallSort && !vis) {
             const auto scatter = n <= 4 * kSortThreads ? k_sb_scatter<4, true, false>
                                : n <= 8 * kSortThreads ? k_sb_scatter<8, true, false>
@@ -2212,20 +2235,13 @@ gsb_status bin_fill(const float *means2d, const int32_t *radii, const float *con
                                  reinterpret_cast<const uint2 *>(ranges), point_list);
         return check_launch("bin_fill");
     }
-    k_bin_init<<<dim3(unsigned((2 * n_tiles + 255) / 256)), 256, 0, s>>>(ranges, 2 * n_tiles,
-                                                                       sorts, hdr, n, nullptr,
-                                                                       status_dev);
     if (by_superblock(G)) {       // no Gaussians, or no room for a pair
         k_tile_scan<<<1, kScanTopThreads, 0, s>>>(reinterpret_cast<uint2 *>(ranges), 0, hdr, cap,
                                                   status_dev);
         return check_launch("bin_fill");
     }
-    // 1. Gaussians by depth (ties by index: the sort is stable over index order); the last pass
-    //    also lays out each Gaussian's pair count and emission rectangle in rank order
-    sort_depth<kSortItems>(depths, dka, dkb, dva, dvb, &hdr->gaussians, n, sorts, sortbuf, status_dev,
-                           at<uint4>(ws, L.recs), offs, at<unsigned long long>(ws, L.rects), s);
     const uint32_t *sorted_idx = dva;
-    // 2. offsets in rank order; pairs emitted in rank order
+    // (1. the depth sort) 2. offsets in rank order; pairs emitted in rank order
     launch_scan<unsigned long long>(offs, n, partial64, nullptr, nullptr, s);
     const int tile_bits = ceil_log2(n_tiles) > 0 ? ceil_log2(n_tiles) : 1;
     const int tp = (tile_bits + kRadixBits - 1) / kRadixBits;
@@ -2255,6 +2271,16 @@ gsb_status bin_fill(const float *means2d, const int32_t *radii, const float *con
     else
         emit_sort_range(at<uint32_t>(ws, L.tkey_a), at<uint32_t>(ws, L.tkey_b));
     return check_launch("bin_fill");
+}
+
+gsb_status bin_fill(const float *means2d, const float *conics, const float *opacity, int32_t mode,
+                    const float *depths, int64_t n, int32_t W, int32_t H, void *ws,
+                    uint32_t *point_list, int64_t cap, uint32_t *ranges,
+                    int32_t *status_dev, hipStream_t s) {
+    const gsb_status st = bin_sort(mode, depths, n, W, H, ws, ranges, status_dev, s);
+    if (st != GSB_OK) return st;
+    return bin_fill_sorted(means2d, conics, opacity, mode, n, W, H, ws, point_list, cap, ranges,
+                           status_dev, s);
 }
 
 // ------------------------------------------------------------------------------- pair sort
@@ -2323,7 +2349,7 @@ gsb_status bin_noalloc(const float *means2d, const int32_t *radii, const float *
     const gsb_status st = bin_count(means2d, radii, conics, opacity, mode, n, W, H, ws,
                                     n_pairs_dev, s);
     if (st != GSB_OK) return st;
-    return bin_fill(means2d, radii, conics, opacity, mode, depths, n, W, H, ws, point_list, cap,
+    return bin_fill(means2d, conics, opacity, mode, depths, n, W, H, ws, point_list, cap,
                     ranges, status_dev, s);
 }
 

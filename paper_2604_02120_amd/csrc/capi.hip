@@ -205,11 +205,12 @@ gsb_status gsb_bin_count(const float *means2d, const int32_t *radii, const float
                      static_cast<hipStream_t>(stream));
 }
 
-gsb_status gsb_bin_fill(const float *means2d, const int32_t *radii, const float *conics,
-                        const float *opacity, gsb_bin_mode mode, const float *depths, int64_t n,
-                        int32_t W, int32_t H, void *ws, size_t ws_bytes, uint32_t *point_list,
-                        int64_t pair_capacity, uint32_t *ranges, int32_t *status_dev,
-                        void *stream) {
+// bin_fill's arguments; `mode` and its arrays, the workspace for pair_capacity, the outputs
+static gsb_status check_bin_fill(const float *means2d, const int32_t *radii, const float *conics,
+                                 const float *opacity, gsb_bin_mode mode, const float *depths,
+                                 int64_t n, int32_t W, int32_t H, void *ws, size_t ws_bytes,
+                                 uint32_t *point_list, int64_t pair_capacity, uint32_t *ranges,
+                                 int32_t *status_dev) {
     size_t need = 0;
     GSB_TRY(gsb_bin_workspace_bytes(n, pair_capacity, W, H, &need));
     GSB_REQUIRE(n == 0 || (means2d && radii && depths), "means2d, radii and depths must be non-null");
@@ -219,9 +220,38 @@ gsb_status gsb_bin_fill(const float *means2d, const int32_t *radii, const float 
     GSB_REQUIRE(ws_bytes >= need, "workspace of %zu bytes is smaller than the %zu needed", ws_bytes, need);
     GSB_REQUIRE(pair_capacity == 0 || point_list != nullptr, "point_list must be non-null");
     GSB_REQUIRE(ranges != nullptr && status_dev != nullptr, "ranges and status_dev must be non-null");
-    GSB_TRY(check_device());
-    return bin_fill(means2d, radii, conics, opacity, mode, depths, n, W, H, ws, point_list,
-                    pair_capacity, ranges, status_dev, static_cast<hipStream_t>(stream));
+    return check_device();
+}
+
+gsb_status gsb_bin_fill(const float *means2d, const int32_t *radii, const float *conics,
+                        const float *opacity, gsb_bin_mode mode, const float *depths, int64_t n,
+                        int32_t W, int32_t H, void *ws, size_t ws_bytes, uint32_t *point_list,
+                        int64_t pair_capacity, uint32_t *ranges, int32_t *status_dev,
+                        void *stream) {
+    GSB_TRY(check_bin_fill(means2d, radii, conics, opacity, mode, depths, n, W, H, ws, ws_bytes,
+                           point_list, pair_capacity, ranges, status_dev));
+    return bin_fill(means2d, conics, opacity, mode, depths, n, W, H, ws, point_list, pair_capacity,
+                    ranges, status_dev, static_cast<hipStream_t>(stream));
+}
+
+gsb_status gsb_bin_sort(const float *means2d, const int32_t *radii, const float *conics,
+                        const float *opacity, gsb_bin_mode mode, const float *depths, int64_t n,
+                        int32_t W, int32_t H, void *ws, size_t ws_bytes, uint32_t *ranges,
+                        int32_t *status_dev, void *stream) {
+    GSB_TRY(check_bin_fill(means2d, radii, conics, opacity, mode, depths, n, W, H, ws, ws_bytes,
+                           nullptr, 0, ranges, status_dev));
+    return bin_sort(mode, depths, n, W, H, ws, ranges, status_dev, static_cast<hipStream_t>(stream));
+}
+
+gsb_status gsb_bin_fill_sorted(const float *means2d, const int32_t *radii, const float *conics,
+                               const float *opacity, gsb_bin_mode mode, const float *depths,
+                               int64_t n, int32_t W, int32_t H, void *ws, size_t ws_bytes,
+                               uint32_t *point_list, int64_t pair_capacity, uint32_t *ranges,
+                               int32_t *status_dev, void *stream) {
+    GSB_TRY(check_bin_fill(means2d, radii, conics, opacity, mode, depths, n, W, H, ws, ws_bytes,
+                           point_list, pair_capacity, ranges, status_dev));
+    return bin_fill_sorted(means2d, conics, opacity, mode, n, W, H, ws, point_list, pair_capacity,
+                           ranges, status_dev, static_cast<hipStream_t>(stream));
 }
 
 gsb_status gsb_bin_noalloc(const float *means2d, const int32_t *radii, const float *conics,
