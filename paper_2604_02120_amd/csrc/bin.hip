@@ -260,7 +260,7 @@ __global__ __launch_bounds__(kScanTopThreads) void k_scan_top(T *partial, int64_
 // partial[0, b) itself (a few hundred values at most, read from L2) instead of a separate
 // single-block scan of them, which saves a launch; the last block writes the total.
 template <typename T>
-__global__ __launch_bounds__(kScanThreads) void k_scan_down_fused(T *data, int64_t m,
+__global__ __launch_bounds__(kScanThreads) void k_scan_down_fused(const T *in, T *data, int64_t m,
                                                                    const T *partial, int64_t nb,
                                                                    unsigned long long *total_a,
                                                                    long long *total_b) {
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down_fused(T *data, int64
     T v[kScanItems], sum = 0;
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
-        v[k] = (base + k < m) ? data[base + k] : T(0);
+        v[k] = (base + k < m) ? in[base + k] : T(0);
         sum += v[k];
     }
     T tot;
@@ -299,7 +299,7 @@ void launch_scan(T *data, int64_t m, T *partial, unsigned long long *total_a, lo
         return;
     }
     k_scan_reduce<T><<<dim3(unsigned(nb)), kScanThreads, 0, s>>>(data, m, partial);
-    k_scan_down_fused<T><<<dim3(unsigned(nb)), kScanThreads, 0, s>>>(data, m, partial, nb, total_a,
+    k_scan_down_fused<T><<<dim3(unsigned(nb)), kScanThreads, 0, s>>>(data, data, m, partial, nb, total_a,
                                                                       total_b);
 }
 
@@ -2283,29 +2283,20 @@ gsb_status bin_fill(const float *means2d, const float *conics, const float *opac
                            status_dev, s);
 }
 
-// ------------------------------------------------------------------------------- pair sort
-// The binning's stable pair sort and range extraction, for other steps that group (key, value)
-// pairs by key (the deterministic backward groups list positions by Gaussian).
-size_t pair_sort_scratch_bytes(int64_t cap) {
-    return align256(sizeof(uint32_t) * kRadix * size_t(sort_blocks(cap > 0 ? cap : 1))) +
-           align256(sizeof(unsigned long long) * kScanMaxBlocks);
+// ------------------------------------------------------------------------------- offsets
+// The device scan for other steps that group by Gaussian (the deterministic backward); any length.
+size_t offsets_scratch_bytes(int64_t n) {
+    return sizeof(uint32_t) * size_t((n + kScanTile - 1) / kScanTile + 1);
 }
 
-int pair_sort(uint32_t *ka, uint32_t *kb, uint32_t *va, uint32_t *vb,
-              const unsigned long long *count, int64_t cap, int bits, void *scratch,
-              hipStream_t s) {
-    uint32_t *hist = static_cast<uint32_t *>(scratch);
-    uint32_t *partial = reinterpret_cast<uint32_t *>(
-        static_cast<char *>(scratch) +
-        align256(sizeof(uint32_t) * kRadix * size_t(sort_blocks(cap > 0 ? cap : 1))));
-    return sort_tiles<uint32_t>(ka, kb, va, vb, count, cap, bits, hist, partial, nullptr, s);
-}
-
-void key_ranges(const uint32_t *sorted_keys, const unsigned long long *count, int64_t cap,
-                uint32_t *ranges, hipStream_t s) {
-    if (cap > 0)
-        k_ranges<uint32_t><<<dim3(unsigned((cap + 1023) / 1024)), 256, 0, s>>>(sorted_keys, count,
-                                                                                ranges);
+void counts_to_offsets(const uint32_t *counts, uint32_t *offsets, int64_t n, void *scratch,
+                       hipStream_t s) {
+    auto *partial = static_cast<uint32_t *>(scratch);
+    const int64_t nb = (n + kScanTile - 1) / kScanTile;
+    const dim3 grid{unsigned(nb)};
+    k_scan_reduce<uint32_t><<<grid, kScanThreads, 0, s>>>(counts, n, partial);
+    k_scan_down_fused<uint32_t><<<grid, kScanThreads, 0, s>>>(counts, offsets, n, partial, nb, nullptr,
+                                                             nullptr);
 }
 
 // ------------------------------------------------------------------------------- no-alloc binning

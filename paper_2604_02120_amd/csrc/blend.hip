@@ -159,10 +159,9 @@ struct BwdStage<Mode::Plain, NB> : BwdSlots<NB> {
 };
 
 constexpr int kGrad = 9;   // per-Gaussian sums kept per batch
-// Deterministic backward: each list position's nine sums sit in a 64-byte row of 16 words (the
-// last seven zero), so that the per-Gaussian gather, which reads the rows of one Gaussian's
-// positions scattered over the whole list, touches one aligned 64-byte segment per position.
-constexpr int kDetStride = 16;
+// Deterministic backward: the nine sums of a list position are one aligned 64-byte row, with the tile
+// (kDetTile) behind them.
+constexpr int kDetStride = 16, kDetTile = 9;
 
 // dL/do from the sum of alpha dL/dalpha over the Gaussian's pairs (alpha = o e^power below the 0.99
 // clamp): that sum over o. A Gaussian with o < 1/255 is never blended (its sum is zero).
@@ -181,13 +180,14 @@ struct BwdAcc {
 };
 
 // Deterministic backward: each wavefront adds its per-batch sums in a slice of its own (a fixed
-// order); the flush adds the four slices in a fixed order. map[b & 1]: the slot of each entry of
-// batch b as fetched, kNoSlot for one that is not staged (its sums are zero).
+// order); the flush adds the four slices in a fixed order. entry: the slots' places in the batch;
+// list: each wavefront's slots with a nonzero sum.
 constexpr int kNoSlot = 0xffff;
 template <int NB>
 struct BwdAccDet {
     float v[kBlock / 64][NB * kGrad];
-    uint16_t map[2][NB];
+    uint16_t entry[NB];
+    uint16_t list[kBlock / 64][NB / (kBlock / 64)];
 };
 
 // Backward reduction on the matrix cores: each wavefront's dL/dpower values of 8 Gaussians for its
@@ -1012,8 +1012,8 @@ __device__ inline void mm_reduce(uint32_t (*rows)[kDgStride], const h8 (&B)[2], 
 // kMM: the five geometric sums are formed on the matrix cores (mm_reduce) instead of being
 // reduced on the vector ALUs with the other four; `mm` is then the block's transposition tiles.
 // kDet: the batch sums go to the wavefronts' own slices (`det`) instead of `acc_`, and the flush
-// writes each list position's nine sums to v.det_partial in place of the global atomics (every
-// position of the tile's list is written, those past the last contributor with zeros).
+// writes the nine sums of each list position that has a nonzero one to the position's row in place of
+// the global atomics.
 template <Mode M, int NB, bool kMM, bool kPacked = false, bool kDet = false>
 __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, BwdStage<M, NB> &S,
                                 BwdAcc<NB> *acc_, int &s_maxlast, BwdMM *mm,
@@ -1064,14 +1064,6 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, BwdStage<M, NB> 
     const int64_t len = maxlast < int64_t(rg.y) - int64_t(rg.x) ? maxlast
                                                                 : int64_t(rg.y) - int64_t(rg.x);
     const int nb = int((len + NB - 1) / NB);
-    if constexpr (kDet) {
-        // list positions [len, end) are never visited: their sums are zero (positions at or
-        // past det_pairs, which an inconsistent range could name, are never written)
-        const int64_t end = int64_t(rg.y) < v.det_pairs ? int64_t(rg.y) : v.det_pairs;
-        const int64_t tail = (end - start - len) * kDetStride;
-        float *dst = v.det_partial + (start + len) * kDetStride;
-        for (int64_t j = L.t; j < tail; j += kBlock) dst[j] = 0.f;
-    }
     if (nb == 0) return;
 
     // List entries are loaded two batches ahead and attributes one batch ahead.
@@ -1089,29 +1081,50 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, BwdStage<M, NB> 
     // once per sum (4K BF16 backward 1% faster, 1080p 2%). Each
     // item is zeroed by the lane that reads it (an unlisted slot's sums are all +-0 already),
     // ready for batch bb - 1, which adds after the next barrier.
-    // Deterministic form: word k < 9 of entry i's row is the four wavefronts' sum k of its slot added
-    // in wavefront order (0 for an entry that was not staged), words 9..15 are zero; the row is stored
-    // at list position start + bb NB + i (consecutive threads, consecutive words).
-    const auto flush_det = [&](int bb) {
-        const int64_t base = int64_t(bb) * NB;
-        float *dst = v.det_partial + (start + base) * kDetStride;
-        int64_t last = len - base < NB ? len - base : NB;          // slots of this batch
-        if (start + base + last > v.det_pairs) last = v.det_pairs - start - base;
-        const int64_t items = last * kDetStride;
-        for (int j = L.t; j < NB * kDetStride; j += kBlock) {
-            const int i = j / kDetStride, k = j % kDetStride;
+    // Deterministic form: the listed slots' rows are written by 16 lanes each, word k < 9 being the
+    // four wavefronts' sum k of the slot added in wavefront order, and numbered among their
+    // Gaussian's as they come (the gather puts them in order).
+    const auto flush_det = [&](int bb, int filled) {
+        const int per = (filled + 3) >> 2, s0 = L.w * per;
+        uint16_t *list = det->list[L.w];
+        uint32_t bits = 0u;
+        if (L.l < per && s0 + L.l < filled) {
+#pragma unroll
+            for (int w = 0; w < kBlock / 64; ++w) {
+                const float *p = det->v[w] + (s0 + L.l) * kGrad;
+#pragma unroll
+                for (int k = 0; k < kGrad; ++k) bits |= __float_as_uint(p[k]) & 0x7fffffffu;
+            }
+        }
+        const bool touched = bits != 0u;
+        const unsigned long long m = __ballot(touched);
+        const int64_t first = start + int64_t(bb) * NB;
+        if (touched) {
+            const uint32_t g = S.ids[s0 + L.l];
+            const int64_t p = first + det->entry[s0 + L.l];
+            if (g < n && p < v.det_pairs) v.det_seq[p] = atomicAdd(v.det_rows + g, 1u);
+            list[__popcll(m & ((1ull << L.l) - 1ull))] = uint16_t(s0 + L.l);
+        }
+        __builtin_amdgcn_wave_barrier();
+        const int listed = __popcll(m), k = L.l & 15;
+        const uint32_t tile_id = uint32_t(tile.y * v.gx + tile.x);
+#pragma unroll 1
+        for (int i = L.l >> 4; i < listed; i += 4) {
+            const int slot = list[i];
+            const int64_t p = first + det->entry[slot];
             float sum = 0.f;
-            const int slot = det->map[bb & 1][i];
-            if (k < kGrad && slot != kNoSlot) {
+            if (k < kGrad) {
 #pragma unroll
                 for (int w = 0; w < kBlock / 64; ++w) {
-                    float *p = det->v[w] + slot * kGrad + k;
-                    sum += *p;
-                    *p = 0.f;
+                    float *q = det->v[w] + slot * kGrad + k;
+                    sum += *q;
+                    *q = 0.f;
                 }
             }
-            if (j < items) dst[j] = sum;
+            if (k == kDetTile) sum = __uint_as_float(tile_id);
+            if (p < v.det_pairs) v.det_partial[p * kDetStride + k] = sum;
         }
+        __builtin_amdgcn_wave_barrier();
     };
     constexpr int kItemSlots = 64 / kGrad;
     const int item_slot = L.l < kItemSlots * kGrad ? L.l / kGrad : NB, item_k = L.l % kGrad;
@@ -1124,7 +1137,7 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, BwdStage<M, NB> 
     }
     const auto flush = [&](int bb, int staged) {     // the sums of batch bb and its slots
         if constexpr (kDet) {
-            flush_det(bb);
+            flush_det(bb, staged);
             return;
         }
         BwdAcc<NB> &s_acc = *acc_;
@@ -1196,9 +1209,6 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, BwdStage<M, NB> 
             stage<M>(nxt, e, quad, slot, S);
             S.mean[slot] = make_float2(nxt.x, nxt.y);
         }
-        if constexpr (kDet) {
-            if (L.t < NB) det->map[b & 1][L.t] = uint16_t(slot);
-        }
         const int ng = (total + kGroup - 1) / kGroup;
         if constexpr (M != Mode::Plain) {
             if (total + L.t < ng * kGroup) stage_inert<M>(total + L.t, S);
@@ -1214,7 +1224,10 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, BwdStage<M, NB> 
         }
         staged = total;
         __syncthreads();
-        if (keep) S.ids[slot] = nxt.id;
+        if (keep) {
+            S.ids[slot] = nxt.id;
+            if constexpr (kDet) det->entry[slot] = uint16_t(L.t);
+        }
         // unconditional: before the first batch these read entry `start` and Gaussian 0, unused
         nxt = src.fetch(ent.id(), n);
         ent = entry(b - 2);
@@ -1390,75 +1403,222 @@ void k_blend_bwd_det(ViewDesc v) {
     bwd_tile<M, kDetBatch, false, true, true>(v, tile, S, nullptr, s_maxlast, nullptr, &s_det);
 }
 
-// Grouping of the list positions by Gaussian: keys = the list's Gaussian indices, values = the
-// positions; the count for the sort and empty per-Gaussian ranges.
-__global__ __launch_bounds__(256) void k_det_init(const uint32_t *plist, int64_t pairs,
-                                                  uint32_t *keys, uint32_t *vals,
-                                                  unsigned long long *count, uint32_t *seg,
-                                                  int64_t n) {
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < pairs) {
-        // an index outside [0, n) (inconsistent input) is grouped with the last Gaussian: the
-        // backward stages such an entry inert, so its sums are zero
-        const uint32_t g = plist[i];
-        keys[i] = g < uint64_t(n) ? g : uint32_t(n - 1);
-        vals[i] = uint32_t(i);
-    }
-    if (i < 2 * n) seg[i] = 0u;
-    if (i == 0) *count = (unsigned long long)pairs;
+// No rows yet: counts per Gaussian, numbers per list position.
+__global__ __launch_bounds__(256) void k_det_init(uint32_t *rows, int64_t n, uint32_t *seq,
+                                                  int64_t pairs) {
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (i < n) rows[i] = 0u;
+    if (i < pairs) seq[i] = ~0u;
 }
 
-// Per Gaussian g: the nine sums of its list positions in a fixed order, then turned into the
-// gradients as k_bwd_finish does. One wavefront per Gaussian (kGatherPer Gaussians in turn): lane
-// l adds the rows of the Gaussian's positions l, l + 64, ... of its run (in list order, the order
-// the stable sort left them in), and the 64 lane sums are combined by wave_sum9's fixed reduction
-// tree. A thread per Gaussian would leave most lanes of a wavefront idle behind its largest
-// footprint (list runs are heavy-tailed: a few Gaussians cover hundreds of tiles).
+// The positions with a row, by Gaussian (first: the scanned counts). Against a stable sort of all
+// list positions by Gaussian (three passes, each with its counts and scan: 103 us for 150 k Gaussians
+// at 997 x 613) this leaves the order within a Gaussian to the gather: 27 us with the counts' scan.
+// (Ranges that overlap could count more rows than there are positions: those are left out.)
+__global__ __launch_bounds__(256) void k_det_place(const uint32_t *plist, const uint32_t *seq,
+                                                   int64_t pairs, const uint32_t *first, int64_t n,
+                                                   uint32_t *list) {
+    const int64_t i0 = int64_t(blockIdx.x) * 1024 + threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int64_t i = i0 + 256 * k;
+        if (i >= pairs || seq[i] == ~0u || plist[i] >= uint64_t(n)) continue;
+        const uint64_t at = uint64_t(first[plist[i]]) + seq[i];
+        if (at < uint64_t(pairs)) list[at] = uint32_t(i);
+    }
+}
+
+// More rows than lanes: list[0, m) in increasing order, into order, by counting them per tile (a Gaussian
+// has one position in a tile's list; positions increase with the tile), kDetTiles tiles at a time.
+// Should a list name a Gaussian several times, its positions in one tile are put in order by
+// exchanging neighbours.
+constexpr int kDetTiles = 1024;
+__device__ inline void det_order(const float *rows, const uint32_t *list, uint32_t m, int64_t pairs,
+                                 uint32_t *order, uint32_t *cnt, int lane) {
+    const auto tile = [&](uint32_t j) {
+        const uint32_t p = list[j];
+        return p < uint64_t(pairs) ? __float_as_uint(rows[int64_t(p) * kDetStride + kDetTile]) : 0u;
+    };
+    uint32_t lo = ~0u, hi = 0u;
+    for (uint32_t j = lane; j < m; j += 64) {
+        const uint32_t t = tile(j);
+        lo = t < lo ? t : lo;
+        hi = t > hi ? t : hi;
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        const uint32_t a = __shfl_xor(lo, o, 64), b = __shfl_xor(hi, o, 64);
+        lo = a < lo ? a : lo;
+        hi = b > hi ? b : hi;
+    }
+    uint32_t done = 0;
+    bool several = false;
+    for (uint64_t w0 = lo; w0 <= hi && done < m; w0 += kDetTiles) {            // uniform
+        constexpr int kOwn = kDetTiles / 64;
+        for (int k = 0; k < kOwn; ++k) cnt[k * 64 + lane] = 0u;
+        __builtin_amdgcn_wave_barrier();
+        for (uint32_t j = lane; j < m; j += 64) {
+            const uint64_t t = tile(j) - w0;
+            if (t < kDetTiles) atomicAdd(cnt + t, 1u);
+        }
+        __builtin_amdgcn_wave_barrier();
+        uint32_t sum = 0, c[kOwn];
+#pragma unroll
+        for (int k = 0; k < kOwn; ++k) {
+            c[k] = cnt[lane * kOwn + k];
+            several = several || c[k] > 1u;
+            sum += c[k];
+        }
+        uint32_t x = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        uint32_t run = done + x - sum;
+#pragma unroll
+        for (int k = 0; k < kOwn; ++k) {
+            cnt[lane * kOwn + k] = run;
+            run += c[k];
+        }
+        __builtin_amdgcn_wave_barrier();
+        for (uint32_t j = lane; j < m; j += 64) {
+            const uint64_t t = tile(j) - w0;
+            if (t < kDetTiles) order[atomicAdd(cnt + t, 1u)] = list[j];
+        }
+        __builtin_amdgcn_wave_barrier();
+        done += __shfl(x, 63, 64);
+    }
+    __threadfence_block();
+    if (__ballot(several) == 0ull) return;
+    bool again = true;
+    for (uint32_t pass = 0; again && pass <= m; ++pass) {                      // uniform
+        again = false;
+        for (uint32_t odd = 0; odd < 2; ++odd) {
+            bool swapped = false;
+            for (uint32_t j = 2 * lane + odd; j + 1 < m; j += 128) {
+                const uint32_t a = order[j], b = order[j + 1];
+                if (a > b) {
+                    order[j] = b;
+                    order[j + 1] = a;
+                    swapped = true;
+                }
+            }
+            again = again || __ballot(swapped) != 0ull;
+            __threadfence_block();
+        }
+    }
+}
+
+// The gradients of Gaussian g from its nine sums, as k_bwd_finish forms them.
+struct DetOut {
+    const float4 *rec;
+    float *dmeans, *dconics, *dopac, *dcolors;
+};
+__device__ inline void det_store(const DetOut &out, int64_t g, const float *t) {
+    const float4 r0 = out.rec[3 * g], r1 = out.rec[3 * g + 1];
+    const float A = r0.z, B = r0.w, C = r1.x;
+    out.dconics[3 * g] = -0.5f * t[0];
+    out.dconics[3 * g + 1] = -t[1];
+    out.dconics[3 * g + 2] = -0.5f * t[2];
+    out.dmeans[2 * g] = -(A * t[3] + B * t[4]);
+    out.dmeans[2 * g + 1] = -(B * t[3] + C * t[4]);
+    out.dopac[g] = opacity_grad(t[5], r1.y);
+    out.dcolors[3 * g] = t[6];
+    out.dcolors[3 * g + 1] = t[7];
+    out.dcolors[3 * g + 2] = t[8];
+}
+
+// How many of the 16 lanes' keys are less than this lane's.
+template <int kRor>
+__device__ inline uint32_t row_rank(uint32_t key) {
+    if constexpr (kRor == 16) {
+        return 0u;
+    } else {
+        const uint32_t o = uint32_t(__builtin_amdgcn_update_dpp(0, int(key), 0x120 + kRor, 0xf, 0xf, true));
+        return (o < key ? 1u : 0u) + row_rank<kRor + 1>(key);
+    }
+}
+
+// Per Gaussian: its rows' sums in the order of the list positions, in a fixed reduction tree. Four
+// Gaussians per wavefront, 16 lanes each, where they have up to 16 rows (most do): the positions are
+// ranked within the 16 lanes, lane j adds the row of rank j. Those with more take the whole wavefront
+// in turn: lane l adds the rows of rank l, l + 64, ... (A wavefront for each Gaussian took 51 us of
+// 150 k Gaussians, this 27; a thread for each would leave most lanes idle behind the largest footprint.)
 constexpr int kGatherPer = 4;
-__global__ __launch_bounds__(256) void k_det_gather(const float4 *rec, const float *partial,
-                                                    const uint32_t *pos, const uint32_t *seg,
-                                                    int64_t n, float *dmeans, float *dconics,
-                                                    float *dopac, float *dcolors) {
-    const int lane = threadIdx.x & 63;
-    const int64_t wave = (int64_t(blockIdx.x) * blockDim.x + threadIdx.x) >> 6;
-    for (int r = 0; r < kGatherPer; ++r) {
-        const int64_t g = wave * kGatherPer + r;
-        if (g >= n) return;                       // the same in every lane
-        const uint32_t a = seg[2 * g], b = seg[2 * g + 1];
-        float sum[kGrad];
+__global__ __launch_bounds__(256) void k_det_gather(DetOut out, const float *partial,
+                                                    const uint32_t *first, const uint32_t *rows,
+                                                    const uint32_t *list, uint32_t *order,
+                                                    int64_t pairs, int64_t n) {
+    __shared__ uint32_t s_cnt[4][kDetTiles];
+    const int lane = threadIdx.x & 63, j = lane & 15;
+    const int64_t g0 = ((int64_t(blockIdx.x) * blockDim.x + threadIdx.x) >> 6) * kGatherPer;
+    const int64_t g = g0 + (lane >> 4);
+    uint32_t a = 0u, m = 0u;
+    if (g < n) {
+        a = first[g];
+        const int64_t room = pairs - int64_t(a), have = rows[g];
+        m = uint32_t(have < room ? have : room > 0 ? room : 0);
+    }
+    float sum[kGrad];
+    const auto clear = [&] {
 #pragma unroll
         for (int k = 0; k < kGrad; ++k) sum[k] = 0.f;
-        for (uint32_t j = a + uint32_t(lane); j < b; j += 64) {
-            const float *p = partial + int64_t(pos[j]) * kDetStride;
-            const float4 p0 = *reinterpret_cast<const float4 *>(p);
-            const float4 p1 = *reinterpret_cast<const float4 *>(p + 4);
-            sum[0] += p0.x; sum[1] += p0.y; sum[2] += p0.z; sum[3] += p0.w;
-            sum[4] += p1.x; sum[5] += p1.y; sum[6] += p1.z; sum[7] += p1.w;
-            sum[8] += p[8];
+    };
+    const auto add = [&](uint32_t pos) {
+        if (pos >= uint64_t(pairs)) return;
+        const float *p = partial + int64_t(pos) * kDetStride;
+        const float4 p0 = *reinterpret_cast<const float4 *>(p);
+        const float4 p1 = *reinterpret_cast<const float4 *>(p + 4);
+        sum[0] += p0.x; sum[1] += p0.y; sum[2] += p0.z; sum[3] += p0.w;
+        sum[4] += p1.x; sum[5] += p1.y; sum[6] += p1.z; sum[7] += p1.w;
+        sum[8] += p[8];
+    };
+    clear();
+    const bool mine = m <= 16u && uint32_t(j) < m;
+    const uint32_t key = mine ? list[a + uint32_t(j)] : ~0u;
+    const uint32_t rank = row_rank<1>(key);
+    const uint32_t pos = uint32_t(__builtin_amdgcn_ds_permute(
+        4 * ((lane & 48) + (mine ? int(rank) : j)), int(key)));
+    if (mine) add(pos);
+#pragma unroll
+    for (int k = 0; k < kGrad; ++k) {
+        float x = sum[k];
+        x = dpp_add2<0x128>(x, x);               // rotations within the 16 lanes by 8, 4, 2, 1
+        x = dpp_add2<0x124>(x, x);
+        x = dpp_add2<0x122>(x, x);
+        sum[k] = dpp_add2<0x121>(x, x);
+    }
+    if (g < n && m <= 16u && j == 0) det_store(out, g, sum);
+#pragma unroll 1
+    for (int r = 0; r < kGatherPer; ++r) {
+        const uint32_t mr = uint32_t(__builtin_amdgcn_readlane(int(m), 16 * r));
+        if (mr <= 16u) continue;                 // uniform (m is 0 past the last Gaussian)
+        const uint32_t ar = uint32_t(__builtin_amdgcn_readlane(int(a), 16 * r));
+        clear();
+        if (mr <= 64u) {
+            const bool has = uint32_t(lane) < mr;
+            const uint32_t k64 = has ? list[ar + uint32_t(lane)] : ~0u;
+            int at = 0;
+            for (int k = 0; k < int(mr); ++k)
+                at += uint32_t(__builtin_amdgcn_readlane(int(k64), k)) < k64 ? 1 : 0;
+            const uint32_t p = uint32_t(__builtin_amdgcn_ds_permute(4 * (has ? at : lane), int(k64)));
+            if (has) add(p);
+        } else {
+            det_order(partial, list + ar, mr, pairs, order + ar, s_cnt[threadIdx.x >> 6], lane);
+            for (uint32_t k = lane; k < mr; k += 64) add(order[ar + k]);
         }
         float ab, c;
         wave_sum9(sum, lane, ab, c);
         // lane 16r holds sum {0,2,1,3}[r], lane 16r + 8 sum 4 + {0,2,1,3}[r]; lane 0 of c sum 8
-        const auto at = [](float x, int l) {
+        const auto from = [](float x, int l) {
             return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
         };
         float t[kGrad];
-        t[0] = at(ab, 0);  t[2] = at(ab, 16); t[1] = at(ab, 32); t[3] = at(ab, 48);
-        t[4] = at(ab, 8);  t[6] = at(ab, 24); t[5] = at(ab, 40); t[7] = at(ab, 56);
-        t[8] = at(c, 0);
-        if (lane == 0) {
-            const float4 r0 = rec[3 * g], r1 = rec[3 * g + 1];
-            const float A = r0.z, B = r0.w, C = r1.x;
-            dconics[3 * g] = -0.5f * t[0];
-            dconics[3 * g + 1] = -t[1];
-            dconics[3 * g + 2] = -0.5f * t[2];
-            dmeans[2 * g] = -(A * t[3] + B * t[4]);
-            dmeans[2 * g + 1] = -(B * t[3] + C * t[4]);
-            dopac[g] = opacity_grad(t[5], r1.y);
-            dcolors[3 * g] = t[6];
-            dcolors[3 * g + 1] = t[7];
-            dcolors[3 * g + 2] = t[8];
-        }
+        t[0] = from(ab, 0);  t[2] = from(ab, 16); t[1] = from(ab, 32); t[3] = from(ab, 48);
+        t[4] = from(ab, 8);  t[6] = from(ab, 24); t[5] = from(ab, 40); t[7] = from(ab, 56);
+        t[8] = from(c, 0);
+        if (lane == 0) det_store(out, g0 + r, t);
     }
 }
 
@@ -1820,12 +1980,12 @@ gsb_status blend_backward_packed(const ViewDesc &v, gsb_precision prec, hipStrea
     return check_launch("blend_backward_packed");
 }
 
-// Deterministic-backward workspace: per list position its nine sums, the (Gaussian, position)
-// pairs in two buffers each for the sort, the sort's scratch, the pair count and the per-Gaussian
-// ranges of the sorted positions.
+// Deterministic-backward workspace: a row per list position, its number among its Gaussian's rows (then,
+// for Gaussians with many, the ordered positions), the positions by Gaussian, per Gaussian its first and
+// its number of rows, the scan's scratch.
 namespace {
 struct DetLayout {
-    size_t partial, ka, kb, va, vb, count, seg, scratch, end;
+    size_t partial, seq, list, first, rows, scratch, end;
 };
 size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
 DetLayout det_layout(int64_t n, int64_t pairs) {
@@ -1833,20 +1993,13 @@ DetLayout det_layout(int64_t n, int64_t pairs) {
     DetLayout L;
     size_t o = 0;
     L.partial = o; o += al256(sizeof(float) * kDetStride * P);
-    L.ka = o;      o += al256(sizeof(uint32_t) * P);
-    L.kb = o;      o += al256(sizeof(uint32_t) * P);
-    L.va = o;      o += al256(sizeof(uint32_t) * P);
-    L.vb = o;      o += al256(sizeof(uint32_t) * P);
-    L.count = o;   o += al256(sizeof(unsigned long long));
-    L.seg = o;     o += al256(sizeof(uint32_t) * 2 * N);
-    L.scratch = o; o += al256(pair_sort_scratch_bytes(pairs));
+    L.seq = o;     o += al256(sizeof(uint32_t) * P);
+    L.list = o;    o += al256(sizeof(uint32_t) * P);
+    L.first = o;   o += al256(sizeof(uint32_t) * N);
+    L.rows = o;    o += al256(sizeof(uint32_t) * N);
+    L.scratch = o; o += al256(offsets_scratch_bytes(int64_t(N)));
     L.end = o;
     return L;
-}
-int bits_for(int64_t n) {
-    int b = 1;
-    while (b < 32 && (int64_t(1) << b) < n) ++b;
-    return b;
 }
 }  // namespace
 
@@ -1859,14 +2012,13 @@ gsb_status blend_backward_det(const ViewDesc &v0, gsb_precision prec, int64_t pa
     ViewDesc v = v0;
     v.det_partial = reinterpret_cast<float *>(w + D.partial);
     v.det_pairs = pairs;
-    uint32_t *ka = reinterpret_cast<uint32_t *>(w + D.ka), *kb = reinterpret_cast<uint32_t *>(w + D.kb);
-    uint32_t *va = reinterpret_cast<uint32_t *>(w + D.va), *vb = reinterpret_cast<uint32_t *>(w + D.vb);
-    auto *count = reinterpret_cast<unsigned long long *>(w + D.count);
-    uint32_t *seg = reinterpret_cast<uint32_t *>(w + D.seg);
-    const int64_t m = std::max(pairs, 2 * v.n);
-    if (m > 0)
-        k_det_init<<<dim3(unsigned((m + 255) / 256)), 256, 0, s>>>(v.point_list, pairs, ka, va,
-                                                                    count, seg, v.n);
+    uint32_t *first = reinterpret_cast<uint32_t *>(w + D.first);
+    uint32_t *rows = reinterpret_cast<uint32_t *>(w + D.rows);
+    uint32_t *seq = reinterpret_cast<uint32_t *>(w + D.seq), *list = reinterpret_cast<uint32_t *>(w + D.list);
+    v.det_rows = rows;
+    v.det_seq = seq;
+    const int64_t m = std::max(pairs, v.n);
+    if (m > 0) k_det_init<<<dim3(unsigned((m + 255) / 256)), 256, 0, s>>>(rows, v.n, seq, pairs);
     const dim3 grid(unsigned(xcd_grid(v.n_tiles)));
     switch (prec) {
         case GSB_FP32_PLAIN: k_blend_bwd_det<Mode::Plain><<<grid, kBlock, 0, s>>>(v); break;
@@ -1875,14 +2027,12 @@ gsb_status blend_backward_det(const ViewDesc &v0, gsb_precision prec, int64_t pa
         default: return fail(GSB_ERR_INVALID, "unknown precision %d", int(prec));
     }
     if (pairs > 0 && v.n > 0) {
-        const int passes = pair_sort(ka, kb, va, vb, count, pairs, bits_for(v.n), w + D.scratch, s);
-        const uint32_t *skeys = passes % 2 ? kb : ka;
-        const uint32_t *spos = passes % 2 ? vb : va;
-        key_ranges(skeys, count, pairs, seg, s);
-        if (v.n > 0)
-            k_det_gather<<<dim3(unsigned((v.n + 4 * kGatherPer - 1) / (4 * kGatherPer))), 256, 0, s>>>(
-                v.records, v.det_partial, spos, seg, v.n, v.dL_dmeans2d, v.dL_dconics,
-                v.dL_dopacity, v.dL_dcolors);
+        counts_to_offsets(rows, first, v.n, w + D.scratch, s);
+        k_det_place<<<dim3(unsigned((pairs + 1023) / 1024)), 256, 0, s>>>(v.point_list, seq, pairs, first,
+                                                                         v.n, list);
+        k_det_gather<<<dim3(unsigned((v.n + 4 * kGatherPer - 1) / (4 * kGatherPer))), 256, 0, s>>>(
+            DetOut{v.records, v.dL_dmeans2d, v.dL_dconics, v.dL_dopacity, v.dL_dcolors}, v.det_partial,
+            first, rows, list, seq, pairs, v.n);
     } else if (v.n > 0) {
         k_zero_grads<<<dim3(unsigned((v.n + 255) / 256), 1), 256, 0, s>>>(nullptr, v);
     }

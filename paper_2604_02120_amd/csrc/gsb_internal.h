@@ -133,8 +133,11 @@ struct ViewDesc {
     int32_t *last_contrib;
     const float *dL_dimage;
     float *dL_dmeans2d, *dL_dconics, *dL_dopacity, *dL_dcolors;
-    float *det_partial;       // deterministic backward: per list position, its nine sums
-    int64_t det_pairs;        // ... for positions [0, det_pairs)
+    // deterministic backward: a row per list position in [0, det_pairs), the number of each among its
+    // Gaussian's, and the Gaussians' numbers of rows
+    float *det_partial;
+    int64_t det_pairs;
+    uint32_t *det_seq, *det_rows;
 };
 
 ViewDesc make_view(int32_t W, int32_t H, const uint32_t *ranges, const uint32_t *point_list,
@@ -152,13 +155,10 @@ gsb_status blend_backward_packed(const ViewDesc &v, gsb_precision prec, hipStrea
 size_t backward_det_workspace_bytes(int64_t n, int64_t pairs);
 gsb_status blend_backward_det(const ViewDesc &v, gsb_precision prec, int64_t pairs, void *ws,
                               hipStream_t s);
-// The binning's stable pair sort (bin.hip), for grouping (key, value) pairs by key.
-size_t pair_sort_scratch_bytes(int64_t cap);
-int pair_sort(uint32_t *ka, uint32_t *kb, uint32_t *va, uint32_t *vb,
-              const unsigned long long *count, int64_t cap, int bits, void *scratch,
-              hipStream_t s);
-void key_ranges(const uint32_t *sorted_keys, const unsigned long long *count, int64_t cap,
-                uint32_t *ranges, hipStream_t s);
+// The binning's device scan (bin.hip): offsets[0, n) = the exclusive sums of counts.
+size_t offsets_scratch_bytes(int64_t n);
+void counts_to_offsets(const uint32_t *counts, uint32_t *offsets, int64_t n, void *scratch,
+                       hipStream_t s);
 
 // Launch shape choices (all have defaults).
 struct Tuning {
