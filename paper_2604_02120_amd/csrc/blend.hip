@@ -577,9 +577,17 @@ __device__ inline void composite(float q, float lo2o, float cr, float cg, float 
 // Gaussian that some lane takes has its (log2 o, r, g, b) read at one LDS address by every lane.
 // A Gaussian whose bit in `reach` (this wavefront's reach mask of the group) is clear is skipped
 // without evaluating q: no lane would take it.
-template <typename QFn>
+// kFew (see few_tiles): the whole group's values are read ahead, into registers.
+template <bool kFew, typename QFn>
 __device__ inline void composite_group(const float4 *attr, int base, uint32_t reach, FwdState &st,
                                        QFn q_of) {
+    f4x ahead[kFew ? kGroup : 1];
+    if constexpr (kFew) {
+#pragma unroll
+        for (int u = 0; u < kGroup; ++u) ahead[u] = *reinterpret_cast<const f4x *>(&attr[u]);
+#pragma unroll
+        for (int u = 0; u < kGroup; ++u) asm volatile("" : "+v"(ahead[u]));
+    }
 #pragma unroll
     for (int u = 0; u < kGroup; ++u) {
         if (((reach >> u) & 1u) == 0u) continue;
@@ -587,15 +595,15 @@ __device__ inline void composite_group(const float4 *attr, int base, uint32_t re
         if (__builtin_amdgcn_ballot_w64(q >= st.thr) == 0ull) continue;   // no lane takes it
         // one address for every lane (an LDS broadcast), read whole: left to itself the compiler
         // moves the colour reads into the blending lanes' branch, as separate loads
-        f4x a = *reinterpret_cast<const f4x *>(&attr[u]);
-        asm volatile("" : "+v"(a));
+        f4x a = kFew ? ahead[kFew ? u : 0] : *reinterpret_cast<const f4x *>(&attr[u]);
+        if constexpr (!kFew) asm volatile("" : "+v"(a));
         composite(q, a.x, a.y, a.z, a.w, base + u, st);
     }
 }
 
 // Forward of one tile of one view (all 256 threads of the block take part; block-uniform control
 // flow around every barrier).
-template <Mode M, int NB, bool kPacked = false>
+template <Mode M, int NB, bool kPacked = false, bool kFew = false>
 __device__ inline void fwd_tile(const ViewDesc &v, TileXY tile, FwdStage<M, NB> &S,
                                 int tid = threadIdx.x) {
     static_assert(NB % kGroup == 0 && NB <= kBlock, "batch must be whole groups, <= block");
@@ -666,12 +674,28 @@ __device__ inline void fwd_tile(const ViewDesc &v, TileXY tile, FwdStage<M, NB> 
             if (__ballot(st.thr != INFINITY) == 0) break;
             const int s0 = g * kGroup;
             const float4 *attr = &S.attr[s0];
-            if constexpr (M == Mode::Plain) {
-                composite_group(attr, s0, group_reach(S, s0, total, L), st,
-                                [&](int k) { return plain_q(S.geo[s0 + k], S.geo2[s0 + k], L); });
+            if constexpr (M == Mode::Plain && kFew) {
+                f4x geo[kGroup];
+                float2 geo2[kGroup];
+#pragma unroll
+                for (int k = 0; k < kGroup; ++k) {
+                    geo[k] = *reinterpret_cast<const f4x *>(&S.geo[s0 + k]);
+                    geo2[k] = S.geo2[s0 + k];
+                }
+#pragma unroll
+                for (int k = 0; k < kGroup; ++k) {
+                    asm volatile("" : "+v"(geo[k]));
+                    asm volatile("" : "+v"(geo2[k].x), "+v"(geo2[k].y));
+                }
+                composite_group<kFew>(attr, s0, group_reach(S, s0, total, L), st, [&](int k) {
+                    return plain_q(make_float4(geo[k].x, geo[k].y, geo[k].z, geo[k].w), geo2[k], L);
+                });
+            } else if constexpr (M == Mode::Plain) {
+                composite_group<kFew>(attr, s0, group_reach(S, s0, total, L), st,
+                                      [&](int k) { return plain_q(S.geo[s0 + k], S.geo2[s0 + k], L); });
             } else {
                 const f16x q = group_q<M, NB>(S, s0, L, bhi, blo);
-                composite_group(attr, s0, 0xffffu, st, [&](int k) { return q[k]; });
+                composite_group<kFew>(attr, s0, 0xffffu, st, [&](int k) { return q[k]; });
             }
         }
         if (st.last < 0) st.last = base + int(S.pos[~st.last]) + 1;
@@ -1334,18 +1358,31 @@ template <bool kMM> __device__ inline BwdMM *mm_ptr(MMTiles<kMM> &t) {
 template <Mode M, bool kMM> constexpr int waves_bwd_tile() {
     return kMM ? (M == Mode::Plain ? 5 : 4) : (M == Mode::Plain ? 7 : 5);
 }
+// Forward: small grids, all of whose blocks are on the GPU at once also with the registers for a group
+// read ahead, are bound by each wavefront's own chain (an LDS read after a branch for each Gaussian),
+// not by instruction issue. Read ahead, FP16: 256 tiles 35 -> 29 us, 512 tiles 35 -> 31, 1024 tiles
+// 40 -> 37.5; 1536 tiles, past the rule, 47 -> 55. FP32, which holds its geometry too and has half
+// the blocks: 512 tiles 47 -> 41, 768 tiles 49 -> 67. (The backward gains 1%: its chain is the
+// reduction.)
+template <Mode M, bool kFew> constexpr int waves_fwd_tile() {
+    return kFew ? (M == Mode::Plain ? 2 : 4) : (M == Mode::Plain ? 8 : 7);
+}
+constexpr int kCus = 256;
+template <Mode M> inline bool few_tiles(int64_t n_tiles) {
+    return n_tiles <= kCus * waves_fwd_tile<M, true>();
+}
 __device__ inline TileXY view_tile(const ViewDesc &v, uint32_t rank) {
     return strip_tile(rank, uint32_t(v.gx), uint32_t(v.H + kTile - 1) / kTile);
 }
 // Single view: block b renders the tile of rank xcd_rank(b).
-template <Mode M, int NB>
-__global__ __launch_bounds__(kBlock, fit_waves(M == Mode::Plain ? 8 : 7, lds_fwd<M, NB>()))
+template <Mode M, int NB, bool kFew = false>
+__global__ __launch_bounds__(kBlock, fit_waves(waves_fwd_tile<M, kFew>(), lds_fwd<M, NB>()))
 void k_blend_fwd(ViewDesc v) {
     __shared__ FwdStage<M, NB> S;
     const uint32_t rank = xcd_rank(blockIdx.x, uint32_t(v.n_tiles));
     if (rank >= uint32_t(v.n_tiles)) return;
     const TileXY tile = view_tile(v, rank);
-    fwd_tile<M, NB>(v, tile, S);
+    fwd_tile<M, NB, false, kFew>(v, tile, S);
 }
 
 template <Mode M, int NB, bool kMM>
@@ -1363,14 +1400,14 @@ void k_blend_bwd(ViewDesc v) {
 
 // Single view, packed records (gsb_pack_gaussians): the default launch shape (LDS batches of 128,
 // vector-ALU reduction), attributes from one 48-byte record per list entry.
-template <Mode M>
-__global__ __launch_bounds__(kBlock, fit_waves(M == Mode::Plain ? 8 : 7, lds_fwd<M, kDefaultBatchFwd>()))
+template <Mode M, bool kFew>
+__global__ __launch_bounds__(kBlock, fit_waves(waves_fwd_tile<M, kFew>(), lds_fwd<M, kDefaultBatchFwd>()))
 void k_blend_fwd_rec(ViewDesc v) {
     __shared__ FwdStage<M, kDefaultBatchFwd> S;
     const uint32_t rank = xcd_rank(blockIdx.x, uint32_t(v.n_tiles));
     if (rank >= uint32_t(v.n_tiles)) return;
     const TileXY tile = view_tile(v, rank);
-    fwd_tile<M, kDefaultBatchFwd, true>(v, tile, S);
+    fwd_tile<M, kDefaultBatchFwd, true, kFew>(v, tile, S);
 }
 
 template <Mode M>
@@ -1865,6 +1902,7 @@ void launch_fwd_single(const ViewDesc &v, int nb, hipStream_t s) {
     const dim3 grid(unsigned(xcd_grid(v.n_tiles)));
     if (nb == 64) k_blend_fwd<M, 64><<<grid, kBlock, 0, s>>>(v);
     else if (nb == 128) k_blend_fwd<M, 128><<<grid, kBlock, 0, s>>>(v);
+    else if (few_tiles<M>(v.n_tiles)) k_blend_fwd<M, 256, true><<<grid, kBlock, 0, s>>>(v);
     else k_blend_fwd<M, 256><<<grid, kBlock, 0, s>>>(v);
 }
 
@@ -1954,12 +1992,18 @@ gsb_status pack_gaussians(const float *means2d, const float *conics, const float
     return check_launch("pack_gaussians");
 }
 
+template <Mode M>
+static void launch_fwd_rec(const ViewDesc &v, dim3 grid, hipStream_t s) {
+    if (few_tiles<M>(v.n_tiles)) k_blend_fwd_rec<M, true><<<grid, kBlock, 0, s>>>(v);
+    else k_blend_fwd_rec<M, false><<<grid, kBlock, 0, s>>>(v);
+}
+
 gsb_status blend_forward_packed(const ViewDesc &v, gsb_precision prec, hipStream_t s) {
     const dim3 grid(unsigned(xcd_grid(v.n_tiles)));
     switch (prec) {
-        case GSB_FP32_PLAIN: k_blend_fwd_rec<Mode::Plain><<<grid, kBlock, 0, s>>>(v); break;
-        case GSB_FP16_GEMM: k_blend_fwd_rec<Mode::F16><<<grid, kBlock, 0, s>>>(v); break;
-        case GSB_BF16_GEMM: k_blend_fwd_rec<Mode::BF16><<<grid, kBlock, 0, s>>>(v); break;
+        case GSB_FP32_PLAIN: launch_fwd_rec<Mode::Plain>(v, grid, s); break;
+        case GSB_FP16_GEMM: launch_fwd_rec<Mode::F16>(v, grid, s); break;
+        case GSB_BF16_GEMM: launch_fwd_rec<Mode::BF16>(v, grid, s); break;
         default: return fail(GSB_ERR_INVALID, "unknown precision %d", int(prec));
     }
     return check_launch("blend_forward_packed");
