@@ -2031,6 +2031,142 @@ __global__ __launch_bounds__(256) void k_sb_write(const uint32_t *e_idx,
     }
 }
 
+// Few Gaussians on a small grid (n <= kSmallSort, few_lists): steps 1 to 4 in one launch, a block per
+// superblock. Every block counts all tiles, from the rectangles' corners in a table of differences, and
+// so knows where its own tiles' lists start; wave w then owns `per` chunks of 64 ranks, whose masks it
+// transposes, and its lanes, a tile each, write the set bits' Gaussians. 2000 Gaussians on 16 tiles:
+// 14 us and one launch, against 29 us in four.
+constexpr int kListThreads = 1024, kListEdge = 128, kListCells = 9216;
+constexpr int kListPer = kSmallSort / kListThreads;
+inline bool few_lists(const SbGrid &G) {
+    return G.gx <= kListEdge && G.gy <= kListEdge && (G.gx + 1) * (G.gy + 1) <= kListCells;
+}
+__global__ __launch_bounds__(kListThreads) void k_few_lists(const unsigned long long *rank_rects,
+                                                            const uint32_t *sorted_idx, int n, SbGrid G,
+                                                            BinHeader *hdr, int64_t cap, uint2 *ranges,
+                                                            uint32_t *point_list, int32_t *status) {
+    constexpr int kWaves = kListThreads / 64;
+    __shared__ uint32_t s_cell[kListCells];        // differences, counts, then starts, stride gx + 1
+    __shared__ uint32_t s_idx[kSmallSort];
+    __shared__ uint32_t s_cnt[kWaves][kSbTiles];
+    __shared__ uint32_t s_wave[kWaves];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int stride = G.gx + 1, cells = stride * (G.gy + 1), n_tiles = G.gx * G.gy;
+    const unsigned long long all = hdr->total;
+    if (all > (unsigned long long)cap) {                     // block-uniform: every list stays empty
+        if (blockIdx.x == 0 && t == 0) {
+            hdr->pairs = (unsigned long long)cap;
+            *status = GSB_ERR_CAPACITY;
+        }
+        return;
+    }
+    if (blockIdx.x == 0 && t == 0) hdr->pairs = all;
+    for (int i = t; i < cells; i += kListThreads) s_cell[i] = 0u;
+    __syncthreads();
+    const int per = ((n + 63) / 64 + kWaves - 1) / kWaves;   // <= kListPer
+    unsigned long long rect[kListPer];
+#pragma unroll
+    for (int k = 0; k < kListPer; ++k) {
+        const int j = (w * per + k) * 64 + lane;
+        const bool valid = k < per && j < n;
+        rect[k] = valid ? rank_rects[j] : 0ull;
+        if (valid) s_idx[j] = sorted_idx[j];
+    }
+#pragma unroll
+    for (int k = 0; k < kListPer; ++k) {
+        const Rect R = unpack_rect(rect[k]);
+        if (R.tx1 <= R.tx0 || R.ty1 <= R.ty0) continue;
+        atomicAdd(&s_cell[R.ty0 * stride + R.tx0], 1u);
+        atomicAdd(&s_cell[R.ty0 * stride + R.tx1], ~0u);
+        atomicAdd(&s_cell[R.ty1 * stride + R.tx0], ~0u);
+        atomicAdd(&s_cell[R.ty1 * stride + R.tx1], 1u);
+    }
+    __syncthreads();
+    for (int y = w; y < G.gy; y += kWaves) {                 // sums along the rows
+        uint32_t carry = 0;
+        for (int x0 = 0; x0 < G.gx; x0 += 64) {
+            const int x = x0 + lane;
+            uint32_t v = x < G.gx ? s_cell[y * stride + x] : 0u;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t u = __shfl_up(v, o, 64);
+                if (lane >= o) v += u;
+            }
+            v += carry;
+            if (x < G.gx) s_cell[y * stride + x] = v;
+            carry = __shfl(v, 63, 64);
+        }
+    }
+    __syncthreads();
+    if (t < G.gx) {                                          // and along the columns
+        uint32_t v = 0;
+        for (int y = 0; y < G.gy; ++y) s_cell[y * stride + t] = v += s_cell[y * stride + t];
+    }
+    __syncthreads();
+    constexpr int kOwn = kListCells / kListThreads;          // the tiles' starts
+    uint32_t c[kOwn], sum = 0, tot;
+    const int own = (n_tiles + kListThreads - 1) / kListThreads, i0 = t * own;
+    int y = i0 / G.gx, x = i0 % G.gx;
+    const int y0 = y, x0 = x;
+#pragma unroll
+    for (int k = 0; k < kOwn; ++k) {
+        c[k] = 0u;
+        if (k < own && i0 + k < n_tiles) {
+            sum += c[k] = s_cell[y * stride + x];
+            if (++x == G.gx) {
+                x = 0;
+                ++y;
+            }
+        }
+    }
+    uint32_t run = block_exclusive_scan<uint32_t>(sum, s_wave, tot);
+    y = y0;
+    x = x0;
+#pragma unroll
+    for (int k = 0; k < kOwn; ++k) {
+        if (k < own && i0 + k < n_tiles) {
+            s_cell[y * stride + x] = run;
+            run += c[k];
+            if (++x == G.gx) {
+                x = 0;
+                ++y;
+            }
+        }
+    }
+    const int sx = int(blockIdx.x) % G.sx, sy = int(blockIdx.x) / G.sx;
+    unsigned long long hit[kListPer];
+    uint32_t cnt = 0;
+#pragma unroll
+    for (int k = 0; k < kListPer; ++k) {
+        const Rect R = unpack_rect(rect[k]);
+        unsigned long long m = 0;
+        if (R.tx0 < (sx + 1) * kSbEdge && R.tx1 > sx * kSbEdge && R.ty0 < (sy + 1) * kSbEdge &&
+            R.ty1 > sy * kSbEdge && R.tx0 < R.tx1 && R.ty0 < R.ty1)
+            m = sb_mask(sb_span(R.tx0, R.tx1, sx) | (sb_span(R.ty0, R.ty1, sy) << 8));
+        hit[k] = transpose64(m, lane);
+        cnt += uint32_t(__popcll(hit[k]));
+    }
+    s_cnt[w][lane] = cnt;
+    __syncthreads();
+    const int tx = sx * kSbEdge + (lane & (kSbEdge - 1)), ty = sy * kSbEdge + (lane >> kSbShift);
+    if (tx >= G.gx || ty >= G.gy) return;                    // (no barrier below)
+    uint32_t o = s_cell[ty * stride + tx], len = 0;
+    const uint32_t first = o;
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k) {
+        const uint32_t e = s_cnt[k][lane];
+        o += k < w ? e : 0u;
+        len += e;
+    }
+    if (w == 0 && len > 0) ranges[ty * G.gx + tx] = make_uint2(first, first + len);
+#pragma unroll
+    for (int k = 0; k < kListPer; ++k) {
+        const uint32_t *idx = s_idx + (w * per + k) * 64;
+        for (unsigned long long m = hit[k]; m != 0ull; m &= m - 1ull)
+            if (o < cap) point_list[o++] = idx[__ffsll((long long)m) - 1];
+    }
+}
+
 // Start of bin_fill: empty ranges, zeroed sort states, the Gaussian count for the depth sort and
 // a clean status word (later kernels only ever write error codes into it).
 __global__ __launch_bounds__(256) void k_bin_init(uint32_t *ranges, int64_t m, SortState *sorts,
@@ -2201,6 +2337,11 @@ gsb_status bin_fill_sorted(const float *means2d, const float *conics, const floa
                           reinterpret_cast<const float2 *>(means2d), conics, opacity, W, H};
         if (vis)
             k_sb_list<<<dim3(unsigned((n + 63) / 64)), 64, 0, s>>>(V, table, n, G, cap);
+        if (n <= kSmallSort && !vis && few_lists(G)) {
+            k_few_lists<<<dim3(unsigned(G.n)), kListThreads, 0, s>>>(
+                rects, dva, int(n), G, hdr, cap, reinterpret_cast<uint2 *>(ranges), point_list, status_dev);
+            return check_launch("bin_fill");
+        }
         if (n <= kSmallSort && !vis) {
             const auto scatter = n <= 4 * kSortThreads ? k_sb_scatter<4, true, false>
                                : n <= 8 * kSortThreads ? k_sb_scatter<8, true, false>
