@@ -1065,106 +1065,67 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_pass(
     }
 }
 
-// The depth sort of up to kSmallSort Gaussians in one block and one launch: four stable passes in
-// LDS, as k_radix_pass ranks them, then the rectangles in rank order; it also does k_bin_init's work
-// when `ranges_n` words are given. (A histogram and four chained passes over one tile of keys are
-// five launches of 5-9 us each that wait for one another: 36 us at 2000 Gaussians, this one 15.)
-constexpr int kSmallSort = 4096, kSmallThreads = 1024;
 // Up to this many Gaussians the depth sort takes 1024 keys per block instead of 4096: more, shorter
 // blocks (the whole binning at 20k 109 -> 91 us, 60k 118 -> 106, 130k 127 -> 122; at 300k it is even,
 // at 1M smaller tiles' longer look-back costs more: 201 -> 260).
 constexpr int64_t kSort4 = 131072;
-__global__ __launch_bounds__(kSmallThreads) void k_sort_small(const float *depths, int n,
-                                                              uint32_t *sorted_idx,
-                                                              const uint4 *recs_by_idx,
-                                                              unsigned long long *rank_counts,
-                                                              unsigned long long *rank_rects,
-                                                              uint32_t *ranges, int ranges_n,
-                                                              SbTable *table, int32_t *status) {
-    constexpr int kWaves = kSmallThreads / 64, kItems = kSmallSort / kSmallThreads;
-    __shared__ uint16_t s_wcnt[kWaves][kRadix];
-    __shared__ uint32_t s_dstart[kRadix];
-    __shared__ uint32_t s_wave[kWaves];
-    __shared__ uint32_t s_key[kSmallSort];
-    __shared__ uint16_t s_val[kSmallSort];
+// Up to this many Gaussians one block places the entries and one launch may write the lists.
+constexpr int kSmallSort = 4096;
+
+// The depth order of up to kRankSort Gaussians in one launch: a block ranks 64 of them (lane e) by
+// counting the keys before theirs, a sixteenth of all per wavefront, four at a time from LDS (the same
+// address for every lane). Two vector instructions per key and 64 Gaussians, n^2 / 64 of them in all;
+// the passes' six launches wait for one another. Also k_bin_init's work. The whole binning of 2000
+// Gaussians 45 -> 38 us (with four passes in one block's LDS before), of 8192 82 -> 63, 16384 87 -> 79;
+// at 20000, where a second round of blocks begins, 90 -> 110.
+constexpr int kRankSort = 16384, kRankThreads = 1024;
+__global__ __launch_bounds__(kRankThreads) void k_rank(const float *depths, int n, uint32_t *sorted_idx,
+                                                       const uint4 *recs_by_idx,
+                                                       unsigned long long *rank_counts,
+                                                       unsigned long long *rank_rects, uint32_t *ranges,
+                                                       int ranges_n, SbTable *table, int32_t *status) {
+    constexpr int kWaves = kRankThreads / 64;
+    extern __shared__ __align__(16) uint32_t s_key[];        // n keys, to a multiple of 64
+    __shared__ uint32_t s_part[kWaves][64];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    if (t < kSbLists) table->listed[t][0] = 0ull;
-    if (t == 0) *status = GSB_OK;
-    for (int k = t; k < ranges_n; k += kSmallThreads) ranges[k] = 0u;
-    // wave w holds keys [256 w, 256 (w + 1)) in four steps of 64
-    uint32_t key[kItems], val[kItems];
-#pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-        const int i = w * (kItems * 64) + k * 64 + lane;
-        key[k] = i < n ? depth_key(depths[i]) : 0u;
-        val[k] = uint32_t(i);
+    const int e0 = int(blockIdx.x) * 64, e = e0 + lane, padded = (n + 63) & ~63;
+    if (blockIdx.x == 0) {
+        if (t < kSbLists) table->listed[t][0] = 0ull;
+        if (t == 0) *status = GSB_OK;
     }
-    for (int shift = 0; shift < 32; shift += kRadixBits) {
-        for (int k = t; k < kWaves * kRadix; k += kSmallThreads) (&s_wcnt[0][0])[k] = 0;
-        __syncthreads();
-        uint32_t loc[kItems];
-#pragma unroll
-        for (int k = 0; k < kItems; ++k) {
-            const bool valid = w * (kItems * 64) + k * 64 + lane < n;
-            const uint32_t d = (key[k] >> shift) & (kRadix - 1);
-            const unsigned long long vmask = __builtin_amdgcn_ballot_w64(valid);
-            uint32_t plo = uint32_t(vmask), phi = uint32_t(vmask >> 32);
-            const uint32_t nd = ~d;
-#pragma unroll
-            for (int b = 0; b < kRadixBits; ++b) {
-                const uint32_t flip = uint32_t(int32_t(nd << (31 - b)) >> 31);  // ones if bit b clear
-                const unsigned long long vote = __builtin_amdgcn_ballot_w64(flip == 0u);
-                plo &= uint32_t(vote) ^ flip;
-                phi &= uint32_t(vote >> 32) ^ flip;
-            }
-            const uint32_t rank = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0u));
-            uint32_t prior = 0;
-            if (valid) prior = s_wcnt[w][d];
-            if (valid && rank == 0) s_wcnt[w][d] = uint16_t(prior + uint32_t(__popc(plo) + __popc(phi)));
-            loc[k] = prior + rank;
+    for (int k = int(blockIdx.x) * kRankThreads + t; k < ranges_n; k += int(gridDim.x) * kRankThreads)
+        ranges[k] = 0u;
+    for (int i = t; i < padded; i += kRankThreads) s_key[i] = i < n ? depth_key(depths[i]) : ~0u;
+    __syncthreads();
+    const uint32_t my = s_key[e];
+    const int part = (padded / kWaves + 3) & ~3;
+    const int lo = w * part, hi = lo + part < padded ? lo + part : padded;
+    uint32_t before = 0;
+    const auto count = [&](int a, int b, auto test) {        // (a and b multiples of 4)
+#pragma unroll 4
+        for (int j = a; j < b; j += 4) {
+            const uint4 k = *reinterpret_cast<const uint4 *>(&s_key[j]);
+            before += test(k.x, j) ? 1u : 0u;
+            before += test(k.y, j + 1) ? 1u : 0u;
+            before += test(k.z, j + 2) ? 1u : 0u;
+            before += test(k.w, j + 3) ? 1u : 0u;
         }
-        __syncthreads();
-        uint32_t run = 0, tot;
-        if (t < kRadix) {
+    };
+    // equal depths keep the order of the indices
+    count(lo, hi < e0 ? hi : e0, [&](uint32_t k, int) { return k <= my; });
+    count(lo > e0 ? lo : e0, hi < e0 + 64 ? hi : e0 + 64,
+          [&](uint32_t k, int j) { return k < my || (k == my && j < e); });
+    count(lo > e0 + 64 ? lo : e0 + 64, hi, [&](uint32_t k, int) { return k < my; });
+    s_part[w][lane] = before;
+    __syncthreads();
+    if (w != 0 || e >= n) return;
+    uint32_t rank = 0;
 #pragma unroll
-            for (int i = 0; i < kWaves; ++i) {
-                const uint32_t c = s_wcnt[i][t];
-                s_wcnt[i][t] = uint16_t(run);
-                run += c;
-            }
-        }
-        const uint32_t start = block_exclusive_scan<uint32_t>(run, s_wave, tot);
-        if (t < kRadix) s_dstart[t] = start;
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kItems; ++k) {
-            if (w * (kItems * 64) + k * 64 + lane < n) {
-                const uint32_t d = (key[k] >> shift) & (kRadix - 1);
-                const uint32_t r = s_dstart[d] + s_wcnt[w][d] + loc[k];
-                s_key[r] = key[k];
-                s_val[r] = uint16_t(val[k]);
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kItems; ++k) {
-            const int i = w * (kItems * 64) + k * 64 + lane;
-            if (i < n) {
-                key[k] = s_key[i];
-                val[k] = s_val[i];
-            }
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < kItems; ++k) {
-        const int i = w * (kItems * 64) + k * 64 + lane;
-        if (i < n) {
-            const uint4 r = recs_by_idx[val[k]];
-            sorted_idx[i] = val[k];
-            if (rank_counts) rank_counts[i] = (static_cast<unsigned long long>(r.y) << 32) | r.x;
-            rank_rects[i] = (static_cast<unsigned long long>(r.w) << 32) | r.z;
-        }
-    }
+    for (int k = 0; k < kWaves; ++k) rank += s_part[k][lane];
+    const uint4 r = recs_by_idx[e];
+    sorted_idx[rank] = uint32_t(e);
+    if (rank_counts) rank_counts[rank] = (static_cast<unsigned long long>(r.y) << 32) | r.x;
+    rank_rects[rank] = (static_cast<unsigned long long>(r.w) << 32) | r.z;
 }
 
 // Depth sort of the n Gaussians (count on the device): keys made from `depths`, values the
@@ -2282,16 +2243,17 @@ gsb_status bin_sort(int32_t mode, const float *depths, int64_t n, int32_t W, int
     const bool sb = by_superblock(sb_grid(int32_t(grid_x(W)), int32_t(grid_y(H))));
     auto *rank_counts = sb && mode == GSB_BIN_RECT ? nullptr : at<unsigned long long>(ws, L.offs);
     auto *rects = at<unsigned long long>(ws, L.rects);
-    if (sb && n > 0 && n <= kSmallSort) {
-        k_sort_small<<<1, kSmallThreads, 0, s>>>(depths, int(n), dva, at<uint4>(ws, L.recs),
-                                                 rank_counts, rects, ranges, int(2 * n_tiles),
-                                                 at<SbTable>(ws, L.sb_table), status_dev);
+    if (sb && n > 0 && n <= kRankSort) {
+        const size_t lds = sizeof(uint32_t) * size_t((n + 63) & ~int64_t(63));
+        k_rank<<<dim3(unsigned((n + 63) / 64)), kRankThreads, lds, s>>>(
+            depths, int(n), dva, at<uint4>(ws, L.recs), rank_counts, rects, ranges, int(2 * n_tiles),
+            at<SbTable>(ws, L.sb_table), status_dev);
         return check_launch("bin_sort");
     }
     k_bin_init<<<dim3(unsigned((2 * n_tiles + 255) / 256)), 256, 0, s>>>(
         ranges, 2 * n_tiles, sorts, hdr, n, at<SbTable>(ws, L.sb_table), status_dev);
     // the look-back words of the smaller tiles (4096 bytes per 1024 Gaussians) take the place of the
-    // masks by index (8 bytes per Gaussian, and n > kSmallSort here), which superblocks do not use
+    // masks by index (8 bytes per Gaussian, and n > kRankSort here), which superblocks do not use
     if (sb && n > 0 && n <= kSort4)
         sort_depth<4>(depths, dka, dkb, dva, dvb, &hdr->gaussians, n, sorts, at<uint32_t>(ws, L.masks),
                       status_dev, at<uint4>(ws, L.recs), rank_counts, rects, s);

@@ -1,6 +1,7 @@
 """Tile lists of few Gaussians, bit for bit against the oracle, at the edges of what is written in one
 launch: one chunk of 64 ranks, ragged chunks, the most Gaussians and the first past them, the widest
-grid of 128 tile columns beside the first past it, and the most cells."""
+grid of 128 tile columns beside the first past it, and the most cells; and of the most that are
+ranked by counting (16384) beside the first past them."""
 import numpy as np
 import pytest
 import torch
@@ -25,6 +26,10 @@ SCENES = {
     "128 rows": (1120, 2048, 3000, 0, 500),
     "more cells": (1150, 2048, 3000, 0, 500),
     "one column": (10, 2048, 900, 1, 200),
+    "63 ranks": (100, 90, 63, 0, 40),
+    "8191 ranks": (400, 300, 8191, 0, 30),
+    "16384 ranks": (400, 300, 16384, 0, 30),
+    "16385 ranks": (400, 300, 16385, 0, 30),
 }
 
 
