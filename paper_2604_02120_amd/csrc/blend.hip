@@ -1035,6 +1035,18 @@ __device__ inline void mm_reduce(uint32_t (*rows)[kDgStride], const h8 (&B)[2], 
 // Backward of one tile of one view.
 // kMM: the five geometric sums are formed on the matrix cores (mm_reduce) instead of being
 // reduced on the vector ALUs with the other four; `mm` is then the block's transposition tiles.
+// The list entries that the backward takes at a time, of the NB that LDS has room for: a tile whose list
+// is one batch loads, stages, blends and flushes one after the other, so short lists are taken in
+// smaller batches, whose loads and flushes overlap the blending. Long lists, of which fewer entries
+// are kept, fill the groups better in large ones. Backward in us with batches of 64, 128, 256, by the
+// list's mean length: 246 entries 1739, 1835, 2233; 348: 839, 851, 933; 641: 1918, 1890, 2005;
+// 1689: 2275, 2055, 1975. With this rule 1724, 850, 1892 and 1968.
+template <int NB>
+__device__ inline int batch_bwd(int64_t len) {
+    if (NB >= 128 && len <= 256) return 64;
+    if (NB > 128 && len <= 512) return 128;
+    return NB;
+}
 // kDet: the batch sums go to the wavefronts' own slices (`det`) instead of `acc_`, and the flush
 // writes the nine sums of each list position that has a nonzero one to the position's row in place of
 // the global atomics.
@@ -1087,13 +1099,14 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, BwdStage<M, NB> 
     const int maxlast = __builtin_amdgcn_readfirstlane(s_maxlast);
     const int64_t len = maxlast < int64_t(rg.y) - int64_t(rg.x) ? maxlast
                                                                 : int64_t(rg.y) - int64_t(rg.x);
-    const int nb = int((len + NB - 1) / NB);
+    const int B = batch_bwd<NB>(len);
+    const int nb = int((len + B - 1) / B);
     if (nb == 0) return;
 
     // List entries are loaded two batches ahead and attributes one batch ahead.
     const auto entry = [&](int bb) {          // batch bb's entry for this thread (bb may be < 0)
-        const int64_t o = int64_t(bb) * NB + L.t;
-        return load_entry(plist, start + o, bb >= 0 && L.t < NB && o < len, start);
+        const int64_t o = int64_t(bb) * B + L.t;
+        return load_entry(plist, start + o, bb >= 0 && L.t < B && o < len, start);
     };
     // Each wavefront flushes a quarter of the batch's slots. It lists the slots that
     // received a nonzero sum, in slot order, and then spreads their nine sums over its lanes,
@@ -1122,7 +1135,7 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, BwdStage<M, NB> 
         }
         const bool touched = bits != 0u;
         const unsigned long long m = __ballot(touched);
-        const int64_t first = start + int64_t(bb) * NB;
+        const int64_t first = start + int64_t(bb) * B;
         if (touched) {
             const uint32_t g = S.ids[s0 + L.l];
             const int64_t p = first + det->entry[s0 + L.l];
@@ -1206,11 +1219,11 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, BwdStage<M, NB> 
     }
     int staged = 0;                            // slots of the batch before
     for (int b = nb - 1; b >= 0; --b) {
-        const int base = b * NB;
+        const int base = b * B;
         // as in the forward, only the entries that can reach the tile are staged, in order
         const Eval e = evaluate(nxt, xc, yc);
         uint32_t quad;
-        const bool keep = keep_entry<M>(nxt, e, v.reach == 0, L.t < NB && base + L.t < len, quad);
+        const bool keep = keep_entry<M>(nxt, e, v.reach == 0, L.t < B && base + L.t < len, quad);
         const unsigned long long kept = __builtin_amdgcn_ballot_w64(keep);
         if (L.l == 0) S.kept[L.w] = kept;
         __syncthreads();             // every wavefront is done with batch b + 1
@@ -1240,7 +1253,7 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, BwdStage<M, NB> 
         // slots below `last` hold entries up to the lane's last contributor
         int last;
         {
-            const int r = st.last - base < NB ? st.last - base : NB;      // entries of this batch
+            const int r = st.last - base < B ? st.last - base : B;      // entries of this batch
             const int w = r > 0 ? (r - 1) >> 6 : 0, in = r - 64 * w;       // 1 <= in <= 64 if r > 0
             const unsigned long long m = S.kept[w];
             const unsigned long long low = in <= 0 ? 0ull : ~0ull >> (64 - in);
