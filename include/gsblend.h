@@ -292,16 +292,14 @@ gsb_status gsb_blend_backward_packed(int32_t W, int32_t H, const uint32_t *range
  * call computes the same gradient (the product rule of Eq. (volume-render) and Eq. (alpha), as
  * gsb_blend_backward) with every sum in a fixed order, so that its result is identical bit for bit
  * on every run with the same inputs: per list entry, the wavefronts' sums over the tile's pixels
- * are added in wavefront order and stored at the entry's position; the positions are then grouped
- * by Gaussian with a stable sort and each Gaussian's entries are added in a fixed order (lane l of
- * a wavefront takes entries l, l + 64, ... in list order; the lane sums are combined by a fixed
- * reduction tree).
+ * are added in wavefront order and stored at the entry's position; each Gaussian's entries with a
+ * nonzero sum are then put in list order and added by a fixed reduction tree.
  *
  * pairs:   number of entries of point_list; every range must lie in [0, pairs) (the binning's
  *          pair count). Entries outside are neither read nor written.
  * records: the packed attributes (gsb_pack_gaussians).
  * ws:      device workspace of ws_bytes >= gsb_backward_det_workspace_bytes(n, pairs) bytes,
- *          256-byte aligned (about 80 bytes per list entry).
+ *          256-byte aligned (about 72 bytes per list entry).
  * Other arguments and the outputs as gsb_blend_backward_packed. Errors: INVALID, UNSUPPORTED, HIP.
  * ------------------------------------------------------------------------------------------- */
 gsb_status gsb_backward_det_workspace_bytes(int64_t n, int64_t pairs, size_t *bytes);
@@ -354,7 +352,7 @@ typedef struct gsb_view {
 #define GSB_REDUCE_MFMA 1
 typedef struct gsb_tuning {
     int32_t batch_fwd;       /* list entries per LDS batch, forward: 64, 128, 256 (256) */
-    int32_t batch_bwd;       /* same, backward (256) */
+    int32_t batch_bwd;       /* same, backward (256); short lists are taken in smaller batches */
     int32_t blocks_per_cu;   /* persistent: resident blocks per compute unit; 0 = as many as fit */
     int32_t launch;          /* GSB_LAUNCH_PERSISTENT (default) or GSB_LAUNCH_GRID */
     int32_t bwd_reduce;      /* GSB_REDUCE_VALU (default) or GSB_REDUCE_MFMA */

@@ -1411,7 +1411,7 @@ void k_blend_bwd(ViewDesc v) {
     bwd_tile<M, NB, kMM>(v, tile, S, &s_acc, s_maxlast, mm_ptr<kMM>(s_mm));
 }
 
-// Single view, packed records (gsb_pack_gaussians): the default launch shape (LDS batches of 128,
+// Single view, packed records (gsb_pack_gaussians): the default launch shape (LDS batches of 256,
 // vector-ALU reduction), attributes from one 48-byte record per list entry.
 template <Mode M, bool kFew>
 __global__ __launch_bounds__(kBlock, fit_waves(waves_fwd_tile<M, kFew>(), lds_fwd<M, kDefaultBatchFwd>()))
