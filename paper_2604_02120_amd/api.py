@@ -9,6 +9,7 @@ Tensors must be contiguous and on the current HIP device:
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 
 import torch
@@ -149,43 +150,54 @@ def bin_fill(means2d, radii, depths, W: int, H: int, ws: BinWorkspace, point_lis
 def bin_tiles(means2d, radii, depths, W: int, H: int, stream=None, conics=None, opacity=None,
               mode="rect"):
     """Count, then fill with an exactly sized list. Returns (point_list i32[P], ranges
-    i32[gx*gy][2]). Waits once for the pair count, while the GPU sorts the Gaussians."""
+    i32[gx*gy][2]). Waits once for the pair count, while the GPU sorts the Gaussians. ``stream``: as
+    for every call here, the caller orders it after what writes the inputs and before what reads the
+    results. (The first workspace holds _GUESS pairs per Gaussian: 264 bytes per Gaussian, at most 805
+    MB for the pairs; a frame with more pairs holds it and the exact one until the copy is enqueued.)"""
     n = radii.shape[0]
     dev = means2d.device
-    gx, gy = grid(W, H)
-    # room for _GUESS pairs per Gaussian, so that the usual frame needs no second workspace
-    ws = BinWorkspace(n, min(_GUESS * n, n * gx * gy, 1 << 26), W, H, device=dev)
     _req(means2d, torch.float32, "means2d")
     _req(radii, torch.int32, "radii")
     code, cp, op = _bin_mode(mode, conics, opacity)
     _req(depths, torch.float32, "depths")
-    s = torch.cuda.current_stream() if stream is None else stream
+    gx, gy = grid(W, H)
+    cur = torch.cuda.current_stream()
+    s = cur if stream is None else stream
     if not isinstance(s, torch.cuda.Stream):
         s = torch.cuda.ExternalStream(_stream(s))
-    ranges = torch.empty((gx * gy, 2), dtype=torch.int32, device=dev)
-    status = torch.empty(1, dtype=torch.int32, device=dev)
-    n_pairs = torch.empty(1, dtype=torch.int64, pin_memory=True)     # written by the GPU
-    counted = torch.cuda.Event()
-    geom = (means2d.data_ptr(), radii.data_ptr())
-    try:
-        _lib.gsb_bin_count(*geom, n, W, H, ws.ptr(), ws.nbytes, n_pairs.data_ptr(), s.cuda_stream,
-                           cp, op, code)
-        counted.record(s)
-        _lib.gsb_bin_sort(*geom, depths.data_ptr(), n, W, H, ws.ptr(), ws.nbytes,
-                          ranges.data_ptr(), status.data_ptr(), s.cuda_stream, cp, op, code)
-    finally:
-        counted.synchronize()
-    P = int(n_pairs)
-    if P > ws.capacity:
-        lead = _lib.gsb_bin_workspace_bytes(n, 0, W, H)
-        full = BinWorkspace(n, P, W, H, device=dev)
-        with torch.cuda.stream(s):
+    other = s.cuda_stream != cur.cuda_stream
+    # everything is allocated for `s`: its kernels still run when the scratch is released here
+    with torch.cuda.stream(s) if other else contextlib.nullcontext():
+        # room for _GUESS pairs per Gaussian, so that the usual frame needs no second workspace
+        ws = BinWorkspace(n, min(_GUESS * n, n * gx * gy, 1 << 26), W, H, device=dev)
+        ranges = torch.empty((gx * gy, 2), dtype=torch.int32, device=dev)
+        status = torch.empty(1, dtype=torch.int32, device=dev)
+        n_pairs = torch.empty(1, dtype=torch.int64, pin_memory=True)     # written by the GPU
+        counted = torch.cuda.Event()
+        geom = (means2d.data_ptr(), radii.data_ptr())
+        try:
+            _lib.gsb_bin_count(*geom, n, W, H, ws.ptr(), ws.nbytes, n_pairs.data_ptr(),
+                               s.cuda_stream, cp, op, code)
+            counted.record(s)
+            _lib.gsb_bin_sort(*geom, depths.data_ptr(), n, W, H, ws.ptr(), ws.nbytes,
+                              ranges.data_ptr(), status.data_ptr(), s.cuda_stream, cp, op, code)
+        finally:
+            counted.synchronize()
+        P = int(n_pairs)
+        if P > ws.capacity:
+            lead = _lib.gsb_bin_workspace_bytes(n, 0, W, H)
+            full = BinWorkspace(n, P, W, H, device=dev)
             full.buf[:lead].copy_(ws.buf[:lead])
-        ws = full
-    point_list = torch.empty(max(P, 1), dtype=torch.int32, device=dev)
-    _lib.gsb_bin_fill_sorted(*geom, depths.data_ptr(), n, W, H, ws.ptr(), ws.nbytes,
-                             point_list.data_ptr(), P, ranges.data_ptr(), status.data_ptr(),
-                             s.cuda_stream, cp, op, code)
+            ws = full
+        point_list = torch.empty(max(P, 1), dtype=torch.int32, device=dev)
+        _lib.gsb_bin_fill_sorted(*geom, depths.data_ptr(), n, W, H, ws.ptr(), ws.nbytes,
+                                 point_list.data_ptr(), P, ranges.data_ptr(), status.data_ptr(),
+                                 s.cuda_stream, cp, op, code)
+    if other:
+        for t in (point_list, ranges):               # the caller's to use on its own stream
+            t.record_stream(cur)
+        for t in (means2d, radii, depths) + ((conics, opacity) if cp else ()):
+            t.record_stream(s)                       # read by s after the return
     return point_list[:P], ranges
 
 
