@@ -159,9 +159,8 @@ struct BwdStage<Mode::Plain, NB> : BwdSlots<NB> {
 };
 
 constexpr int kGrad = 9;   // per-Gaussian sums kept per batch
-// Deterministic backward: the nine sums of a list position are one aligned 64-byte row, with the tile
-// (kDetTile) behind them.
-constexpr int kDetStride = 16, kDetTile = 9;
+// Deterministic backward: the nine sums of a list position are one aligned 64-byte row.
+constexpr int kDetStride = 16;
 
 // dL/do from the sum of alpha dL/dalpha over the Gaussian's pairs (alpha = o e^power below the 0.99
 // clamp): that sum over o. A Gaussian with o < 1/255 is never blended (its sum is zero).
@@ -1144,7 +1143,6 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, BwdStage<M, NB> 
         }
         __builtin_amdgcn_wave_barrier();
         const int listed = __popcll(m), k = L.l & 15;
-        const uint32_t tile_id = uint32_t(tile.y * v.gx + tile.x);
 #pragma unroll 1
         for (int i = L.l >> 4; i < listed; i += 4) {
             const int slot = list[i];
@@ -1158,7 +1156,6 @@ __device__ inline void bwd_tile(const ViewDesc &v, TileXY tile, BwdStage<M, NB> 
                     *q = 0.f;
                 }
             }
-            if (k == kDetTile) sum = __uint_as_float(tile_id);
             if (p < v.det_pairs) v.det_partial[p * kDetStride + k] = sum;
         }
         __builtin_amdgcn_wave_barrier();
@@ -1453,12 +1450,16 @@ void k_blend_bwd_det(ViewDesc v) {
     bwd_tile<M, kDetBatch, false, true, true>(v, tile, S, nullptr, s_maxlast, nullptr, &s_det);
 }
 
+// Gaussians with more than kDetWaveRows rows are listed (word 0: how many) for blocks of their own
+// (2000 of some 400 rows each at 4K: the gather 162 us with them a wavefront's, 84 with a block each).
+constexpr uint32_t kDetWaveRows = 256;
 // No rows yet: counts per Gaussian, numbers per list position.
 __global__ __launch_bounds__(256) void k_det_init(uint32_t *rows, int64_t n, uint32_t *seq,
-                                                  int64_t pairs) {
+                                                  int64_t pairs, uint32_t *large) {
     const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
     if (i < n) rows[i] = 0u;
     if (i < pairs) seq[i] = ~0u;
+    if (i == 0) large[0] = 0u;
 }
 
 // The positions with a row, by Gaussian (first: the scanned counts). Against a stable sort of all
@@ -1467,57 +1468,87 @@ __global__ __launch_bounds__(256) void k_det_init(uint32_t *rows, int64_t n, uin
 // (Ranges that overlap could count more rows than there are positions: those are left out.)
 __global__ __launch_bounds__(256) void k_det_place(const uint32_t *plist, const uint32_t *seq,
                                                    int64_t pairs, const uint32_t *first, int64_t n,
-                                                   uint32_t *list) {
+                                                   uint32_t *list, uint32_t *large) {
     const int64_t i0 = int64_t(blockIdx.x) * 1024 + threadIdx.x;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int64_t i = i0 + 256 * k;
-        if (i >= pairs || seq[i] == ~0u || plist[i] >= uint64_t(n)) continue;
-        const uint64_t at = uint64_t(first[plist[i]]) + seq[i];
+        if (i >= pairs) continue;
+        const uint32_t nth = seq[i], g = plist[i];
+        if (nth == ~0u || g >= uint64_t(n)) continue;
+        const uint64_t at = uint64_t(first[g]) + nth;
         if (at < uint64_t(pairs)) list[at] = uint32_t(i);
+        if (nth == kDetWaveRows) {               // one of each such Gaussian's
+            const uint32_t o = atomicAdd(large, 1u);
+            if (o < uint64_t(pairs) / kDetWaveRows) large[1 + o] = g;
+        }
     }
 }
 
-// More rows than lanes: list[0, m) in increasing order, into order, by counting them per tile (a Gaussian
-// has one position in a tile's list; positions increase with the tile), kDetTiles tiles at a time.
-// Should a list name a Gaussian several times, its positions in one tile are put in order by
-// exchanging neighbours.
-constexpr int kDetTiles = 1024;
-__device__ inline void det_order(const float *rows, const uint32_t *list, uint32_t m, int64_t pairs,
-                                 uint32_t *order, uint32_t *cnt, int lane) {
-    const auto tile = [&](uint32_t j) {
-        const uint32_t p = list[j];
-        return p < uint64_t(pairs) ? __float_as_uint(rows[int64_t(p) * kDetStride + kDetTile]) : 0u;
+// More than kDetWaveRows rows: list[0, m) in increasing order, by a stable radix sort between `list` and
+// `other` of the block's four wavefronts, kDetBits of the positions' range a pass; returns which of the
+// two holds it. A wavefront counts and places a quarter of the list, 64 at a time, so that the steps
+// grow with m alone. (One wavefront that counted the rows per tile, 1024 tiles at a time, read the
+// list and the rows again for every 1024 tiles: the gather of 16 Gaussians that are on each of the
+// 32400 tiles of a 4K frame took 84.1 ms, now 0.29; of 8 with 600 px at 1080p 2.54 ms, now 0.08.)
+constexpr int kDetBits = 9, kDetRadix = 1 << kDetBits;
+__device__ inline const uint32_t *det_order(uint32_t *list, uint32_t *other, uint32_t m,
+                                            uint32_t (*cnt)[kDetRadix], uint32_t *s_red, int w, int lane) {
+    constexpr int kWaves = 4, kAhead = 4, kOwn = kDetRadix / (64 * kWaves);
+    const uint32_t seg = (m + 64 * kWaves - 1) / (64 * kWaves) * 64;
+    const uint32_t j0 = uint32_t(w) * seg, j1 = j0 + seg < m ? j0 + seg : m;
+    // f(key, whether there is one) for this wavefront's part, in order, kAhead loads at a time
+    const auto each = [&](const uint32_t *from, auto f) {
+        for (uint32_t j = j0; j < j1; j += 64 * kAhead) {                     // uniform
+            uint32_t k[kAhead];
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) {
+                const uint32_t i = j + 64 * q + lane;
+                k[q] = from[i < j1 ? i : j1 - 1];
+            }
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) f(k[q], j + 64 * q + lane < j1);
+        }
     };
     uint32_t lo = ~0u, hi = 0u;
-    for (uint32_t j = lane; j < m; j += 64) {
-        const uint32_t t = tile(j);
-        lo = t < lo ? t : lo;
-        hi = t > hi ? t : hi;
-    }
+    each(list, [&](uint32_t k, bool) {
+        lo = k < lo ? k : lo;
+        hi = k > hi ? k : hi;
+    });
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
         const uint32_t a = __shfl_xor(lo, o, 64), b = __shfl_xor(hi, o, 64);
         lo = a < lo ? a : lo;
         hi = b > hi ? b : hi;
     }
-    uint32_t done = 0;
-    bool several = false;
-    for (uint64_t w0 = lo; w0 <= hi && done < m; w0 += kDetTiles) {            // uniform
-        constexpr int kOwn = kDetTiles / 64;
-        for (int k = 0; k < kOwn; ++k) cnt[k * 64 + lane] = 0u;
-        __builtin_amdgcn_wave_barrier();
-        for (uint32_t j = lane; j < m; j += 64) {
-            const uint64_t t = tile(j) - w0;
-            if (t < kDetTiles) atomicAdd(cnt + t, 1u);
-        }
-        __builtin_amdgcn_wave_barrier();
-        uint32_t sum = 0, c[kOwn];
+    if (lane == 0) {
+        s_red[w] = lo;
+        s_red[kWaves + w] = hi;
+    }
+    __syncthreads();
 #pragma unroll
-        for (int k = 0; k < kOwn; ++k) {
-            c[k] = cnt[lane * kOwn + k];
-            several = several || c[k] > 1u;
-            sum += c[k];
+    for (int i = 0; i < kWaves; ++i) {
+        lo = s_red[i] < lo ? s_red[i] : lo;
+        hi = s_red[kWaves + i] > hi ? s_red[kWaves + i] : hi;
+    }
+    __syncthreads();
+    lo = uint32_t(__builtin_amdgcn_readfirstlane(int(lo)));
+    hi = uint32_t(__builtin_amdgcn_readfirstlane(int(hi)));
+    const int t = 64 * w + lane;
+    for (int shift = 0; shift < 32 && ((hi - lo) >> shift) != 0u; shift += kDetBits) {     // uniform
+        const auto digit = [&](uint32_t k) { return ((k - lo) >> shift) & uint32_t(kDetRadix - 1); };
+        for (int d = lane; d < kDetRadix; d += 64) cnt[w][d] = 0u;
+        __builtin_amdgcn_wave_barrier();
+        each(list, [&](uint32_t k, bool valid) {
+            if (valid) atomicAdd(&cnt[w][digit(k)], 1u);
+        });
+        __syncthreads();
+        // where each wavefront's positions of a digit start: digits before, then wavefronts before
+        uint32_t sum = 0;
+#pragma unroll
+        for (int q = 0; q < kOwn; ++q) {
+#pragma unroll
+            for (int i = 0; i < kWaves; ++i) sum += cnt[i][t * kOwn + q];
         }
         uint32_t x = sum;
 #pragma unroll
@@ -1525,39 +1556,76 @@ __device__ inline void det_order(const float *rows, const uint32_t *list, uint32
             const uint32_t y = __shfl_up(x, o, 64);
             if (lane >= o) x += y;
         }
-        uint32_t run = done + x - sum;
+        uint32_t run = x - sum;
+        if (lane == 63) s_red[w] = x;
+        __syncthreads();
 #pragma unroll
-        for (int k = 0; k < kOwn; ++k) {
-            cnt[lane * kOwn + k] = run;
-            run += c[k];
-        }
-        __builtin_amdgcn_wave_barrier();
-        for (uint32_t j = lane; j < m; j += 64) {
-            const uint64_t t = tile(j) - w0;
-            if (t < kDetTiles) order[atomicAdd(cnt + t, 1u)] = list[j];
-        }
-        __builtin_amdgcn_wave_barrier();
-        done += __shfl(x, 63, 64);
-    }
-    __threadfence_block();
-    if (__ballot(several) == 0ull) return;
-    bool again = true;
-    for (uint32_t pass = 0; again && pass <= m; ++pass) {                      // uniform
-        again = false;
-        for (uint32_t odd = 0; odd < 2; ++odd) {
-            bool swapped = false;
-            for (uint32_t j = 2 * lane + odd; j + 1 < m; j += 128) {
-                const uint32_t a = order[j], b = order[j + 1];
-                if (a > b) {
-                    order[j] = b;
-                    order[j + 1] = a;
-                    swapped = true;
-                }
+        for (int i = 0; i < kWaves; ++i) run += i < w ? s_red[i] : 0u;
+#pragma unroll
+        for (int q = 0; q < kOwn; ++q) {
+#pragma unroll
+            for (int i = 0; i < kWaves; ++i) {
+                const uint32_t c = cnt[i][t * kOwn + q];
+                cnt[i][t * kOwn + q] = run;
+                run += c;
             }
-            again = again || __ballot(swapped) != 0ull;
-            __threadfence_block();
+        }
+        __syncthreads();
+        each(list, [&](uint32_t k, bool valid) {
+            const uint32_t d = digit(k);
+            unsigned long long same = __builtin_amdgcn_ballot_w64(valid);      // lanes with this digit
+#pragma unroll
+            for (int b = 0; b < kDetBits; ++b) {
+                const bool set = ((d >> b) & 1u) != 0u;
+                const unsigned long long vote = __builtin_amdgcn_ballot_w64(set);
+                same &= set ? vote : ~vote;
+            }
+            const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
+                uint32_t(same >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(same), 0u));
+            if (valid) {
+                const uint32_t at = cnt[w][d];
+                if (rank == 0u) cnt[w][d] = at + uint32_t(__popcll(same));
+                other[at + rank] = k;
+            }
+        });
+        __syncthreads();
+        uint32_t *swap = list;
+        list = other;
+        other = swap;
+    }
+    return list;
+}
+
+// list[0, m), 64 < m <= kDetWaveRows, into increasing order in s_key, by one wavefront that counts the
+// positions before each.
+__device__ inline void det_order_wave(const uint32_t *list, uint32_t m, uint32_t *s_key, int lane) {
+    constexpr int kOwn = int(kDetWaveRows) / 64;
+    uint32_t key[kOwn], at[kOwn];
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+        if (uint32_t(64 * q) >= m) break;                    // uniform
+        const uint32_t i = 64 * q + lane;
+        key[q] = i < m ? list[i] : ~0u;
+        at[q] = 0u;
+        s_key[i] = key[q];
+    }
+    __builtin_amdgcn_wave_barrier();
+    for (uint32_t j = 0; j < m; j += 4) {
+        const uint4 k = *reinterpret_cast<const uint4 *>(s_key + j);
+#pragma unroll
+        for (int q = 0; q < kOwn; ++q) {
+            if (uint32_t(64 * q) >= m) break;
+            at[q] += (k.x < key[q] ? 1u : 0u) + (k.y < key[q] ? 1u : 0u) + (k.z < key[q] ? 1u : 0u) +
+                     (k.w < key[q] ? 1u : 0u);
         }
     }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+        if (uint32_t(64 * q) >= m) break;
+        if (uint32_t(64 * q) + lane < m) s_key[at[q]] = key[q];
+    }
+    __builtin_amdgcn_wave_barrier();
 }
 
 // The gradients of Gaussian g from its nine sums, as k_bwd_finish forms them.
@@ -1595,21 +1663,25 @@ __device__ inline uint32_t row_rank(uint32_t key) {
 // ranked within the 16 lanes, lane j adds the row of rank j. Those with more take the whole wavefront
 // in turn: lane l adds the rows of rank l, l + 64, ... (A wavefront for each Gaussian took 51 us of
 // 150 k Gaussians, this 27; a thread for each would leave most lanes idle behind the largest footprint.)
-constexpr int kGatherPer = 4;
-__global__ __launch_bounds__(256) void k_det_gather(DetOut out, const float *partial,
+// The listed ones, with more than kDetWaveRows, are the first kDetBlocks blocks' (four per compute unit;
+// they cost nothing measurable where there are none), a block at a time each: thread t adds the rows
+// of rank t, t + 256, ..., the four wavefronts' sums are added in order.
+constexpr int kGatherPer = 4, kDetBlocks = 1024;
+__global__ __launch_bounds__(256, 7) void k_det_gather(DetOut out, const float *partial,
                                                     const uint32_t *first, const uint32_t *rows,
-                                                    const uint32_t *list, uint32_t *order,
-                                                    int64_t pairs, int64_t n) {
-    __shared__ uint32_t s_cnt[4][kDetTiles];
-    const int lane = threadIdx.x & 63, j = lane & 15;
-    const int64_t g0 = ((int64_t(blockIdx.x) * blockDim.x + threadIdx.x) >> 6) * kGatherPer;
-    const int64_t g = g0 + (lane >> 4);
-    uint32_t a = 0u, m = 0u;
-    if (g < n) {
+                                                    uint32_t *list, uint32_t *other,
+                                                    const uint32_t *large, int64_t pairs, int64_t n) {
+    static_assert(kDetWaveRows <= kDetRadix, "a wavefront's positions in its row of counters");
+    __shared__ __align__(16) uint32_t s_cnt[4][kDetRadix];
+    __shared__ uint32_t s_red[8];
+    __shared__ float s_sum[4][kGrad];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, j = lane & 15;
+    // the rows of Gaussian g in the list: from place a, m of them
+    const auto rows_of = [&](int64_t g, uint32_t &a) {
         a = first[g];
         const int64_t room = pairs - int64_t(a), have = rows[g];
-        m = uint32_t(have < room ? have : room > 0 ? room : 0);
-    }
+        return uint32_t(have < room ? have : room > 0 ? room : 0);
+    };
     float sum[kGrad];
     const auto clear = [&] {
 #pragma unroll
@@ -1624,6 +1696,55 @@ __global__ __launch_bounds__(256) void k_det_gather(DetOut out, const float *par
         sum[4] += p1.x; sum[5] += p1.y; sum[6] += p1.z; sum[7] += p1.w;
         sum[8] += p[8];
     };
+    // the wavefront's nine sums, in every lane
+    const auto total = [&](float (&t)[kGrad]) {
+        float ab, c;
+        wave_sum9(sum, lane, ab, c);
+        // lane 16r holds sum {0,2,1,3}[r], lane 16r + 8 sum 4 + {0,2,1,3}[r]; lane 0 of c sum 8
+        const auto from = [](float x, int l) {
+            return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
+        };
+        t[0] = from(ab, 0);  t[2] = from(ab, 16); t[1] = from(ab, 32); t[3] = from(ab, 48);
+        t[4] = from(ab, 8);  t[6] = from(ab, 24); t[5] = from(ab, 40); t[7] = from(ab, 56);
+        t[8] = from(c, 0);
+    };
+    if (blockIdx.x < kDetBlocks) {               // block-uniform
+        const uint64_t room = uint64_t(pairs) / kDetWaveRows, have = large[0];
+        for (uint64_t b = blockIdx.x; b < (have < room ? have : room); b += kDetBlocks) {
+            const uint32_t g = large[1 + b];
+            uint32_t a = 0u;
+            const uint32_t m = g < n ? rows_of(g, a) : 0u;
+            if (m <= kDetWaveRows) continue;     // block-uniform
+            const uint32_t *order = det_order(list + a, other + a, m, s_cnt, s_red, w, lane);
+            clear();
+            for (uint32_t k = threadIdx.x; k < m; k += 4 * 256) {
+                uint32_t p[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) p[q] = k + 256 * q < m ? order[k + 256 * q] : ~0u;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) add(p[q]);       // (~0: no row)
+            }
+            float t[kGrad];
+            total(t);
+            if (lane == 0) {
+#pragma unroll
+                for (int k = 0; k < kGrad; ++k) s_sum[w][k] = t[k];
+            }
+            __syncthreads();
+            if (threadIdx.x == 0) {
+#pragma unroll
+                for (int k = 0; k < kGrad; ++k)
+                    t[k] = ((s_sum[0][k] + s_sum[1][k]) + s_sum[2][k]) + s_sum[3][k];
+                det_store(out, g, t);
+            }
+            __syncthreads();
+        }
+        return;
+    }
+    const int64_t wave = ((int64_t(blockIdx.x) - kDetBlocks) * blockDim.x + threadIdx.x) >> 6;
+    const int64_t g0 = wave * kGatherPer, g = g0 + (lane >> 4);
+    uint32_t a = 0u, m = 0u;
+    if (g < n) m = rows_of(g, a);
     clear();
     const bool mine = m <= 16u && uint32_t(j) < m;
     const uint32_t key = mine ? list[a + uint32_t(j)] : ~0u;
@@ -1643,7 +1764,7 @@ __global__ __launch_bounds__(256) void k_det_gather(DetOut out, const float *par
 #pragma unroll 1
     for (int r = 0; r < kGatherPer; ++r) {
         const uint32_t mr = uint32_t(__builtin_amdgcn_readlane(int(m), 16 * r));
-        if (mr <= 16u) continue;                 // uniform (m is 0 past the last Gaussian)
+        if (mr <= 16u || mr > kDetWaveRows) continue;        // uniform (m is 0 past the last Gaussian)
         const uint32_t ar = uint32_t(__builtin_amdgcn_readlane(int(a), 16 * r));
         clear();
         if (mr <= 64u) {
@@ -1655,19 +1776,12 @@ __global__ __launch_bounds__(256) void k_det_gather(DetOut out, const float *par
             const uint32_t p = uint32_t(__builtin_amdgcn_ds_permute(4 * (has ? at : lane), int(k64)));
             if (has) add(p);
         } else {
-            det_order(partial, list + ar, mr, pairs, order + ar, s_cnt[threadIdx.x >> 6], lane);
-            for (uint32_t k = lane; k < mr; k += 64) add(order[ar + k]);
+            det_order_wave(list + ar, mr, s_cnt[w], lane);
+            for (uint32_t k = lane; k < mr; k += 64) add(s_cnt[w][k]);
+            __builtin_amdgcn_wave_barrier();     // (before the next one's are written there)
         }
-        float ab, c;
-        wave_sum9(sum, lane, ab, c);
-        // lane 16r holds sum {0,2,1,3}[r], lane 16r + 8 sum 4 + {0,2,1,3}[r]; lane 0 of c sum 8
-        const auto from = [](float x, int l) {
-            return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
-        };
         float t[kGrad];
-        t[0] = from(ab, 0);  t[2] = from(ab, 16); t[1] = from(ab, 32); t[3] = from(ab, 48);
-        t[4] = from(ab, 8);  t[6] = from(ab, 24); t[5] = from(ab, 40); t[7] = from(ab, 56);
-        t[8] = from(c, 0);
+        total(t);
         if (lane == 0) det_store(out, g0 + r, t);
     }
 }
@@ -2038,11 +2152,11 @@ gsb_status blend_backward_packed(const ViewDesc &v, gsb_precision prec, hipStrea
 }
 
 // Deterministic-backward workspace: a row per list position, its number among its Gaussian's rows (then,
-// for Gaussians with many, the ordered positions), the positions by Gaussian, per Gaussian its first and
-// its number of rows, the scan's scratch.
+// for Gaussians with many, room to order them), the positions by Gaussian, per Gaussian its first and
+// its number of rows, the scan's scratch, the Gaussians with many rows.
 namespace {
 struct DetLayout {
-    size_t partial, seq, list, first, rows, scratch, end;
+    size_t partial, seq, list, first, rows, scratch, large, end;
 };
 size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
 DetLayout det_layout(int64_t n, int64_t pairs) {
@@ -2055,6 +2169,7 @@ DetLayout det_layout(int64_t n, int64_t pairs) {
     L.first = o;   o += al256(sizeof(uint32_t) * N);
     L.rows = o;    o += al256(sizeof(uint32_t) * N);
     L.scratch = o; o += al256(offsets_scratch_bytes(int64_t(N)));
+    L.large = o;   o += al256(sizeof(uint32_t) * (1 + P / kDetWaveRows));
     L.end = o;
     return L;
 }
@@ -2072,10 +2187,11 @@ gsb_status blend_backward_det(const ViewDesc &v0, gsb_precision prec, int64_t pa
     uint32_t *first = reinterpret_cast<uint32_t *>(w + D.first);
     uint32_t *rows = reinterpret_cast<uint32_t *>(w + D.rows);
     uint32_t *seq = reinterpret_cast<uint32_t *>(w + D.seq), *list = reinterpret_cast<uint32_t *>(w + D.list);
+    uint32_t *large = reinterpret_cast<uint32_t *>(w + D.large);
     v.det_rows = rows;
     v.det_seq = seq;
     const int64_t m = std::max(pairs, v.n);
-    if (m > 0) k_det_init<<<dim3(unsigned((m + 255) / 256)), 256, 0, s>>>(rows, v.n, seq, pairs);
+    if (m > 0) k_det_init<<<dim3(unsigned((m + 255) / 256)), 256, 0, s>>>(rows, v.n, seq, pairs, large);
     const dim3 grid(unsigned(xcd_grid(v.n_tiles)));
     switch (prec) {
         case GSB_FP32_PLAIN: k_blend_bwd_det<Mode::Plain><<<grid, kBlock, 0, s>>>(v); break;
@@ -2086,10 +2202,11 @@ gsb_status blend_backward_det(const ViewDesc &v0, gsb_precision prec, int64_t pa
     if (pairs > 0 && v.n > 0) {
         counts_to_offsets(rows, first, v.n, w + D.scratch, s);
         k_det_place<<<dim3(unsigned((pairs + 1023) / 1024)), 256, 0, s>>>(v.point_list, seq, pairs, first,
-                                                                         v.n, list);
-        k_det_gather<<<dim3(unsigned((v.n + 4 * kGatherPer - 1) / (4 * kGatherPer))), 256, 0, s>>>(
+                                                                         v.n, list, large);
+        const int64_t per = 4 * kGatherPer, blocks = kDetBlocks + (v.n + per - 1) / per;
+        k_det_gather<<<dim3(unsigned(blocks)), 256, 0, s>>>(
             DetOut{v.records, v.dL_dmeans2d, v.dL_dconics, v.dL_dopacity, v.dL_dcolors}, v.det_partial,
-            first, rows, list, seq, pairs, v.n);
+            first, rows, list, seq, large, pairs, v.n);
     } else if (v.n > 0) {
         k_zero_grads<<<dim3(unsigned((v.n + 255) / 256), 1), 256, 0, s>>>(nullptr, v);
     }
