@@ -84,7 +84,7 @@ struct Layout {
     size_t hdr, counts, masks, recs, partials;
     // bin_fill's part
     size_t sorts, dkey_a, dkey_b, dval_a, dval_b, offs, rects, tkey_a, tkey_b, vals_tmp, sortbuf, end;
-    size_t sb_mask, sb_idx, sb_counts, sb_table;   // superblock path, in the places of others
+    size_t sb_mask, sb_idx, sb_counts, sb_groups, sb_table;   // superblock path, in the places of others
 };
 
 int64_t sort_blocks(int64_t m, int items = kSortItems) {
@@ -111,6 +111,9 @@ struct SbTable {
 int64_t sb_max_chunks(int64_t cap) {
     return cap / sb_chunk_size(cap) + (cap < kMaxSb ? cap : kMaxSb);
 }
+// Chunks per group: the tiles' pairs before each group of a superblock's chunks are summed once
+// (k_tile_scan), so that a chunk adds the counts of its own group's chunks alone.
+constexpr int kSbGroup = 64;
 
 Layout layout(int64_t n, int64_t cap) {
     Layout L;
@@ -134,7 +137,7 @@ Layout layout(int64_t n, int64_t cap) {
     // depth sort: look-back words of every pass, [pass][block][digit]; tile sort, afterwards:
     // the per-block digit histograms of one pass, [digit][block]; superblocks, afterwards: the
     // counts [superblock][block] of the entries, then, unless they fit the offsets' place, the
-    // tile counts of every chunk
+    // tile counts of every chunk, and the groups' sums
     const int64_t lb_d = int64_t(kMaxPasses) * sort_blocks(n > 0 ? n : 1);
     const int64_t lb_t = sort_blocks(cap > 0 ? cap : 1);
     const size_t words = sizeof(uint32_t) * kRadix * size_t(lb_d > lb_t ? lb_d : lb_t);
@@ -144,8 +147,11 @@ Layout layout(int64_t n, int64_t cap) {
         chunks = sb_max_chunks(kSbSmallPairs);
     const size_t chunk_counts = sizeof(uint16_t) * kSbTiles * size_t(chunks);
     const bool in_offs = chunk_counts <= sizeof(unsigned long long) * nn;
-    L.sortbuf = o;   o += align256(in_offs || words > chunk_counts ? words : chunk_counts);
+    const size_t before = in_offs ? 0 : align256(chunk_counts);
+    const size_t sums = before + sizeof(uint32_t) * kSbTiles * size_t(chunks / kSbGroup + 1);
+    L.sortbuf = o;   o += align256(words > sums ? words : sums);
     L.sb_counts = in_offs ? L.offs : L.sortbuf;
+    L.sb_groups = L.sortbuf + before;
     // superblock entries: masks in the place of the tile keys, indices in that of the values
     L.sb_mask = L.tkey_a;
     L.sb_idx = L.vals_tmp;
@@ -1838,13 +1844,66 @@ __global__ __launch_bounds__(256) void k_sb_count(const unsigned long long *e_ma
     }
 }
 
-// ranges[tile].y holds the list length: [start, end) in tile order, [0, 0) for an empty list. One
-// block (at most 65536 tiles) that takes 16384 tiles at a time, moved through LDS so that memory is
+// Place of the sum before group j >= 1 of the superblock whose first chunk is `first`: a superblock's
+// places start behind those of the one before, as its chunks do.
+__device__ inline int64_t sb_group_place(uint32_t first, uint32_t j) { return int64_t(first / kSbGroup + j); }
+
+// A superblock of more than kSbGroup chunks: per group j >= 1 and tile the pairs in the groups before
+// it. Two steps: the groups' own sums, a wavefront each, then their running sum.
+__device__ inline void sb_group_sums(const uint16_t *counts, uint32_t first, uint32_t chunks, uint32_t *groups) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint32_t last = (chunks - 1) / kSbGroup;           // the last group
+    for (uint32_t j = w; j < last; j += kScanTopThreads / 64) {
+        const uint16_t *c = counts + (int64_t(first) + int64_t(j) * kSbGroup) * kSbTiles + lane;
+        uint32_t sum = 0;
+#pragma unroll 16
+        for (int k = 0; k < kSbGroup; ++k) sum += c[k * kSbTiles];
+        groups[sb_group_place(first, j + 1) * kSbTiles + lane] = sum;
+    }
+    __syncthreads();
+    if (w != 0) return;
+    uint32_t run = 0;
+    for (uint32_t j = 1; j <= last; j += 8) {
+        uint32_t v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            v[k] = groups[sb_group_place(first, j + k <= last ? j + k : last) * kSbTiles + lane];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            run += v[k];
+            if (j + k <= last) groups[sb_group_place(first, j + k) * kSbTiles + lane] = run;
+        }
+    }
+}
+
+// Block 0: ranges[tile].y holds the list length: [start, end) in tile order, [0, 0) for an empty list.
+// One block (at most 65536 tiles) that takes 16384 tiles at a time, moved through LDS so that memory is
 // read and written in order (each thread reading its own 16 tiles took 35 us at 4K, now 13). Also
 // the header's pair count and the capacity status.
+// The other blocks, kSumBlocks where there are superblocks to look at: the sums of the superblocks b - 1,
+// b - 1 + kSumBlocks, ... with many chunks (few or none: while block 0 scans, on compute units of their own).
+constexpr int kSumBlocks = 64;
 __global__ __launch_bounds__(kScanTopThreads) void k_tile_scan(uint2 *ranges, int32_t n_tiles,
                                                                BinHeader *hdr, int64_t cap,
-                                                               int32_t *status) {
+                                                               int32_t *status, const SbTable *T,
+                                                               const uint16_t *counts, uint32_t *groups) {
+    if (blockIdx.x > 0) {                                    // block-uniform
+        static_assert(kMaxSb <= 64 * kSumBlocks, "a lane for each superblock");
+        const int sb0 = int(blockIdx.x) - 1 + int(threadIdx.x & 63) * kSumBlocks;
+        uint32_t first = 0, chunks = 0;
+        if (sb0 < kMaxSb) {
+            first = T->chunk[sb0];
+            chunks = T->chunk[sb0 + 1] - first;
+        }
+        unsigned long long many = __ballot(chunks > uint32_t(kSbGroup));
+        while (many) {                                       // (the same in every wavefront)
+            const int src = __ffsll((long long)many) - 1;
+            many &= many - 1;
+            sb_group_sums(counts, uint32_t(__builtin_amdgcn_readlane(int(first), src)),
+                          uint32_t(__builtin_amdgcn_readlane(int(chunks), src)), groups);
+        }
+        return;
+    }
     constexpr int kItems = 16, kStep = kScanTopThreads * kItems;
     __shared__ uint32_t s_v[kStep + kStep / kItems];         // a word of padding per thread's items
     __shared__ uint32_t s_wave[kScanTopThreads / 64];
@@ -1897,13 +1956,14 @@ __global__ __launch_bounds__(kScanTopThreads) void k_tile_scan(uint2 *ranges, in
 // uneven steps before, and not tile by tile, where each step waits for the last: 109 us at 4K, now
 // 79). A chunk's pairs go
 // through LDS at once when they fit kSbStage, else in halves, quarters or two groups of 64 entries
-// (at most kSbStage pairs) at a time.
+// (at most kSbStage pairs) at a time. (Six wavefronts per SIMD: left alone, a few registers more make it
+// five and the lists of 1 M Gaussians at 1080p 27 us, not 21.7.)
 template <int kSbChunk>
-__global__ __launch_bounds__(256) void k_sb_write(const uint32_t *e_idx,
+__global__ __launch_bounds__(256, 6) void k_sb_write(const uint32_t *e_idx,
                                                   const unsigned long long *e_mask,
                                                   const SbTable *T, SbGrid G,
-                                                  const uint16_t *counts, const uint2 *ranges,
-                                                  uint32_t *point_list) {
+                                                  const uint16_t *counts, const uint32_t *groups,
+                                                  const uint2 *ranges, uint32_t *point_list) {
     constexpr int kSbGroups = kSbChunk / 64;
     __shared__ uint32_t s_idx[kSbChunk];
     __shared__ uint16_t s_cnt[kSbGroups][kSbTiles];
@@ -1924,9 +1984,16 @@ __global__ __launch_bounds__(256) void k_sb_write(const uint32_t *e_idx,
             hit[g] = transpose64(e < C.hi ? e_mask[e] : 0ull, lane);
             s_cnt[gr][lane] = uint16_t(__popcll(hit[g]));
         }
-        // the tile's entries in the superblock's earlier chunks
+        // the tile's entries in the superblock's earlier chunks: the groups before the chunk's own, and
+        // the chunks of that. (All earlier chunks one by one: 3 M Gaussians on 128 x 128 px, 2930
+        // chunks, took 193 us, now 59; 10 M 1581, now 152.)
+        const uint32_t group = (c - C.first) / kSbGroup;
         uint32_t before = 0;
-        for (uint32_t r = C.first + w; r < c; r += 4) before += counts[int64_t(r) * kSbTiles + lane];
+        if (w == 0 && group > 0)
+            before = groups[sb_group_place(C.first, group) * kSbTiles + lane];
+#pragma unroll 2
+        for (uint32_t r = C.first + group * kSbGroup + w; r < c; r += 4)
+            before += counts[int64_t(r) * kSbTiles + lane];
         s_pre[w][lane] = before;
         __syncthreads();
         const int32_t tile = sb_tile(G, C.sb, lane);
@@ -2288,6 +2355,7 @@ gsb_status bin_fill_sorted(const float *means2d, const float *conics, const floa
         auto *e_mask = at<unsigned long long>(ws, L.sb_mask);
         auto *e_idx = at<uint32_t>(ws, L.sb_idx);
         auto *counts16 = at<uint16_t>(ws, L.sb_counts);
+        auto *groups = at<uint32_t>(ws, L.sb_groups);
         auto *table = at<SbTable>(ws, L.sb_table);
         const int bits = G.n > 1 ? ceil_log2(G.n) : 0;
         const int chunk = sb_chunk_size(cap);
@@ -2332,15 +2400,16 @@ gsb_status bin_fill_sorted(const float *means2d, const float *conics, const floa
         const auto count = chunk == kSbChunkSmall ? k_sb_count<kSbChunkSmall> : k_sb_count<kSbChunkLarge>;
         const auto write = chunk == kSbChunkSmall ? k_sb_write<kSbChunkSmall> : k_sb_write<kSbChunkLarge>;
         count<<<gc, 256, 0, s>>>(e_mask, table, G, counts16, ranges);
-        k_tile_scan<<<1, kScanTopThreads, 0, s>>>(reinterpret_cast<uint2 *>(ranges),
-                                                  int32_t(n_tiles), hdr, cap, status_dev);
-        write<<<gc, 256, 0, s>>>(e_idx, e_mask, table, G, counts16,
+        k_tile_scan<<<1 + kSumBlocks, kScanTopThreads, 0, s>>>(
+            reinterpret_cast<uint2 *>(ranges), int32_t(n_tiles), hdr, cap, status_dev, table, counts16,
+            groups);
+        write<<<gc, 256, 0, s>>>(e_idx, e_mask, table, G, counts16, groups,
                                  reinterpret_cast<const uint2 *>(ranges), point_list);
         return check_launch("bin_fill");
     }
     if (by_superblock(G)) {       // no Gaussians, or no room for a pair
         k_tile_scan<<<1, kScanTopThreads, 0, s>>>(reinterpret_cast<uint2 *>(ranges), 0, hdr, cap,
-                                                  status_dev);
+                                                  status_dev, nullptr, nullptr, nullptr);
         return check_launch("bin_fill");
     }
     const uint32_t *sorted_idx = dva;
