@@ -341,7 +341,8 @@ typedef struct gsb_view {
 
 /* Launch shape. Zero fields take the defaults in parentheses. */
 #define GSB_LAUNCH_PERSISTENT 0   /* resident blocks pull items from the per-XCD queues */
-#define GSB_LAUNCH_GRID 1         /* one block per item: block b takes item b/8 of queue b%8 */
+#define GSB_LAUNCH_GRID 1         /* one block per item: block b takes item b/8 of queue b%8 (more items
+                                   * than one launch holds, 2^24 - 1: as GSB_LAUNCH_PERSISTENT) */
 /* How the backward sums each Gaussian's per-pixel gradient terms over a wavefront's 64 pixels:
  * GSB_REDUCE_VALU: all nine sums by cross-lane adds on the vector ALUs (default);
  * GSB_REDUCE_MFMA: the five geometric sums (of dL/dpower times dx^2, dx dy, dy^2, dx, dy) as a

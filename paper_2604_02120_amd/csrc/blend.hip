@@ -2260,6 +2260,8 @@ gsb_status plan_create(const ViewDesc *views, int n_views, gsb_precision prec, c
         prefix[size_t(x) * (n_views + 1) + n_views] = run;
         p->grid_items = std::max(p->grid_items, run * kXcds);
     }
+    // one launch holds 2^32 - 1 threads; past that its grid would be cut short without an error
+    if (p->grid_items > int64_t(0xffffffffu) / kBlock) p->tune.launch = kLaunchPersistent;
     if (e == hipSuccess) e = hipMalloc(&p->d_views, sizeof(ViewDesc) * size_t(n_views));
     if (e == hipSuccess) e = hipMalloc(&p->d_prefix, sizeof(int64_t) * prefix.size());
     if (e == hipSuccess) e = hipMalloc(&p->d_counters, sizeof(unsigned int) * 2 * kXcds);
