@@ -339,7 +339,8 @@ typedef struct gsb_view {
     float *dL_dmeans2d, *dL_dconics, *dL_dopacity, *dL_dcolors;   /* backward outputs */
 } gsb_view;
 
-/* Launch shape. Zero fields take the defaults in parentheses. */
+/* Launch shape. Zero fields take the defaults in parentheses; a launch of 0 is GSB_LAUNCH_PERSISTENT, also
+ * in a zeroed struct (only without a tuning does the library choose it). */
 #define GSB_LAUNCH_PERSISTENT 0   /* resident blocks pull items from the per-XCD queues */
 #define GSB_LAUNCH_GRID 1         /* one block per item: block b takes item b/8 of queue b%8 (more items
                                    * than one launch holds, 2^24 - 1: as GSB_LAUNCH_PERSISTENT) */
@@ -355,7 +356,7 @@ typedef struct gsb_tuning {
     int32_t batch_fwd;       /* list entries per LDS batch, forward: 64, 128, 256 (256) */
     int32_t batch_bwd;       /* same, backward (256); short lists are taken in smaller batches */
     int32_t blocks_per_cu;   /* persistent: resident blocks per compute unit; 0 = as many as fit */
-    int32_t launch;          /* GSB_LAUNCH_PERSISTENT (default) or GSB_LAUNCH_GRID */
+    int32_t launch;          /* GSB_LAUNCH_PERSISTENT or GSB_LAUNCH_GRID */
     int32_t bwd_reduce;      /* GSB_REDUCE_VALU (default) or GSB_REDUCE_MFMA */
 } gsb_tuning;
 

@@ -67,7 +67,7 @@ class GsbView(ctypes.Structure):
 
 
 class GsbTuning(ctypes.Structure):
-    """struct gsb_tuning (zero fields take the library defaults)."""
+    """struct gsb_tuning (zero fields take the library defaults, a launch of 0 is the persistent one)."""
     _fields_ = [("batch_fwd", ctypes.c_int32), ("batch_bwd", ctypes.c_int32),
                 ("blocks_per_cu", ctypes.c_int32), ("launch", ctypes.c_int32),
                 ("bwd_reduce", ctypes.c_int32)]

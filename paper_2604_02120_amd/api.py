@@ -336,14 +336,14 @@ def blend_backward_deterministic(records, ranges, point_list, W: int, H: int, fi
 
 
 class BatchedViews:
-    """Many views blended by one persistent launch per direction (gsb_plan_*).
+    """Many views blended by one launch per direction (gsb_plan_*).
 
     ``scenes``: list of dicts of contiguous device tensors (means2d, conics, opacity, colors,
     depths, radii) plus ``width``/``height``. Each view's binning buffers are sized once, eagerly,
     from its exact pair count (times ``capacity_slack``), so that ``bin()``, ``forward()`` and
     ``backward()`` afterwards enqueue kernels only: the whole step can be captured in a hipGraph.
     ``tuning``: None (library defaults), a dict (batch_fwd, batch_bwd, blocks_per_cu, launch,
-    bwd_reduce) or "auto" (``autotune.tune``). ``dL_dimage[v]`` is allocated here (zeros) for the caller to fill.
+    bwd_reduce; what it leaves out is as with None) or "auto" (``autotune.tune``). ``dL_dimage[v]`` is allocated here (zeros) for the caller to fill.
     """
 
     def __init__(self, scenes, prec="fp16", tuning=None, bg=(0.0, 0.0, 0.0),
@@ -405,8 +405,12 @@ class BatchedViews:
             self.plan = None
         t = None
         if tuning:
+            # a launch left out is as without a tuning (in the struct 0 is the persistent one), unless the
+            # dict names the persistent launch's blocks
+            launch = tuning.get("launch", _lib.GSB_LAUNCH_PERSISTENT if tuning.get("blocks_per_cu")
+                                else _lib.GSB_LAUNCH_GRID)
             t = _lib.GsbTuning(int(tuning.get("batch_fwd", 0)), int(tuning.get("batch_bwd", 0)),
-                               int(tuning.get("blocks_per_cu", 0)), int(tuning.get("launch", 0)),
+                               int(tuning.get("blocks_per_cu", 0)), int(launch),
                                int(tuning.get("bwd_reduce", 0)))
         self.plan = _lib.gsb_plan_create(self._gsb_views(), self.prec, t)
 
