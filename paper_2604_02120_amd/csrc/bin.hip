@@ -828,11 +828,6 @@ constexpr uint32_t kSpinLimit = 1u << 22;
 constexpr int kLookback = 16;           // preceding tiles read per look-back step
 constexpr int kHistBlocks = 256;        // histogram kernel: at most this many blocks
 
-__global__ void k_zero_u32(uint32_t *p, int64_t m) {
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < m) p[i] = 0u;
-}
-
 // The keys are made here from the depths (and written with the identity values).
 template <int kItems>
 __global__ __launch_bounds__(kSortThreads) void k_sort_hist(const float *depths, uint32_t *keys_io,
