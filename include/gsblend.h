@@ -59,6 +59,8 @@ typedef int32_t gsb_precision;
  * pixel, the per-pixel loop of Alg. 1 as written. */
 #define GSB_FULL_SCAN 0x100
 
+/* (8 also names libraries without gsb_bin_sort and gsb_bin_fill_sorted, which were added within it: a caller
+ * that may meet one looks the names up.) */
 #define GSB_ABI_VERSION 8
 
 /* Version of this interface (GSB_ABI_VERSION of the library that was loaded). */
@@ -148,8 +150,9 @@ typedef int32_t gsb_bin_mode;
 #define GSB_BIN_RECT 0
 #define GSB_BIN_VISIBLE 1
 
-/* Counts the pairs each Gaussian emits (kept in `ws`) and writes the total to the device int64
- * *n_pairs_dev. Asynchronous on `stream`.
+/* Counts the pairs each Gaussian emits (kept in `ws`) and writes the total to the int64 *n_pairs_dev, which
+ * the GPU must be able to write: device memory, or pinned host memory (read it once an event recorded
+ * behind this call is done). Asynchronous on `stream`.
  * conics, opacity: device f32[n][3], f32[n], read in GSB_BIN_VISIBLE only (may be NULL in
  *            GSB_BIN_RECT). gsb_bin_fill must then be called with the same mode and arrays.
  * ws: device workspace of ws_bytes >= gsb_bin_workspace_bytes(n, 0, W, H) bytes.
@@ -183,7 +186,9 @@ gsb_status gsb_bin_fill(const float *means2d, const int32_t *radii, const float 
  * ranges, a clean status word), then gsb_bin_fill_sorted on the same stream with the same arguments.
  * A host that reads *n_pairs to size the list calls gsb_bin_sort before it waits, so that the GPU
  * sorts meanwhile. Here ws_bytes must be >= gsb_bin_workspace_bytes(n, 0, W, H); the workspace of the
- * second call may be another one whose leading so many bytes are a copy, as for gsb_bin_fill. */
+ * second call may be another one whose leading so many bytes are a copy, as for gsb_bin_fill. Each
+ * gsb_bin_sort is followed by one gsb_bin_fill_sorted, also after GSB_ERR_CAPACITY: what the sort left
+ * (the empty ranges among it) is used up. */
 gsb_status gsb_bin_sort(const float *means2d, const int32_t *radii, const float *conics,
                         const float *opacity, gsb_bin_mode mode, const float *depths, int64_t n,
                         int32_t W, int32_t H, void *ws, size_t ws_bytes, uint32_t *ranges,

@@ -152,8 +152,9 @@ def bin_tiles(means2d, radii, depths, W: int, H: int, stream=None, conics=None, 
     """Count, then fill with an exactly sized list. Returns (point_list i32[P], ranges
     i32[gx*gy][2]). Waits once for the pair count, while the GPU sorts the Gaussians. ``stream``: as
     for every call here, the caller orders it after what writes the inputs and before what reads the
-    results. (The first workspace holds _GUESS pairs per Gaussian: 264 bytes per Gaussian, at most 805
-    MB for the pairs; a frame with more pairs holds it and the exact one until the copy is enqueued.)"""
+    results. (The first workspace holds _GUESS pairs per Gaussian: 260 bytes each, 195 of them, at most
+    818 MB in all, for the pairs; a frame with more pairs holds it and the exact one until the copy is
+    enqueued.)"""
     n = radii.shape[0]
     dev = means2d.device
     _req(means2d, torch.float32, "means2d")

@@ -624,7 +624,10 @@ __device__ inline void fwd_tile(const ViewDesc &v, TileXY tile, FwdStage<M, NB> 
             for (FwdStage<M, NB> &S : stages) S.zero = Op<M>::cvt(z);
         }
     }
-    const uint2 rg = reinterpret_cast<const uint2 *>(v.ranges)[tile.y * v.gx + tile.x];
+    uint2 rg = reinterpret_cast<const uint2 *>(v.ranges)[tile.y * v.gx + tile.x];
+    // (the same in every lane, which the compiler does not see in a plan's kernels: their loops over batches
+    // and groups ran on vector registers, 1 M Gaussians at 1080p in batches of 128 196 us, now 185)
+    rg = make_uint2(uniform(rg.x), uniform(rg.y));
     // without Gaussians every list entry would be invalid: the tile shows the background
     const int64_t start = rg.x, len = n == 0 ? 0 : int64_t(rg.y) - int64_t(rg.x);
     const int nb = int((len + NB - 1) / NB);
@@ -1456,8 +1459,9 @@ void k_blend_bwd_rec(ViewDesc v) {
     bwd_tile<M, kDefaultBatchBwd, false, true>(v, tile, S, &s_acc, s_maxlast, nullptr);
 }
 
-// Deterministic backward, one tile per block: LDS batches of 64 (the four wavefront slices of the
-// batch sums take four times the LDS of the shared accumulator), records as attributes.
+// Deterministic backward, one tile per block: LDS for batches of 128 (the four wavefront slices of the
+// batch sums take four times the LDS of the shared accumulator), lists of up to 256 entries in batches
+// of 64 (batch_bwd); records as attributes.
 constexpr int kDetBatch = 128;
 template <Mode M> constexpr size_t lds_bwd_det() {
     return sizeof(BwdStage<M, kDetBatch>) + sizeof(BwdAccDet<kDetBatch>) + 64;
@@ -1902,10 +1906,10 @@ __device__ inline bool next_item(const Queues &Q, int &q, int &tried, int &view,
 template <Mode M> constexpr int waves_fwd() { return M == Mode::Plain ? 8 : 7; }
 template <Mode M> constexpr int waves_bwd() { return M == Mode::Plain ? 6 : 5; }
 
-template <Mode M, int NB>
+template <Mode M, int NB, bool kAll = false>
 __global__ __launch_bounds__(kBlock, fit_waves(waves_fwd<M>(), lds_fwd<M, NB>()))
 void k_blend_fwd_batched(Queues Q) {
-    __shared__ FwdStage<M, NB> S[1];
+    __shared__ FwdStage<M, NB> S[kFwdBuffers<kAll>];
     __shared__ int s_view;
     __shared__ uint32_t s_rank;
     int q = int(blockIdx.x % kXcds), tried = 0;
@@ -1925,7 +1929,7 @@ void k_blend_fwd_batched(Queues Q) {
         __syncthreads();
         if (view < 0) break;
         const ViewDesc vd = load_view(Q, view);
-        fwd_tile<M, NB>(vd, view_tile(vd, rank), S, loop_tid());
+        fwd_tile<M, NB, false, false, kAll>(vd, view_tile(vd, rank), S, loop_tid());
         __syncthreads();
     }
 }
@@ -1979,15 +1983,15 @@ __device__ inline bool grid_item(const Queues &Q, int64_t b, int &view, uint32_t
     return true;
 }
 
-template <Mode M, int NB>
+template <Mode M, int NB, bool kAll = false>
 __global__ __launch_bounds__(kBlock, fit_waves(M == Mode::Plain ? 8 : 7, lds_fwd<M, NB>()))
 void k_blend_fwd_grid(Queues Q) {
-    __shared__ FwdStage<M, NB> S[1];
+    __shared__ FwdStage<M, NB> S[kFwdBuffers<kAll>];
     int view;
     uint32_t rank;
     if (!grid_item(Q, blockIdx.x, view, rank)) return;
     const ViewDesc vd = load_view(Q, view);
-    fwd_tile<M, NB>(vd, view_tile(vd, rank), S);
+    fwd_tile<M, NB, false, false, kAll>(vd, view_tile(vd, rank), S);
 }
 
 template <Mode M, int NB, bool kMM>
@@ -2072,8 +2076,11 @@ void launch_bwd_single(const ViewDesc &v, int nb, bool mm, hipStream_t s) {
     else launch_bwd_single<M, false>(v, nb, s);
 }
 
+// `all`: the plan's views are scanned in full (GSB_FULL_SCAN), in batches of at most kAllBatchFwd.
 template <Mode M>
-const void *fwd_batched_fn(int nb) {
+const void *fwd_batched_fn(int nb, bool all) {
+    if (all && nb == 64) return reinterpret_cast<const void *>(&k_blend_fwd_batched<M, 64, true>);
+    if (all) return reinterpret_cast<const void *>(&k_blend_fwd_batched<M, kAllBatchFwd, true>);
     if (nb == 64) return reinterpret_cast<const void *>(&k_blend_fwd_batched<M, 64>);
     if (nb == 128) return reinterpret_cast<const void *>(&k_blend_fwd_batched<M, 128>);
     return reinterpret_cast<const void *>(&k_blend_fwd_batched<M, 256>);
@@ -2088,11 +2095,11 @@ template <Mode M>
 const void *bwd_batched_fn(int nb, bool mm) {
     return mm ? bwd_batched_fn<M, true>(nb) : bwd_batched_fn<M, false>(nb);
 }
-const void *batched_fn(gsb_precision prec, bool fwd, int nb, bool mm) {
+const void *batched_fn(gsb_precision prec, bool fwd, int nb, bool mm, bool all) {
     switch (prec) {
-        case GSB_FP32_PLAIN: return fwd ? fwd_batched_fn<Mode::Plain>(nb) : bwd_batched_fn<Mode::Plain>(nb, mm);
-        case GSB_FP16_GEMM: return fwd ? fwd_batched_fn<Mode::F16>(nb) : bwd_batched_fn<Mode::F16>(nb, mm);
-        default: return fwd ? fwd_batched_fn<Mode::BF16>(nb) : bwd_batched_fn<Mode::BF16>(nb, mm);
+        case GSB_FP32_PLAIN: return fwd ? fwd_batched_fn<Mode::Plain>(nb, all) : bwd_batched_fn<Mode::Plain>(nb, mm);
+        case GSB_FP16_GEMM: return fwd ? fwd_batched_fn<Mode::F16>(nb, all) : bwd_batched_fn<Mode::F16>(nb, mm);
+        default: return fwd ? fwd_batched_fn<Mode::BF16>(nb, all) : bwd_batched_fn<Mode::BF16>(nb, mm);
     }
 }
 
@@ -2248,6 +2255,7 @@ struct Plan {
     gsb_precision prec = GSB_FP16_GEMM;
     Tuning tune{};
     int64_t max_n = 0;
+    bool all = false;               // every entry is staged (the views' reach is 0)
     ViewDesc *d_views = nullptr;    // device copy, plan order
     int64_t *d_prefix = nullptr;    // [8][n_views + 1]
     unsigned int *d_counters = nullptr;   // [16]: forward queues, backward queues
@@ -2277,6 +2285,7 @@ gsb_status plan_create(const ViewDesc *views, int n_views, gsb_precision prec, c
         ordered[i] = views[order[i]];
         p->max_n = std::max(p->max_n, ordered[i].n);
     }
+    p->all = n_views > 0 && ordered[0].reach == 0;           // (the precision's flag: the same for all)
     std::vector<int64_t> prefix(size_t(kXcds) * (n_views + 1), 0);
     for (int x = 0; x < kXcds; ++x) {
         int64_t run = 0;
@@ -2297,8 +2306,8 @@ gsb_status plan_create(const ViewDesc *views, int n_views, gsb_precision prec, c
     if (e == hipSuccess) e = hipMemcpy(p->d_prefix, prefix.data(), sizeof(int64_t) * prefix.size(), hipMemcpyHostToDevice);
     int cus = 0, occ_f = 0, occ_b = 0;
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device);
-    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_f, batched_fn(prec, true, t.batch_fwd, false), kBlock, 0);
-    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_b, batched_fn(prec, false, t.batch_bwd, t.bwd_mm != 0), kBlock, 0);
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_f, batched_fn(prec, true, t.batch_fwd, false, p->all), kBlock, 0);
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_b, batched_fn(prec, false, t.batch_bwd, t.bwd_mm != 0, p->all), kBlock, 0);
     if (e != hipSuccess) {
         (void)plan_destroy(p);      // the creation error is the one reported
         return fail(GSB_ERR_HIP, "plan_create: %s", hipGetErrorString(e));
@@ -2331,13 +2340,18 @@ template <Mode M>
 void launch_fwd_batched(const Queues &Q, int nb, const Plan &p, hipStream_t s) {
     if (p.tune.launch == kLaunchGrid) {
         const dim3 g(unsigned(p.grid_items));
-        if (nb == 64) k_blend_fwd_grid<M, 64><<<g, kBlock, 0, s>>>(Q);
+        if (p.all)
+            (nb == 64 ? k_blend_fwd_grid<M, 64, true> : k_blend_fwd_grid<M, kAllBatchFwd, true>)<<<g, kBlock, 0, s>>>(Q);
+        else if (nb == 64) k_blend_fwd_grid<M, 64><<<g, kBlock, 0, s>>>(Q);
         else if (nb == 128) k_blend_fwd_grid<M, 128><<<g, kBlock, 0, s>>>(Q);
         else k_blend_fwd_grid<M, 256><<<g, kBlock, 0, s>>>(Q);
         return;
     }
     const int grid = p.grid_fwd;
-    if (nb == 64) k_blend_fwd_batched<M, 64><<<grid, kBlock, 0, s>>>(Q);
+    if (p.all)
+        (nb == 64 ? k_blend_fwd_batched<M, 64, true>
+                  : k_blend_fwd_batched<M, kAllBatchFwd, true>)<<<grid, kBlock, 0, s>>>(Q);
+    else if (nb == 64) k_blend_fwd_batched<M, 64><<<grid, kBlock, 0, s>>>(Q);
     else if (nb == 128) k_blend_fwd_batched<M, 128><<<grid, kBlock, 0, s>>>(Q);
     else k_blend_fwd_batched<M, 256><<<grid, kBlock, 0, s>>>(Q);
 }

@@ -38,3 +38,30 @@ def test_forward(gpu, W, H, n, opaque, prec):
                 api.blend_forward(*a, rg, pl, W, H, bg, full)):
         for x, y in zip(out, ref):
             np.testing.assert_array_equal(x.cpu().numpy(), y)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("launch", [0, 1])
+@pytest.mark.parametrize("batch", [64, 128, 256])
+def test_plan(gpu, batch, launch, prec):
+    """The same through a plan of two views, whose lists are of 9 and of 300 entries a tile."""
+    say(f"[full scan] plan batch={batch} launch={launch} {prec}")
+    scenes = []
+    for n, W, H in ((9, 130, 65), (300, 200, 120)):
+        rng = np.random.default_rng(n)
+        i2 = rng.uniform(2.0, 40.0, n) ** -2
+        sd = upload(dict(width=W, height=H, means2d=(rng.uniform(-0.1, 1.1, (n, 2)) * [W, H]).astype(np.float32),
+                         conics=np.stack([i2, 0.3 * i2, 1.5 * i2], 1).astype(np.float32),
+                         opacity=rng.uniform(0.003, 0.5, n).astype(np.float32),
+                         colors=rng.uniform(0.0, 1.0, (n, 3)).astype(np.float32),
+                         depths=rng.uniform(1.0, 9.0, n).astype(np.float32),
+                         radii=np.full(n, 2 * max(W, H), np.int32)), gpu)
+        scenes.append(sd)
+    outs = []
+    for code in (api.prec_code(prec), api.prec_code(prec) | _lib.GSB_FULL_SCAN):
+        bv = api.BatchedViews(scenes, prec=code, tuning=dict(batch_fwd=batch, launch=launch), bg=(0.1, 0.2, 0.3))
+        bv.step()
+        outs.append([v[k].cpu().numpy() for v in bv.views for k in ("image", "final_T", "last_contrib")])
+        bv.close()
+    for x, y in zip(*outs):
+        np.testing.assert_array_equal(x, y)
