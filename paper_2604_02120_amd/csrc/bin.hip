@@ -115,6 +115,14 @@ int64_t sb_max_chunks(int64_t cap) {
 // (k_tile_scan), so that a chunk adds the counts of its own group's chunks alone.
 constexpr int kSbGroup = 64;
 
+// Words of the depth sort's look-back and of the tile sort's histograms, which also hold the counts of
+// step 1 of the superblocks
+int64_t sort_words(int64_t n, int64_t cap) {
+    const int64_t lb_d = int64_t(kMaxPasses) * sort_blocks(n > 0 ? n : 1);
+    const int64_t lb_t = sort_blocks(cap > 0 ? cap : 1);
+    return kRadix * (lb_d > lb_t ? lb_d : lb_t);
+}
+
 Layout layout(int64_t n, int64_t cap) {
     Layout L;
     const size_t nn = size_t(n > 0 ? n : 1), cc = size_t(cap > 0 ? cap : 1);
@@ -138,9 +146,7 @@ Layout layout(int64_t n, int64_t cap) {
     // the per-block digit histograms of one pass, [digit][block]; superblocks, afterwards: the
     // counts [superblock][block] of the entries, then, unless they fit the offsets' place, the
     // tile counts of every chunk, and the groups' sums
-    const int64_t lb_d = int64_t(kMaxPasses) * sort_blocks(n > 0 ? n : 1);
-    const int64_t lb_t = sort_blocks(cap > 0 ? cap : 1);
-    const size_t words = sizeof(uint32_t) * kRadix * size_t(lb_d > lb_t ? lb_d : lb_t);
+    const size_t words = sizeof(uint32_t) * size_t(sort_words(n, cap));
     // (never less than a smaller capacity's: a workspace also serves every shorter list)
     int64_t chunks = sb_max_chunks(int64_t(cc));
     if (int64_t(cc) > kSbSmallPairs && chunks < sb_max_chunks(kSbSmallPairs))
@@ -1070,8 +1076,10 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_pass(
 // blocks (the whole binning at 20k 109 -> 91 us, 60k 118 -> 106, 130k 127 -> 122; at 300k it is even,
 // at 1M smaller tiles' longer look-back costs more: 201 -> 260).
 constexpr int64_t kSort4 = 131072;
-// Up to this many Gaussians one block places the entries and one launch may write the lists.
+// Up to this many Gaussians one launch may write the lists, or one block place the entries (as many as are
+// expected to be kSbOneEntries: two windows).
 constexpr int kSmallSort = 4096;
+constexpr double kSbOneEntries = 8192.0;
 
 // The depth order of up to kRankSort Gaussians in one launch: a block ranks 64 of them (lane e) by
 // counting the keys before theirs, a sixteenth of all per wavefront, four at a time from LDS (the same
@@ -1209,9 +1217,25 @@ __host__ __device__ inline SbGrid sb_grid(int32_t gx, int32_t gy) {
     const int32_t sx = (gx + kSbEdge - 1) >> kSbShift, sy = (gy + kSbEdge - 1) >> kSbShift;
     return SbGrid{gx, gy, sx, sx * sy};
 }
-// Ranks per block of step 1: the digit counts (superblocks x blocks) then fit the words of the
-// depth sort's look-back, which they replace (256 per 1024 Gaussians).
-inline int sb_ranks(int32_t n_sb) { return n_sb <= 256 ? 1024 : n_sb <= 512 ? 2048 : 4096; }
+// Entries per Gaussian to expect of `cap` pairs of n: a square of that many tiles, anywhere.
+inline double sb_entries(int64_t n, int64_t cap) {
+    const double side = sqrt(double(cap) / double(n)) / kSbEdge + 1.0;
+    return side * side;
+}
+// Ranks per block of step 1. The digit counts (superblocks x blocks) take the place of the depth sort's
+// look-back words (256 per 1024 Gaussians): 1024 to 4096 always fit. Of Gaussians of more than 64 tiles
+// (about four entries) as many as one window of entries is expected of, if the counts have room, which
+// grows with the pairs: with 1024 and more, a few blocks had all the entries of large Gaussians (the
+// whole binning at 4K: 4000 Gaussians of 1000 px 124 ms, now 0.31, of 100 px 3.7 ms, now 0.11; 16384 of 100
+// px 1.56 ms, now 0.16; 5000 of 1000 px in mode 1 58 ms, now 25).
+inline int sb_ranks(int32_t n_sb, int64_t n, int64_t cap) {
+    int ranks = n_sb <= 256 ? 1024 : n_sb <= 512 ? 2048 : 4096;
+    if (cap / 64 <= n) return ranks;
+    const double want = 4096.0 / sb_entries(n, cap);
+    const int64_t words = sort_words(n, cap), room = words < kScanMaxLen ? words : kScanMaxLen;
+    while (ranks > 8 && ranks > want && int64_t(n_sb) * ((2 * n + ranks - 1) / ranks + 1) <= room) ranks /= 2;
+    return ranks;
+}
 // The superblock path where it applies: a grid of at most kMaxSb superblocks
 inline bool by_superblock(const SbGrid &G) { return G.n <= kMaxSb; }
 
@@ -1345,13 +1369,15 @@ __device__ inline void sb_visible(const SbVisible &V, const SbGrid &G, const Rec
 
 // The list of the Gaussians with candidates past a mask's 8 x 8, each tested by a whole wavefront,
 // a superblock's 64 tiles at a time. In the order of the indices, as large Gaussians are neighbours
-// in the order of depth. Masks are gathered in LDS, for an atomic per kMaxSb of them or wavefront.
+// in the order of depth. Masks are gathered in LDS, for an atomic per kMaxSb of them or wavefront. A
+// wavefront takes eight at a time (a cache line of records) from all over the indices, so that a run of
+// large ones is not one wavefront's (64 of 1500 px in a row at 4K: 5.9 ms, now 0.74).
 __global__ __launch_bounds__(64, 5) void k_sb_list(SbVisible V, SbTable *table,
                                                 int64_t n, SbGrid G, int64_t cap) {
     __shared__ unsigned long long s_mask[kMaxSb];
     __shared__ uint16_t s_sb[kMaxSb];
     const int lane = threadIdx.x, l = int(blockIdx.x) & (V.lists - 1);    // (an XCD's own list)
-    const int64_t i = int64_t(blockIdx.x) * 64 + lane;
+    const int64_t i = (int64_t(lane >> 3) * gridDim.x + blockIdx.x) * 8 + (lane & 7);
     Rect R{0, 0, 0, 0};
     if (i < n) {
         const uint2 z = reinterpret_cast<const uint2 *>(V.recs + i)[1];
@@ -1419,15 +1445,23 @@ __global__ __launch_bounds__(64, 5) void k_sb_list(SbVisible V, SbTable *table,
     flush();
 }
 
+// A Gaussian with more than kSbSerial entries in a window of k_sb_scatter is listed in LDS there, and a
+// wavefront writes them, an entry per lane: by their owner alone, a window of Gaussians of 500 entries
+// took 230 us. Blocks without one (all but a few on usual frames, whose largest have 16 to 25) skip the
+// listing's barriers.
+constexpr int kSbSerial = 32;
+
 // Mode 1: as k_sb_hist, for the superblocks with a visible tile; also the place of each rank's first
-// entry among its block's, and the number of the block's.
+// entry among its block's, and the number of the block's (with kSbMany: a rank has more than kSbSerial).
+constexpr uint32_t kSbMany = 1u << 31;
 __global__ __launch_bounds__(kSortThreads, 6) void k_sb_hist_visible(
     const unsigned long long *rank_rects, const uint32_t *sorted_idx, SbVisible V, int64_t n, int ranks,
     SbGrid G, uint32_t *hist, int64_t nblk, int64_t cap, uint32_t *rank_pos,
     uint32_t *block_entries) {
-    __shared__ uint32_t s_h[kMaxSb], s_wave[kSortThreads / 64];
+    __shared__ uint32_t s_h[kMaxSb], s_wave[kSortThreads / 64], s_many;
     const int t = threadIdx.x;
     for (int d = t; d < G.n; d += kSortThreads) s_h[d] = 0u;
+    if (t == 0) s_many = 0u;
     __syncthreads();
     const int64_t blk = xcd_rank(blockIdx.x, uint32_t(nblk));
     if (blk >= nblk) return;                                 // block-uniform
@@ -1435,32 +1469,34 @@ __global__ __launch_bounds__(kSortThreads, 6) void k_sb_hist_visible(
     const int64_t j0 = blk * ranks;
     uint32_t first = 0;
     unsigned long long rect = 0, mask = 0, next_rect = 0, next_mask = 0;   // loaded a step ahead
+    const int64_t end = n - j0 < ranks ? n : j0 + ranks;
     const auto load = [&](int64_t j) {
         next_rect = next_mask = 0;
-        if (j < n) {
+        if (j < end) {
             next_rect = rank_rects[j];
             next_mask = V.rank_masks[j];
         }
     };
     load(j0 + t);
-    for (int k = 0; k < ranks && j0 + k < n; k += kSortThreads) {       // block-uniform
+    for (int k = 0; j0 + k < end; k += kSortThreads) {                  // block-uniform
         const int64_t j = j0 + k + t;
         uint32_t e = 0, step;
         rect = next_rect;
         mask = next_mask;
-        if (k + kSortThreads < ranks) load(j + kSortThreads);
-        if (j < n)
+        load(j + kSortThreads);
+        if (j < end)
             sb_visible(V, G, unpack_rect(rect), mask, sorted_idx + j, listed,
                        [&](uint32_t sb, unsigned long long) {
                            atomicAdd(&s_h[sb], 1u);
                            ++e;
                        });
+        if (e > uint32_t(kSbSerial)) s_many = kSbMany;
         const uint32_t pos = block_exclusive_scan<uint32_t>(e, s_wave, step);
-        if (j < n) rank_pos[j] = first + pos;
+        if (j < end) rank_pos[j] = first + pos;
         first += step;
     }
-    if (t == 0) block_entries[blk] = first;
     __syncthreads();
+    if (t == 0) block_entries[blk] = first | s_many;
     for (int d = t; d < G.n; d += kSortThreads) hist[int64_t(d) * nblk + blk] = s_h[d];
 }
 
@@ -1476,7 +1512,7 @@ __global__ __launch_bounds__(kSortThreads, 6) void k_sb_hist_visible(
 // tile and their masks (half the window, as masks do not fit the keys' spare bits).
 template <int kPer, bool kOne, bool kVis>
 __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
-    const unsigned long long *rank_rects, const uint32_t *sorted_idx, int64_t n, SbGrid G, int bits,
+    const unsigned long long *rank_rects, const uint32_t *sorted_idx, int64_t n, int ranks, SbGrid G, int bits,
     const uint32_t *hist, int64_t nblk, BinHeader *hdr, int64_t cap, uint32_t chunk, uint32_t *e_idx,
     unsigned long long *e_mask, SbTable *table, SbVisible V,
     const uint32_t *rank_pos, const uint32_t *block_entries) {
@@ -1484,7 +1520,13 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
     constexpr int kSbWindow = kVis ? 2048 : 4096, kSbSteps = kSbWindow / kSortThreads;
     constexpr int kWaves = kSortThreads / 64, kDig = kMaxSb / kSortThreads;
     __shared__ uint32_t s_gofs[kMaxSb];                 // next global position of each superblock
-    __shared__ uint16_t s_wcnt[kWaves][kMaxSb];         // per-wave counts, then prefixes
+    // per-wave counts, then prefixes; before that the window's listed ranks (rectangle, or mode 1 the
+    // masks' place; index; first entry, from the window's start)
+    __shared__ __align__(16) uint16_t s_wcnt[kWaves][kMaxSb];
+    uint4 *const s_list = reinterpret_cast<uint4 *>(&s_wcnt[0][0]);
+    static_assert(sizeof(s_wcnt) / sizeof(uint4) > kSbWindow / (kSbSerial + 1), "a place for each listed rank");
+    __shared__ int s_listed;
+    __shared__ uint32_t s_large[kWaves];                // a rank of the wavefront has many entries
     __shared__ uint16_t s_dstart[kMaxSb];               // start of each superblock in the window
     __shared__ uint32_t s_wave[kWaves];
     __shared__ uint32_t s_key[kSbWindow];               // superblock | columns << 16 | rows << 24
@@ -1497,32 +1539,49 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
     // this thread's ranks: superblocks (0 x 0 where the rectangle is empty or past the end),
     // rectangle and index. kPer is a multiple of 4 and the buffers are padded to 256 bytes, so the
     // vector loads that straddle n stay inside them.
-    const int64_t j0 = (blk * kSortThreads + t) * kPer;
+    // (`ranks` is a multiple of kPer, at most kPer per thread.)
+    const int64_t j0 = blk * ranks + int64_t(t) * kPer;
+    const int64_t n_own = t * kPer < ranks ? n : 0;          // past the block's ranks: none
     unsigned long long rects[kPer];
     uint32_t idx[kPer], mine = 0;
-#pragma unroll
-    for (int k = 0; k < (kVis ? 0 : kPer); k += 4) {
-        ulonglong2 r01{0, 0}, r23{0, 0};
-        uint4 i4{0, 0, 0, 0};
-        if (j0 + k < n) {
-            r01 = *reinterpret_cast<const ulonglong2 *>(rank_rects + j0 + k);
-            i4 = *reinterpret_cast<const uint4 *>(sorted_idx + j0 + k);
+    // (loaded again for a second window: kept through the first, their registers cost a block per CU)
+    const auto load_ranks = [&] {
+        if constexpr (kPer == 1) {
+            rects[0] = j0 < n_own ? rank_rects[j0] : 0ull;
+            idx[0] = j0 < n_own ? sorted_idx[j0] : 0u;
         }
-        if (j0 + k + 2 < n) r23 = *reinterpret_cast<const ulonglong2 *>(rank_rects + j0 + k + 2);
-        rects[k] = r01.x;
-        rects[k + 1] = j0 + k + 1 < n ? r01.y : 0;
-        rects[k + 2] = r23.x;
-        rects[k + 3] = j0 + k + 3 < n ? r23.y : 0;
-        idx[k] = i4.x; idx[k + 1] = i4.y; idx[k + 2] = i4.z; idx[k + 3] = i4.w;
-    }
+#pragma unroll
+        for (int k = 0; k < (kPer == 1 ? 0 : kPer); k += 4) {
+            ulonglong2 r01{0, 0}, r23{0, 0};
+            uint4 i4{0, 0, 0, 0};
+            if (j0 + k < n_own) {
+                r01 = *reinterpret_cast<const ulonglong2 *>(rank_rects + j0 + k);
+                i4 = *reinterpret_cast<const uint4 *>(sorted_idx + j0 + k);
+            }
+            if (j0 + k + 2 < n_own) r23 = *reinterpret_cast<const ulonglong2 *>(rank_rects + j0 + k + 2);
+            rects[k] = r01.x;
+            rects[k + 1] = j0 + k + 1 < n_own ? r01.y : 0;
+            rects[k + 2] = r23.x;
+            rects[k + 3] = j0 + k + 3 < n_own ? r23.y : 0;
+            idx[k] = i4.x; idx[k + 1] = i4.y; idx[k + 2] = i4.z; idx[k + 3] = i4.w;
+        }
+    };
+    if constexpr (!kVis) load_ranks();
     const auto entries = [](const Rect &r) {
         if (r.tx1 <= r.tx0 || r.ty1 <= r.ty0) return 0u;
         const Rect q = sb_rect(r);
         return uint32_t((q.tx1 - q.tx0) * (q.ty1 - q.ty0));
     };
+    bool large = false;
     if constexpr (!kVis) {
 #pragma unroll
-        for (int k = 0; k < kPer; ++k) mine += entries(unpack_rect(rects[k]));
+        for (int k = 0; k < kPer; ++k) {
+            const uint32_t e = entries(unpack_rect(rects[k]));
+            mine += e;
+            large = large || e > uint32_t(kSbSerial);
+        }
+        const bool any = __ballot(large) != 0ull;
+        if (lane == 0) s_large[w] = any ? 1u : 0u;           // (read behind the scan's barriers)
     }
     uint32_t n_entries;
     if constexpr (kOne) {
@@ -1582,8 +1641,15 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
     }
     if (kVis && hdr->total > (unsigned long long)cap) return;   // block-uniform; every list is empty
     uint32_t total = 0, pos0 = 0;
-    if constexpr (kVis) total = block_entries[blk];
-    else pos0 = block_exclusive_scan<uint32_t>(mine, s_wave, total);
+    if constexpr (kVis) {
+        total = block_entries[blk];
+        large = (total & kSbMany) != 0u;
+        total &= kSbMany - 1u;
+    } else {
+        pos0 = block_exclusive_scan<uint32_t>(mine, s_wave, total);
+        large = (s_large[0] | s_large[1] | s_large[2] | s_large[3]) != 0u;
+    }
+    const uint32_t serial = large ? uint32_t(kSbSerial) : ~0u;
     for (uint32_t w0 = 0; w0 < total; w0 += kSbWindow) {      // block-uniform
         const int cnt = int(total - w0 < uint32_t(kSbWindow) ? total - w0 : uint32_t(kSbWindow));
         [[maybe_unused]] uint32_t pos = pos0;
@@ -1595,17 +1661,17 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
         if constexpr (kVis) {
             // rank k kSortThreads + t of the block, the next one's data loaded ahead
             const bool listed = sb_listed(V) + hdr->entries <= (unsigned long long)cap;
-            const int64_t b0 = blk * kSortThreads * kPer;
-            const int ranks = int(n - b0 < kSortThreads * kPer ? n - b0 : kSortThreads * kPer);
+            const int64_t b0 = blk * ranks;
+            const int own = int(n - b0 < ranks ? n - b0 : ranks);
             struct Rank {
                 uint32_t pos, end, idx;
                 unsigned long long rect, mask;
             };
             const auto load = [&](int r) {
                 Rank a{total, total, 0, 0, 0};
-                if (r < ranks) {
+                if (r < own) {
                     a.pos = rank_pos[b0 + r];
-                    if (r + 1 < ranks) a.end = rank_pos[b0 + r + 1];
+                    if (r + 1 < own) a.end = rank_pos[b0 + r + 1];
                     a.idx = sorted_idx[b0 + r];
                     a.rect = rank_rects[b0 + r];
                     a.mask = V.rank_masks[b0 + r];
@@ -1614,15 +1680,23 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
             };
             const int r0 = w0 > 0 ? s_rank : 0;              // the window's first rank
             Rank next = load(r0 + t);
-            if (w0 > 0) __syncthreads();                     // s_rank has been read
+            if (large && t == 0) s_listed = 0;
+            if (large || w0 > 0) __syncthreads();            // s_rank has been read
 #pragma unroll 1
-            for (int r = r0 + t; r < ranks; r += kSortThreads) {
+            for (int r = r0 + t; r < own; r += kSortThreads) {
                 const Rank a = next;
                 if (a.pos >= w0 + kSbWindow) break;
                 next = load(r + kSortThreads);
                 if (a.end >= w0 + kSbWindow) s_rank = r;     // the last rank that starts here
                 if (a.end <= w0 || a.pos == a.end) continue;
                 uint32_t o = a.pos - w0;                 // (wraps while before the window)
+                const uint32_t lo = a.pos > w0 ? a.pos : w0;
+                const uint32_t hi = a.end < w0 + kSbWindow ? a.end : w0 + kSbWindow;
+                if (large && listed && hi - lo > uint32_t(kSbSerial) && sb_big(unpack_rect(a.rect))) {
+                    const uint2 p = reinterpret_cast<const uint2 *>(V.recs + a.idx)[0];
+                    s_list[atomicAdd(&s_listed, 1)] = make_uint4(p.x, p.y, a.idx, o);
+                    continue;
+                }
                 sb_visible(V, G, unpack_rect(a.rect), a.mask, &a.idx, listed,
                            [&](uint32_t sb, unsigned long long m) {
                                if (o < uint32_t(kSbWindow)) {
@@ -1633,14 +1707,33 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
                                ++o;
                            });
             }
+            if (large) {                                     // block-uniform
+                __syncthreads();
+                const int listed_n = s_listed;
+                for (int i = w; i < listed_n; i += kWaves) {
+                    const uint4 q = s_list[i];
+                    const unsigned long long p = (static_cast<unsigned long long>(q.y) << 32) | q.x;
+                    const unsigned long long place = p & ((1ull << 45) - 1ull);
+                    const int l = int(p >> 45) & 7, e = int(p >> 48), first = int(q.w);
+                    const int last = first + e < kSbWindow ? first + e : kSbWindow;
+                    for (int o = (first > 0 ? first : 0) + lane; o < last; o += 64) {
+                        const int64_t at = int64_t(sb_place(place + (o - first), l, V.lists));
+                        s_key[o] = V.sbs[-1 - at];
+                        s_mask[o] = V.masks[-1 - at];
+                        s_idx[o] = q.z;
+                    }
+                }
+                __syncthreads();                             // before the counts take the list's place
+            }
         } else {
+            if (w0 > 0) load_ranks();
 #pragma unroll
             for (int k = 0; k < kPer; ++k) {
                 const Rect R = unpack_rect(rects[k]);
                 const uint32_t e = entries(R);
                 uint32_t lo, hi;
                 part(e, lo, hi);
-                if (lo < hi) {
+                if (lo < hi && hi - lo <= serial) {
                     const Rect q = sb_rect(R);
                     const uint32_t wd = uint32_t(q.tx1 - q.tx0);
                     int sy = q.ty0, sx = q.tx0;
@@ -1660,6 +1753,39 @@ __global__ __launch_bounds__(kSortThreads) void k_sb_scatter(
                     }
                 }
                 pos += e;
+            }
+            if (large) {                                     // block-uniform
+                if (t == 0) s_listed = 0;
+                __syncthreads();
+                // (the ranks are loaded again: held for this, their registers cost a block per CU)
+                pos = pos0;
+#pragma unroll 1
+                for (int k = 0; k < kPer && j0 + k < n_own; ++k) {
+                    const unsigned long long rect = rank_rects[j0 + k];
+                    const uint32_t e = entries(unpack_rect(rect));
+                    uint32_t lo, hi;
+                    part(e, lo, hi);
+                    if (lo < hi && hi - lo > serial)
+                        s_list[atomicAdd(&s_listed, 1)] = make_uint4(uint32_t(rect), uint32_t(rect >> 32),
+                                                                     sorted_idx[j0 + k], pos - w0);
+                    pos += e;
+                }
+                __syncthreads();
+                const int listed_n = s_listed;
+                for (int i = w; i < listed_n; i += kWaves) {
+                    const uint4 p = s_list[i];
+                    const Rect R = unpack_rect((static_cast<unsigned long long>(p.y) << 32) | p.x);
+                    const Rect q = sb_rect(R);
+                    const int wd = q.tx1 - q.tx0, e = wd * (q.ty1 - q.ty0), first = int(p.w);
+                    const int last = first + e < kSbWindow ? first + e : kSbWindow;
+                    for (int o = (first > 0 ? first : 0) + lane; o < last; o += 64) {
+                        const int sy = q.ty0 + (o - first) / wd, sx = q.tx0 + (o - first) % wd;
+                        s_key[o] = uint32_t(sy * G.sx + sx) | (sb_span(R.tx0, R.tx1, sx) << 16) |
+                                   (sb_span(R.ty0, R.ty1, sy) << 24);
+                        s_idx[o] = p.z;
+                    }
+                }
+                __syncthreads();                             // before the counts take the list's place
             }
         }
         for (int d = t; d < kMaxSb; d += kSortThreads) {
@@ -1986,7 +2112,7 @@ __global__ __launch_bounds__(256, 6) void k_sb_write(const uint32_t *e_idx,
         uint32_t before = 0;
         if (w == 0 && group > 0)
             before = groups[sb_group_place(C.first, group) * kSbTiles + lane];
-#pragma unroll 2
+#pragma unroll 1
         for (uint32_t r = C.first + group * kSbGroup + w; r < c; r += 4)
             before += counts[int64_t(r) * kSbTiles + lane];
         s_pre[w][lane] = before;
@@ -2367,14 +2493,15 @@ gsb_status bin_fill_sorted(const float *means2d, const float *conics, const floa
                 rects, dva, int(n), G, hdr, cap, reinterpret_cast<uint2 *>(ranges), point_list, status_dev);
             return check_launch("bin_fill");
         }
-        if (n <= kSmallSort && !vis) {
+        if (n <= kSmallSort && !vis && double(n) * sb_entries(n, cap) <= kSbOneEntries) {
             const auto scatter = n <= 4 * kSortThreads ? k_sb_scatter<4, true, false>
                                : n <= 8 * kSortThreads ? k_sb_scatter<8, true, false>
                                                        : k_sb_scatter<16, true, false>;
-            scatter<<<1, kSortThreads, 0, s>>>(rects, dva, n, G, bits, nullptr, 1, hdr, cap, chunk, e_idx,
+            const int ranks = kSortThreads * (n <= 4 * kSortThreads ? 4 : n <= 8 * kSortThreads ? 8 : 16);
+            scatter<<<1, kSortThreads, 0, s>>>(rects, dva, n, ranks, G, bits, nullptr, 1, hdr, cap, chunk, e_idx,
                                                e_mask, table, V, nullptr, nullptr);
         } else {
-            const int ranks = sb_ranks(G.n);
+            const int ranks = sb_ranks(G.n, n, cap);
             const int64_t nblk = (n + ranks - 1) / ranks;
             const dim3 gb{unsigned(xcd_grid(nblk))};
             if (vis)
@@ -2384,10 +2511,11 @@ gsb_status bin_fill_sorted(const float *means2d, const float *conics, const floa
                 k_sb_hist<<<gb, kSortThreads, 0, s>>>(rects, n, ranks, G, sortbuf, nblk);
             launch_scan<uint32_t>(sortbuf, int64_t(G.n) * nblk, partial32, &hdr->entries, nullptr, s);
             const auto scatter =
-                ranks == 1024 ? (vis ? k_sb_scatter<4, false, true> : k_sb_scatter<4, false, false>)
+                ranks <= 256 ? (vis ? k_sb_scatter<1, false, true> : k_sb_scatter<1, false, false>)
+              : ranks <= 1024 ? (vis ? k_sb_scatter<4, false, true> : k_sb_scatter<4, false, false>)
               : ranks == 2048 ? (vis ? k_sb_scatter<8, false, true> : k_sb_scatter<8, false, false>)
                               : (vis ? k_sb_scatter<16, false, true> : k_sb_scatter<16, false, false>);
-            scatter<<<gb, kSortThreads, 0, s>>>(rects, dva, n, G, bits, sortbuf, nblk, hdr, cap, chunk,
+            scatter<<<gb, kSortThreads, 0, s>>>(rects, dva, n, ranks, G, bits, sortbuf, nblk, hdr, cap, chunk,
                                                 e_idx, e_mask, table, V, dka, dkb);
         }
         const int64_t mc = sb_max_chunks(cap);
