@@ -1478,9 +1478,9 @@ void k_blend_bwd_det(ViewDesc v) {
     bwd_tile<M, kDetBatch, false, true, true>(v, tile, S, nullptr, s_maxlast, nullptr, &s_det);
 }
 
-// Gaussians with more than kDetWaveRows rows are listed (word 0: how many) for blocks of their own
-// (2000 of some 400 rows each at 4K: the gather 162 us with them a wavefront's, 84 with a block each).
-constexpr uint32_t kDetWaveRows = 256;
+// Gaussians with more than kDetWaveRows rows are listed (word 0: how many) for blocks of their own; those
+// of up to kDetCountRows rows are put in order by counting there, others by a sort.
+constexpr uint32_t kDetWaveRows = 64, kDetCountRows = 256;
 // No rows yet: counts per Gaussian, numbers per list position.
 __global__ __launch_bounds__(256) void k_det_init(uint32_t *rows, int64_t n, uint32_t *seq,
                                                   int64_t pairs, uint32_t *large) {
@@ -1513,7 +1513,7 @@ __global__ __launch_bounds__(256) void k_det_place(const uint32_t *plist, const 
     }
 }
 
-// More than kDetWaveRows rows: list[0, m) in increasing order, by a stable radix sort between `list` and
+// More than kDetCountRows rows: list[0, m) in increasing order, by a stable radix sort between `list` and
 // `other` of the block's four wavefronts, kDetBits of the positions' range a pass; returns which of the
 // two holds it. A wavefront counts and places a quarter of the list, 64 at a time, so that the steps
 // grow with m alone. (One wavefront that counted the rows per tile, 1024 tiles at a time, read the
@@ -1624,36 +1624,23 @@ __device__ inline const uint32_t *det_order(uint32_t *list, uint32_t *other, uin
     return list;
 }
 
-// list[0, m), 64 < m <= kDetWaveRows, into increasing order in s_key, by one wavefront that counts the
-// positions before each.
-__device__ inline void det_order_wave(const uint32_t *list, uint32_t m, uint32_t *s_key, int lane) {
-    constexpr int kOwn = int(kDetWaveRows) / 64;
-    uint32_t key[kOwn], at[kOwn];
-#pragma unroll
-    for (int q = 0; q < kOwn; ++q) {
-        if (uint32_t(64 * q) >= m) break;                    // uniform
-        const uint32_t i = 64 * q + lane;
-        key[q] = i < m ? list[i] : ~0u;
-        at[q] = 0u;
-        s_key[i] = key[q];
-    }
-    __builtin_amdgcn_wave_barrier();
+// list[0, m), m <= kDetCountRows, into increasing order in s_key: each thread of the block counts the
+// positions before its own. (By a wavefront for its four Gaussians, one after the other, the whole call for
+// 25 Gaussians on each of 208 tiles took 92 us, now 49, and the gather of 2000 of up to some 400 rows
+// at 4K 84, now 58.)
+__device__ inline void det_count_order(const uint32_t *list, uint32_t m, uint32_t *s_key) {
+    const uint32_t t = threadIdx.x;
+    const uint32_t key = t < m ? list[t] : ~0u;
+    s_key[t] = key;
+    __syncthreads();
+    uint32_t at = 0;
     for (uint32_t j = 0; j < m; j += 4) {
         const uint4 k = *reinterpret_cast<const uint4 *>(s_key + j);
-#pragma unroll
-        for (int q = 0; q < kOwn; ++q) {
-            if (uint32_t(64 * q) >= m) break;
-            at[q] += (k.x < key[q] ? 1u : 0u) + (k.y < key[q] ? 1u : 0u) + (k.z < key[q] ? 1u : 0u) +
-                     (k.w < key[q] ? 1u : 0u);
-        }
+        at += (k.x < key ? 1u : 0u) + (k.y < key ? 1u : 0u) + (k.z < key ? 1u : 0u) + (k.w < key ? 1u : 0u);
     }
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int q = 0; q < kOwn; ++q) {
-        if (uint32_t(64 * q) >= m) break;
-        if (uint32_t(64 * q) + lane < m) s_key[at[q]] = key[q];
-    }
-    __builtin_amdgcn_wave_barrier();
+    __syncthreads();
+    if (t < m) s_key[at] = key;
+    __syncthreads();
 }
 
 // The gradients of Gaussian g from its nine sums, as k_bwd_finish forms them.
@@ -1689,17 +1676,18 @@ __device__ inline uint32_t row_rank(uint32_t key) {
 // Per Gaussian: its rows' sums in the order of the list positions, in a fixed reduction tree. Four
 // Gaussians per wavefront, 16 lanes each, where they have up to 16 rows (most do): the positions are
 // ranked within the 16 lanes, lane j adds the row of rank j. Those with more take the whole wavefront
-// in turn: lane l adds the rows of rank l, l + 64, ... (A wavefront for each Gaussian took 51 us of
-// 150 k Gaussians, this 27; a thread for each would leave most lanes idle behind the largest footprint.)
+// in turn, up to 64. (A wavefront for each Gaussian took 51 us of 150 k Gaussians, this 27; a thread for
+// each would leave most lanes idle behind the largest footprint.)
 // The listed ones, with more than kDetWaveRows, are the first kDetBlocks blocks' (four per compute unit;
-// they cost nothing measurable where there are none), a block at a time each: thread t adds the rows
-// of rank t, t + 256, ..., the four wavefronts' sums are added in order.
+// they cost nothing measurable where there are none), a block at a time each. Up to kDetCountRows its
+// first wavefront adds the rows of rank l, l + 64, ... in lane l, beyond that thread t those of rank t,
+// t + 256, ..., and the four wavefronts' sums are added in order.
 constexpr int kGatherPer = 4, kDetBlocks = 1024;
 __global__ __launch_bounds__(256, 7) void k_det_gather(DetOut out, const float *partial,
                                                     const uint32_t *first, const uint32_t *rows,
                                                     uint32_t *list, uint32_t *other,
                                                     const uint32_t *large, int64_t pairs, int64_t n) {
-    static_assert(kDetWaveRows <= kDetRadix, "a wavefront's positions in its row of counters");
+    static_assert(kDetCountRows <= 256 && kDetCountRows <= kDetRadix, "a thread and a word for each position");
     __shared__ __align__(16) uint32_t s_cnt[4][kDetRadix];
     __shared__ uint32_t s_red[8];
     __shared__ float s_sum[4][kGrad];
@@ -1743,6 +1731,18 @@ __global__ __launch_bounds__(256, 7) void k_det_gather(DetOut out, const float *
             uint32_t a = 0u;
             const uint32_t m = g < n ? rows_of(g, a) : 0u;
             if (m <= kDetWaveRows) continue;     // block-uniform
+            if (m <= kDetCountRows) {
+                det_count_order(list + a, m, s_cnt[0]);
+                if (w == 0) {
+                    clear();
+                    for (uint32_t k = lane; k < m; k += 64) add(s_cnt[0][k]);
+                    float t[kGrad];
+                    total(t);
+                    if (lane == 0) det_store(out, g, t);
+                }
+                __syncthreads();                 // (before the next one's are written there)
+                continue;
+            }
             const uint32_t *order = det_order(list + a, other + a, m, s_cnt, s_red, w, lane);
             clear();
             for (uint32_t k = threadIdx.x; k < m; k += 4 * 256) {
@@ -1795,19 +1795,13 @@ __global__ __launch_bounds__(256, 7) void k_det_gather(DetOut out, const float *
         if (mr <= 16u || mr > kDetWaveRows) continue;        // uniform (m is 0 past the last Gaussian)
         const uint32_t ar = uint32_t(__builtin_amdgcn_readlane(int(a), 16 * r));
         clear();
-        if (mr <= 64u) {
-            const bool has = uint32_t(lane) < mr;
-            const uint32_t k64 = has ? list[ar + uint32_t(lane)] : ~0u;
-            int at = 0;
-            for (int k = 0; k < int(mr); ++k)
-                at += uint32_t(__builtin_amdgcn_readlane(int(k64), k)) < k64 ? 1 : 0;
-            const uint32_t p = uint32_t(__builtin_amdgcn_ds_permute(4 * (has ? at : lane), int(k64)));
-            if (has) add(p);
-        } else {
-            det_order_wave(list + ar, mr, s_cnt[w], lane);
-            for (uint32_t k = lane; k < mr; k += 64) add(s_cnt[w][k]);
-            __builtin_amdgcn_wave_barrier();     // (before the next one's are written there)
-        }
+        const bool has = uint32_t(lane) < mr;
+        const uint32_t k64 = has ? list[ar + uint32_t(lane)] : ~0u;
+        int at = 0;
+        for (int k = 0; k < int(mr); ++k)
+            at += uint32_t(__builtin_amdgcn_readlane(int(k64), k)) < k64 ? 1 : 0;
+        const uint32_t p = uint32_t(__builtin_amdgcn_ds_permute(4 * (has ? at : lane), int(k64)));
+        if (has) add(p);
         float t[kGrad];
         total(t);
         if (lane == 0) det_store(out, g0 + r, t);

@@ -1,5 +1,5 @@
 """The deterministic backward of Gaussians with many rows: at both sides of what is ranked in registers
-(64), counted by one wavefront (256) and sorted by a block, and on more tiles than 8 x 1024. Runs are
+(64), counted by a block (256) and sorted by one, and on more tiles than 8 x 1024. Runs are
 the same bit for bit and the gradients are within the bound that the FP32 form has for large
 footprints; and its time grows with the rows: for a frame-filling Gaussian it stays near the atomic
 backward's, which adds the same sums."""
